@@ -17,7 +17,8 @@ extern "C" {
  * each group of small kernels between them is bracketed by a pair of HIP events on the launch
  * stream.  alst_profile_read() waits for the recorded events, writes per kind the summed
  * milliseconds and the number of spans into the HOST arrays ms_total[8] and launches[8], and
- * forgets the spans.  Kinds: 0 logits GEMM, 1 dHidden GEMM, 2 dW GEMM, 3 the small kernels of a
+ * forgets the spans.  A logits or dHidden launch may cover several of the caller's tiles; its span
+ * counts as that many, so ms_total / launches is the time per tile.  Kinds: 0 logits GEMM, 1 dHidden GEMM, 2 dW GEMM, 3 the small kernels of a
  * cross-entropy tile; 4 the projection GEMMs of the tiled MLP (alst_mlp.h), 5 its weight-gradient
  * GEMMs, 6 its small kernels; 7 unused.  The recorded spans are process-wide state behind a lock:
  * calls from several host threads are safe, and their spans land in one list.

@@ -25,10 +25,11 @@ enum {
 
 struct ProfScope {
     hipEvent_t a, b;
-    int kind;
+    int kind, count;
     hipStream_t s;
     bool on;
-    ProfScope(int kind, hipStream_t stream);
+    // count: what the span is counted as (a launch over several of the caller's tiles: their number)
+    ProfScope(int kind, hipStream_t stream, int count = 1);
     ~ProfScope();
 };
 

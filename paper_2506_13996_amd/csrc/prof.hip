@@ -11,7 +11,7 @@
 
 namespace alst {
 
-struct ProfSpan { hipEvent_t a, b; int kind; };
+struct ProfSpan { hipEvent_t a, b; int kind, count; };
 static std::atomic<bool> g_prof_on{false};
 static std::mutex g_prof_lock;                  // guards the two vectors
 static std::vector<ProfSpan> g_prof_spans;
@@ -31,8 +31,8 @@ static hipEvent_t prof_event() {
     return e;
 }
 
-ProfScope::ProfScope(int kind_, hipStream_t stream)
-    : a(nullptr), b(nullptr), kind(kind_), s(stream), on(g_prof_on.load(std::memory_order_relaxed)) {
+ProfScope::ProfScope(int kind_, hipStream_t stream, int count_)
+    : a(nullptr), b(nullptr), kind(kind_), count(count_), s(stream), on(g_prof_on.load(std::memory_order_relaxed)) {
     if (!on) return;
     a = prof_event();
     b = prof_event();
@@ -44,7 +44,7 @@ ProfScope::~ProfScope() {
     if (!on) return;
     (void)hipEventRecord(b, s);
     std::lock_guard<std::mutex> hold(g_prof_lock);
-    g_prof_spans.push_back(ProfSpan{a, b, kind});
+    g_prof_spans.push_back(ProfSpan{a, b, kind, count});
 }
 
 // Register-resident MFMA loops for alst_debug_mfma_rate: every wavefront multiplies A and B operand
@@ -132,7 +132,7 @@ int alst_profile_read(double* ms_total, int64_t* launches) {
         if (hipEventSynchronize(sp.b) != hipSuccess ||
             hipEventElapsedTime(&ms, sp.a, sp.b) != hipSuccess) rc = ALST_ERR_HIP;
         ms_total[sp.kind] += ms;
-        launches[sp.kind] += 1;
+        launches[sp.kind] += sp.count;
     }
     std::lock_guard<std::mutex> hold(g_prof_lock);
     for (const ProfSpan& sp : spans) {

@@ -4,20 +4,20 @@
 // Footprint": forward and backward of each logits shard are done together and the shard's
 // intermediates are dropped before the next shard):
 //
-//   0. tile_info /       rows whose label is ignored take no part in the loss or in either gradient:
-//      gather_rows       once per call the valid rows are numbered densely in sequence order
-//                        (block_count / block_offsets / scatter_index, which also zero-fill the
-//                        dHidden rows and loss terms of ignored tokens), and a tile is T
-//                        consecutive dense rows, gathered into a dense [T, H] copy (behind the
-//                        rows of the earlier tiles of its dW group).  Their number
-//                        M lives on the device: the host walks ceil(N / T) tiles and the kernels
-//                        of a tile beyond the dense rows leave at once, so nothing waits for the
-//                        host.
+//   0. index / gather    rows whose label is ignored take no part in the loss or in either gradient:
+//                        once per call the valid rows are numbered densely in sequence order, and
+//                        the launches below work on CHUNKS of consecutive dense rows, gathered into
+//                        a dense [rows, H] copy (behind the rows of the earlier chunks of their dW
+//                        group).  A chunk is as many of the caller's tiles as the scratch holds
+//                        anyway for the dW group (one tile under ALST_FLAG_TILE_SCRATCH).  The
+//                        number M of dense rows lives on the device: the host walks the chunks of
+//                        N rows and the kernels of a chunk beyond the dense rows leave at once, so
+//                        nothing waits for the host.
 //   1. logits_kernel     Z = H_c W^T in 256x256 blocks, fp32 accumulators.  The logits never
 //                        leave the registers: the epilogue picks out the label logit, writes
-//                        e = exp(z - ref_i) as bf16 to a [T, V] scratch ("stash", also laid out
+//                        e = exp(z - ref_i) as bf16 to a [rows, V] scratch ("stash", also laid out
 //                        per dW group) and reduces each row over the block's columns to
-//                        (max, sum e) partials per 128-column group.  ref_i is ONE reference per
+//                        a sum-of-e partial per 128-column group.  ref_i is ONE reference per
 //                        row (0 to begin with), so a row's softmax is e / S_i with S_i = sum_v e:
 //                        the scale is a per-row scalar that the consumers of the stash apply.
 //   2. row_finish        partials -> S_i, lse_i = ref_i + log S_i, per-row loss; the label entry of
@@ -26,7 +26,7 @@
 //                        whose S_i left the safe range of the bf16 / fp32 exponents (logits
 //                        beyond about +-40) is redone with ref_i = its exact maximum: a second,
 //                        conditional launch of 1. and 2. whose workgroups leave at once when no
-//                        row of the tile asked for it.
+//                        row of the chunk asked for it.
 //   3. dhidden_kernel    dH_i = (g/M) (1/S_i) e'_i W   (contraction over V), rows scattered back
 //   4. dw_kernel         acc += (H_c / S)^T e'         once per group of tiles (contraction over
 //                        the group's dense rows, fp32)
@@ -59,16 +59,14 @@ struct Header {
     double loss_sum;
 };
 
-// What tile_info_kernel leaves for the other kernels of a tile.
-struct TileInfo {
-    int Tc;                // rows of the tile that take part (valid label)
+// What gather_rows_kernel leaves for the other kernels of a chunk.
+struct ChunkInfo {
+    int Tc;                // dense rows of the chunk (valid label)
     int Trc;               // Tc rounded up to the block height (256)
-    int Tkc;               // Tc rounded up to the k-step (64)
-    int kofs;              // where the tile's dense rows start along k in the dW group buffers
-    int splits;            // dHidden: ranges the contraction over V is cut into for this tile
+    int splits;            // dHidden: ranges the contraction over V is cut into for this chunk
     int ksteps;            //          k-steps of 64 per range (the last range may be shorter)
-    int redo;              // set by row_finish: some row of the tile needs the second logits pass
-    int pad;
+    int redo;              // set by row_finish: some row of the chunk needs the second logits pass
+    int pad[3];
 };
 
 // dW is accumulated into the fp32 [V, H] sums once per GROUP of consecutive tiles: the dense
@@ -92,42 +90,43 @@ constexpr int kScanThreads = 1024;   // rows per block of the compaction kernels
 struct Layout {
     int64_t Tp, Vp, ng;    // padded tile rows, padded vocabulary, 128-column groups
     int64_t Hk;            // row pitch of the dense hidden copy: H rounded up to whole k-steps
-    int g;                 // tiles per dW group
-    int64_t Kg;            // dense rows a group can hold: g * Tp
+    int g;                 // the caller's tiles per dW group
+    int64_t Kg;            // dense rows the group's buffers hold: g * Tp
+    int64_t Rc;            // most dense rows per chunk of launches, a multiple of 256
     int dh_PR, dh_PC;      // dHidden: patch shape of the block -> tile mapping
-    int64_t dh_patches;    //          most patches (over all ranges) a tile of any number of rows needs
-    int64_t dh_part_rows;  //          most rows of fp32 partial products (0: never cut)
-    size_t header, tinfo, loss_rows, lse, idx, block_cnt, block_ofs, zlabel, yc, ref, frow, rowstate,
-        pm, ps, hc, stash, wt, part, acc, total;
+    int64_t dh_patches;    //          most patches (over all ranges) a chunk of any number of rows needs
+    int64_t dh_part_rows;  //          most rows of fp32 partial products
+    bool dh_cut;           //          some number of rows has its contraction cut into ranges
+    size_t header, cinfo, loss_rows, lse, idx, block_cnt, block_ofs, zlabel, yc, ref, frow, rowstate,
+        rmax, ps, part, hc, stash, wt, acc, total;
 };
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// dHidden has (rows / 256) * (H / 256) output blocks for a tile of `rows` dense rows (a multiple
-// of 256).  Picks the number of ranges (1..8) the contraction over V is cut into so that the
-// workgroups fill the 256 compute units of the chip most evenly (ties: fewest ranges), each range
-// keeping at least 64 k-steps.  The tile's row count is known on the device only, so
-// tile_info_kernel makes the choice; the host evaluates the same function for every possible row
-// count to size the launch and the buffer of partial products.
+// dHidden has (rows / 256) * (H / 256) output blocks for a chunk of `rows` dense rows (a multiple
+// of 256).  Picks the number of ranges (1..8) the contraction over V is cut into: the one with the
+// least estimated time, in units of a k-step of one block (1.5 us on gfx950): rounds of the 256
+// compute units times (k-steps per range + about 4 for the block's start and epilogue) and, if cut,
+// the partial products' way through memory (256 KB per block and range written and read back at
+// about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps at least 16 k-steps.
+// The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
+// host evaluates the same function for every possible row count to size the launch.
 constexpr int kComputeUnits = 256;
-// part_rows_cap: the ranges' fp32 partial products (splits * rows rows) must fit that many rows
-// (0: no limit).
+// part_rows_cap: the ranges' fp32 partial products (splits * rows rows) must fit that many rows.
 __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t V, int64_t part_rows_cap,
                                                int& splits, int& ksteps) {
     const int64_t blocks = (rows / kBlockR) * ((H + kBlockC - 1) / kBlockC);
     const int KT = (int)((V + kBlockK - 1) / kBlockK);
-    int64_t best_wg = 0, best_slots = 1;               // fill = best_wg / best_slots
     splits = 1;
-    // with 16 or more rounds of workgroups the chip is filled to 16/17 or better as it is (and the
-    // products below stay small)
+    int64_t best = INT64_MAX;
+    // (with 16 or more rounds of workgroups the chip is filled to 16/17 or better as it is)
     const int sp_max = blocks >= 16 * kComputeUnits ? 1 : 8;
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int per = (KT + sp - 1) / sp;
-        if (sp > 1 && (per < 64 || (int64_t)(sp - 1) * per >= KT)) break;
-        if (sp > 1 && part_rows_cap > 0 && sp * rows > part_rows_cap) break;
-        const int64_t wg = blocks * sp;
-        const int64_t slots = (wg + kComputeUnits - 1) / kComputeUnits * kComputeUnits;
-        if (wg * best_slots > best_wg * slots) { best_wg = wg; best_slots = slots; splits = sp; }
+        if (sp > 1 && (per < 16 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
+        const int64_t rounds = (blocks * sp + kComputeUnits - 1) / kComputeUnits;
+        const int64_t cost = 16 * rounds * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
+        if (cost < best) { best = cost; splits = sp; }
     }
     ksteps = (KT + splits - 1) / splits;
 }
@@ -145,7 +144,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     L.header = take(sizeof(Header));
-    L.tinfo = take(sizeof(TileInfo) * kDwGroupMax);
+    L.cinfo = take(sizeof(ChunkInfo));
     // the O(N) part: 12 bytes per row + 12 bytes per kScanThreads rows
     const size_t nblocks = ((size_t)N + kScanThreads - 1) / kScanThreads;
     L.loss_rows = take((size_t)N * 4);
@@ -153,40 +152,51 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     L.idx = take((size_t)N * 4);
     L.block_cnt = take(nblocks * 4);
     L.block_ofs = take(nblocks * 8);
-    L.zlabel = take((size_t)L.Tp * 4);
-    L.yc = take((size_t)L.Tp * 4);
-    L.ref = take((size_t)L.Tp * 4);
-    L.frow = take((size_t)L.Tp * 4);
-    L.rowstate = take((size_t)L.Tp * 4);
-    L.pm = take((size_t)L.ng * L.Tp * 4);
-    L.ps = take((size_t)L.ng * L.Tp * 4);
-    // hc and stash hold the dense rows of the whole group, each tile at its k offset: they are
-    // the two operands of the group's dW product as they are (k = dense row, the slow index)
+    // Per-row arrays, softmax partials and partial dHidden products of one chunk.  The region is
+    // sized for one tile (20 bytes per row, 8 per row and 128-column group, the partial products a
+    // full tile needs); a chunk then takes as many rows of the dW group as fit it with 24 bytes
+    // per row and 4 per row and group (the partial products of dHidden reuse the softmax partials'
+    // place, which row_finish has consumed by then).
+    int sp_full, ks;
+    dhidden_splits(L.Tp, H, V, 8 * L.Tp, sp_full, ks);
+    const size_t region = (size_t)L.Tp * (20 + 8 * (size_t)L.ng) +
+                          (fwd_only ? 0 : (size_t)sp_full * L.Tp * H * 4);
+    const size_t at = take(region);
+    const int64_t fit = (int64_t)(region / (24 + 4 * (size_t)L.ng)) / kBlockR * kBlockR;
+    const int64_t rows = (N + kBlockR - 1) / kBlockR * kBlockR, Kn = L.Kg < rows ? L.Kg : rows;
+    const int64_t parts = (Kn + fit - 1) / fit;
+    L.Rc = ((Kn + parts - 1) / parts + kBlockR - 1) / kBlockR * kBlockR;     // <= fit, a multiple of 256
+    L.zlabel = at;
+    L.yc = L.zlabel + (size_t)L.Rc * 4;
+    L.ref = L.yc + (size_t)L.Rc * 4;
+    L.frow = L.ref + (size_t)L.Rc * 4;
+    L.rowstate = L.frow + (size_t)L.Rc * 4;
+    L.rmax = L.rowstate + (size_t)L.Rc * 4;
+    L.ps = L.part = L.rmax + (size_t)L.Rc * 4;
+    // hc and stash hold the dense rows of the whole group: they are the two operands of the
+    // group's dW product as they are (k = dense row, the slow index)
     L.hc = take((size_t)L.Kg * L.Hk * 2);
     L.stash = take(fwd_only ? 0 : (size_t)L.Kg * L.Vp * 2);
     // W transposed, [H, Vp] with zeros beyond V: the second operand of dH = dZ W, k-contiguous
     L.wt = take(fwd_only ? 0 : (size_t)H * L.Vp * 2);
-    {   // dHidden: the launch and the partial products are sized for the worst tile
-        const PatchGrid pg = choose_patches((int)(L.Tp / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
+    {   // dHidden: the launch is sized for the worst chunk
+        const PatchGrid pg = choose_patches((int)(L.Rc / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
         L.dh_PR = pg.PR; L.dh_PC = pg.PC;
-        // partial products: what a full tile needs, and no less than one tile's rows, so that a
-        // smaller last tile may be cut into more ranges than a full one
-        int sp_full, ks;
-        dhidden_splits(L.Tp, H, V, 0, sp_full, ks);
-        L.dh_part_rows = (int64_t)sp_full * L.Tp;
+        L.dh_part_rows = (int64_t)((at + region - L.part) / ((size_t)H * 4));
         L.dh_patches = 0;
-        // (beyond 4096 row blocks per tile only the full tile is looked at; tile_info_kernel then
-        // keeps a smaller tile's choice within these bounds)
-        const int64_t rb_max = L.Tp / kBlockR, rb_lo = rb_max > 4096 ? rb_max : 1;
+        L.dh_cut = false;
+        // (beyond 4096 row blocks per chunk only the full chunk is looked at; gather_rows_kernel
+        // then keeps a smaller chunk's choice within these bounds)
+        const int64_t rb_max = L.Rc / kBlockR, rb_lo = rb_max > 4096 ? rb_max : 1;
         for (int64_t rb = rb_lo; rb <= rb_max; ++rb) {
             int sp;
             dhidden_splits(rb * kBlockR, H, V, L.dh_part_rows, sp, ks);
             const PatchGrid g = {(int)rb, pg.tiles_c, pg.PR, pg.PC};
             const int64_t patches = g.patches64() * sp;
             if (patches > L.dh_patches) L.dh_patches = patches;
+            L.dh_cut = L.dh_cut || sp > 1;
         }
     }
-    L.part = take(fwd_only ? 0 : (size_t)L.dh_part_rows * H * 4);
     const bool acc_in_dw = (flags & ALST_FLAG_DW_FP32) && !(flags & ALST_FLAG_DW_ACCUMULATE);
     L.acc = take(acc_in_dw || fwd_only ? 0 : (size_t)V * H * 4);
     L.total = o;
@@ -214,8 +224,9 @@ __device__ __forceinline__ bool label_valid(int y, int ignore_index, int V) {
 //   block_count_kernel   valid rows per block
 //   block_offsets_kernel exclusive scan of the block counts (one workgroup), M = their sum
 //   scatter_index_kernel rank inside the block + block offset -> idx; rows that take no part get
-//                        loss term 0 and lse 0 (forward) and a zero dHidden row (backward).
-// The dense rows are then cut into tiles of T rows: tile t = dense rows [t T, min((t + 1) T, M)).
+//                        loss term 0 and lse 0 (forward).
+// and, for up to kIndexRows rows, one kernel of one workgroup in place of the four launches (a
+// launch costs about 5 us; at 32768 rows the one workgroup takes 8 us).
 __device__ __forceinline__ int block_rank(bool valid, int* wave_total, int& total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long mask = __ballot(valid);
@@ -282,99 +293,179 @@ __global__ __launch_bounds__(kScanThreads) void block_offsets_kernel(
 }
 
 __global__ __launch_bounds__(kScanThreads) void scatter_index_kernel(
-    const int32_t* __restrict__ labels, int64_t N, int H, int ignore_index, int V,
+    const int32_t* __restrict__ labels, int64_t N, int ignore_index, int V,
     const int64_t* __restrict__ block_ofs, int32_t* __restrict__ idx, float* __restrict__ lse,
-    float* __restrict__ loss_rows, uint16_t* __restrict__ dHidden) {
+    float* __restrict__ loss_rows) {
     __shared__ int wave_total[kScanThreads / 64];
-    __shared__ unsigned char is_valid[kScanThreads];
-    const int64_t row0 = (int64_t)blockIdx.x * kScanThreads;
-    const int64_t i = row0 + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * kScanThreads + threadIdx.x;
     const int y = i < N ? labels[i] : ignore_index;
     const bool valid = i < N && label_valid(y, ignore_index, V);
     int total;
     const int rank = block_rank(valid, wave_total, total);
-    is_valid[threadIdx.x] = valid ? 1 : 0;
     if (valid) idx[block_ofs[blockIdx.x] + rank] = (int32_t)i;
     else if (i < N) {
         if (lse) lse[i] = 0.f;
         if (loss_rows) loss_rows[i] = 0.f;
     }
-    if (!dHidden || total == kScanThreads) return;
-    __syncthreads();
-    const int chunks = H / 8;
-    const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-    for (int r = 0; r < kScanThreads && row0 + r < N; ++r) {
-        if (is_valid[r]) continue;
-        u32x4_t* dst = reinterpret_cast<u32x4_t*>(dHidden + (row0 + r) * H);
-        for (int c = threadIdx.x; c < chunks; c += kScanThreads) dst[c] = zero4;
-    }
 }
 
-// The counts of tile t (dense rows [t T, t T + T) cut at M) and its k offset inside its dW group.
-__global__ void tile_info_kernel(const Header* __restrict__ h, int64_t t, int64_t T,
-                                 TileInfo* __restrict__ info, const TileInfo* __restrict__ prev,
-                                 int64_t H, int64_t V, int64_t Tp, int64_t dh_patches,
-                                 int64_t dh_part_rows, int PR, int PC) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    long long left = h->n_valid - t * T;
-    const int Tc = (int)(left < 0 ? 0 : (left > T ? T : left));
-    const int Trc = (Tc + kBlockR - 1) / kBlockR * kBlockR;
-    info->Tc = Tc;
-    info->Trc = Trc;
-    info->Tkc = (Tc + kBlockK - 1) / kBlockK * kBlockK;
-    info->kofs = prev ? prev->kofs + prev->Tkc : 0;     // prev: the tile before, same dW group
-    // dHidden of this tile: as many ranges of V as fill the chip best for its Trc rows, within
-    // what the launch and the buffer of partial products were sized for
-    int sp = 1, ks = (int)((V + kBlockK - 1) / kBlockK);
-    if (Trc > 0) {
-        dhidden_splits(Trc, H, V, dh_part_rows, sp, ks);
-        const PatchGrid g = {Trc / kBlockR, (int)((H + kBlockC - 1) / kBlockC), PR, PC};
-        if ((int64_t)g.patches() * sp > dh_patches || (sp > 1 && (int64_t)sp * Trc > dh_part_rows))
-            dhidden_splits(Tp, H, V, 0, sp, ks);        // the full tile's choice always fits
-        if ((int64_t)g.patches() * sp > dh_patches || (sp > 1 && (int64_t)sp * Trc > dh_part_rows)) {
-            sp = 1;
-            ks = (int)((V + kBlockK - 1) / kBlockK);
+// The whole compaction in one workgroup: wavefront w owns the consecutive rows [w span, (w + 1) span),
+// counts them, and after one scan over the wavefronts numbers them.
+constexpr int64_t kIndexRows = 32768;
+__global__ __launch_bounds__(kScanThreads) void index_rows_kernel(
+    const int32_t* __restrict__ labels, int N, int ignore_index, int V, float grad_loss, int sum_mode,
+    int32_t* __restrict__ idx, float* __restrict__ lse, float* __restrict__ loss_rows, Header* h,
+    int64_t* __restrict__ n_valid_out) {
+    constexpr int kWaves = kScanThreads / 64;
+    __shared__ int wave_total[kWaves], wave_bad[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int span = (N + kScanThreads - 1) / kScanThreads * 64, lo = wave * span;
+    int count = 0, bad = 0;
+    // eight loads in flight; act(row, label) for the wavefront's rows in order, 64 at a time
+    auto for_rows = [&](auto act) {
+        for (int o = 0; o < span; o += 512) {
+            int y[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int i = lo + o + j * 64 + lane;
+                y[j] = o + j * 64 < span && i < N ? labels[i] : ignore_index;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) act(lo + o + j * 64 + lane, y[j], o + j * 64 < span);
         }
+    };
+    for_rows([&](int, int y, bool) {
+        const bool valid = label_valid(y, ignore_index, V);
+        count += __popcll(__ballot(valid));
+        bad |= (y != ignore_index && !valid) ? 1 : 0;
+    });
+    bad = __ballot(bad != 0) != 0ull ? 1 : 0;
+    if (lane == 0) {
+        wave_total[wave] = count;
+        wave_bad[wave] = bad;
     }
-    info->splits = sp;
-    info->ksteps = ks;
-    info->redo = 0;
+    __syncthreads();
+    int before = 0, total = 0;
+    bad = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const int c = wave_total[w];
+        if (w < wave) before += c;
+        total += c;
+        bad |= wave_bad[w];
+    }
+    if (threadIdx.x == 0) {
+        h->status = bad ? (int)ALST_ERR_LABEL_RANGE : 0;
+        h->n_valid = total;
+        h->inv = total > 0 ? (sum_mode ? grad_loss : grad_loss / (float)total) : 0.f;
+        h->loss_sum = 0.0;
+        if (n_valid_out) *n_valid_out = total;
+    }
+    for_rows([&](int i, int y, bool mine) {
+        const bool valid = label_valid(y, ignore_index, V);
+        const unsigned long long mask = __ballot(valid);
+        if (valid)
+            idx[before + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0))] = i;
+        else if (mine && i < N) {
+            if (lse) lse[i] = 0.f;
+            if (loss_rows) loss_rows[i] = 0.f;
+        }
+        before += __popcll(mask);
+    });
 }
 
-// Block b: dense row b of the tile.  Copies the hidden row of token idx_t[b] into the dense
-// matrix Hc (row pitch Hk = H rounded up to whole k-steps, zeros behind the H elements: the logits
-// GEMM contracts over Hk) and its label into yc; rows Tc <= b < Trc are zero padding.  Hc holds
-// the whole dW group and the tile's rows start at its k offset.  Also sets the row's softmax reference for the
-// first logits pass (0; backward from a saved lse: that lse, so that e is the probability itself)
-// and marks the row as taking part in that pass.
-__global__ __launch_bounds__(256) void gather_rows_kernel(
-    const uint16_t* __restrict__ hidden, const int32_t* __restrict__ labels, int H, int Hk,
-    const int32_t* __restrict__ idx_t, const TileInfo* __restrict__ info,
-    const float* __restrict__ lse_in, uint16_t* __restrict__ Hc, int32_t* __restrict__ yc,
-    float* __restrict__ ref, int32_t* __restrict__ rowstate) {
-    const int b = blockIdx.x;
-    const int chunks = Hk / 8, src_chunks = H / 8;      // the row pitch Hk is H in whole k-steps
-    if (b >= info->Trc) return;
-    Hc += (int64_t)info->kofs * Hk;
-    u32x4_t* dst = reinterpret_cast<u32x4_t*>(Hc + (int64_t)b * Hk);
-    if (b < info->Tc) {
-        const int64_t row = idx_t[b];
-        const u32x4_t* src = reinterpret_cast<const u32x4_t*>(hidden + row * H);
-        const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+// A row's maximum travels as an integer of the same order (atomicMax).
+__device__ __forceinline__ int ordered_int(float v) {
+    const int b = __builtin_bit_cast(int, v);
+    return b >= 0 ? b : b ^ 0x7fffffff;
+}
+__device__ __forceinline__ float from_ordered_int(int k) {
+    return __builtin_bit_cast(float, k >= 0 ? k : k ^ 0x7fffffff);
+}
+
+// Workgroup b < Rc: dense row b of the chunk that starts at dense row `first`.  Copies the hidden
+// row of its token into the dense matrix Hc (the chunk's rows; row pitch Hk = H rounded up to whole
+// k-steps, zeros behind the H elements: the logits GEMM contracts over Hk) and its label into yc;
+// rows Tc <= b < Trc are zero padding.  Also sets the row's softmax reference for the first logits
+// pass (0; backward from a saved lse: that lse, so that e is the probability itself) and marks the
+// row as taking part in that pass.  Workgroup 0 leaves the chunk's counts and its dHidden ranges.
+// Workgroups from Rc on (first chunk, if a gradient is wanted) take kZeroRows rows of the sequence at a
+// time; the dHidden rows of ignored tokens become zeros.
+constexpr int kZeroRows = 16, kZeroBlocksMax = 32768;
+struct GatherParams {
+    const uint16_t* hidden;      // [N, H]
+    const int32_t* labels;       // [N]
+    const int32_t* idx;          // [N]        dense row -> row of the sequence
+    const float* lse_in;         // [N]        backward from a saved lse, or null
+    const Header* hdr;
+    ChunkInfo* info;
+    uint16_t* Hc;                // [Rc, Hk]   the chunk's rows of the dense matrix
+    int32_t* yc;                 // [Rc]
+    float* ref;
+    int32_t *rowstate, *rmax;
+    uint16_t* dHidden;           // [N, H]
+    int64_t N, first;
+    int64_t Rc;                  // the chunk's rows, rounded up to the block height
+    int64_t H, V, dh_patches, dh_part_rows;
+    int Hk, dh_PR, dh_PC, ignore_index;
+};
+__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) {
+    const int64_t b = blockIdx.x;
+    const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+    const int src_chunks = (int)(p.H / 8);
+    if (b >= p.Rc) {
+        const int lane = threadIdx.x & 63;
+        for (int64_t row0 = (b - p.Rc) * kZeroRows; row0 < p.N; row0 += (gridDim.x - p.Rc) * kZeroRows) {
+            const int64_t i = row0 + lane;
+            const bool ignored = lane < kZeroRows && i < p.N && !label_valid(p.labels[i], p.ignore_index, (int)p.V);
+            for (unsigned long long mask = __ballot(ignored); mask; mask &= mask - 1) {
+                u32x4_t* dst = reinterpret_cast<u32x4_t*>(p.dHidden + (row0 + (__ffsll(mask) - 1)) * p.H);
+                for (int c = threadIdx.x; c < src_chunks; c += 256) dst[c] = zero4;
+            }
+        }
+        return;
+    }
+    const long long left = p.hdr->n_valid - p.first;
+    const int Tc = (int)(left < 0 ? 0 : (left > p.Rc ? p.Rc : left));
+    const int Trc = (Tc + kBlockR - 1) / kBlockR * kBlockR;
+    if (b == 0 && threadIdx.x == 0) {
+        p.info->Tc = Tc;
+        p.info->Trc = Trc;
+        p.info->redo = 0;
+        // dHidden of this chunk: the ranges of V that suit its Trc rows, within what the launch
+        // and the buffer of partial products were sized for
+        int sp = 1, ks = 0;
+        dhidden_splits(Trc, p.H, p.V, p.dh_part_rows, sp, ks);
+        const PatchGrid g = {Trc / kBlockR, (int)((p.H + kBlockC - 1) / kBlockC), p.dh_PR, p.dh_PC};
+        if ((int64_t)g.patches() * sp > p.dh_patches) {
+            sp = 1;
+            ks = (int)((p.V + kBlockK - 1) / kBlockK);
+        }
+        p.info->splits = sp;
+        p.info->ksteps = ks;
+    }
+    if (b >= Trc) return;
+    const int chunks = p.Hk / 8;
+    u32x4_t* dst = reinterpret_cast<u32x4_t*>(p.Hc + b * p.Hk);
+    int y = -1;
+    float ref = 0.f;
+    if (b < Tc) {
+        const int64_t row = p.idx[p.first + b];
+        const u32x4_t* src = reinterpret_cast<const u32x4_t*>(p.hidden + row * p.H);
         for (int c = threadIdx.x; c < chunks; c += 256) dst[c] = c < src_chunks ? src[c] : zero4;
         if (threadIdx.x == 0) {
-            yc[b] = labels[row];
-            ref[b] = lse_in ? lse_in[row] : 0.f;
-            rowstate[b] = 1;
+            y = p.labels[row];
+            if (p.lse_in) ref = p.lse_in[row];
         }
     } else {
-        const u32x4_t zero4 = {0u, 0u, 0u, 0u};
         for (int c = threadIdx.x; c < chunks; c += 256) dst[c] = zero4;
-        if (threadIdx.x == 0) {
-            yc[b] = -1;
-            ref[b] = 0.f;
-            rowstate[b] = 1;
-        }
+    }
+    if (threadIdx.x == 0) {
+        p.yc[b] = y;
+        p.ref[b] = ref;
+        p.rowstate[b] = 1;
+        p.rmax[b] = ordered_int(-INFINITY);
     }
 }
 
@@ -386,26 +477,28 @@ enum { MODE_FWD = 0, MODE_FUSED = 1, MODE_BWD = 2 };
 // from overflow.  A row outside is redone with ref = its exact maximum (then 1 <= S <= V).
 constexpr float kSumLo = 8.673617379884035e-19f;      // 2^-60
 constexpr float kSumHi = 1.2676506002282294e30f;      // 2^100
+constexpr float kGroupHi = 1.1805916207174113e21f;    // 2^70
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct RowFinishParams {
-    const float* pm;         // [ng, Tp]  per 128-column group: max z          (first pass only)
-    const float* ps;         // [ng, Tp]  per 128-column group: sum of e
-    const float* zlabel;     // [Tp]      label logit of each dense row
-    const int32_t* yc;       // [Tp]      label of each dense row
-    const int32_t* idx;      // [Tp]      dense row -> row of the sequence
-    TileInfo* info;
-    float* ref;              // [Tp]      the row's reference; rewritten for a row that is redone
-    float* frow;             // [Tp]      1 / S of a finished row (MODE_FUSED), 1 (MODE_BWD)
-    int32_t* rowstate;       // [Tp]      1: the row takes part in the next logits pass, 0: finished
+    const float* ps;         // [ng, Rc]  per 128-column group: sum of e
+    const float* zlabel;     // [Rc]      label logit of each dense row
+    const int32_t* yc;       // [Rc]      label of each dense row
+    const int32_t* idx;      // [Rc]      dense row -> row of the sequence
+    const int32_t* rmax;     // [Rc]      maximum of a row whose sum left the safe range (ordered_int)
+    ChunkInfo* info;
+    float* ref;              // [Rc]      the row's reference; rewritten for a row that is redone
+    float* frow;             // [Rc]      1 / S of a finished row (MODE_FUSED), 1 (MODE_BWD)
+    int32_t* rowstate;       // [Rc]      1: the row takes part in the next logits pass, 0: finished
     float* lse_t;            // [N]       by row of the sequence
     float* loss_rows_t;      // [N]
-    uint16_t* hc;            // [Kg, Hk]  dense hidden rows of the group (scaled in place, MODE_FUSED)
-    uint16_t* stash;         // [Kg, Vp]
-    int Tp, ng, H, Hk, Vp;
+    uint16_t* hc;            // [Rc, Hk]  the chunk's dense hidden rows (scaled in place, MODE_FUSED)
+    uint16_t* stash;         // [Rc, Vp]
+    int64_t Rc;
+    int ng, H, Hk, Vp;
 };
 
-// Per dense row of the tile, after a logits pass: S = sum of the per-group sums of e (fixed order,
+// Per dense row of the chunk, after a logits pass: S = sum of the per-group sums of e (fixed order,
 // so a row's lse depends on nothing but its own partials), lse = ref + log S, the row's loss term
 // (both written to the row's original position) and, when gradients follow,
 //   * the stash entry of the label becomes e_label - S (MODE_FUSED) or p_label - 1 (MODE_BWD),
@@ -416,7 +509,7 @@ struct RowFinishParams {
 //   * the row's dense hidden row is multiplied by f in place: it is the other operand of the
 //     dW product, whose contraction index is the row.
 // First pass (REDO = false): a row whose S is outside [kSumLo, kSumHi] is not finished; its
-// reference becomes its exact maximum, it stays marked, and the tile is flagged for the second
+// reference becomes its exact maximum, it stays marked, and the chunk is flagged for the second
 // pass.  Second pass (REDO = true): leaves at once unless flagged; finishes the marked rows.
 // MODE_BWD has no sums to combine (e is the probability itself): label entries only.
 // Block = 16 rows x 64 lanes: thread (x, y) owns groups y, y + 64, ... of row x; the 64 lanes of a
@@ -432,26 +525,17 @@ __global__ __launch_bounds__(kCombineRows * kCombineLanes) void row_finish_kerne
     const bool inrow = i < p.info->Tc;                    // every dense row below Tc is valid
     const bool marked = p.rowstate[i] != 0;
     __syncthreads();                                      // every thread of a row has read its mark
-    const int Tp = p.Tp, ng = p.ng;
-    float S = 1.f, M = 0.f;
+    const int64_t Rc = p.Rc;
+    const int ng = p.ng;
+    float S = 1.f;
     if (MODE != MODE_BWD) {
         float sum = 0.f;
-        for (int g = y; g < ng; g += kCombineLanes) sum += p.ps[(int64_t)g * Tp + i];
+        for (int g = y; g < ng; g += kCombineLanes) sum += p.ps[g * Rc + i];
         red[y][x] = sum;
         __syncthreads();
         S = red[0][x];
 #pragma unroll
         for (int l = 1; l < kCombineLanes; ++l) S += red[l][x];
-        __syncthreads();
-        if (!REDO) {
-            float m = -INFINITY;
-            for (int g = y; g < ng; g += kCombineLanes) m = fmaxf(m, p.pm[(int64_t)g * Tp + i]);
-            red[y][x] = m;
-            __syncthreads();
-            M = red[0][x];
-#pragma unroll
-            for (int l = 1; l < kCombineLanes; ++l) M = fmaxf(M, red[l][x]);
-        }
     }
     // (rowstate, ref and frow of row i are written by the row's thread y == 0 only, and read above
     // or below by the same thread or before the barriers)
@@ -463,12 +547,12 @@ __global__ __launch_bounds__(kCombineRows * kCombineLanes) void row_finish_kerne
     const bool ok = MODE == MODE_BWD || REDO || (S >= kSumLo && S <= kSumHi);
     if (!ok) {
         if (y == 0) {
+            const float M = from_ordered_int(p.rmax[i]);
             p.ref[i] = (M == -INFINITY || M != M) ? 0.f : M;
             atomicOr(&p.info->redo, 1);
         }
         return;
     }
-    const int kofs = p.info->kofs;
     const float ref = p.ref[i], zl = p.zlabel[i];
     // the label's e, as the logits pass formed it before rounding it to bf16, minus S (MODE_BWD:
     // p - 1, S = 1), rounded to bf16 for the stash
@@ -487,13 +571,13 @@ __global__ __launch_bounds__(kCombineRows * kCombineLanes) void row_finish_kerne
             p.loss_rows_t[orig] = lse - zl;
         }
         if (MODE != MODE_FWD) {
-            p.stash[(int64_t)(kofs + i) * p.Vp + p.yc[i]] = __builtin_bit_cast(uint16_t, d);
+            p.stash[(int64_t)i * p.Vp + p.yc[i]] = __builtin_bit_cast(uint16_t, d);
             p.frow[i] = f;
         }
         p.rowstate[i] = 0;
     }
     if (MODE == MODE_FUSED) {
-        uint16_t* row = p.hc + (int64_t)(kofs + i) * p.Hk;
+        uint16_t* row = p.hc + (int64_t)i * p.Hk;
         for (int c = y; c < p.H / 8; c += kCombineLanes) {
             bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(row + c * 8);
 #pragma unroll
@@ -509,6 +593,7 @@ __global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restri
                                                            float* __restrict__ loss_out) {
     __shared__ double part[1024];
     double s = 0.0;
+#pragma unroll 8
     for (int64_t i = threadIdx.x; i < N; i += 1024) s += (double)loss_rows[i];
     part[threadIdx.x] = s;
     __syncthreads();
@@ -569,26 +654,26 @@ __global__ void shift_labels_kernel(const int32_t* __restrict__ labels, int32_t*
 // the three block GEMMs
 // ---------------------------------------------------------------------------------------------
 struct LogitsParams {
-    const uint16_t* hidden_t;   // [Kg, Hk]     dense (valid) rows of the dW group; the tile's rows
-                                //              start at its k offset and are zero padded to Trc
+     const uint16_t* hidden_t;   // [Rc, Hk]     the chunk's dense (valid) rows, zero padded to Trc
     const uint16_t* W;          // [V, H]
-    const int32_t* labels_t;    // [Tp]         labels of the dense rows
-    const TileInfo* info;
-    const float* ref;           // [Tp]         reference of each dense row: e = exp(z - ref)
-    const int32_t* rowstate;    // [Tp]         second pass: rows that are redone (others keep their results)
-    float* pm;                  // [ng, Tp]     MODE_FWD / MODE_FUSED
-    float* ps;                  // [ng, Tp]
-    float* zlabel;              // [Tp]
-    uint16_t* stash;            // [Kg, Vp]     MODE_FUSED / MODE_BWD; rows as in hidden_t
-    int Tp, H, Hk, V, Vp;       // Tp = row stride of the per-tile arrays
+    const int32_t* labels_t;    // [Rc]         labels of the dense rows
+    const ChunkInfo* info;
+    const float* ref;           // [Rc]         reference of each dense row: e = exp(z - ref)
+    const int32_t* rowstate;    // [Rc]         second pass: rows that are redone (others keep their results)
+    int32_t* rmax;              // [Rc]         maximum of rows whose sums leave the safe range (ordered_int)
+    float* ps;                  // [ng, Rc]     MODE_FWD / MODE_FUSED
+    float* zlabel;              // [Rc]
+    uint16_t* stash;            // [Rc, Vp]     MODE_FUSED / MODE_BWD
+    int64_t Rc;                 // row stride of ps
+    int H, Hk, V, Vp;
     int PR, PC;                 // patch shape of the block -> tile mapping
 };
 
-// r = token row of the tile (MFMA lane dimension), c = vocabulary id (register dimension).
+// r = token row of the chunk (MFMA lane dimension), c = vocabulary id (register dimension).
 // KTAIL: the hidden size is not whole k-steps; the contraction runs over Hk, the dense hidden rows
 // are zero beyond H and the chunks of W's rows beyond H are read from each row's last chunk.
-// REDO: the second pass over a tile, for the rows whose first-pass sums left the safe range; its
-// workgroups leave at once unless row_finish flagged the tile, and rows that are not marked keep
+// REDO: the second pass over a chunk, for the rows whose first-pass sums left the safe range; its
+// workgroups leave at once unless row_finish flagged the chunk, and rows that are not marked keep
 // what the first pass wrote.
 template <class Core, bool KTAIL, int MODE, bool REDO>
 __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsParams p) {
@@ -610,8 +695,7 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
     typename Core::acc_t acc[kMT][kNT];
     zero_acc<Core>(acc);
 
-    const int kofs = p.info->kofs;
-    const uint16_t* const hidden_t = p.hidden_t + (int64_t)kofs * p.Hk;
+    const uint16_t* const hidden_t = p.hidden_t;
     const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, p.V);
     Core::template gemm<false, KTAIL>(hidden_t, p.Hk, Trc, p.W, p.H, p.V, p.Hk, r0, c0, smem, acc, warm,
                                       kBlockK, nullptr, p.H);
@@ -632,15 +716,6 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
             }
         }
         const float ref = p.ref[i];
-        float m = 0.f;
-        if (MODE != MODE_BWD && !REDO) {                  // the row's exact maximum, for a redo
-            m = -INFINITY;
-#pragma unroll
-            for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-                for (int j = 0; j < kRegs; ++j) m = fmaxf(m, acc[mt][nt][j]);
-            m = groups_max<Core::kGroups>(m);
-        }
         {
             // label logit: exactly one lane of one block holds column y of row i.  Few wavefronts
             // hold any (a tile's rows x 128 of V columns), so the search sits behind a uniform branch.
@@ -686,7 +761,7 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
         if (MODE != MODE_FWD) {
             const int lrow = lp.lane >> 4, lcol = lp.lane & 15;        // 4 rows x 16 chunks of 16 B
             const int rb = r0 + lp.rbase(nt);
-            uint16_t* const out = p.stash + (int64_t)(kofs + rb) * p.Vp + c0 + lp.wc * kGroupC + lcol * 8;
+            uint16_t* const out = p.stash + (int64_t)rb * p.Vp + c0 + lp.wc * kGroupC + lcol * 8;
 #pragma unroll
             for (int it = 0; it < Core::kTile / 4; ++it) {
                 const int row = it * 4 + lrow;
@@ -697,26 +772,37 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
         }
         if (MODE != MODE_BWD) {
             s = groups_sum<Core::kGroups>(s);
-            if (lp.grp == 0 && act) {
-                const int64_t g = (c0 + lp.wc * kGroupC) >> 7;
-                if (!REDO) p.pm[g * p.Tp + i] = m;
-                p.ps[g * p.Tp + i] = s;
+            if (lp.grp == 0 && act) p.ps[((c0 + lp.wc * kGroupC) >> 7) * p.Rc + i] = s;
+            if (!REDO) {
+                // A row whose total will leave [kSumLo, kSumHi] needs its exact maximum for the second
+                // pass.  The group that holds it then has s > kSumHi / 2^17 groups / 128 columns, or
+                // (with every other group) s < kSumLo: groups outside [kSumLo, 2^70] report theirs.
+                const bool out = !(s >= kSumLo && s <= kGroupHi);
+                if (__ballot(out) != 0ull) {
+                    float m = -INFINITY;
+#pragma unroll
+                    for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+                        for (int j = 0; j < kRegs; ++j) m = fmaxf(m, acc[mt][nt][j]);
+                    m = groups_max<Core::kGroups>(m);
+                    if (out && lp.grp == 0) atomicMax(p.rmax + i, ordered_int(m));
+                }
             }
         }
     }
 }
 
 struct DHiddenParams {
-    const uint16_t* dz;      // [Kg, Vp]     dense rows of the dW group; the tile starts at its k offset
+    const uint16_t* dz;      // [Rc, Vp]     the chunk's dense rows
     const uint16_t* Wt;      // [H, Vp]      W transposed (k = vocabulary id contiguous), zero beyond V
     uint16_t* dH_t;          // [N, H]       whole dHidden; dense row i goes to row idx[i]
     const int32_t* idx;
-    const TileInfo* info;
+    const ChunkInfo* info;
     const Header* hdr;
-    const float* frow;       // [Tp]         scale of each dense row's result: 1 / S of its softmax
+    const float* frow;       // [Rc]         scale of each dense row's result: 1 / S of its softmax
     float* part;             // [splits, Trc, H] fp32 partial products (splits > 1); the number
-                             // of ranges and their length are the tile's (TileInfo)
-    int Tp, H, V, Vp;
+                             // of ranges and their length are the chunk's (ChunkInfo)
+    int H, V, Vp;
     int PR, PC;              // patch shape of the block -> tile mapping
 };
 
@@ -726,7 +812,7 @@ struct DHiddenParams {
 
 // r = token row (lane dimension), c = hidden index (register dimension), k = vocabulary; both
 // operands k-contiguous (dZ rows and the rows of W transposed).
-// The output has only (T / 256) * (H / 256) blocks, each with a long contraction: when that
+// The output has only (rows / 256) * (H / 256) blocks, each with a long contraction: when that
 // number does not fill the compute units evenly, the contraction is cut into `splits` ranges, each
 // range's blocks write fp32 partial products, and dhidden_reduce_kernel adds them in a fixed
 // order.
@@ -753,7 +839,7 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
     typename Core::acc_t acc[kMT][kNT];
     zero_acc<Core>(acc);
 
-    const uint16_t* const dz = p.dz + (int64_t)p.info->kofs * p.Vp + k0;
+    const uint16_t* const dz = p.dz + k0;
     const uint16_t* const Wk = p.Wt + k0;
     // (a hidden size that ends inside the block: the rows of Wt beyond H are read from its last
     // row, and the epilogue skips those columns)
@@ -802,10 +888,10 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
 }
 
 // dH[idx[i]] = (g/M) (1/S_i) * sum over the ranges of the partial products of dense row i, in
-// range order.  Tiles whose contraction was not cut were written by dhidden_kernel itself.
+// range order.  Chunks whose contraction was not cut were written by dhidden_kernel itself.
 __global__ __launch_bounds__(256) void dhidden_reduce_kernel(const float* __restrict__ part, int H,
                                                              const int32_t* __restrict__ idx,
-                                                             const TileInfo* __restrict__ info,
+                                                             const ChunkInfo* __restrict__ info,
                                                              const Header* __restrict__ hdr,
                                                              const float* __restrict__ frow,
                                                              uint16_t* __restrict__ dH) {
@@ -826,10 +912,11 @@ __global__ __launch_bounds__(256) void dhidden_reduce_kernel(const float* __rest
 }
 
 struct DWParams {
-    const uint16_t* hg;      // [Kg, Hk]     dense hidden rows of the group's tiles (H of the Hk columns used)
+    const uint16_t* hg;      // [Kg, Hk]     the group's dense hidden rows (H of the Hk columns used)
     const uint16_t* dzg;     // [Kg, Vp]     their dZ rows
     float* acc;              // [V, H]
-    const TileInfo* info;    // of the group's last tile: k extent = kofs + Tkc
+    const Header* hdr;
+    int64_t row0, rows;      // the group's dense rows: row0 .. row0 + rows - 1, as far as they exist
     int H, Hk, V, Vp;
     int first;               // first group: store instead of add
     int PR, PC;              // patch shape of the block -> tile mapping
@@ -844,7 +931,9 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     int tr, tc;
     const int tiles_r = (p.H + kBlockR - 1) / kBlockR;
-    const int Tkc = p.info->kofs + p.info->Tkc;      // k extent of the whole group
+    // k extent of the group (its dense rows are zero padded to whole blocks)
+    const int64_t left = p.hdr->n_valid - p.row0;
+    const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
     if (Tkc == 0 && !p.first) return;
     {
         const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
@@ -937,16 +1026,16 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
     if (need_bwd_out && (!aligned16(P.dHidden) || !aligned16(P.dW))) return ALST_ERR_ALIGN;
     const Layout L = make_layout(P.N, P.H, P.V, P.tile, P.flags);
     // every launch must fit a one-dimensional grid
-    if (!checked_grid(L.Tp / kBlockR, L.Vp / kBlockC) ||
+    if (!checked_grid(L.Rc / kBlockR, L.Vp / kBlockC) ||
         !checked_grid((P.H + kBlockR - 1) / kBlockR, L.Vp / kBlockC) ||
         L.dh_patches * 32 > 0x7fffff00 ||                                        // dHidden
-        (L.Vp / 256) * (L.Tp / 64) > 0x7fffffff)
+        L.Rc + kZeroBlocksMax > 0x7fffffff)
         return ALST_ERR_SHAPE;
     if (workspace_bytes < L.total) return own_scratch ? ALST_ERR_NOALLOC_LIMIT : ALST_ERR_WORKSPACE;
     return ALST_OK;
 }
 
-// Grids are sized for Tr (the tile's rows rounded up to the block height); the kernels read the
+// Grids are sized for Tr (the chunk's rows rounded up to the block height); the kernels read the
 // number of rows that take part from the device and surplus blocks leave at once.
 template <int MODE, bool REDO>
 static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
@@ -962,15 +1051,15 @@ static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
-// The logits pass of a tile and the per-row work behind it; for the modes that form the softmax
+// The logits pass of a chunk and the per-row work behind it; for the modes that form the softmax
 // sums, followed by the conditional second pass (see row_finish_kernel).
 template <int MODE>
-static int logits_and_finish(const LogitsParams& lp, const RowFinishParams& fp, int Tr, bool ktail,
+static int logits_and_finish(const LogitsParams& lp, const RowFinishParams& fp, int Tr, int tiles, bool ktail,
                              hipStream_t s) {
     const dim3 fgrid(Tr / kCombineRows), fblock(kCombineRows, kCombineLanes);
     int rc;
     {
-        ProfScope ps_(PROF_LOGITS, s);
+        ProfScope ps_(PROF_LOGITS, s, tiles);
         rc = launch_logits<MODE, false>(lp, Tr, ktail, s);
     }
     if (rc != ALST_OK) return rc;
@@ -997,7 +1086,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     const Layout L = make_layout(P.N, P.H, P.V, P.tile, P.flags);
     hipStream_t s = P.stream;
     Header* hdr = reinterpret_cast<Header*>(P.ws + L.header);
-    TileInfo* infos = reinterpret_cast<TileInfo*>(P.ws + L.tinfo);
+    ChunkInfo* info = reinterpret_cast<ChunkInfo*>(P.ws + L.cinfo);
     float* loss_rows = reinterpret_cast<float*>(P.ws + L.loss_rows);
     float* lse_buf = P.lse_out ? P.lse_out : reinterpret_cast<float*>(P.ws + L.lse);
     float* zlabel = reinterpret_cast<float*>(P.ws + L.zlabel);
@@ -1005,7 +1094,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     int32_t* idx = reinterpret_cast<int32_t*>(P.ws + L.idx);
     int32_t* block_cnt = reinterpret_cast<int32_t*>(P.ws + L.block_cnt);
     int64_t* block_ofs = reinterpret_cast<int64_t*>(P.ws + L.block_ofs);
-    float* pm = reinterpret_cast<float*>(P.ws + L.pm);
+    int32_t* rmax = reinterpret_cast<int32_t*>(P.ws + L.rmax);
     float* ps = reinterpret_cast<float*>(P.ws + L.ps);
     float* ref = reinterpret_cast<float*>(P.ws + L.ref);
     float* frow = reinterpret_cast<float*>(P.ws + L.frow);
@@ -1016,25 +1105,28 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     const bool acc_in_dw = (P.flags & ALST_FLAG_DW_FP32) && !(P.flags & ALST_FLAG_DW_ACCUMULATE);
     float* acc = acc_in_dw ? reinterpret_cast<float*>(P.dW) : reinterpret_cast<float*>(P.ws + L.acc);
 
-    const int H = (int)P.H, V = (int)P.V, Tp = (int)L.Tp, Vp = (int)L.Vp, ng = (int)L.ng;
+    const int H = (int)P.H, V = (int)P.V, Vp = (int)L.Vp, ng = (int)L.ng;
     const int64_t T = P.tile < P.N ? P.tile : P.N;
+    const int sum_mode = (P.flags & ALST_FLAG_REDUCE_SUM) ? 1 : 0;
 
-    hipLaunchKernelGGL(init_header_kernel, dim3(1), dim3(64), 0, s, hdr);
-    {
+    if (P.N <= kIndexRows) {
+        hipLaunchKernelGGL(index_rows_kernel, dim3(1), dim3(kScanThreads), 0, s, P.labels, (int)P.N,
+                           P.ignore_index, V, P.grad_loss, sum_mode, idx, do_fwd ? lse_buf : nullptr,
+                           do_fwd ? loss_rows : nullptr, hdr, P.n_valid_out);
+    } else {
         const int64_t nblocks = (P.N + kScanThreads - 1) / kScanThreads;
+        hipLaunchKernelGGL(init_header_kernel, dim3(1), dim3(64), 0, s, hdr);
         hipLaunchKernelGGL(block_count_kernel, dim3((unsigned)nblocks), dim3(kScanThreads), 0, s,
                            P.labels, P.N, P.ignore_index, V, block_cnt, hdr);
         hipLaunchKernelGGL(block_offsets_kernel, dim3(1), dim3(kScanThreads), 0, s, block_cnt,
-                           nblocks, block_ofs, hdr, P.grad_loss,
-                           (P.flags & ALST_FLAG_REDUCE_SUM) ? 1 : 0, P.n_valid_out);
+                           nblocks, block_ofs, hdr, P.grad_loss, sum_mode, P.n_valid_out);
         hipLaunchKernelGGL(scatter_index_kernel, dim3((unsigned)nblocks), dim3(kScanThreads), 0, s,
-                           P.labels, P.N, H, P.ignore_index, V, block_ofs, idx,
-                           do_fwd ? lse_buf : nullptr, do_fwd ? loss_rows : nullptr,
-                           do_bwd ? P.dHidden : nullptr);
+                           P.labels, P.N, P.ignore_index, V, block_ofs, idx,
+                           do_fwd ? lse_buf : nullptr, do_fwd ? loss_rows : nullptr);
     }
     ALST_HIP(hipGetLastError());
 
-    // The GEMM cores without bounds checks serve every shape.  The row extent of a tile is always
+    // The GEMM cores without bounds checks serve every shape.  The row extent of a chunk is always
     // block-aligned (dense rows are zero padded to a multiple of the block height).
     // (a vocabulary that ends inside a column block: the logits kernel reads the last row of W
     // in place of the missing ones and masks those columns; a hidden size that is not whole
@@ -1052,66 +1144,79 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
         ALST_HIP(hipGetLastError());
     }
 
-    // The host does not know M: it walks ceil(N / T) tiles, the most there can be; the kernels of
-    // a tile beyond the dense rows find Tc = 0 on the device and leave at once.
-    const int64_t ntiles = (P.N + T - 1) / T;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int T_cur = (int)T;
-        const int Tr = (T_cur + kBlockR - 1) / kBlockR * kBlockR;
-        const int slot = (int)(t % L.g);                // position inside the dW group
-        TileInfo* info = infos + slot;
-        const int32_t* idx_t = idx + t * T;             // the tile's dense rows -> sequence rows
+    // The host does not know M: it walks the chunks of N rows, the most there can be; the kernels of
+    // a chunk beyond the dense rows find Tc = 0 on the device and leave at once.
+    int64_t group0 = 0;                                 // first dense row of the dW group
+    for (int64_t first = 0, rows = 0; first < P.N; first += rows) {
+        if (first - group0 == L.Kg) group0 = first;
+        const int64_t at = first - group0;              // the chunk's rows inside the group
+        rows = L.Rc < L.Kg - at ? L.Rc : L.Kg - at;
+        if (rows > P.N - first) rows = P.N - first;
+        const int Tr = (int)((rows + kBlockR - 1) / kBlockR * kBlockR);
+        const bool group_done = at + rows == L.Kg || first + rows == P.N;
+        const int32_t* idx_t = idx + first;             // the chunk's dense rows -> sequence rows
+        // the caller's tiles that begin in this chunk, for the timers
+        const int tiles = (int)((first + rows + T - 1) / T - (first + T - 1) / T);
+        // (the forward-only layout has the rows of one chunk)
+        uint16_t* const hc_t = hc + (do_bwd ? at : 0) * L.Hk;
+        uint16_t* const stash_t = stash + (do_bwd ? at : 0) * L.Vp;
 
         {
             ProfScope small_(PROF_OTHER, s);
-            hipLaunchKernelGGL(tile_info_kernel, dim3(1), dim3(64), 0, s, hdr, t, T, info,
-                               slot ? info - 1 : nullptr, P.H, P.V, L.Tp, L.dh_patches, L.dh_part_rows,
-                               L.dh_PR, L.dh_PC);
-            hipLaunchKernelGGL(gather_rows_kernel, dim3(Tr), dim3(256), 0, s, P.hidden, P.labels, H,
-                               (int)L.Hk, idx_t, info, do_fwd ? nullptr : P.lse_in, hc, yc, ref, rowstate);
+            GatherParams gp;
+            gp.hidden = P.hidden; gp.labels = P.labels; gp.idx = idx; gp.lse_in = do_fwd ? nullptr : P.lse_in;
+            gp.hdr = hdr; gp.info = info; gp.Hc = hc_t; gp.yc = yc; gp.ref = ref; gp.rowstate = rowstate;
+            gp.rmax = rmax; gp.dHidden = P.dHidden;
+            gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
+            gp.dh_patches = L.dh_patches; gp.dh_part_rows = L.dh_part_rows;
+            gp.Hk = (int)L.Hk; gp.dh_PR = L.dh_PR; gp.dh_PC = L.dh_PC; gp.ignore_index = P.ignore_index;
+            int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
+            if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
+            hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(Tr + zero_blocks)), dim3(256), 0, s, gp);
             ALST_HIP(hipGetLastError());
         }
 
         LogitsParams lp;
-        lp.hidden_t = hc;
+        lp.hidden_t = hc_t;
         lp.W = P.W;
         lp.labels_t = yc;
         lp.info = info;
         lp.ref = ref; lp.rowstate = rowstate;
-        lp.pm = pm; lp.ps = ps; lp.zlabel = zlabel; lp.stash = stash;
-        lp.Tp = Tp; lp.H = H; lp.Hk = (int)L.Hk; lp.V = V; lp.Vp = Vp;
+        lp.rmax = rmax; lp.ps = ps; lp.zlabel = zlabel; lp.stash = stash_t;
+        lp.Rc = L.Rc; lp.H = H; lp.Hk = (int)L.Hk; lp.V = V; lp.Vp = Vp;
         RowFinishParams fp;
-        fp.pm = pm; fp.ps = ps; fp.zlabel = zlabel; fp.yc = yc; fp.idx = idx_t; fp.info = info;
+        fp.ps = ps; fp.rmax = rmax; fp.zlabel = zlabel; fp.yc = yc; fp.idx = idx_t; fp.info = info;
         fp.ref = ref; fp.frow = frow; fp.rowstate = rowstate;
-        fp.lse_t = lse_buf; fp.loss_rows_t = loss_rows; fp.hc = hc; fp.stash = stash;
-        fp.Tp = Tp; fp.ng = ng; fp.H = H; fp.Hk = (int)L.Hk; fp.Vp = Vp;
-        if (do_fwd && do_bwd) rc = logits_and_finish<MODE_FUSED>(lp, fp, Tr, ktail_logits, s);
-        else if (do_fwd) rc = logits_and_finish<MODE_FWD>(lp, fp, Tr, ktail_logits, s);
-        else rc = logits_and_finish<MODE_BWD>(lp, fp, Tr, ktail_logits, s);
+        fp.lse_t = lse_buf; fp.loss_rows_t = loss_rows; fp.hc = hc_t; fp.stash = stash_t;
+        fp.Rc = L.Rc; fp.ng = ng; fp.H = H; fp.Hk = (int)L.Hk; fp.Vp = Vp;
+        if (do_fwd && do_bwd) rc = logits_and_finish<MODE_FUSED>(lp, fp, Tr, tiles, ktail_logits, s);
+        else if (do_fwd) rc = logits_and_finish<MODE_FWD>(lp, fp, Tr, tiles, ktail_logits, s);
+        else rc = logits_and_finish<MODE_BWD>(lp, fp, Tr, tiles, ktail_logits, s);
         if (rc != ALST_OK) return rc;
         if (!do_bwd) continue;
 
         {
             DHiddenParams dp;
-            dp.dz = stash; dp.Wt = wt; dp.dH_t = P.dHidden; dp.idx = idx_t;
+            dp.dz = stash_t; dp.Wt = wt; dp.dH_t = P.dHidden; dp.idx = idx_t;
             dp.info = info; dp.hdr = hdr; dp.frow = frow;
             dp.part = reinterpret_cast<float*>(P.ws + L.part);
-            dp.Tp = Tp; dp.H = H; dp.V = V; dp.Vp = Vp;
+            dp.H = H; dp.V = V; dp.Vp = Vp;
             dp.PR = L.dh_PR; dp.PC = L.dh_PC;
-            // enough workgroups for whatever number of rows and ranges the tile turns out to have
+            // enough workgroups for whatever number of rows and ranges the chunk turns out to have
             const int grid = grid_for_patches(L.dh_patches);
-            ProfScope ps_(PROF_DHIDDEN, s);
+            ProfScope ps_(PROF_DHIDDEN, s, tiles);
             hipLaunchKernelGGL((dhidden_kernel<DirectCore>), dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
                                s, dp);
-            if (L.dh_part_rows > 0)
+            if (L.dh_cut)
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr), dim3(256), 0, s, dp.part, H, idx_t,
                                    info, hdr, frow, P.dHidden);
             ALST_HIP(hipGetLastError());
         }
-        if (slot == L.g - 1 || t == ntiles - 1) {           // the group is complete
+        if (group_done) {
             DWParams wp;
-            wp.hg = hc; wp.dzg = stash; wp.acc = acc; wp.info = info;
-            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp; wp.first = (t < L.g);
+            wp.hg = hc; wp.dzg = stash; wp.acc = acc; wp.hdr = hdr;
+            wp.row0 = group0; wp.rows = L.Kg;
+            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp; wp.first = group0 == 0;
             const PatchGrid pg = choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
             wp.PR = pg.PR; wp.PC = pg.PC;
             const int grid = grid_for_patches(pg.patches());
@@ -1124,7 +1229,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
 
     if (do_fwd) {
         hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, loss_rows, P.N, hdr,
-                           (P.flags & ALST_FLAG_REDUCE_SUM) ? 1 : 0, P.loss_out);
+                           sum_mode, P.loss_out);
         ALST_HIP(hipGetLastError());
     }
     if (do_bwd) {
