@@ -5,9 +5,9 @@
 // One workgroup owns a 256 (r) x 256 (c) block of D and walks k in steps of 64 through two LDS
 // stages.  The c index is the MFMA row (register) dimension and r the MFMA column (lane)
 // dimension, so a lane holds, for one r, runs of 4 consecutive c: reductions over c stay mostly
-// inside a lane and stores along c are vector stores.  The DMA cores multiply with
-// v_mfma_f32_16x16x32_bf16 (accumulator tiles of 16 x 16, 4 registers per lane), the
-// register-staged cores with v_mfma_f32_32x32x16_bf16 (32 x 32, 16 registers): on random operands
+// inside a lane and stores along c are vector stores.  The core with two k-contiguous operands
+// multiplies with v_mfma_f32_16x16x32_bf16 (accumulator tiles of 16 x 16, 4 registers per lane), the
+// k-major ones with v_mfma_f32_32x32x16_bf16 (32 x 32, 16 registers): on random operands
 // the 16 x 16 form draws less power per flop (a register-resident loop sustains 1.89 against
 // 1.80 PFLOP/s) and the same block GEMM runs 5.5 - 7.5 % faster with it.  The kernels' epilogues
 // are written against the layout description every core carries (Lane, kTile, kRuns, kGroups).
@@ -21,18 +21,17 @@
 //                                           the token row
 // so that every operand is read from memory as it is and nothing is ever transposed.
 //
-// Two families of cores with the same accumulator interface, each in the three layouts:
-//   DirectCore, MixedCore, KMajorCore
-//               4 wavefronts (one per SIMD), 128 x 128 per wavefront, operands DMA'd straight from
-//               global memory into LDS (global_load_lds_dwordx4), MFMA operands of the two
-//               k-slices of a step held in registers, one barrier in the middle of a k-step so
-//               that the next stage's first operands are read while the second half is
-//               multiplied.  A k-major tile lands in LDS as 64 k-rows and the MFMA operands are
-//               formed by the transposing LDS read (ds_read_b64_tr_b16).  No bounds checks in the
-//               DMA path: every extent block-aligned (see gemm for the exceptions).
-//   StagedCore, StagedMixedCore, StagedKMajorCore
-//               8 wavefronts, 64 x 128 per wavefront, operands staged through registers with
-//               zero fill outside the matrices: the fallback for ragged shapes.
+// Three cores with the same accumulator interface, one per layout: DirectCore, MixedCore, KMajorCore.
+// 4 wavefronts (one per SIMD), 128 x 128 per wavefront, operands DMA'd straight from global memory
+// into LDS (global_load_lds_dwordx4), MFMA operands of the two k-slices of a step held in registers,
+// one barrier in the middle of a k-step so that the next stage's first operands are read while the
+// second half is multiplied.  A k-major tile lands in LDS as 64 k-rows and the MFMA operands are
+// formed by the transposing LDS read (ds_read_b64_tr_b16).
+//
+// Ragged extents cost the k-loop nothing: a lane chooses where its DMA reads from, so the rows (or
+// columns) an operand lacks inside a block are read from its last one (finite or not, they only
+// reach accumulators that the caller discards), and in the last k-step the k that do not exist are
+// read from a chunk of zeros, for both operands (so that no infinity meets a zero).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -56,6 +55,9 @@ constexpr int kTileBytes = kBlockR * kBlockK * 2;       // one operand tile in L
 constexpr int kStageBytes = 4 * kTileBytes;             // X, Y, two stages each (128 KB)
 constexpr int kLdsBytes = kStageBytes + 1024;           // + landing area of the L2 warm-up loads
 constexpr int kWarmAhead = 3;                           // k-steps between warm-up and DMA of a line
+
+// What a lane reads in place of k that do not exist.
+static __device__ __align__(16) uint32_t zero_chunk[4];
 
 // XCD-aware block -> tile mapping.  Workgroups are dealt round-robin to the 8 XCDs (each with its
 // own L2); the 32 workgroups that are resident together on one XCD get a compact PR x PC patch of
@@ -128,60 +130,40 @@ __device__ __forceinline__ const uint16_t* paired_row(const uint16_t* Y, const u
 // is the launch's patch shape (2 x 16, 4 x 8, 8 x 4 or 16 x 2).
 __device__ __forceinline__ const uint16_t* warm_row(int PR, int PC, const uint16_t* X, int64_t ldx,
                                                     int r0, int tr, const uint16_t* Y, int64_t ldy,
-                                                    int c0, int tc, const uint16_t* Y2 = nullptr,
-                                                    int rows_y = 0x7fffffff) {
+                                                    int c0, int tc, const uint16_t* Y2, int rows_x,
+                                                    int rows_y) {
     const int nx = kBlockR / PC, ny = kBlockC / PR, total = nx + ny, per = (total + 3) / 4;   // per <= 36
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int l = w * per + (lane < per ? lane : per - 1);
     if (l > total - 1) l = total - 1;
-    if (l < nx) return X + (int64_t)(r0 + (tc % PC) * nx + l) * ldx;
+    if (l < nx) {
+        const int row = r0 + (tc % PC) * nx + l;                      // as the DMA: clamped to X (and Y)
+        return X + (int64_t)(row < rows_x ? row : rows_x - 1) * ldx;
+    }
     if (Y2) {
         bool valid;
         return paired_row(Y, Y2, ldy, c0, (tr % PR) * ny + (l - nx), rows_y, valid);
     }
     const int row = c0 + (tr % PR) * ny + (l - nx);
-    return Y + (int64_t)(row < rows_y ? row : rows_y - 1) * ldy;      // as the DMA: clamped to Y
+    return Y + (int64_t)(row < rows_y ? row : rows_y - 1) * ldy;
 }
 
-// The same for k-major operands X[k][ldx], Y[k][ldy]: the 64 k-rows x 512 bytes of a k-step's tile
-// are 256 lines, line L = (k-row L / 4, 128-byte piece L % 4).  `step` = elements between the
-// lane's line in one k-step and the next.
-__device__ __forceinline__ const uint16_t* warm_line_kmajor(int PR, int PC, const uint16_t* X,
-                                                            int64_t ldx, int r0, int tr,
-                                                            const uint16_t* Y, int64_t ldy, int c0,
-                                                            int tc, int64_t& step,
-                                                            int cols_x = 0x7fffffff,
-                                                            int cols_y = 0x7fffffff) {
-    const int nx = kBlockR / PC, ny = kBlockC / PR, total = nx + ny, per = (total + 3) / 4;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int l = w * per + (lane < per ? lane : per - 1);
-    if (l > total - 1) l = total - 1;
-    if (l < nx) {
-        const int L = (tc % PC) * nx + l;
-        step = ldx * kBlockK;
-        const int col = r0 + (L & 3) * 64;
-        return X + (int64_t)(L >> 2) * ldx + (col < cols_x ? col : cols_x - 8);
-    }
-    const int L = (tr % PR) * ny + (l - nx);
-    step = ldy * kBlockK;
-    const int col = c0 + (L & 3) * 64;
-    return Y + (int64_t)(L >> 2) * ldy + (col < cols_y ? col : cols_y - 8);
-}
-
-// X k-contiguous (its lines are rows), Y k-major.
+// The same with a k-major Y[k][ldy]: the 64 k-rows x 512 bytes of a k-step's tile are 256 lines, line
+// L = (k-row L / 4, 128-byte piece L % 4).  `step` = elements between the lane's line in one k-step
+// and the next.
 __device__ __forceinline__ const uint16_t* warm_line_mixed(int PR, int PC, const uint16_t* X,
                                                            int64_t ldx, int r0, int tr,
                                                            const uint16_t* Y, int64_t ldy, int c0,
-                                                           int tc, int64_t& step,
-                                                           int cols_y = 0x7fffffff,
-                                                           int krows_y = 0x7fffffff) {
+                                                           int tc, int64_t& step, int rows_x,
+                                                           int cols_y, int krows_y) {
     const int nx = kBlockR / PC, ny = kBlockC / PR, total = nx + ny, per = (total + 3) / 4;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int l = w * per + (lane < per ? lane : per - 1);
     if (l > total - 1) l = total - 1;
     if (l < nx) {
         step = kBlockK;
-        return X + (int64_t)(r0 + (tc % PC) * nx + l) * ldx;
+        const int row = r0 + (tc % PC) * nx + l;
+        return X + (int64_t)(row < rows_x ? row : rows_x - 1) * ldx;
     }
     const int L = (tr % PR) * ny + (l - nx);
     step = ldy * kBlockK;
@@ -190,10 +172,7 @@ __device__ __forceinline__ const uint16_t* warm_line_mixed(int PR, int PC, const
     return Y + (int64_t)krow * ldy + (col < cols_y ? col : cols_y - 8);
 }
 
-// ---------------------------------------------------------------------------------------------
-// StagedCore: 8 wavefronts, register staging, optional bounds checks
-// ---------------------------------------------------------------------------------------------
-// k-major LDS tiles (both cores): an LDS row is one k-row of 512 bytes = 8 granules of 64 bytes
+// k-major LDS tiles: an LDS row is one k-row of 512 bytes = 8 granules of 64 bytes
 // (32 r or c each); granule g of k-row k lives at granule slot g ^ kswz(k).  One transposing read
 // covers k-rows {R .. R+3, R+8 .. R+11} (R % 4 == 0) at one granule: 8 different slots.
 __device__ __forceinline__ int kswz(int k) { return (k & 3) | (((k >> 3) & 1) << 2); }
@@ -255,179 +234,6 @@ __device__ __forceinline__ float groups_sum(float v) {
     return v + __shfl_xor(v, 32);
 }
 
-// XK / YK: that operand is k-major.
-template <bool XK, bool YK>
-struct StagedCoreT {
-    static constexpr int kThreads = 512;
-    static constexpr int kMT = 4;     // 32-wide c tiles per wavefront
-    static constexpr int kNT = 2;     // 32-wide r tiles per wavefront
-    static constexpr bool kCanGuard = true;
-    // accumulator layout: tiles of kTile x kTile; a lane holds kRuns runs of 4 consecutive c per
-    // tile; kGroups lane groups hold the same r
-    typedef f32x16_t acc_t;
-    static constexpr int kTile = 32, kRuns = 4, kGroups = 2;
-
-    // Where the calling lane's accumulators sit inside the block.
-    struct Lane {
-        int lane, grp, lrow, wr, wc;
-        __device__ __forceinline__ Lane() {
-            const int tid = threadIdx.x;
-            lane = tid & 63;
-            grp = lane >> 5;
-            lrow = lane & 31;
-            const int wave = tid >> 6;
-            wr = wave & 3;
-            wc = wave >> 2;
-        }
-        // row of X (r index inside the block) of accumulator tile nt
-        __device__ __forceinline__ int r(int nt) const { return wr * 64 + nt * 32 + lrow; }
-        // first of the 32 rows of accumulator tile nt that this wavefront holds
-        __device__ __forceinline__ int rbase(int nt) const { return wr * 64 + nt * 32; }
-        // first of the 4 consecutive c held in registers 4q..4q+3 of accumulator tile mt: inside
-        // the wavefront's 128 columns (cw) and inside the block (c)
-        __device__ __forceinline__ int cw(int mt, int q) const { return mt * 32 + q * 8 + grp * 4; }
-        __device__ __forceinline__ int c(int mt, int q) const { return wc * kGroupC + cw(mt, q); }
-    };
-
-    // acc[mt][nt] += X-block(r0) * Y-block(c0)^T over all of K.
-    // GUARD = false requires r0 + 256 <= rows_x, c0 + 256 <= rows_y and K % 64 == 0.
-    // GUARD = true zero-fills outside the operands.  A k-contiguous operand is [rows][ld] with
-    // its rows beyond rows_x / rows_y and its k beyond K read as zero (K % 8 == 0 required); a
-    // k-major operand is [K][ld], the block takes its columns r0 .. r0 + 255 (c0 ..), rows_x
-    // (rows_y) is its number of columns (a multiple of 8), and any K goes.  K_y, if given, is the
-    // k extent of Y where that is shorter than the loop's K (X zero-padded along k, Y not).
-    // Y2: gated pair, see paired_row (k-contiguous Y only).
-    template <bool GUARD>
-    static __device__ __forceinline__ void gemm(const uint16_t* __restrict__ X, int64_t ldx,
-                                                int rows_x, const uint16_t* __restrict__ Y,
-                                                int64_t ldy, int rows_y, int K, int r0, int c0,
-                                                unsigned char* smem, f32x16_t (&acc)[kMT][kNT],
-                                                const uint16_t* /*warm*/ = nullptr,
-                                                int64_t /*warm_stride*/ = 0,
-                                                const uint16_t* Y2 = nullptr, int K_y = -1) {
-        const int tid = threadIdx.x;
-        const Lane lp;
-        if (K_y < 0) K_y = K;
-        // k-contiguous operand: thread -> (row tid / 8 inside a 64-row slab of the tile, 16-byte
-        // chunk tid % 8 along k), slab j = 0..3;  k-major operand: thread -> (k-row tid / 32 + 16 j,
-        // 16-byte chunk of 8 columns tid % 32)
-        const int xrow = XK ? (tid >> 5) : (tid >> 3), xch = XK ? (tid & 31) : (tid & 7);
-        const int yrow = YK ? (tid >> 5) : (tid >> 3), ych = YK ? (tid & 31) : (tid & 7);
-
-        const uint16_t* xp[4];
-        const uint16_t* yp[4];
-        bool xv[4], yv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (XK) {
-                xv[j] = !GUARD || r0 + xch * 8 < rows_x;
-                xp[j] = X + (int64_t)(xrow + 16 * j) * ldx + (xv[j] ? r0 + xch * 8 : 0);
-            } else {
-                const int gx = r0 + xrow + 64 * j;
-                xv[j] = !GUARD || gx < rows_x;
-                xp[j] = X + (int64_t)(xv[j] ? gx : 0) * ldx + xch * 8;
-            }
-            if (YK) {
-                yv[j] = !GUARD || c0 + ych * 8 < rows_y;
-                yp[j] = Y + (int64_t)(yrow + 16 * j) * ldy + (yv[j] ? c0 + ych * 8 : 0);
-            } else if (Y2) {
-                bool valid;
-                yp[j] = paired_row(Y, Y2, ldy, c0, yrow + 64 * j, rows_y, valid) + ych * 8;
-                yv[j] = !GUARD || valid;
-            } else {
-                const int gy = c0 + yrow + 64 * j;
-                yv[j] = !GUARD || gy < rows_y;
-                yp[j] = Y + (int64_t)(yv[j] ? gy : 0) * ldy + ych * 8;
-            }
-        }
-        // k-contiguous tile: 16-byte chunk kc of row `row` lives at chunk slot kc ^ (row & 7) of
-        // its 128-byte row (+ j * 64 rows * 128 B);  k-major tile: see kswz (+ j * 16 k-rows * 512 B)
-        const int xwofs = XK ? xrow * 512 + ((xch ^ (kswz(xrow) << 2)) * 16)
-                             : (xrow * 8 + (xch ^ (xrow & 7))) * 16;
-        const int ywofs = YK ? yrow * 512 + ((ych ^ (kswz(yrow) << 2)) * 16)
-                             : (yrow * 8 + (ych ^ (yrow & 7))) * 16;
-        int rofs[4], xofs[kNT], yofs[kMT];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) rofs[s] = ((2 * s + lp.grp) ^ (lp.lane & 7)) * 16;
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt) xofs[nt] = kmajor_lane_offset(lp.lane, lp.wr * kNT + nt);
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) yofs[mt] = kmajor_lane_offset(lp.lane, lp.wc * kMT + mt);
-        const int xbase = (lp.wr * 64 + lp.lrow) * 128;
-        const int ybase = (lp.wc * kGroupC + lp.lrow) * 128;
-
-        unsigned char* const Xs = smem;
-        unsigned char* const Ys = smem + 2 * kTileBytes;
-
-        u32x4_t xg[4], yg[4];
-        const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-
-        auto load_global = [&](int kt) {
-            const int koff = kt * kBlockK;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (XK) {
-                    const bool kok = !GUARD || (koff + xrow + 16 * j < K);
-                    xg[j] = (xv[j] && kok) ? *reinterpret_cast<const u32x4_t*>(xp[j] + (int64_t)koff * ldx) : zero4;
-                } else {
-                    const bool kok = !GUARD || (koff + xch * 8 + 8 <= K);
-                    xg[j] = (xv[j] && kok) ? *reinterpret_cast<const u32x4_t*>(xp[j] + koff) : zero4;
-                }
-                if (YK) {
-                    const bool kok = !GUARD || (koff + yrow + 16 * j < K_y);
-                    yg[j] = (yv[j] && kok) ? *reinterpret_cast<const u32x4_t*>(yp[j] + (int64_t)koff * ldy) : zero4;
-                } else {
-                    const bool kok = !GUARD || (koff + ych * 8 + 8 <= K_y);
-                    yg[j] = (yv[j] && kok) ? *reinterpret_cast<const u32x4_t*>(yp[j] + koff) : zero4;
-                }
-            }
-        };
-        auto store_lds = [&](int stage) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                *reinterpret_cast<u32x4_t*>(Xs + stage * kTileBytes + xwofs + j * 8192) = xg[j];
-                *reinterpret_cast<u32x4_t*>(Ys + stage * kTileBytes + ywofs + j * 8192) = yg[j];
-            }
-        };
-
-        const int KT = (K + kBlockK - 1) / kBlockK;
-        load_global(0);
-        store_lds(0);
-        __syncthreads();
-
-        for (int kt = 0; kt < KT; ++kt) {
-            const int cur = kt & 1;
-            const bool more = kt + 1 < KT;
-            if (more) load_global(kt + 1);
-            const unsigned char* xs = Xs + cur * kTileBytes + xbase;
-            const unsigned char* ys = Ys + cur * kTileBytes + ybase;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                bf16x8_t yf[kMT], xf[kNT];
-#pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
-                    yf[mt] = YK ? read_kmajor(Ys + cur * kTileBytes + yofs[mt] + s * 8192)
-                                : *reinterpret_cast<const bf16x8_t*>(ys + mt * 4096 + rofs[s]);
-#pragma unroll
-                for (int nt = 0; nt < kNT; ++nt)
-                    xf[nt] = XK ? read_kmajor(Xs + cur * kTileBytes + xofs[nt] + s * 8192)
-                                : *reinterpret_cast<const bf16x8_t*>(xs + nt * 4096 + rofs[s]);
-#pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-                    for (int nt = 0; nt < kNT; ++nt)
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(yf[mt], xf[nt],
-                                                                              acc[mt][nt], 0, 0, 0);
-            }
-            if (more) store_lds(cur ^ 1);
-            __syncthreads();
-        }
-    }
-};
-typedef StagedCoreT<false, false> StagedCore;
-typedef StagedCoreT<true, true> StagedKMajorCore;
-typedef StagedCoreT<false, true> StagedMixedCore;
-
 // ---------------------------------------------------------------------------------------------
 // KMajorDirectT: the DMA core for a k-major Y (and, with XK, a k-major X): v_mfma_f32_32x32x16_bf16
 // ---------------------------------------------------------------------------------------------
@@ -441,7 +247,6 @@ struct KMajorDirectT {
     static constexpr int kThreads = 256;
     static constexpr int kMT = 4;     // 32-wide c tiles per wavefront
     static constexpr int kNT = 4;     // 32-wide r tiles per wavefront
-    static constexpr bool kCanGuard = false;
     typedef f32x16_t acc_t;
     static constexpr int kTile = 32, kRuns = 4, kGroups = 2;
 
@@ -466,24 +271,20 @@ struct KMajorDirectT {
     // kc ^ ((row >> 1) & 7): sixteen consecutive rows at one kc then cover all 64 banks once.
     static __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
-    // Requires K % 64 == 0, K >= 64, 16-byte aligned rows, and a k-contiguous X with r0 + 256 <= its
-    // rows.  GUARD must be false.  Y is [K][ldy] and the block takes its columns c0 .. c0 + 255; a
-    // k-major X is [K][ldx], columns r0 .. r0 + 255.  A k-major operand with rows_x / rows_y
-    // columns (a multiple of 8) may end inside the block: it is read from its last 8 columns in
-    // place of those beyond (a hidden size that is not a multiple of the block width), finite data
-    // of the operand, and the caller discards the accumulator rows / columns that lie outside.
-    // With YTAIL (k-contiguous X only): K_y (if >= 0 and < K) is the k extent Y has when X is
-    // zero-padded along k beyond it (W in dH = dZ W for a vocabulary that is not whole k-steps):
-    // the k-rows of the last step that Y lacks are read from its last row and meet zeros of X.
-    // warm_stride = elements between the lane's warm-up line of one k-step and the next.
-    template <bool GUARD, bool YTAIL = false>
+    // acc += the block's product over all of K >= 1 (16-byte aligned rows).  Y is [K][ldy] and the block
+    // takes its columns c0 .. c0 + 255; a k-major X is [K][ldx], columns r0 .. r0 + 255, a
+    // k-contiguous one [rows_x][ldx] (K a multiple of 8).  Operands may end inside the block: columns of a k-major
+    // operand beyond its rows_x / rows_y (a multiple of 8) are read from its last 8, rows of a
+    // k-contiguous X beyond rows_x from its last row, and the caller discards those accumulators.
+    // KTAIL: K need not be whole k-steps of 64 (see the top of this file).
+    // warm (k-contiguous X only): the lane's warm-up line, warm_stride = elements from one k-step's to
+    // the next.
+    template <bool KTAIL>
     static __device__ __forceinline__ void gemm(const uint16_t* __restrict__ X, int64_t ldx,
                                                 int rows_x, const uint16_t* __restrict__ Y,
                                                 int64_t ldy, int rows_y, int K, int r0, int c0,
                                                 unsigned char* smem, acc_t (&acc)[kMT][kNT],
-                                                const uint16_t* warm, int64_t warm_stride = kBlockK,
-                                                const uint16_t* /*Y2*/ = nullptr, int K_y = -1) {
-        static_assert(!GUARD, "the DMA cores have no bounds checks");
+                                                const uint16_t* warm, int64_t warm_stride) {
         const int tid = threadIdx.x, lane = tid & 63;
         const int w = __builtin_amdgcn_readfirstlane(tid >> 6);       // wave id, provably uniform
         const int wr = w & 1, wc = w >> 1;
@@ -505,37 +306,33 @@ struct KMajorDirectT {
             const int kc = pc ^ swz(row);
             // (the clamps: see the comment of this function)
             if (XK) xg[q] = X + (int64_t)krow * ldx + (r0 + ch * 8 < rows_x ? r0 + ch * 8 : rows_x - 8);
-            else xg[q] = X + (int64_t)(r0 + row) * ldx + kc * 8;
+            else xg[q] = X + (int64_t)(r0 + row < rows_x ? r0 + row : rows_x - 1) * ldx + kc * 8;
             yg[q] = Y + (int64_t)krow * ldy + (c0 + ch * 8 < rows_y ? c0 + ch * 8 : rows_y - 8);
         }
         // elements from one k-step's tile to the next
         const int64_t xstep = XK ? ldx * kBlockK : kBlockK, ystep = ldy * kBlockK;
-        // Y shorter than the loop's K (X zero-padded along k beyond K_y): the lane's sources in the
-        // last k-step, the k-rows Y lacks read from its last row.
-        constexpr bool kTail = YTAIL && !XK;
-        const int KT_ = K / kBlockK;
-        const bool ytail = kTail && K_y >= 0 && K_y < K;
-        const uint16_t* yg_tail[8];
-        if (kTail) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int krow = (KT_ - 1) * kBlockK + w * 16 + q * 2 + (lane >> 5);
-                const int ch = (lane & 31) ^ (kswz(krow) << 2);
-                const int kr = ytail && krow >= K_y ? K_y - 1 : krow;
-                yg_tail[q] = Y + (int64_t)kr * ldy + (c0 + ch * 8 < rows_y ? c0 + ch * 8 : rows_y - 8);
-            }
-        }
-        auto ysrc = [&](int q, int kt) -> const uint16_t* {
-            if (kTail) return (ytail && kt == KT_ - 1) ? yg_tail[q] : yg[q] + kt * ystep;
-            return yg[q] + kt * ystep;
+        const int KT = (K + kBlockK - 1) / kBlockK;
+        const int klast = K - (KT - 1) * kBlockK;                     // k of the last k-step, 1 .. 64
+        // where instruction q of k-step kt reads from; tail: kt is the last k-step
+        auto krow_in = [&](int q) { return w * 16 + q * 2 + (lane >> 5) < klast; };
+        auto zeros = [] { return reinterpret_cast<const uint16_t*>(zero_chunk); };
+        auto xsrc = [&](int q, int kt, bool tail) -> const uint16_t* {
+            const uint16_t* p = xg[q] + kt * xstep;
+            if (!tail) return p;
+            return (XK ? krow_in(q) : (pc ^ swz(q * 8 + lr)) * 8 < klast) ? p : zeros();
+        };
+        auto ysrc = [&](int q, int kt, bool tail) -> const uint16_t* {
+            const uint16_t* p = yg[q] + kt * ystep;
+            return !tail || krow_in(q) ? p : zeros();
         };
         auto issue_loads = [&](int stage, int kt) {
             unsigned char* xs = smem + stage * kTileBytes + w * 8192;
             unsigned char* ys = smem + 2 * kTileBytes + stage * kTileBytes + w * 8192;
+            const bool tail = KTAIL && kt == KT - 1;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                dma_to_lds<16>(xg[q] + kt * xstep, xs + q * 1024);
-                dma_to_lds<16>(ysrc(q, kt), ys + q * 1024);
+                dma_to_lds<16>(xsrc(q, kt, tail), xs + q * 1024);
+                dma_to_lds<16>(ysrc(q, kt, tail), ys + q * 1024);
             }
         };
 
@@ -570,7 +367,6 @@ struct KMajorDirectT {
                                                                       acc[mt][n0 + 1], 0, 0, 0);
         };
 
-        const int KT = K / kBlockK;
         // One 4-byte DMA per wavefront and k-step into a landing area nobody reads: it only pulls
         // the line into L2.  `warm` (see warm_row) must be a valid row pointer in every lane.
         // Not for two k-major operands (the weight-gradient products): measured there, the extra
@@ -578,9 +374,8 @@ struct KMajorDirectT {
         constexpr bool warming = !XK;
         unsigned char* const dump = smem + kStageBytes + w * 256;
         auto warm_step = [&](int kt) {
-            // (with a Y that lacks k-rows of the last step, that step is not warmed: the lane's
-            // line may be one of them)
-            const int last = ytail && KT > 1 ? KT - 2 : KT - 1;
+            // (the last step may lack k-rows, and the lane's line may be one of them: not warmed)
+            const int last = KTAIL && KT > 1 ? KT - 2 : KT - 1;
             const int kk = kt < last ? kt : last;
             dma_to_lds<4>(warm + kk * warm_stride, dump);
         };
@@ -611,11 +406,12 @@ struct KMajorDirectT {
         // burst of DMA writes into LDS delays reads without draining the matrix pipe, and the DMA
         // issue is spread over half a step (left to the scheduler the sixteen DMA instructions
         // come out back to back and the matrix pipe idles behind their issue).
-        // LOADS: step kt + 2 exists.  NEXT: step kt + 1 exists.  The tail steps skip the DMA so
-        // that none is in flight when the workgroup ends.
+        // LOADS: step kt + 2 exists (TAIL: and is the last).  NEXT: step kt + 1 exists.  The last steps skip
+        // the DMA so that none is in flight when the workgroup ends.
         // BEHIND: the previous k-step issued a warm-up load after its DMA.
-        auto kstep = [&](int kt, auto loads, auto next, bool behind) {
+        auto kstep = [&](int kt, auto loads, auto next, auto tail, bool behind) {
             constexpr bool LOADS = decltype(loads)::value, NEXT = decltype(next)::value;
+            constexpr bool TAIL = decltype(tail)::value;
             const int cur = kt & 1;
             unsigned char* const xs = smem + cur * kTileBytes + w * 8192;
             unsigned char* const ys = smem + 2 * kTileBytes + cur * kTileBytes + w * 8192;
@@ -637,7 +433,7 @@ struct KMajorDirectT {
             for (int i = 0; i < 8; ++i) {
                 mfma_pair(2, i);
                 if (LOADS)
-                    dma_to_lds<16>(xg[i] + (kt + 2) * xstep, xs + i * 1024);
+                    dma_to_lds<16>(xsrc(i, kt + 2, TAIL), xs + i * 1024);
                 if (NEXT) read_item(cur ^ 1, 0, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -645,20 +441,26 @@ struct KMajorDirectT {
             for (int i = 0; i < 8; ++i) {
                 mfma_pair(3, i);
                 if (LOADS)
-                    dma_to_lds<16>(ysrc(i, kt + 2), ys + i * 1024);
+                    dma_to_lds<16>(ysrc(i, kt + 2, TAIL), ys + i * 1024);
                 if (NEXT) read_item(cur ^ 1, 1, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (LOADS && warming) warm_step(kt + 2 + kWarmAhead);
         };
         // a step's barrier may leave one load in flight iff the step before it had LOADS and warmed
+        constexpr auto yes = std::true_type{};
+        constexpr auto no = std::false_type{};
         int kt = 0;
-        for (; kt + 2 < KT; ++kt) kstep(kt, std::true_type{}, std::true_type{}, warming && kt > 0);
-        if (KT >= 2) {
-            kstep(kt, std::false_type{}, std::true_type{}, warming && kt > 0);
+        for (; kt + (KTAIL ? 3 : 2) < KT; ++kt) kstep(kt, yes, yes, no, warming && kt > 0);
+        if (KTAIL && KT >= 3) {
+            kstep(kt, yes, yes, yes, warming && kt > 0);
             ++kt;
         }
-        kstep(kt, std::false_type{}, std::false_type{}, false);
+        if (KT >= 2) {
+            kstep(kt, no, yes, no, warming && kt > 0);
+            ++kt;
+        }
+        kstep(kt, no, no, no, false);
     }
 };
 typedef KMajorDirectT<true> KMajorCore;
@@ -676,7 +478,6 @@ struct DirectCore {
     static constexpr int kThreads = 256;
     static constexpr int kMT = 8;     // 16-wide c tiles per wavefront
     static constexpr int kNT = 8;     // 16-wide r tiles per wavefront
-    static constexpr bool kCanGuard = false;
     typedef f32x4_t acc_t;
     static constexpr int kTile = 16, kRuns = 1, kGroups = 4;
 
@@ -704,16 +505,11 @@ struct DirectCore {
     static __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
     // The operands of one output block: D[r0 + r][c0 + c] = sum_k X[r0 + r][k] Y[c0 + c][k].
-    // Requires K % 64 == 0, K >= 64, 16-byte aligned rows and r0 + 256 <= rows of X.
-    // Y (without Y2) may end inside the block: it is read from its row rows_y - 1 in
-    // place of the rows from rows_y on (the logits of a vocabulary that is not a multiple of the
-    // block width), finite data of Y, and the caller discards those accumulator columns.
-    // K_y (used with YTAIL, no Y2): if >= 0 and < K, the k extent Y has when X is zero-padded along k
-    // beyond it (the logits of a hidden size that is not whole k-steps, X being the library's own
-    // zero-padded copy of the hidden rows): the chunks of a row of Y beyond K_y are read from the
-    // row's last chunk (K_y a multiple of 8) and meet zeros of X.
+    // K >= 1 a multiple of 8 (of 64 without KTAIL), 16-byte aligned rows.  Operands may end inside
+    // the block: their rows beyond rows_x / rows_y are read from the last one and the caller
+    // discards those accumulators.
     // Y2: gated pair, see paired_row; rows_y is then the rows of Y and of Y2, the rows of the pair
-    // beyond it are read from row 0 (finite data) and the caller discards those columns.
+    // beyond it are read from row 0 and the caller discards those columns.
     // warm (see warm_row): the lane's warm-up row; warm_stride = elements between its line of one
     // k-step and the next.
     struct Block {
@@ -721,11 +517,10 @@ struct DirectCore {
         int64_t ldx;
         const uint16_t* Y;
         int64_t ldy;
-        int rows_y, K, r0, c0;
+        int rows_x, rows_y, K, r0, c0;
         const uint16_t* warm;
         int64_t warm_stride;
         const uint16_t* Y2;
-        int K_y;
     };
 
     // The k-loop's state: the DMA sources of the block whose operands are being fetched, the LDS
@@ -742,20 +537,18 @@ struct DirectCore {
     //    alternate: a block's step 0 must meet stage 0) and >= 256.  Between start() and
     //    finish() the first kLdsBytes of LDS belong to the chain: an epilogue that turns data
     //    around in LDS does it behind them.
-    template <bool YTAIL>
+    template <bool KTAIL>
     struct Pipe {
         unsigned char* smem;
         int w, lr, pc;                 // wavefront, the lane's row and chunk slot in a DMA instruction
         int rofs[2], xbase, ybase;     // LDS read offsets
-        // the block the DMA works for: the lane's sources of k-step 0, its sources in the last
-        // k-step where Y is shorter than K (clamped), the warm-up row
+        // the block the DMA works for: the lane's sources of k-step 0, the warm-up row, the k-steps
+        // and (KTAIL) the k of the last one
         const uint16_t* xg[8];
         const uint16_t* yg[8];
-        const uint16_t* yg_tail[8];
         const uint16_t* warm;
         int64_t warm_stride;
-        int KT_;
-        bool ytail;
+        int KT_, klast;
         // MFMA operands of the two k-slices of a step: fy[s][t], fx[s][t] for slice s
         bf16x8_t fy[2][8], fx[2][8];
 
@@ -777,39 +570,40 @@ struct DirectCore {
             ybase = 2 * kTileBytes + (wc * kGroupC + l15) * 128;
         }
         __device__ __forceinline__ void target(const Block& b) {
-            KT_ = b.K / kBlockK;
-            ytail = YTAIL && b.K_y >= 0 && b.K_y < b.K;
+            KT_ = (b.K + kBlockK - 1) / kBlockK;
+            if (KTAIL) klast = b.K - (KT_ - 1) * kBlockK;
             warm = b.warm;
             warm_stride = b.warm_stride;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int row = (w * 8 + q) * 8 + lr;
                 const int kc = pc ^ swz(row);
-                xg[q] = b.X + (int64_t)(b.r0 + row) * b.ldx + kc * 8;
+                const int xrow = b.r0 + row < b.rows_x ? b.r0 + row : b.rows_x - 1;     // (the clamps: see Block)
+                xg[q] = b.X + (int64_t)xrow * b.ldx + kc * 8;
                 if (b.Y2) {                         // gated pair
                     bool valid;
                     yg[q] = paired_row(b.Y, b.Y2, b.ldy, b.c0, row, b.rows_y, valid) + kc * 8;   // (missing rows: row 0)
                 } else {
-                    const int yrow = b.c0 + row < b.rows_y ? b.c0 + row : b.rows_y - 1;    // (the clamp: see Block)
+                    const int yrow = b.c0 + row < b.rows_y ? b.c0 + row : b.rows_y - 1;
                     yg[q] = b.Y + (int64_t)yrow * b.ldy + kc * 8;
-                    if (YTAIL) {
-                        const int k = (KT_ - 1) * kBlockK + kc * 8;
-                        yg_tail[q] = b.Y + (int64_t)yrow * b.ldy + (ytail && k >= b.K_y ? b.K_y - 8 : k);
-                    }
                 }
             }
         }
-        __device__ __forceinline__ const uint16_t* ysrc(int q, int kt) const {
-            if (YTAIL) return (ytail && kt == KT_ - 1) ? yg_tail[q] : yg[q] + kt * kBlockK;
-            return yg[q] + kt * kBlockK;
+        // where a lane reads from in DMA instruction q: `base` (xg[q] or yg[q]) moved on to k-step
+        // kt; tail: that is the last k-step, in which the chunks beyond K are zeros
+        __device__ __forceinline__ const uint16_t* src(const uint16_t* base, int q, int kt, bool tail) const {
+            const uint16_t* const p = base + kt * kBlockK;
+            return !tail || (pc ^ swz(q * 8 + lr)) * 8 < klast ? p
+                                                               : reinterpret_cast<const uint16_t*>(zero_chunk);
         }
         __device__ __forceinline__ void issue_loads(int stage, int kt) {
             unsigned char* xs = smem + stage * kTileBytes + w * 8192;
             unsigned char* ys = smem + 2 * kTileBytes + stage * kTileBytes + w * 8192;
+            const bool tail = KTAIL && kt == KT_ - 1;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                dma_to_lds<16>(xg[q] + kt * kBlockK, xs + q * 1024);
-                dma_to_lds<16>(ysrc(q, kt), ys + q * 1024);
+                dma_to_lds<16>(src(xg[q], q, kt, tail), xs + q * 1024);
+                dma_to_lds<16>(src(yg[q], q, kt, tail), ys + q * 1024);
             }
         }
         // item 0..7: the Y operand of accumulator row t = item, 8..15: the X operand of column t
@@ -836,10 +630,7 @@ struct DirectCore {
                 dma_to_lds<4>(ahead->warm + (kt - KT_) * ahead->warm_stride, dump);
                 return;
             }
-            // (with a Y that lacks k of the last step, that step is not warmed: the lane's line
-            // may lie beyond K_y)
-            const int last = ytail && KT_ > 1 ? KT_ - 2 : KT_ - 1;
-            const int kk = kt < last ? kt : last;
+            const int kk = kt < KT_ - 1 ? kt : KT_ - 1;
             dma_to_lds<4>(warm + kk * warm_stride, dump);
         }
         // Joins the wavefronts once this wavefront's DMA of the next stage has landed.  The warm-up
@@ -864,9 +655,10 @@ struct DirectCore {
         // first MFMA then covers reads issued long ago, not the slot's own (1.5 % of the kernel).
         // kt: the step computed (its stage is kt & 1).  LOADS: the DMA of step dkt + 2 of the
         // targeted block is issued (dkt = kt, or kt - KT when the target is the next block of a
-        // chain).  NEXT: step kt + 1 exists.  Steps without LOADS leave no DMA in flight.
+        // chain; TAIL: that is the block's last step).  NEXT: step kt + 1 exists.  Steps without LOADS
+        // leave no DMA in flight.
         // BEHIND: the previous k-step issued a warm-up load after its DMA.
-        template <bool LOADS, bool NEXT>
+        template <bool LOADS, bool NEXT, bool TAIL = false>
         __device__ __forceinline__ void kstep(acc_t (&acc)[kMT][kNT], int kt, int dkt, bool behind,
                                               const Block* ahead) {
             const int cur_stage = kt & 1;
@@ -891,7 +683,7 @@ struct DirectCore {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 mfma_quad(acc, 1, i);
-                if (LOADS) dma_to_lds<16>(xg[i] + (dkt + 2) * kBlockK, xs + i * 1024);
+                if (LOADS) dma_to_lds<16>(src(xg[i], i, dkt + 2, TAIL), xs + i * 1024);
                 if (NEXT) read_item(cur_stage ^ 1, 0, i);
                 __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
                 if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -901,7 +693,7 @@ struct DirectCore {
 #pragma unroll
             for (int i = 8; i < 16; ++i) {
                 mfma_quad(acc, 1, i);
-                if (LOADS) dma_to_lds<16>(ysrc(i - 8, dkt + 2), ys + (i - 8) * 1024);
+                if (LOADS) dma_to_lds<16>(src(yg[i - 8], i - 8, dkt + 2, TAIL), ys + (i - 8) * 1024);
                 if (NEXT) read_item(cur_stage ^ 1, 0, i);
                 __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
                 if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -913,7 +705,7 @@ struct DirectCore {
 
         // ---- one block per workgroup
         __device__ __forceinline__ void single(const Block& b, acc_t (&acc)[kMT][kNT]) {
-            const int KT = b.K / kBlockK;
+            const int KT = (b.K + kBlockK - 1) / kBlockK;
             target(b);
             for (int p = 2; p < 2 + kWarmAhead; ++p) warm_step(p, nullptr);
             issue_loads(0, 0);
@@ -923,7 +715,11 @@ struct DirectCore {
             for (int item = 0; item < 16; ++item) read_item(0, 0, item);
             // a step's barrier may leave one load in flight iff the step before it had LOADS and warmed
             int kt = 0;
-            for (; kt + 2 < KT; ++kt) kstep<true, true>(acc, kt, kt, kt > 0, nullptr);
+            for (; kt + (KTAIL ? 3 : 2) < KT; ++kt) kstep<true, true>(acc, kt, kt, kt > 0, nullptr);
+            if (KTAIL && KT >= 3) {
+                kstep<true, true, true>(acc, kt, kt, kt > 0, nullptr);
+                ++kt;
+            }
             if (KT >= 2) {
                 kstep<false, true>(acc, kt, kt, kt > 0, nullptr);
                 ++kt;
@@ -963,17 +759,10 @@ struct DirectCore {
         __device__ __forceinline__ void finish() { stage_barrier(false); }
     };
 
-    // One block on its own.  GUARD must be false.
-    template <bool GUARD, bool YTAIL = false>
-    static __device__ __forceinline__ void gemm(const uint16_t* __restrict__ X, int64_t ldx,
-                                                int /*rows_x*/, const uint16_t* __restrict__ Y,
-                                                int64_t ldy, int rows_y, int K, int r0, int c0,
-                                                unsigned char* smem, acc_t (&acc)[kMT][kNT],
-                                                const uint16_t* warm, int64_t warm_stride = kBlockK,
-                                                const uint16_t* Y2 = nullptr, int K_y = -1) {
-        static_assert(!GUARD, "the DMA cores have no bounds checks");
-        const Block b = {X, ldx, Y, ldy, rows_y, K, r0, c0, warm, warm_stride, Y2, K_y};
-        Pipe<YTAIL> pipe(smem);
+    // One block on its own.
+    template <bool KTAIL>
+    static __device__ __forceinline__ void gemm(const Block& b, unsigned char* smem, acc_t (&acc)[kMT][kNT]) {
+        Pipe<KTAIL> pipe(smem);
         pipe.single(b, acc);
     }
 };
@@ -1084,7 +873,7 @@ __device__ __forceinline__ void store_block_bf16(const typename Core::acc_t (&ac
 // fire-and-forget fp32 atomic add per register (a plain store when `first`).  Each element
 // belongs to exactly one lane per launch; launches on one stream are ordered, so the sums are
 // formed in launch order: deterministic.  Rows r >= r_valid and c >= c_valid are skipped.
-template <class Core, bool GUARD>
+template <class Core>
 __device__ __forceinline__ void accumulate_block_f32(const typename Core::acc_t (&acc)[Core::kMT][Core::kNT],
                                                      float* __restrict__ out, int64_t ld, int r0,
                                                      int c0, int r_valid, int c_valid, bool first) {

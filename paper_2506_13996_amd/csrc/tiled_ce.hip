@@ -670,8 +670,7 @@ struct LogitsParams {
 };
 
 // r = token row of the chunk (MFMA lane dimension), c = vocabulary id (register dimension).
-// KTAIL: the hidden size is not whole k-steps; the contraction runs over Hk, the dense hidden rows
-// are zero beyond H and the chunks of W's rows beyond H are read from each row's last chunk.
+// KTAIL: the hidden size is not whole k-steps.
 // REDO: the second pass over a chunk, for the rows whose first-pass sums left the safe range; its
 // workgroups leave at once unless row_finish flagged the chunk, and rows that are not marked keep
 // what the first pass wrote.
@@ -696,9 +695,9 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
     zero_acc<Core>(acc);
 
     const uint16_t* const hidden_t = p.hidden_t;
-    const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, p.V);
-    Core::template gemm<false, KTAIL>(hidden_t, p.Hk, Trc, p.W, p.H, p.V, p.Hk, r0, c0, smem, acc, warm,
-                                      kBlockK, nullptr, p.H);
+    const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V);
+    Core::template gemm<KTAIL>({hidden_t, p.Hk, p.W, p.H, Trc, p.V, p.H, r0, c0, warm, kBlockK, nullptr}, smem,
+                               acc);
 
     const typename Core::Lane lp;
 #pragma unroll
@@ -843,8 +842,8 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
     const uint16_t* const Wk = p.Wt + k0;
     // (a hidden size that ends inside the block: the rows of Wt beyond H are read from its last
     // row, and the epilogue skips those columns)
-    const uint16_t* warm = warm_row(p.PR, p.PC, dz, p.Vp, r0, tr, Wk, p.Vp, c0, tc, nullptr, p.H);
-    Core::template gemm<false>(dz, p.Vp, Trc, Wk, p.Vp, p.H, klen, r0, c0, smem, acc, warm);
+    const uint16_t* warm = warm_row(p.PR, p.PC, dz, p.Vp, r0, tr, Wk, p.Vp, c0, tc, nullptr, Trc, p.H);
+    Core::template gemm<false>({dz, p.Vp, Wk, p.Vp, Trc, p.H, klen, r0, c0, warm, kBlockK, nullptr}, smem, acc);
 
     const typename Core::Lane lp;
     if (splits > 1) {
@@ -925,7 +924,7 @@ struct DWParams {
 // r = hidden index (lane dimension), c = vocabulary id (register dimension), k = dense token row:
 // both operands have k as the slow index (k-major cores).  With the hidden index along the lanes
 // the accumulate moves full 128-byte lines of acc (accumulate_block_f32).
-template <class Core, bool GUARD>
+template <class Core>
 __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -946,15 +945,10 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     typename Core::acc_t acc[kMT][kNT];
     zero_acc<Core>(acc);
 
-    if (Tkc > 0) {
-        int64_t step = 0;
-        const uint16_t* warm = Core::kCanGuard ? nullptr
-                                               : warm_line_kmajor(p.PR, p.PC, p.hg, p.Hk, r0, tr, p.dzg,
-                                                                  p.Vp, c0, tc, step, p.H, p.Vp);
-        Core::template gemm<GUARD>(p.hg, p.Hk, p.H, p.dzg, p.Vp, p.Vp, Tkc, r0, c0, smem, acc, warm, step);
-    }
+    if (Tkc > 0)
+        Core::template gemm<false>(p.hg, p.Hk, p.H, p.dzg, p.Vp, p.Vp, Tkc, r0, c0, smem, acc, nullptr, 0);
 
-    accumulate_block_f32<Core, GUARD>(acc, p.acc, p.H, r0, c0, p.H, p.V, p.first != 0);
+    accumulate_block_f32<Core>(acc, p.acc, p.H, r0, c0, p.H, p.V, p.first != 0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -974,7 +968,7 @@ static int prepare_kernels_on_current_device() {
     acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_FUSED, true>));
     acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_FUSED, true>));
     acc(allow_big_lds(dhidden_kernel<DirectCore>));
-    acc(allow_big_lds(dw_kernel<KMajorCore, false>));
+    acc(allow_big_lds(dw_kernel<KMajorCore>));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -1130,8 +1124,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     // block-aligned (dense rows are zero padded to a multiple of the block height).
     // (a vocabulary that ends inside a column block: the logits kernel reads the last row of W
     // in place of the missing ones and masks those columns; a hidden size that is not whole
-    // k-steps: the dense hidden rows are zero padded to Hk and the chunks of W's rows beyond H
-    // are read from each row's last chunk)
+    // k-steps: the chunks of W's rows and of the dense hidden rows beyond H are zeros)
     const bool ktail_logits = (H % kBlockK) != 0;
     // (a hidden size that ends inside a block is handled by the unguarded dHidden and dW kernels:
     // the missing rows of W transposed / columns of the dense hidden rows are read from the last
@@ -1221,7 +1214,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             wp.PR = pg.PR; wp.PC = pg.PC;
             const int grid = grid_for_patches(pg.patches());
             ProfScope ps_(PROF_DW, s);
-            hipLaunchKernelGGL((dw_kernel<KMajorCore, false>), dim3(grid), dim3(KMajorCore::kThreads),
+            hipLaunchKernelGGL((dw_kernel<KMajorCore>), dim3(grid), dim3(KMajorCore::kThreads),
                                kLdsBytes, s, wp);
             ALST_HIP(hipGetLastError());
         }

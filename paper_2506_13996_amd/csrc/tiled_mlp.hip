@@ -93,8 +93,7 @@ struct LinearParams {
     const uint16_t* X2;      // second product summed into the same D (y_kmajor only, same K and
     const uint16_t* Y2;      // leading dimensions), or null
     int64_t ldx, ldy, ldd;
-    int rows_x, rows_y, K;
-    int rows_out, cols_out;  // guarded builds write only r < rows_out, 8-column chunks below cols_out
+    int rows_x, rows_y, K;   // D is [rows_x, rows_y]; rows_y and K multiples of 8
     int y_kmajor;
 };
 
@@ -125,7 +124,8 @@ struct LinearBatch {
     BatchMap map;
 };
 
-template <class Core, bool GUARD>
+// KTAIL: K is not whole k-steps.
+template <class Core, bool KTAIL>
 __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatch b) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -137,27 +137,23 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
     typename Core::acc_t acc[kMT][kNT];
     zero_acc<Core>(acc);
 
-    constexpr bool kMixed = std::is_same<Core, MixedCore>::value || std::is_same<Core, StagedMixedCore>::value;
-    if constexpr (kMixed) {
+    if constexpr (std::is_same<Core, MixedCore>::value) {
         int64_t step = 0;
-        const uint16_t* warm = Core::kCanGuard ? nullptr
-                                               : warm_line_mixed(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy,
-                                                                 c0, tc, step);
-        Core::template gemm<GUARD>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, warm,
-                                   step);
+        const uint16_t* warm = warm_line_mixed(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc, step, p.rows_x,
+                                               p.rows_y, p.K);
+        Core::template gemm<KTAIL>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, warm, step);
         if (p.X2) {
             __syncthreads();        // every wavefront is done with the first product's LDS stages
-            warm = Core::kCanGuard ? nullptr
-                                   : warm_line_mixed(PR, PC, p.X2, p.ldx, r0, tr, p.Y2, p.ldy, c0, tc, step);
-            Core::template gemm<GUARD>(p.X2, p.ldx, p.rows_x, p.Y2, p.ldy, p.rows_y, p.K, r0, c0, smem, acc,
+            warm = warm_line_mixed(PR, PC, p.X2, p.ldx, r0, tr, p.Y2, p.ldy, c0, tc, step, p.rows_x, p.rows_y, p.K);
+            Core::template gemm<KTAIL>(p.X2, p.ldx, p.rows_x, p.Y2, p.ldy, p.rows_y, p.K, r0, c0, smem, acc,
                                        warm, step);
         }
     } else {
-        const uint16_t* warm = Core::kCanGuard ? nullptr
-                                               : warm_row(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc);
-        Core::template gemm<GUARD>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, warm);
+        const uint16_t* warm = warm_row(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc, nullptr, p.rows_x, p.rows_y);
+        Core::template gemm<KTAIL>({p.X, p.ldx, p.Y, p.ldy, p.rows_x, p.rows_y, p.K, r0, c0, warm, kBlockK, nullptr},
+                                   smem, acc);
     }
-    store_block_bf16<Core, GUARD>(acc, p.D, p.ldd, r0, c0, p.rows_out, p.cols_out, smem);
+    store_block_bf16<Core, true>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
 }
 
 // The k-contiguous products on persistent workgroups: one workgroup per compute unit walks the
@@ -166,6 +162,8 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
 // k-steps of its next block while the current block's last two k-steps and epilogue run
 // (DirectCore::Pipe).  total = the launch's block numbers (grid_for_patches).  Every product of
 // the launch has the same K, a multiple of 128 and >= 256.
+// GUARD: some product's rows or columns are not whole blocks.
+template <bool GUARD>
 __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(const LinearBatch b, int total) {
     typedef DirectCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -176,9 +174,10 @@ __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(cons
             if (!b.map.locate(bid, which, tr, tc, PR, PC)) continue;
             const LinearParams& p = b.p[which];
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
-            blk = {uniform(p.X), uniform(p.ldx), uniform(p.Y), uniform(p.ldy), uniform(p.rows_y), uniform(p.K),
-                   uniform(r0), uniform(c0), warm_row(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc), kBlockK,
-                   nullptr, -1};
+            blk = {uniform(p.X), uniform(p.ldx), uniform(p.Y), uniform(p.ldy), uniform(p.rows_x), uniform(p.rows_y),
+                   uniform(p.K), uniform(r0), uniform(c0),
+                   warm_row(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc, nullptr, p.rows_x, p.rows_y), kBlockK,
+                   nullptr};
             which = uniform(which);
             return uniform(bid);
         }
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(cons
         zero_acc<Core>(acc);
         pipe.run(cur, nxt, acc);
         const LinearParams& p = b.p[which];
-        store_block_bf16<Core, false>(acc, p.D, p.ldd, cur.r0, cur.c0, p.rows_out, p.cols_out,
+        store_block_bf16<Core, GUARD>(acc, p.D, p.ldd, cur.r0, cur.c0, p.rows_x, p.rows_y,
                                       smem + kChainTurnOffset);
         cur = nxt;
         which = which_next;
@@ -219,17 +218,16 @@ struct GatedParams {
     const uint16_t* X;       // [rows_x, ldx]   the tile's rows of x
     const uint16_t* Wg;      // [I, ldw]
     const uint16_t* Wu;      // [I, ldw]
-    const uint16_t* da;      // [rows_out, I]   backward
-    uint16_t* a;             // [rows_out, I]
-    uint16_t* dgu;           // [rows_out, 2I]  backward
+    const uint16_t* da;      // [rows_x, I]     backward
+    uint16_t* a;             // [rows_x, I]
+    uint16_t* dgu;           // [rows_x, 2I]    backward
     int64_t ldx, ldw;
     int rows_x, I, K;
-    int rows_out;            // rows written; those from rows_x on come out as zeros
     PatchGrid grid;
 };
 
 // The SwiGLU epilogue of a block whose accumulators hold g (tiles mt < kMT / 2) and u (tile mt + kMT / 2)
-// of the same elements.  CHECK: rows >= rows_out and 8-column chunks beyond I are neither read nor
+// of the same elements.  CHECK: rows >= rows_x and 8-column chunks beyond I are neither read nor
 // written.  tw: this wavefront's LDS turn-around region (kTile rows of kTurnPitch bytes).
 template <class Core, bool BWD, bool CHECK>
 __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
@@ -237,7 +235,6 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
                                                int r0, int c0, unsigned char* tw) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     constexpr int kHalfMT = kMT / 2;
-    constexpr bool kCheckCols = CHECK;
     // Per wavefront and accumulator column nt: kTile rows x 64 columns of I.  Everything that goes
     // to or comes from memory is turned around in the wavefront's own LDS region (as in
     // store_block_bf16) so that global accesses are whole 128-byte row segments.
@@ -245,7 +242,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
     constexpr int kRuns = Core::kRuns, kTile = Core::kTile;
     const int lrow = lp.lane >> 3, lcol = lp.lane & 7;             // 8 rows x 8 chunks of 16 B
     const int gc = (c0 >> 1) + lp.wc * 64 + lcol * 8;              // this lane's 8 columns of I
-    const bool col_ok = !kCheckCols || gc + 8 <= p.I;
+    const bool col_ok = !CHECK || gc + 8 <= p.I;
     const u32x4_t zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int nt = 0; nt < kNT; ++nt) {
@@ -261,7 +258,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
             for (int it = 0; it < kTile / 8; ++it) {
                 const int row = it * 8 + lrow;
                 const u32x4_t val = *reinterpret_cast<const u32x4_t*>(tw + row * kTurnPitch + lcol * 16);
-                if (!kCheckCols || (row0 + row < p.rows_out && col_ok))
+                if (!CHECK || (row0 + row < p.rows_x && col_ok))
                     *reinterpret_cast<u32x4_t*>(dst + (int64_t)(row0 + row) * ld + gc) = val;
             }
         };
@@ -270,7 +267,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
 #pragma unroll
             for (int it = 0; it < kTile / 8; ++it) {
                 const int row = it * 8 + lrow;
-                const bool ok = !kCheckCols || (row0 + row < p.rows_out && col_ok);
+                const bool ok = !CHECK || (row0 + row < p.rows_x && col_ok);
                 const u32x4_t val = ok ? *reinterpret_cast<const u32x4_t*>(p.da + (int64_t)(row0 + row) * p.I + gc)
                                        : zero4;
                 *reinterpret_cast<u32x4_t*>(tw + row * kTurnPitch + lcol * 16) = val;
@@ -305,32 +302,29 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
     }
 }
 
-// CGUARD: I ends inside the block's 128 columns (the unguarded core reads row 0 of Wg / Wu in place
-// of the missing rows; the epilogue skips those columns).
-template <class Core, bool GUARD, bool BWD, bool CGUARD = false>
-__global__ __launch_bounds__(Core::kThreads) void gated_kernel(const GatedParams p) {
-    constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    static_assert(kMT * Core::kTile == kGroupC, "a wavefront's 128 Y rows: 64 of Wg, then the same 64 of Wu");
+// KTAIL: H is not whole k-steps.
+template <bool BWD, bool KTAIL>
+__global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const GatedParams p) {
+    typedef DirectCore Core;
+    static_assert(Core::kMT * Core::kTile == kGroupC, "a wavefront's 128 Y rows: 64 of Wg, then the same 64 of Wu");
     extern __shared__ __align__(16) unsigned char smem[];
     int P, w, tr, tc;
     patch_of_block(blockIdx.x, P, w);
     if (P >= p.grid.patches() || !tile_in_patch(p.grid, P, w, tr, tc)) return;
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;      // c0 / 2 = first of the block's 128 columns of I
 
-    typename Core::acc_t acc[kMT][kNT];
+    Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
 
-    const uint16_t* warm = Core::kCanGuard ? nullptr
-                                           : warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg,
-                                                      p.ldw, c0, tc, p.Wu, p.I);
-    Core::template gemm<GUARD>(p.X, p.ldx, p.rows_x, p.Wg, p.ldw, p.I, p.K, r0, c0, smem, acc, warm,
-                               kBlockK, p.Wu);
-    gated_epilogue<Core, BWD, GUARD || CGUARD>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
+    const uint16_t* warm = warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x,
+                                    p.I);
+    Core::gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, warm, kBlockK, p.Wu}, smem, acc);
+    gated_epilogue<Core, BWD, true>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
 }
 
-// The same on persistent workgroups of the unguarded core (see linear_chain_kernel): K = H a
-// multiple of 128 and >= 256.  total = the launch's block numbers.
-template <bool BWD, bool CGUARD>
+// The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 128 and >= 256.
+// total = the launch's block numbers.  GUARD: rows_x or I is not whole blocks.
+template <bool BWD, bool GUARD>
 __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const GatedParams p, int total) {
     typedef DirectCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -340,9 +334,9 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
             patch_of_block(bid, P, w);
             if (P >= p.grid.patches() || !tile_in_patch(p.grid, P, w, tr, tc)) continue;
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
-            blk = {uniform(p.X), p.ldx, uniform(p.Wg), p.ldw, p.I, p.K, uniform(r0), uniform(c0),
-                   warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.I), kBlockK,
-                   uniform(p.Wu), -1};
+            blk = {uniform(p.X), p.ldx, uniform(p.Wg), p.ldw, p.rows_x, p.I, p.K, uniform(r0), uniform(c0),
+                   warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x, p.I),
+                   kBlockK, uniform(p.Wu)};
             return uniform(bid);
         }
         return -1;
@@ -359,7 +353,7 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
         typename Core::acc_t acc[Core::kMT][Core::kNT];
         zero_acc<Core>(acc);
         pipe.run(cur, nxt, acc);
-        gated_epilogue<Core, BWD, CGUARD>(p, acc, cur.r0, cur.c0, tw);
+        gated_epilogue<Core, BWD, GUARD>(p, acc, cur.r0, cur.c0, tw);
         cur = nxt;
         bid = nbid;
     }
@@ -380,25 +374,20 @@ struct WgradBatch {
     BatchMap map;
 };
 
-template <class Core, bool GUARD>
-__global__ __launch_bounds__(Core::kThreads) void wgrad_kernel(const WgradBatch b) {
-    constexpr int kMT = Core::kMT, kNT = Core::kNT;
+// KTAIL: K is not whole k-steps.
+template <bool KTAIL>
+__global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const WgradBatch b) {
+    typedef KMajorCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
     int which, tr, tc, PR, PC;
     if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC)) return;
     const WgradParams& p = b.p[which];
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
 
-    typename Core::acc_t acc[kMT][kNT];
+    Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
-
-    int64_t step = 0;
-    const uint16_t* warm = Core::kCanGuard ? nullptr
-                                           : warm_line_kmajor(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy,
-                                                              c0, tc, step, p.rows_x, p.rows_y);
-    Core::template gemm<GUARD>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, warm,
-                               step);
-    accumulate_block_f32<Core, GUARD>(acc, p.out, p.ld, r0, c0, p.rows_x, p.rows_y, p.first != 0);
+    Core::gemm<KTAIL>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, nullptr, 0);
+    accumulate_block_f32<Core>(acc, p.out, p.ld, r0, c0, p.rows_x, p.rows_y, p.first != 0);
 }
 
 // out = sums (bf16 or fp32, overwrite or +=).  `sums` may alias `out` (fp32 overwrite mode).
@@ -433,22 +422,21 @@ static int prepare_mlp_kernels_on_current_device() {
     int rc = ALST_OK;
     auto acc = [&](int r) { if (r != ALST_OK) rc = r; };
     acc(allow_big_lds(linear_kernel<DirectCore, false>));
-    acc(allow_big_lds(linear_chain_kernel, kChainLdsBytes));
-    acc(allow_big_lds(linear_kernel<StagedCore, true>));
+    acc(allow_big_lds(linear_kernel<DirectCore, true>));
     acc(allow_big_lds(linear_kernel<MixedCore, false>));
-    acc(allow_big_lds(linear_kernel<StagedMixedCore, true>));
-    acc(allow_big_lds(gated_kernel<DirectCore, false, false>));
-    acc(allow_big_lds(gated_kernel<StagedCore, true, false>));
-    acc(allow_big_lds(gated_kernel<DirectCore, false, true>));
-    acc(allow_big_lds(gated_kernel<DirectCore, false, false, true>));
-    acc(allow_big_lds(gated_kernel<DirectCore, false, true, true>));
+    acc(allow_big_lds(linear_kernel<MixedCore, true>));
+    acc(allow_big_lds(linear_chain_kernel<false>, kChainLdsBytes));
+    acc(allow_big_lds(linear_chain_kernel<true>, kChainLdsBytes));
+    acc(allow_big_lds(gated_kernel<false, false>));
+    acc(allow_big_lds(gated_kernel<false, true>));
+    acc(allow_big_lds(gated_kernel<true, false>));
+    acc(allow_big_lds(gated_kernel<true, true>));
     acc(allow_big_lds(gated_chain_kernel<false, false>, kChainLdsBytes));
     acc(allow_big_lds(gated_chain_kernel<true, false>, kChainLdsBytes));
     acc(allow_big_lds(gated_chain_kernel<false, true>, kChainLdsBytes));
     acc(allow_big_lds(gated_chain_kernel<true, true>, kChainLdsBytes));
-    acc(allow_big_lds(gated_kernel<StagedCore, true, true>));
-    acc(allow_big_lds(wgrad_kernel<KMajorCore, false>));
-    acc(allow_big_lds(wgrad_kernel<StagedKMajorCore, true>));
+    acc(allow_big_lds(wgrad_kernel<false>));
+    acc(allow_big_lds(wgrad_kernel<true>));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -463,11 +451,13 @@ static int prepare_mlp_kernels() {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// One launch for the n products (n <= kMaxBatch).
+// One launch for the n products (n <= kMaxBatch), all of one kind (y_kmajor).
 static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     LinearBatch b = {};
     b.map.n = n;
-    bool direct = true;
+    bool guard = false, ktail = false;
+    // persistent workgroups that fetch their next block early: one K, whole pairs of k-steps
+    bool chain = !ps[0].y_kmajor && ps[0].K % (2 * kBlockK) == 0 && ps[0].K >= 4 * kBlockK;
     int64_t patches = 0;
     for (int i = 0; i < n; ++i) {
         const LinearParams& p = ps[i];
@@ -476,39 +466,35 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
         const int tiles_r = (p.rows_x + kBlockR - 1) / kBlockR, tiles_c = (p.rows_y + kBlockC - 1) / kBlockC;
         b.map.g[i] = choose_patches(tiles_r, tiles_c);
         patches += b.map.g[i].patches();
-        // the unguarded core needs every extent block-aligned and writes every row it computes
-        direct = direct && p.rows_x % kBlockR == 0 && p.rows_y % kBlockC == 0 && p.K % kBlockK == 0 &&
-                 p.K >= kBlockK && p.rows_out >= p.rows_x && p.cols_out >= p.rows_y;
+        guard = guard || p.rows_x % kBlockR != 0 || p.rows_y % kBlockC != 0;
+        ktail = ktail || p.K % kBlockK != 0;
+        chain = chain && p.K == ps[0].K;
     }
     if (patches * 32 > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_patch[i] = (int)patches;
     const int blocks = grid_for_patches(patches);
     ProfScope pr(PROF_MLP_LINEAR, s);
-    const bool mixed = ps[0].y_kmajor != 0;           // the products of one launch are of one kind
-    // persistent workgroups that fetch their next block early: one K, whole pairs of k-steps
-    bool chain = ps[0].K % (2 * kBlockK) == 0 && ps[0].K >= 4 * kBlockK;
-    for (int i = 1; i < n; ++i) chain = chain && ps[i].K == ps[0].K;
-    if (direct && mixed)
-        hipLaunchKernelGGL((linear_kernel<MixedCore, false>), dim3((unsigned)blocks),
-                           dim3(MixedCore::kThreads), kLdsBytes, s, b);
-    else if (direct && chain)
-        hipLaunchKernelGGL(linear_chain_kernel, dim3((unsigned)std::min(blocks, persistent_grid())),
-                           dim3(DirectCore::kThreads), kChainLdsBytes, s, b, blocks);
-    else if (direct)
-        hipLaunchKernelGGL((linear_kernel<DirectCore, false>), dim3((unsigned)blocks),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, b);
-    else if (mixed)
-        hipLaunchKernelGGL((linear_kernel<StagedMixedCore, true>), dim3((unsigned)blocks),
-                           dim3(StagedMixedCore::kThreads), kLdsBytes, s, b);
+    const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
+    const dim3 threads(DirectCore::kThreads);
+    if (ps[0].y_kmajor && ktail)
+        hipLaunchKernelGGL((linear_kernel<MixedCore, true>), all, threads, kLdsBytes, s, b);
+    else if (ps[0].y_kmajor)
+        hipLaunchKernelGGL((linear_kernel<MixedCore, false>), all, threads, kLdsBytes, s, b);
+    else if (chain && guard)
+        hipLaunchKernelGGL((linear_chain_kernel<true>), persistent, threads, kChainLdsBytes, s, b, blocks);
+    else if (chain)
+        hipLaunchKernelGGL((linear_chain_kernel<false>), persistent, threads, kChainLdsBytes, s, b, blocks);
+    else if (ktail)
+        hipLaunchKernelGGL((linear_kernel<DirectCore, true>), all, threads, kLdsBytes, s, b);
     else
-        hipLaunchKernelGGL((linear_kernel<StagedCore, true>), dim3((unsigned)blocks),
-                           dim3(StagedCore::kThreads), kLdsBytes, s, b);
+        hipLaunchKernelGGL((linear_kernel<DirectCore, false>), all, threads, kLdsBytes, s, b);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
 static int launch_linear(const LinearParams& p, hipStream_t s) { return launch_linear(&p, 1, s); }
 
-static int launch_wgrad_batch(const WgradParams* ps, int n, bool direct, hipStream_t s) {
+// The n weight-gradient products (n <= kMaxBatch, all with the same K) in one launch.
+static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
     WgradBatch b = {};
     b.map.n = n;
     int64_t patches = 0;
@@ -522,34 +508,13 @@ static int launch_wgrad_batch(const WgradParams* ps, int n, bool direct, hipStre
     }
     if (patches * 32 > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_patch[i] = (int)patches;
-    const int blocks = grid_for_patches(patches);
+    const dim3 blocks((unsigned)grid_for_patches(patches)), threads(KMajorCore::kThreads);
     ProfScope pr(PROF_MLP_WGRAD, s);
-    if (direct)
-        hipLaunchKernelGGL((wgrad_kernel<KMajorCore, false>), dim3((unsigned)blocks),
-                           dim3(KMajorCore::kThreads), kLdsBytes, s, b);
+    if (ps[0].K % kBlockK != 0)
+        hipLaunchKernelGGL((wgrad_kernel<true>), blocks, threads, kLdsBytes, s, b);
     else
-        hipLaunchKernelGGL((wgrad_kernel<StagedKMajorCore, true>), dim3((unsigned)blocks),
-                           dim3(StagedKMajorCore::kThreads), kLdsBytes, s, b);
+        hipLaunchKernelGGL((wgrad_kernel<false>), blocks, threads, kLdsBytes, s, b);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
-}
-
-// The n weight-gradient products (n <= kMaxBatch, all with the same K) in one launch.  The
-// unguarded core needs K in whole k-steps (output extents that end inside a block are its
-// business): the whole k-steps go to it and the K % 64 rows left over to a second, guarded launch.
-static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
-    const int K = ps[0].K, K_whole = K / kBlockK * kBlockK;
-    if (K_whole == 0) return launch_wgrad_batch(ps, n, false, s);
-    WgradParams part[kMaxBatch];
-    for (int i = 0; i < n; ++i) { part[i] = ps[i]; part[i].K = K_whole; }
-    int rc = launch_wgrad_batch(part, n, true, s);
-    if (rc != ALST_OK || K_whole == K) return rc;
-    for (int i = 0; i < n; ++i) {
-        part[i].X += (int64_t)K_whole * ps[i].ldx;
-        part[i].Y += (int64_t)K_whole * ps[i].ldy;
-        part[i].K = K - K_whole;
-        part[i].first = 0;
-    }
-    return launch_wgrad_batch(part, n, false, s);
 }
 
 static int launch_wgrad(const WgradParams& p, hipStream_t s) { return launch_wgrad(&p, 1, s); }
@@ -584,47 +549,30 @@ static int validate_mlp(const MlpProblem& P, size_t workspace_bytes, bool backwa
     return ALST_OK;
 }
 
-// a = silu(x_t Wg^T) * (x_t Wu^T) for the tile's T_cur rows (rows up to Tr come out as zeros);
-// backward (da given): also [dg | du].
-static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int T_cur, int Tr,
-                        const uint16_t* da, uint16_t* a, uint16_t* dgu, hipStream_t s) {
+// a = silu(x_t Wg^T) * (x_t Wu^T) for `rows` rows of x; backward (da given): also [dg | du].
+static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, const uint16_t* da, uint16_t* a,
+                        uint16_t* dgu, hipStream_t s) {
     GatedParams gp = {};
-    gp.X = x_t; gp.ldx = P.H; gp.rows_x = T_cur; gp.K = (int)P.H;
+    gp.X = x_t; gp.ldx = P.H; gp.rows_x = rows; gp.K = (int)P.H;
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
-    gp.da = da; gp.a = a; gp.dgu = dgu; gp.rows_out = Tr;
-    gp.grid = choose_patches(Tr / kBlockR, (int)((P.I + 127) / 128));
+    gp.da = da; gp.a = a; gp.dgu = dgu;
+    gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
     const int blocks = grid_for_patches(gp.grid.patches());
-    // the unguarded core needs whole blocks of rows and whole k-steps; an I that ends inside a
-    // block's 128 columns is handled by its epilogue
-    const bool direct = T_cur % kBlockR == 0 && P.H % kBlockK == 0;
-    const bool cguard = P.I % 128 != 0;
+    const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
     // persistent workgroups that fetch their next block early: whole pairs of k-steps
-    const bool chain = direct && P.H % (2 * kBlockK) == 0 && P.H >= 4 * kBlockK;
+    const bool chain = P.H % (2 * kBlockK) == 0 && P.H >= 4 * kBlockK;
+    const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
+    const dim3 threads(DirectCore::kThreads);
     ProfScope pr(PROF_MLP_LINEAR, s);
     if (chain) {
-        const dim3 grid((unsigned)std::min(blocks, persistent_grid())), block(DirectCore::kThreads);
-        if (cguard && da) hipLaunchKernelGGL((gated_chain_kernel<true, true>), grid, block, kChainLdsBytes, s, gp, blocks);
-        else if (cguard) hipLaunchKernelGGL((gated_chain_kernel<false, true>), grid, block, kChainLdsBytes, s, gp, blocks);
-        else if (da) hipLaunchKernelGGL((gated_chain_kernel<true, false>), grid, block, kChainLdsBytes, s, gp, blocks);
-        else hipLaunchKernelGGL((gated_chain_kernel<false, false>), grid, block, kChainLdsBytes, s, gp, blocks);
-    } else if (direct && cguard && da)
-        hipLaunchKernelGGL((gated_kernel<DirectCore, false, true, true>), dim3((unsigned)blocks),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, gp);
-    else if (direct && cguard)
-        hipLaunchKernelGGL((gated_kernel<DirectCore, false, false, true>), dim3((unsigned)blocks),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, gp);
-    else if (direct && da)
-        hipLaunchKernelGGL((gated_kernel<DirectCore, false, true>), dim3((unsigned)blocks),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, gp);
-    else if (direct)
-        hipLaunchKernelGGL((gated_kernel<DirectCore, false, false>), dim3((unsigned)blocks),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, gp);
-    else if (da)
-        hipLaunchKernelGGL((gated_kernel<StagedCore, true, true>), dim3((unsigned)blocks),
-                           dim3(StagedCore::kThreads), kLdsBytes, s, gp);
-    else
-        hipLaunchKernelGGL((gated_kernel<StagedCore, true, false>), dim3((unsigned)blocks),
-                           dim3(StagedCore::kThreads), kLdsBytes, s, gp);
+        if (guard && da) hipLaunchKernelGGL((gated_chain_kernel<true, true>), persistent, threads, kChainLdsBytes, s, gp, blocks);
+        else if (guard) hipLaunchKernelGGL((gated_chain_kernel<false, true>), persistent, threads, kChainLdsBytes, s, gp, blocks);
+        else if (da) hipLaunchKernelGGL((gated_chain_kernel<true, false>), persistent, threads, kChainLdsBytes, s, gp, blocks);
+        else hipLaunchKernelGGL((gated_chain_kernel<false, false>), persistent, threads, kChainLdsBytes, s, gp, blocks);
+    } else if (ktail && da) hipLaunchKernelGGL((gated_kernel<true, true>), all, threads, kLdsBytes, s, gp);
+    else if (ktail) hipLaunchKernelGGL((gated_kernel<false, true>), all, threads, kLdsBytes, s, gp);
+    else if (da) hipLaunchKernelGGL((gated_kernel<true, false>), all, threads, kLdsBytes, s, gp);
+    else hipLaunchKernelGGL((gated_kernel<false, false>), all, threads, kLdsBytes, s, gp);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
@@ -640,13 +588,12 @@ static int run_mlp_forward(const MlpProblem& P) {
     for (int64_t t = 0; t < ntiles; ++t) {
         const int64_t i0 = t * T;
         const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
-        const int Tr = (T_cur + kBlockR - 1) / kBlockR * kBlockR;
-        rc = launch_gated(P, P.x + i0 * P.H, T_cur, Tr, nullptr, a, nullptr, s);
+        rc = launch_gated(P, P.x + i0 * P.H, T_cur, nullptr, a, nullptr, s);
         if (rc != ALST_OK) return rc;
         LinearParams lp = {};
-        lp.X = a; lp.ldx = I; lp.rows_x = Tr; lp.K = I;
+        lp.X = a; lp.ldx = I; lp.rows_x = T_cur; lp.K = I;
         lp.Y = P.Wd; lp.ldy = I; lp.rows_y = H;
-        lp.D = P.y + i0 * P.H; lp.ldd = H; lp.rows_out = T_cur; lp.cols_out = H;
+        lp.D = P.y + i0 * P.H; lp.ldd = H;
         rc = launch_linear(lp, s);
         if (rc != ALST_OK) return rc;
     }
@@ -695,13 +642,11 @@ static int run_mlp_backward(const MlpProblem& P) {
     for (int64_t t = 0; t < ntiles; ++t) {
         const int64_t i0 = t * T;
         const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
-        const int Tr = (T_cur + kBlockR - 1) / kBlockR * kBlockR;
         const int slot = (int)(t % L.g);
         if (slot == 0) { kofs = 0; group_row0 = i0; }
         const uint16_t* x_t = P.x + i0 * P.H;
         const uint16_t* dy_t = P.dy + i0 * P.H;
-        // the tile's rows of a and [dg | du] sit behind those of the group's earlier tiles (rows
-        // T_cur .. Tr come out as zeros and are overwritten by the next tile)
+        // the tile's rows of a and [dg | du] sit behind those of the group's earlier tiles
         uint16_t* a_t = a + (int64_t)kofs * I;
         uint16_t* dgu_t = dgu + (int64_t)kofs * I2;
 
@@ -710,14 +655,14 @@ static int run_mlp_backward(const MlpProblem& P) {
             lp.X = dy_t; lp.ldx = H; lp.rows_x = T_cur; lp.K = H;
             if (L.weights_t) { lp.Y = wdt; lp.ldy = H; lp.rows_y = I; }            // Wd^T [I, H]
             else { lp.Y = P.Wd; lp.ldy = I; lp.rows_y = I; lp.y_kmajor = 1; }      // Wd [H, I]: k = h
-            lp.D = da; lp.ldd = I; lp.rows_out = Tr; lp.cols_out = I;
+            lp.D = da; lp.ldd = I;
             rc = launch_linear(lp, s);
-            if (rc == ALST_OK) rc = launch_gated(P, x_t, T_cur, Tr, da, a_t, dgu_t, s);
+            if (rc == ALST_OK) rc = launch_gated(P, x_t, T_cur, da, a_t, dgu_t, s);
             if (rc != ALST_OK) return rc;
         }
         {   // dx = dg Wg + du Wu
             LinearParams lp = {};
-            lp.X = dgu_t; lp.ldx = I2; lp.rows_x = Tr;
+            lp.X = dgu_t; lp.ldx = I2; lp.rows_x = T_cur;
             if (L.weights_t) {
                 // one contraction over the 2 I columns of [dg | du] against [Wg | Wu]^T [H, 2 I]
                 lp.K = (int)I2; lp.Y = wgut; lp.ldy = I2; lp.rows_y = H;
@@ -726,7 +671,7 @@ static int run_mlp_backward(const MlpProblem& P) {
                 lp.K = I; lp.Y = P.Wg; lp.ldy = H; lp.rows_y = H; lp.y_kmajor = 1;     // Wg [I, H]: k = i
                 lp.X2 = dgu_t + I; lp.Y2 = P.Wu;
             }
-            lp.D = P.dx + i0 * P.H; lp.ldd = H; lp.rows_out = T_cur; lp.cols_out = H;
+            lp.D = P.dx + i0 * P.H; lp.ldd = H;
             rc = launch_linear(lp, s);
             if (rc != ALST_OK) return rc;
         }
@@ -837,7 +782,7 @@ static int run_lin_forward(const LinProblem& P) {
         LinearParams lp = {};
         lp.X = P.x + i0 * P.K; lp.ldx = P.K; lp.rows_x = T_cur; lp.K = (int)P.K;
         lp.Y = P.W; lp.ldy = P.K; lp.rows_y = (int)P.M;
-        lp.D = P.y + i0 * P.M; lp.ldd = P.M; lp.rows_out = T_cur; lp.cols_out = (int)P.M;
+        lp.D = P.y + i0 * P.M; lp.ldd = P.M;
         rc = launch_linear(lp, P.stream);
         if (rc != ALST_OK) return rc;
     }
@@ -873,7 +818,7 @@ static int run_lin_backward(const LinProblem& P) {
         lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = T_cur; lp.K = M;
         if (L.weight_t) { lp.Y = wt; lp.ldy = M; lp.rows_y = K; }         // W^T [K, M]
         else { lp.Y = P.W; lp.ldy = K; lp.rows_y = K; lp.y_kmajor = 1; }  // W [M, K]: k = m
-        lp.D = P.dx + i0 * P.K; lp.ldd = K; lp.rows_out = T_cur; lp.cols_out = K;
+        lp.D = P.dx + i0 * P.K; lp.ldd = K;
         rc = launch_linear(lp, s);
         if (rc != ALST_OK) return rc;
         kofs += T_cur;
