@@ -31,7 +31,8 @@
 //   4. dw_kernel         acc += (H_c / S)^T e'         once per group of tiles (contraction over
 //                        the group's dense rows, fp32)
 //
-// After the last tile: loss = sum(per-row loss) / M in a fixed order, dW = (g/M) acc.
+// After the last tile: loss = sum(per-row loss) / M in a fixed order.  The last group's dw_kernel writes
+// dW = (g/M) acc.
 // The contractions share the block GEMM of gemm_tile.h: logits and dHidden with both operands
 // k-contiguous (dHidden against a copy of W transposed once per call), dW with both operands
 // k-major (the group's dense hidden rows and dZ rows as they are).  No per-tile array is
@@ -610,33 +611,6 @@ __global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restri
     }
 }
 
-// dW = (g/M) acc  (bf16 or fp32, overwrite or +=).  acc may alias dW (fp32 overwrite mode).
-template <bool OUT_F32, bool ACCUM>
-__global__ void dw_finalize_kernel(const float* acc, void* dW, int64_t n4, const Header* h) {
-    const float inv = h->inv;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        f32x4_t a = reinterpret_cast<const f32x4_t*>(acc)[i];
-        a *= inv;
-        if (OUT_F32) {
-            f32x4_t* o = reinterpret_cast<f32x4_t*>(dW) + i;
-            if (ACCUM) a += *o;
-            *o = a;
-        } else {
-            bf16x4_t* o = reinterpret_cast<bf16x4_t*>(dW) + i;
-            if (ACCUM) {
-                const bf16x4_t old = *o;
-#pragma unroll
-                for (int x = 0; x < 4; ++x) a[x] += (float)old[x];
-            }
-            bf16x4_t r;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) r[x] = (__bf16)a[x];
-            *o = r;
-        }
-    }
-}
-
 __global__ void copy_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
@@ -913,17 +887,16 @@ __global__ __launch_bounds__(256) void dhidden_reduce_kernel(const float* __rest
 struct DWParams {
     const uint16_t* hg;      // [Kg, Hk]     the group's dense hidden rows (H of the Hk columns used)
     const uint16_t* dzg;     // [Kg, Vp]     their dZ rows
-    float* acc;              // [V, H]
+    GradOut out;             // [V, H] (scale and last: the kernel finds them)
     const Header* hdr;
     int64_t row0, rows;      // the group's dense rows: row0 .. row0 + rows - 1, as far as they exist
     int H, Hk, V, Vp;
-    int first;               // first group: store instead of add
     int PR, PC;              // patch shape of the block -> tile mapping
 };
 
 // r = hidden index (lane dimension), c = vocabulary id (register dimension), k = dense token row:
 // both operands have k as the slow index (k-major cores).  With the hidden index along the lanes
-// the accumulate moves full 128-byte lines of acc (accumulate_block_f32).
+// the accumulate moves full 128-byte lines of the sums (weight_grad_block).
 template <class Core>
 __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
@@ -933,7 +906,7 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     // k extent of the group (its dense rows are zero padded to whole blocks)
     const int64_t left = p.hdr->n_valid - p.row0;
     const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
-    if (Tkc == 0 && !p.first) return;
+    if (Tkc == 0 && !p.out.first) return;
     {
         const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
         int P, w;
@@ -948,7 +921,11 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     if (Tkc > 0)
         Core::template gemm<false>(p.hg, p.Hk, p.H, p.dzg, p.Vp, p.Vp, Tkc, r0, c0, smem, acc, nullptr, 0);
 
-    accumulate_block_f32<Core>(acc, p.acc, p.H, r0, c0, p.H, p.V, p.first != 0);
+    // the last group with dense rows finishes dW = (g/M) sums
+    GradOut out = p.out;
+    out.scale = p.hdr->inv;
+    out.last = left <= p.rows;
+    weight_grad_block<Core>(acc, out, r0, c0, p.H, p.V, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1207,9 +1184,11 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
         }
         if (group_done) {
             DWParams wp;
-            wp.hg = hc; wp.dzg = stash; wp.acc = acc; wp.hdr = hdr;
+            wp.hg = hc; wp.dzg = stash; wp.hdr = hdr;
+            wp.out = {acc, P.dW, P.H, 0.f, group0 == 0, 0, (P.flags & ALST_FLAG_DW_FP32) != 0,
+                      (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
             wp.row0 = group0; wp.rows = L.Kg;
-            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp; wp.first = group0 == 0;
+            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
             const PatchGrid pg = choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
             wp.PR = pg.PR; wp.PC = pg.PC;
             const int grid = grid_for_patches(pg.patches());
@@ -1223,21 +1202,6 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     if (do_fwd) {
         hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, loss_rows, P.N, hdr,
                            sum_mode, P.loss_out);
-        ALST_HIP(hipGetLastError());
-    }
-    if (do_bwd) {
-        const int64_t n4 = P.V * P.H / 4;
-        int blocks = (int)((n4 + 255) / 256);
-        if (blocks > 8192) blocks = 8192;
-        const bool f32 = P.flags & ALST_FLAG_DW_FP32, accum = P.flags & ALST_FLAG_DW_ACCUMULATE;
-        if (f32 && accum)
-            hipLaunchKernelGGL((dw_finalize_kernel<true, true>), dim3(blocks), dim3(256), 0, s, acc, P.dW, n4, hdr);
-        else if (f32)
-            hipLaunchKernelGGL((dw_finalize_kernel<true, false>), dim3(blocks), dim3(256), 0, s, acc, P.dW, n4, hdr);
-        else if (accum)
-            hipLaunchKernelGGL((dw_finalize_kernel<false, true>), dim3(blocks), dim3(256), 0, s, acc, P.dW, n4, hdr);
-        else
-            hipLaunchKernelGGL((dw_finalize_kernel<false, false>), dim3(blocks), dim3(256), 0, s, acc, P.dW, n4, hdr);
         ALST_HIP(hipGetLastError());
     }
     return ALST_OK;

@@ -363,10 +363,9 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
 struct WgradParams {
     const uint16_t* X;       // [K, ldx]        r (columns 0 .. rows_x): the contiguous index of `out`
     const uint16_t* Y;       // [K, ldy]        c (columns 0 .. rows_y): the row index of `out`
-    float* out;              // [rows_y, ld]    out[c][r] (+)= sum_k X[k][r] Y[k][c]
-    int64_t ldx, ldy, ld;
+    GradOut out;             // [rows_y, ld]    out[c][r] (+)= sum_k X[k][r] Y[k][c]
+    int64_t ldx, ldy;
     int rows_x, rows_y, K;
-    int first;               // store instead of add
 };
 
 struct WgradBatch {
@@ -387,32 +386,7 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const Wgrad
     Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
     Core::gemm<KTAIL>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, nullptr, 0);
-    accumulate_block_f32<Core>(acc, p.out, p.ld, r0, c0, p.rows_x, p.rows_y, p.first != 0);
-}
-
-// out = sums (bf16 or fp32, overwrite or +=).  `sums` may alias `out` (fp32 overwrite mode).
-template <bool OUT_F32, bool ACCUM>
-__global__ void convert_sums_kernel(const float* sums, void* out, int64_t n4) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        f32x4_t a = reinterpret_cast<const f32x4_t*>(sums)[i];
-        if (OUT_F32) {
-            f32x4_t* o = reinterpret_cast<f32x4_t*>(out) + i;
-            if (ACCUM) a += *o;
-            *o = a;
-        } else {
-            bf16x4_t* o = reinterpret_cast<bf16x4_t*>(out) + i;
-            if (ACCUM) {
-                const bf16x4_t old = *o;
-#pragma unroll
-                for (int x = 0; x < 4; ++x) a[x] += (float)old[x];
-            }
-            bf16x4_t r;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) r[x] = (__bf16)a[x];
-            *o = r;
-        }
-    }
+    weight_grad_block<Core>(acc, p.out, r0, c0, p.rows_x, p.rows_y, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -600,14 +574,6 @@ static int run_mlp_forward(const MlpProblem& P) {
     return ALST_OK;
 }
 
-template <bool F32, bool ACC>
-static void launch_convert(const float* sums, void* out, int64_t n, hipStream_t s) {
-    const int64_t n4 = n / 4;
-    int blocks = (int)((n4 + 255) / 256);
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL((convert_sums_kernel<F32, ACC>), dim3(blocks), dim3(256), 0, s, sums, out, n4);
-}
-
 static int run_mlp_backward(const MlpProblem& P) {
     int rc = prepare_mlp_kernels();
     if (rc != ALST_OK) return rc;
@@ -677,33 +643,24 @@ static int run_mlp_backward(const MlpProblem& P) {
         }
         kofs += T_cur;
         if (slot == L.g - 1 || t == ntiles - 1) {       // the group is complete
-            const int first = t < L.g;
+            GradOut out = {nullptr, nullptr, 0, 1.f, t < L.g, t == ntiles - 1, f32, accum};
+            auto into = [&](float* sums, void* dW, int64_t ld) { out.sums = sums; out.out = dW; out.ld = ld; return out; };
             const uint16_t* x_g = P.x + group_row0 * P.H;
             const uint16_t* dy_g = P.dy + group_row0 * P.H;
             WgradParams wp[kMaxBatch] = {};
-            wp[0].K = kofs; wp[0].first = first;
-            wp[0].X = x_g; wp[0].ldx = H; wp[0].rows_x = H; wp[0].ld = H;
-            wp[0].Y = dgu; wp[0].ldy = I2; wp[0].rows_y = I; wp[0].out = acc_g;      // dWg[i][h]
+            wp[0].K = kofs;
+            wp[0].X = x_g; wp[0].ldx = H; wp[0].rows_x = H;
+            wp[0].Y = dgu; wp[0].ldy = I2; wp[0].rows_y = I;
+            wp[0].out = into(acc_g, P.dWg, H);                                       // dWg[i][h]
             wp[1] = wp[0];
-            wp[1].Y = dgu + I; wp[1].out = acc_u;                                    // dWu[i][h]
+            wp[1].Y = dgu + I; wp[1].out = into(acc_u, P.dWu, H);                    // dWu[i][h]
             wp[2] = wp[0];
-            wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I; wp[2].ld = I;
-            wp[2].Y = dy_g; wp[2].ldy = H; wp[2].rows_y = H; wp[2].out = acc_d;      // dWd[h][i]
+            wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I;
+            wp[2].Y = dy_g; wp[2].ldy = H; wp[2].rows_y = H;
+            wp[2].out = into(acc_d, P.dWd, I);                                       // dWd[h][i]
             rc = launch_wgrad(wp, 3, s);                                             // one launch
             if (rc != ALST_OK) return rc;
         }
-    }
-    if (!in_out) {
-        ProfScope ps(PROF_MLP_OTHER, s);
-        const int64_t n = P.I * P.H;
-        float* sums[3] = {acc_g, acc_u, acc_d};
-        void* outs[3] = {P.dWg, P.dWu, P.dWd};
-        for (int k = 0; k < 3; ++k) {
-            if (f32) launch_convert<true, true>(sums[k], outs[k], n, s);          // fp32 +=
-            else if (accum) launch_convert<false, true>(sums[k], outs[k], n, s);
-            else launch_convert<false, false>(sums[k], outs[k], n, s);
-        }
-        ALST_HIP(hipGetLastError());
     }
     return ALST_OK;
 }
@@ -828,18 +785,11 @@ static int run_lin_backward(const LinProblem& P) {
             WgradParams wp = {};
             wp.X = P.x + group_row0 * P.K; wp.ldx = K; wp.rows_x = K;
             wp.Y = P.dy + group_row0 * P.M; wp.ldy = M; wp.rows_y = M;
-            wp.K = kofs; wp.out = acc; wp.ld = K; wp.first = t < L.g;
+            wp.K = kofs;
+            wp.out = {acc, P.dW, K, 1.f, t < L.g, t == ntiles - 1, f32, accum};
             rc = launch_wgrad(wp, s);
             if (rc != ALST_OK) return rc;
         }
-    }
-    if (!in_out) {
-        ProfScope ps(PROF_MLP_OTHER, s);
-        const int64_t n = P.M * P.K;
-        if (f32) launch_convert<true, true>(acc, P.dW, n, s);
-        else if (accum) launch_convert<false, true>(acc, P.dW, n, s);
-        else launch_convert<false, false>(acc, P.dW, n, s);
-        ALST_HIP(hipGetLastError());
     }
     return ALST_OK;
 }
