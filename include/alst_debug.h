@@ -29,8 +29,8 @@ int alst_profile_read(double* ms_total, int64_t* launches);
 /*
  * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched).  The block
  * GEMM launches deal their workgroups round-robin to the 8 XCDs of the chip and give the 32
- * workgroups resident on one XCD a compact patch of output blocks; a launch may hold several
- * products ("parts") whose patches are numbered through.  For a launch of `parts` products of
+ * workgroups resident on one XCD a compact run of output blocks; a launch may hold several
+ * products ("parts") whose blocks are numbered through.  For a launch of `parts` products of
  * tiles_r x tiles_c blocks this returns the number of workgroups and writes, for workgroup `bid`,
  * the part and block it computes (part = -1: the workgroup leaves at once), evaluated with the
  * same functions the kernels use.  A negative return value is minus an alst_status.

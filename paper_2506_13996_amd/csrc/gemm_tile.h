@@ -59,51 +59,61 @@ constexpr int kWarmAhead = 3;                           // k-steps between warm-
 // What a lane reads in place of k that do not exist.
 static __device__ __align__(16) uint32_t zero_chunk[4];
 
-// XCD-aware block -> tile mapping.  Workgroups are dealt round-robin to the 8 XCDs (each with its
-// own L2); the 32 workgroups that are resident together on one XCD get a compact PR x PC patch of
-// output blocks so that they share operand tiles through that L2.  The patch shape is chosen per
-// launch, and a launch may hold several products ("parts"): the patches of all parts are numbered
-// through, and patch P goes to XCD P % 8, so the XCDs stay evenly loaded whatever the number of
-// patches of one part is.
+// XCD-aware block numbering.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2);
+// the 32 workgroups that are resident together on one XCD get a run of 32 consecutive blocks of an
+// order that walks the output in PR x PC patches (patches down the rows first, a patch's rows
+// fastest), so that they share operand tiles through that L2.  The order has no holes: an output
+// that is not whole patches has narrower ones at its edges, a run may straddle two, and a launch
+// of several products ("parts") numbers their blocks through.  The blocks that do not fill a round
+// of 256 are spread evenly over the XCDs.  (Numbering padded patches instead, patch P on XCD P % 8, left
+// an XCD with a second patch while others had none: 9 patches took the time of 16.)
+constexpr int kXcds = 8, kPerXcd = 32, kRound = kXcds * kPerXcd;
 struct PatchGrid {
     int tiles_r, tiles_c;      // output blocks of one part
     int PR, PC;                // patch shape, PR * PC = 32
-    __host__ __device__ int patches_r() const { return (tiles_r + PR - 1) / PR; }
     // (int: the launches are checked to fit a one-dimensional grid before any kernel sees this)
-    __host__ __device__ int patches() const { return patches_r() * ((tiles_c + PC - 1) / PC); }
+    __host__ __device__ int blocks() const { return tiles_r * tiles_c; }
     // for the host-side sizing, which also meets shapes no launch can hold
-    int64_t patches64() const { return (int64_t)patches_r() * ((tiles_c + PC - 1) / PC); }
+    int64_t padded() const {
+        return (int64_t)((tiles_r + PR - 1) / PR) * ((tiles_c + PC - 1) / PC) * 32;
+    }
 };
 
 // Patch shape: 4 x 8 (12 operand tiles per k-step for 32 blocks), unless 8 x 4 or one of the
-// flat shapes 2 x 16, 16 x 2 (18 tiles per k-step) pads so much less that it needs under 9/10 of
-// the patches.
+// flat shapes 2 x 16, 16 x 2 (18 tiles per k-step) has so much less outside the output that it needs
+// under 9/10 of the patches.
 inline PatchGrid choose_patches(int tiles_r, int tiles_c) {
     const int shapes[4][2] = {{4, 8}, {8, 4}, {2, 16}, {16, 2}};
     PatchGrid best = {tiles_r, tiles_c, 4, 8};
     for (int i = 1; i < 4; ++i) {
         const PatchGrid g = {tiles_r, tiles_c, shapes[i][0], shapes[i][1]};
-        if (10 * g.patches64() < 9 * best.patches64()) best = g;
+        if (10 * g.padded() < 9 * best.padded()) best = g;
     }
     return best;
 }
 
-inline int grid_for_patches(int64_t patches) { return (int)(((patches + 7) / 8) * 8 * 32); }
+inline int grid_for_blocks(int64_t blocks) { return (int)((blocks + kRound - 1) / kRound * kRound); }
 
-// Workgroup -> (global patch number, position inside the patch).
-__host__ __device__ __forceinline__ void patch_of_block(int bid, int& P, int& w) {
-    const int slot = bid >> 3;
-    P = (slot >> 5) * 8 + (bid & 7);
-    w = slot & 31;
+// Workgroup -> number of its block among the launch's `total`, or -1.
+__host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
+    const int round = bid / kRound, xcd = bid % kXcds, slot = (bid / kXcds) % kPerXcd;
+    const int left = total - round * kRound;
+    if (left >= kRound) return round * kRound + xcd * kPerXcd + slot;
+    if (left <= 0) return -1;
+    const int per = left / kXcds, more = left % kXcds;       // the first `more` XCDs have per + 1
+    if (slot >= per + (xcd < more ? 1 : 0)) return -1;
+    return round * kRound + xcd * per + (xcd < more ? xcd : more) + slot;
 }
 
-// Block (tr, tc) of position w in local patch P of g; false if the patch sticks out there.
-__host__ __device__ __forceinline__ bool tile_in_patch(const PatchGrid& g, int P, int w, int& tr,
-                                                       int& tc) {
-    const int pr = g.patches_r();
-    tr = (P % pr) * g.PR + (w % g.PR);
-    tc = (P / pr) * g.PC + (w / g.PR);
-    return tr < g.tiles_r && tc < g.tiles_c;
+// Block (tr, tc) of number i < g.blocks() in the order.
+__host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, int& tr, int& tc) {
+    const int column = i / (g.tiles_r * g.PC);               // column of patches
+    i -= column * g.tiles_r * g.PC;
+    const int c0 = column * g.PC, cols = g.tiles_c - c0 < g.PC ? g.tiles_c - c0 : g.PC;
+    const int r0 = i / (g.PR * cols) * g.PR, rows = g.tiles_r - r0 < g.PR ? g.tiles_r - r0 : g.PR;
+    i -= r0 * cols;
+    tr = r0 + i % rows;
+    tc = c0 + i / rows;
 }
 
 // Gated pair of Y operands: with Y2 given, the 256 Y rows of the block at c0 are four runs of 64

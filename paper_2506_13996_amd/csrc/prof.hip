@@ -150,17 +150,15 @@ int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* par
     if (!part || !tr || !tc) return -ALST_ERR_NULL;
     if (tiles_r < 1 || tiles_c < 1 || parts < 1 || bid < 0) return -ALST_ERR_SHAPE;
     const PatchGrid g = choose_patches(tiles_r, tiles_c);
-    const int64_t total = (int64_t)g.patches() * parts;
-    if (total * 32 > 0x7fffff00) return -ALST_ERR_SHAPE;
-    int P, w;
-    patch_of_block(bid, P, w);
+    const int64_t total = (int64_t)tiles_r * tiles_c * parts;
+    if (total > 0x7fffff00) return -ALST_ERR_SHAPE;
     *part = -1; *tr = 0; *tc = 0;
-    if (P < total) {
-        const int which = P / g.patches();
-        int r, c;
-        if (tile_in_patch(g, P - which * g.patches(), w, r, c)) { *part = which; *tr = r; *tc = c; }
+    const int i = block_of_workgroup(bid, (int)total);
+    if (i >= 0) {
+        *part = i / g.blocks();
+        block_at(g, i % g.blocks(), *tr, *tc);
     }
-    return grid_for_patches(total);
+    return grid_for_blocks(total);
 }
 
 // Sustained rate of the bf16 matrix instructions the block GEMMs use, on this device now: 256

@@ -95,7 +95,7 @@ struct Layout {
     int64_t Kg;            // dense rows the group's buffers hold: g * Tp
     int64_t Rc;            // most dense rows per chunk of launches, a multiple of 256
     int dh_PR, dh_PC;      // dHidden: patch shape of the block -> tile mapping
-    int64_t dh_patches;    //          most patches (over all ranges) a chunk of any number of rows needs
+    int64_t dh_blocks;     //          most blocks (over all ranges) a chunk of any number of rows needs
     int64_t dh_part_rows;  //          most rows of fp32 partial products
     bool dh_cut;           //          some number of rows has its contraction cut into ranges
     size_t header, cinfo, loss_rows, lse, idx, block_cnt, block_ofs, zlabel, yc, ref, frow, rowstate,
@@ -184,7 +184,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
         const PatchGrid pg = choose_patches((int)(L.Rc / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
         L.dh_PR = pg.PR; L.dh_PC = pg.PC;
         L.dh_part_rows = (int64_t)((at + region - L.part) / ((size_t)H * 4));
-        L.dh_patches = 0;
+        L.dh_blocks = 0;
         L.dh_cut = false;
         // (beyond 4096 row blocks per chunk only the full chunk is looked at; gather_rows_kernel
         // then keeps a smaller chunk's choice within these bounds)
@@ -192,9 +192,8 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
         for (int64_t rb = rb_lo; rb <= rb_max; ++rb) {
             int sp;
             dhidden_splits(rb * kBlockR, H, V, L.dh_part_rows, sp, ks);
-            const PatchGrid g = {(int)rb, pg.tiles_c, pg.PR, pg.PC};
-            const int64_t patches = g.patches64() * sp;
-            if (patches > L.dh_patches) L.dh_patches = patches;
+            const int64_t blocks = rb * pg.tiles_c * sp;
+            if (blocks > L.dh_blocks) L.dh_blocks = blocks;
             L.dh_cut = L.dh_cut || sp > 1;
         }
     }
@@ -408,8 +407,8 @@ struct GatherParams {
     uint16_t* dHidden;           // [N, H]
     int64_t N, first;
     int64_t Rc;                  // the chunk's rows, rounded up to the block height
-    int64_t H, V, dh_patches, dh_part_rows;
-    int Hk, dh_PR, dh_PC, ignore_index;
+    int64_t H, V, dh_blocks, dh_part_rows;
+    int Hk, ignore_index;
 };
 __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) {
     const int64_t b = blockIdx.x;
@@ -438,8 +437,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) 
         // and the buffer of partial products were sized for
         int sp = 1, ks = 0;
         dhidden_splits(Trc, p.H, p.V, p.dh_part_rows, sp, ks);
-        const PatchGrid g = {Trc / kBlockR, (int)((p.H + kBlockC - 1) / kBlockC), p.dh_PR, p.dh_PC};
-        if ((int64_t)g.patches() * sp > p.dh_patches) {
+        if ((int64_t)(Trc / kBlockR) * ((p.H + kBlockC - 1) / kBlockC) * sp > p.dh_blocks) {
             sp = 1;
             ks = (int)((p.V + kBlockK - 1) / kBlockK);
         }
@@ -658,9 +656,9 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
     if (REDO && !p.info->redo) return;
     {
         const PatchGrid pg = {Trc / kBlockR, p.Vp / kBlockC, p.PR, p.PC};
-        int P, w;
-        patch_of_block(blockIdx.x, P, w);
-        if (P >= pg.patches() || !tile_in_patch(pg, P, w, tr, tc)) return;
+        const int i = block_of_workgroup(blockIdx.x, pg.blocks());
+        if (i < 0) return;
+        block_at(pg, i, tr, tc);
     }
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
     constexpr int kRegs = 4 * Core::kRuns;          // accumulator registers of a tile
@@ -797,13 +795,13 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
     const int tiles_c = (p.H + kBlockC - 1) / kBlockC;
     const int T_cur = p.info->Tc, Trc = p.info->Trc;
     if (T_cur == 0) return;
-    // the ranges are parts of one launch: their patches are numbered through
+    // the ranges are parts of one launch: their blocks are numbered through
     const PatchGrid pg = {Trc / kBlockR, tiles_c, p.PR, p.PC};
-    int P, w;
-    patch_of_block(blockIdx.x, P, w);
-    const int np = pg.patches(), split = P / np;
     const int splits = p.info->splits, ksteps = p.info->ksteps;
-    if (split >= splits || !tile_in_patch(pg, P - split * np, w, tr, tc)) return;
+    const int i = block_of_workgroup(blockIdx.x, pg.blocks() * splits);
+    if (i < 0) return;
+    const int split = i / pg.blocks();
+    block_at(pg, i - split * pg.blocks(), tr, tc);
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
     // k runs over V rounded up to whole k-steps: dZ and Wt are zero there
     const int k0 = split * ksteps * kBlockK;
@@ -909,9 +907,9 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     if (Tkc == 0 && !p.out.first) return;
     {
         const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
-        int P, w;
-        patch_of_block(blockIdx.x, P, w);
-        if (P >= pg.patches() || !tile_in_patch(pg, P, w, tr, tc)) return;
+        const int i = block_of_workgroup(blockIdx.x, pg.blocks());
+        if (i < 0) return;
+        block_at(pg, i, tr, tc);
     }
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
 
@@ -999,7 +997,7 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
     // every launch must fit a one-dimensional grid
     if (!checked_grid(L.Rc / kBlockR, L.Vp / kBlockC) ||
         !checked_grid((P.H + kBlockR - 1) / kBlockR, L.Vp / kBlockC) ||
-        L.dh_patches * 32 > 0x7fffff00 ||                                        // dHidden
+        L.dh_blocks > 0x7fffff00 ||                                        // dHidden
         L.Rc + kZeroBlocksMax > 0x7fffffff)
         return ALST_ERR_SHAPE;
     if (workspace_bytes < L.total) return own_scratch ? ALST_ERR_NOALLOC_LIMIT : ALST_ERR_WORKSPACE;
@@ -1012,7 +1010,7 @@ template <int MODE, bool REDO>
 static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
     const PatchGrid pg = choose_patches(Tr / kBlockR, lp.Vp / kBlockC);
     lp.PR = pg.PR; lp.PC = pg.PC;
-    const int grid = grid_for_patches(pg.patches());
+    const int grid = grid_for_blocks(pg.blocks());
     if (ktail)
         hipLaunchKernelGGL((logits_kernel<DirectCore, true, MODE, REDO>), dim3(grid),
                            dim3(DirectCore::kThreads), kLdsBytes, s, lp);
@@ -1138,8 +1136,8 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.hdr = hdr; gp.info = info; gp.Hc = hc_t; gp.yc = yc; gp.ref = ref; gp.rowstate = rowstate;
             gp.rmax = rmax; gp.dHidden = P.dHidden;
             gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
-            gp.dh_patches = L.dh_patches; gp.dh_part_rows = L.dh_part_rows;
-            gp.Hk = (int)L.Hk; gp.dh_PR = L.dh_PR; gp.dh_PC = L.dh_PC; gp.ignore_index = P.ignore_index;
+            gp.dh_blocks = L.dh_blocks; gp.dh_part_rows = L.dh_part_rows;
+            gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
             int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
             if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
             hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(Tr + zero_blocks)), dim3(256), 0, s, gp);
@@ -1173,7 +1171,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             dp.H = H; dp.V = V; dp.Vp = Vp;
             dp.PR = L.dh_PR; dp.PC = L.dh_PC;
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
-            const int grid = grid_for_patches(L.dh_patches);
+            const int grid = grid_for_blocks(L.dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
             hipLaunchKernelGGL((dhidden_kernel<DirectCore>), dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
                                s, dp);
@@ -1191,7 +1189,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
             const PatchGrid pg = choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
             wp.PR = pg.PR; wp.PC = pg.PC;
-            const int grid = grid_for_patches(pg.patches());
+            const int grid = grid_for_blocks(pg.blocks());
             ProfScope ps_(PROF_DW, s);
             hipLaunchKernelGGL((dw_kernel<KMajorCore>), dim3(grid), dim3(KMajorCore::kThreads),
                                kLdsBytes, s, wp);

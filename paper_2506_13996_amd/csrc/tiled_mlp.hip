@@ -97,26 +97,26 @@ struct LinearParams {
     int y_kmajor;
 };
 
-// Up to three independent products in one launch: their patches of output blocks are numbered
+// Up to three independent products in one launch: their output blocks are numbered
 // through (gemm_tile.h), so the XCDs stay evenly loaded and the tail of one product is filled by
 // the first workgroups of the next instead of leaving compute units idle.
 constexpr int kMaxBatch = 3;
 struct BatchMap {
     PatchGrid g[kMaxBatch];
-    int first_patch[kMaxBatch + 1];      // first_patch[i] .. first_patch[i + 1]: patches of part i
+    int first_block[kMaxBatch + 1];      // first_block[i] .. first_block[i + 1]: blocks of part i
     int n;
     // which part and which of its blocks a workgroup works on; false for padding workgroups
     __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC) const {
-        int P, w;
-        patch_of_block(bid, P, w);
-        if (P >= first_patch[n]) return false;
+        const int i = block_of_workgroup(bid, first_block[n]);
+        if (i < 0) return false;
         which = 0;
 #pragma unroll
-        for (int i = 1; i < kMaxBatch; ++i)
-            if (i < n && P >= first_patch[i]) which = i;
+        for (int k = 1; k < kMaxBatch; ++k)
+            if (k < n && i >= first_block[k]) which = k;
         PR = g[which].PR;
         PC = g[which].PC;
-        return tile_in_patch(g[which], P - first_patch[which], w, tr, tc);
+        block_at(g[which], i - first_block[which], tr, tc);
+        return true;
     }
 };
 struct LinearBatch {
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
 // launch's blocks bid = blockIdx.x, blockIdx.x + gridDim.x, ... (the same block numbering as
 // linear_kernel, so the 32 workgroups of an XCD still share a patch) and fetches the first two
 // k-steps of its next block while the current block's last two k-steps and epilogue run
-// (DirectCore::Pipe).  total = the launch's block numbers (grid_for_patches).  Every product of
+// (DirectCore::Pipe).  total = the launch's block numbers (grid_for_blocks).  Every product of
 // the launch has the same K, a multiple of 128 and >= 256.
 // GUARD: some product's rows or columns are not whole blocks.
 template <bool GUARD>
@@ -308,9 +308,10 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const Gated
     typedef DirectCore Core;
     static_assert(Core::kMT * Core::kTile == kGroupC, "a wavefront's 128 Y rows: 64 of Wg, then the same 64 of Wu");
     extern __shared__ __align__(16) unsigned char smem[];
-    int P, w, tr, tc;
-    patch_of_block(blockIdx.x, P, w);
-    if (P >= p.grid.patches() || !tile_in_patch(p.grid, P, w, tr, tc)) return;
+    const int i = block_of_workgroup(blockIdx.x, p.grid.blocks());
+    if (i < 0) return;
+    int tr, tc;
+    block_at(p.grid, i, tr, tc);
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;      // c0 / 2 = first of the block's 128 columns of I
 
     Core::acc_t acc[Core::kMT][Core::kNT];
@@ -330,9 +331,10 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
     extern __shared__ __align__(16) unsigned char smem[];
     auto next_block = [&](int bid, Core::Block& blk) {
         for (; bid < total; bid += gridDim.x) {
-            int P, w, tr, tc;
-            patch_of_block(bid, P, w);
-            if (P >= p.grid.patches() || !tile_in_patch(p.grid, P, w, tr, tc)) continue;
+            const int i = block_of_workgroup(bid, p.grid.blocks());
+            if (i < 0) continue;
+            int tr, tc;
+            block_at(p.grid, i, tr, tc);
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
             blk = {uniform(p.X), p.ldx, uniform(p.Wg), p.ldw, p.rows_x, p.I, p.K, uniform(r0), uniform(c0),
                    warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x, p.I),
@@ -432,21 +434,21 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     bool guard = false, ktail = false;
     // persistent workgroups that fetch their next block early: one K, whole pairs of k-steps
     bool chain = !ps[0].y_kmajor && ps[0].K % (2 * kBlockK) == 0 && ps[0].K >= 4 * kBlockK;
-    int64_t patches = 0;
+    int64_t total = 0;
     for (int i = 0; i < n; ++i) {
         const LinearParams& p = ps[i];
         b.p[i] = p;
-        b.map.first_patch[i] = (int)patches;
+        b.map.first_block[i] = (int)total;
         const int tiles_r = (p.rows_x + kBlockR - 1) / kBlockR, tiles_c = (p.rows_y + kBlockC - 1) / kBlockC;
         b.map.g[i] = choose_patches(tiles_r, tiles_c);
-        patches += b.map.g[i].patches();
+        total += (int64_t)tiles_r * tiles_c;
         guard = guard || p.rows_x % kBlockR != 0 || p.rows_y % kBlockC != 0;
         ktail = ktail || p.K % kBlockK != 0;
         chain = chain && p.K == ps[0].K;
     }
-    if (patches * 32 > 0x7fffff00) return ALST_ERR_SHAPE;
-    for (int i = n; i <= kMaxBatch; ++i) b.map.first_patch[i] = (int)patches;
-    const int blocks = grid_for_patches(patches);
+    if (total > 0x7fffff00) return ALST_ERR_SHAPE;
+    for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
+    const int blocks = grid_for_blocks(total);
     ProfScope pr(PROF_MLP_LINEAR, s);
     const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
     const dim3 threads(DirectCore::kThreads);
@@ -471,18 +473,18 @@ static int launch_linear(const LinearParams& p, hipStream_t s) { return launch_l
 static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
     WgradBatch b = {};
     b.map.n = n;
-    int64_t patches = 0;
+    int64_t total = 0;
     for (int i = 0; i < n; ++i) {
         const WgradParams& p = ps[i];
         b.p[i] = p;
-        b.map.first_patch[i] = (int)patches;
+        b.map.first_block[i] = (int)total;
         const int tiles_r = (p.rows_x + kBlockR - 1) / kBlockR, tiles_c = (p.rows_y + kBlockC - 1) / kBlockC;
         b.map.g[i] = choose_patches(tiles_r, tiles_c);
-        patches += b.map.g[i].patches();
+        total += (int64_t)tiles_r * tiles_c;
     }
-    if (patches * 32 > 0x7fffff00) return ALST_ERR_SHAPE;
-    for (int i = n; i <= kMaxBatch; ++i) b.map.first_patch[i] = (int)patches;
-    const dim3 blocks((unsigned)grid_for_patches(patches)), threads(KMajorCore::kThreads);
+    if (total > 0x7fffff00) return ALST_ERR_SHAPE;
+    for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
+    const dim3 blocks((unsigned)grid_for_blocks(total)), threads(KMajorCore::kThreads);
     ProfScope pr(PROF_MLP_WGRAD, s);
     if (ps[0].K % kBlockK != 0)
         hipLaunchKernelGGL((wgrad_kernel<true>), blocks, threads, kLdsBytes, s, b);
@@ -531,7 +533,7 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
     gp.da = da; gp.a = a; gp.dgu = dgu;
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
-    const int blocks = grid_for_patches(gp.grid.patches());
+    const int blocks = grid_for_blocks(gp.grid.blocks());
     const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
     // persistent workgroups that fetch their next block early: whole pairs of k-steps
     const bool chain = P.H % (2 * kBlockK) == 0 && P.H >= 4 * kBlockK;
