@@ -132,6 +132,23 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
     ksteps = (KT + splits - 1) / splits;
 }
 
+// Ranges of V whose partial products of a full tile the workspace has room for.  The workspace's size is
+// part of the interface, so this is not the choice of dhidden_splits: the number (1..8) that fills the
+// compute units most evenly (ties: fewest), each range keeping at least 64 k-steps.
+static int64_t workspace_ranges(int64_t rows, int64_t H, int64_t V) {
+    const int64_t blocks = (rows / kBlockR) * ((H + kBlockC - 1) / kBlockC);
+    const int64_t KT = (V + kBlockK - 1) / kBlockK;
+    int64_t ranges = 1, best = 0, best_slots = 1;          // share of busy compute units: best / best_slots
+    const int sp_max = blocks >= 16 * kComputeUnits ? 1 : 8;
+    for (int sp = 1; sp <= sp_max; ++sp) {
+        const int64_t per = (KT + sp - 1) / sp;
+        if (sp > 1 && (per < 64 || (sp - 1) * per >= KT)) break;
+        const int64_t slots = (blocks * sp + kComputeUnits - 1) / kComputeUnits * kComputeUnits;
+        if (blocks * sp * best_slots > best * slots) { best = blocks * sp; best_slots = slots; ranges = sp; }
+    }
+    return ranges;
+}
+
 static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags) {
     Layout L;
     const int64_t T = tile < N ? tile : N;
@@ -158,10 +175,8 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     // full tile needs); a chunk then takes as many rows of the dW group as fit it with 24 bytes
     // per row and 4 per row and group (the partial products of dHidden reuse the softmax partials'
     // place, which row_finish has consumed by then).
-    int sp_full, ks;
-    dhidden_splits(L.Tp, H, V, 8 * L.Tp, sp_full, ks);
     const size_t region = (size_t)L.Tp * (20 + 8 * (size_t)L.ng) +
-                          (fwd_only ? 0 : (size_t)sp_full * L.Tp * H * 4);
+                          (fwd_only ? 0 : (size_t)workspace_ranges(L.Tp, H, V) * L.Tp * H * 4);
     const size_t at = take(region);
     const int64_t fit = (int64_t)(region / (24 + 4 * (size_t)L.ng)) / kBlockR * kBlockR;
     const int64_t rows = (N + kBlockR - 1) / kBlockR * kBlockR, Kn = L.Kg < rows ? L.Kg : rows;
@@ -190,7 +205,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
         // then keeps a smaller chunk's choice within these bounds)
         const int64_t rb_max = L.Rc / kBlockR, rb_lo = rb_max > 4096 ? rb_max : 1;
         for (int64_t rb = rb_lo; rb <= rb_max; ++rb) {
-            int sp;
+            int sp, ks;
             dhidden_splits(rb * kBlockR, H, V, L.dh_part_rows, sp, ks);
             const int64_t blocks = rb * pg.tiles_c * sp;
             if (blocks > L.dh_blocks) L.dh_blocks = blocks;

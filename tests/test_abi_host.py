@@ -42,6 +42,25 @@ def test_version_and_status_strings(lib):
     assert B.alst_status_string(99) == "unknown status"
 
 
+def test_workspace_sizes_stay_what_callers_have_allocated(lib):
+    """The sizes are part of the interface: a caller's buffer (or the static scratch) that held a problem
+    has to go on holding it, whatever the launches inside are."""
+    for N, H, V, tile, flags, size in [
+        (512, 256, 4096, 128, 0, 24457216),
+        (40575, 8, 24643, 731, 1, 308162304),
+        (84231, 32, 4374, 60, 8, 4371712),
+        (10, 2456, 27714, 536, 2, 549388288),
+        (3001, 1600, 50257, 1024, 0, 1391233536),
+        (131072, 4096, 128256, 4096, 0, 7590529024),
+        (32768, 4096, 128256, 2048, 16, 33629184),
+    ]:
+        assert B.alst_tiled_ce_workspace_bytes(N, H, V, tile, flags) == size, (N, H, V, tile, flags)
+    assert B.alst_tiled_mlp_workspace_bytes(4500, 72, 136, 100, True) == 1858304
+    assert B.alst_tiled_mlp_workspace_bytes(256000, 4096, 14336, 4096, True) == 2583691264
+    assert B.alst_tiled_mlp_workspace_bytes(256000, 4096, 14336, 4096, False) == 117440512
+    assert B.alst_tiled_linear_workspace_bytes(10000, 4096, 4096, 4096, True) == 100663296
+
+
 def test_workspace_is_independent_of_n_beyond_12_bytes_per_row(lib):
     H, V, T = 4096, 128256, 4096
     w = [B.alst_tiled_ce_workspace_bytes(N, H, V, T) for N in (32768, 131072, 524288)]
