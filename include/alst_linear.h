@@ -34,7 +34,7 @@ extern "C" {
 size_t alst_tiled_linear_workspace_bytes(int64_t N, int64_t K, int64_t M, int64_t tile, int backward,
                                          uint32_t flags);
 
-/* y [N,M] bf16 = x W^T, tile by tile (2 N K M flop). */
+/* y [N,M] bf16 = x W^T, in chunks of rows (2 N K M flop). */
 int alst_tiled_linear_forward(const void* x, const void* W, int64_t N, int64_t K, int64_t M,
                               int64_t tile, void* y, void* workspace, size_t workspace_bytes,
                               uint32_t flags, void* stream);

@@ -18,11 +18,15 @@
 //                                             k-major operands, dx as two contractions over I)
 //   per group  dWg += dg^T x, dWu += du^T x, dWd += dy^T a   (fp32, contraction over the group's rows)
 //
-// As in the cross-entropy path the weight gradients are accumulated once per group of tiles
-// (about 16384 rows), so the read-modify-write of the fp32 sums is paid once per group.  Their
-// operands have the contraction index (the token row) as the slow index and are read as they are
-// by the k-major cores: x and dy straight from the caller's arrays, a and [dg | du] from the
-// group's buffers.
+// The launches work on CHUNKS of consecutive rows whose length is chosen for the hardware
+// (chunk_rows), not by the caller's tile: the tile bounds the workspace and with it the chunks, of
+// the MLP forward to one tile rounded up to 256 rows, backward to a GROUP of tiles (about 16384
+// rows); the linear layer has no scratch per row.  a and [dg | du] of a group are kept for the weight
+// gradients, so that the read-modify-write of the fp32 sums is paid once per group.  da lives in
+// a's place: the gated epilogue reads an element of da and writes a's over it, from the same lane.
+// The weight gradients' operands have the contraction index (the token row) as the slow index and
+// are read as they are by the k-major cores: x and dy straight from the caller's arrays, a and
+// [dg | du] from the group's buffers.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <mutex>
@@ -40,29 +44,45 @@ constexpr int kMlpGroupRows = 16384;
 constexpr int kMlpGroupMax = 8;
 
 struct MlpLayout {
-    int64_t Tp, Kg;        // tile rows rounded up to 256; rows a weight-gradient group can hold
-    int g;                 // tiles per weight-gradient group
-    size_t a, da, dgu, wdt, wgut, acc_g, acc_u, acc_d, total;
+    int64_t Tp;            // tile rows rounded up to 256
+    int64_t chunk;         // rows per chunk of launches
+    int64_t rows;          // backward: rows of a weight-gradient group, whole chunks
+    size_t a, dgu, wdt, wgut, acc_g, acc_u, acc_d, total;
     bool weights_t;        // backward multiplies by transposed copies of the weights
 };
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// Rows of a chunk with `width` bf16 intermediates (or operand elements) per row: enough to fill the
+// chip, few enough that what one launch of a chunk writes is still in the 256 MB memory-side cache when
+// the next reads it.  4096 rows of a, dg and du of a 14336-wide MLP (352 MB): 244.9 ms for
+// 256000 x 4096; chunks of a whole group (17664 rows) 250.6 ms.  Launches of one 128-row
+// tile of a 256 x 768 MLP took 441 us where chunks take 175 us (N = 512).
+static int64_t chunk_rows(int64_t width) {
+    const int64_t rows = (int64_t)4096 * 3 * 14336 / width / kBlockR * kBlockR;
+    return rows < 4096 ? 4096 : rows > 65536 ? 65536 : rows;
+}
 
 static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, bool backward,
                                  uint32_t flags) {
     MlpLayout L = {};
     const int64_t T = tile < N ? tile : N;
     L.Tp = (T + 255) / 256 * 256;
-    int64_t g = kMlpGroupRows / L.Tp;
-    L.g = (int)(g < 1 ? 1 : (g > kMlpGroupMax ? kMlpGroupMax : g));
-    L.Kg = (int64_t)L.g * L.Tp;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    // backward keeps a and [dg | du] of the whole group, each tile behind the one before
-    L.a = take((size_t)(backward ? L.Kg : L.Tp) * I * 2);
-    if (backward) {
-        L.da = take((size_t)L.Tp * I * 2);
-        L.dgu = take((size_t)L.Kg * 2 * I * 2);
+    if (!backward) {
+        L.chunk = std::min(L.Tp, chunk_rows(3 * I));
+        L.a = take((size_t)L.Tp * I * 2);
+    } else {
+        // a and [dg | du] of a chunk, in the room that those of a group of g tiles and the da of one
+        // tile take
+        int64_t g = kMlpGroupRows / L.Tp;
+        g = g < 1 ? 1 : (g > kMlpGroupMax ? kMlpGroupMax : g);
+        const int64_t room = (g * 3 + 1) * L.Tp / 3 / kBlockR * kBlockR;
+        L.chunk = std::min(room, chunk_rows(3 * I));
+        L.rows = room / L.chunk * L.chunk;
+        L.a = take((size_t)(g * 3 + 1) * L.Tp * I * 2);
+        L.dgu = L.a + (size_t)L.rows * I * 2;
         // Wd transposed [I, H] and [Wg | Wu] transposed [H, 2 I], made once per call: da = dy Wd and
         // dx = [dg | du] [Wg ; Wu] then read both operands along their rows (the fastest layout
         // of the block GEMM).  For H and I that are whole k-steps; else the weights are read as
@@ -218,7 +238,7 @@ struct GatedParams {
     const uint16_t* X;       // [rows_x, ldx]   the tile's rows of x
     const uint16_t* Wg;      // [I, ldw]
     const uint16_t* Wu;      // [I, ldw]
-    const uint16_t* da;      // [rows_x, I]     backward
+    const uint16_t* da;      // [rows_x, I]     backward; may be `a`
     uint16_t* a;             // [rows_x, I]
     uint16_t* dgu;           // [rows_x, 2I]    backward
     int64_t ldx, ldw;
@@ -559,15 +579,12 @@ static int run_mlp_forward(const MlpProblem& P) {
     hipStream_t s = P.stream;
     uint16_t* a = reinterpret_cast<uint16_t*>(P.ws + L.a);
     const int H = (int)P.H, I = (int)P.I;
-    const int64_t T = P.tile < P.N ? P.tile : P.N;
-    const int64_t ntiles = (P.N + T - 1) / T;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int64_t i0 = t * T;
-        const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
-        rc = launch_gated(P, P.x + i0 * P.H, T_cur, nullptr, a, nullptr, s);
+    for (int64_t i0 = 0; i0 < P.N; i0 += L.chunk) {
+        const int rows = (int)std::min(L.chunk, P.N - i0);
+        rc = launch_gated(P, P.x + i0 * P.H, rows, nullptr, a, nullptr, s);
         if (rc != ALST_OK) return rc;
         LinearParams lp = {};
-        lp.X = a; lp.ldx = I; lp.rows_x = T_cur; lp.K = I;
+        lp.X = a; lp.ldx = I; lp.rows_x = rows; lp.K = I;
         lp.Y = P.Wd; lp.ldy = I; lp.rows_y = H;
         lp.D = P.y + i0 * P.H; lp.ldd = H;
         rc = launch_linear(lp, s);
@@ -582,7 +599,6 @@ static int run_mlp_backward(const MlpProblem& P) {
     const MlpLayout L = make_mlp_layout(P.N, P.H, P.I, P.tile, true, P.flags);
     hipStream_t s = P.stream;
     uint16_t* a = reinterpret_cast<uint16_t*>(P.ws + L.a);
-    uint16_t* da = reinterpret_cast<uint16_t*>(P.ws + L.da);
     uint16_t* dgu = reinterpret_cast<uint16_t*>(P.ws + L.dgu);
     const bool f32 = P.flags & ALST_FLAG_DW_FP32, accum = P.flags & ALST_FLAG_DW_ACCUMULATE;
     const bool in_out = f32 && !accum;
@@ -603,66 +619,57 @@ static int run_mlp_backward(const MlpProblem& P) {
         ALST_HIP(hipGetLastError());
     }
 
-    const int64_t T = P.tile < P.N ? P.tile : P.N;
-    const int64_t ntiles = (P.N + T - 1) / T;
-    int kofs = 0;                                   // rows of the group so far
-    int64_t group_row0 = 0;                         // first row of the group in x and dy
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int64_t i0 = t * T;
-        const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
-        const int slot = (int)(t % L.g);
-        if (slot == 0) { kofs = 0; group_row0 = i0; }
-        const uint16_t* x_t = P.x + i0 * P.H;
-        const uint16_t* dy_t = P.dy + i0 * P.H;
-        // the tile's rows of a and [dg | du] sit behind those of the group's earlier tiles
-        uint16_t* a_t = a + (int64_t)kofs * I;
-        uint16_t* dgu_t = dgu + (int64_t)kofs * I2;
+    for (int64_t i0 = 0; i0 < P.N; i0 += L.chunk) {
+        const int rows = (int)std::min(L.chunk, P.N - i0);
+        const int64_t group0 = i0 / L.rows * L.rows;         // first row of the chunk's group
+        uint16_t* const a_c = a + (i0 - group0) * I;
+        uint16_t* const dgu_c = dgu + (i0 - group0) * I2;
+        const uint16_t* x_c = P.x + i0 * P.H;
+        const uint16_t* dy_c = P.dy + i0 * P.H;
 
-        {   // da = dy_t Wd (contraction over H), then g and u again with a, dg, du made in the epilogue
+        {   // da = dy Wd (contraction over H), then g and u again with a, dg, du made in the epilogue
             LinearParams lp = {};
-            lp.X = dy_t; lp.ldx = H; lp.rows_x = T_cur; lp.K = H;
+            lp.X = dy_c; lp.ldx = H; lp.rows_x = rows; lp.K = H;
             if (L.weights_t) { lp.Y = wdt; lp.ldy = H; lp.rows_y = I; }            // Wd^T [I, H]
             else { lp.Y = P.Wd; lp.ldy = I; lp.rows_y = I; lp.y_kmajor = 1; }      // Wd [H, I]: k = h
-            lp.D = da; lp.ldd = I;
+            lp.D = a_c; lp.ldd = I;
             rc = launch_linear(lp, s);
-            if (rc == ALST_OK) rc = launch_gated(P, x_t, T_cur, da, a_t, dgu_t, s);
+            if (rc == ALST_OK) rc = launch_gated(P, x_c, rows, a_c, a_c, dgu_c, s);
             if (rc != ALST_OK) return rc;
         }
         {   // dx = dg Wg + du Wu
             LinearParams lp = {};
-            lp.X = dgu_t; lp.ldx = I2; lp.rows_x = T_cur;
+            lp.X = dgu_c; lp.ldx = I2; lp.rows_x = rows;
             if (L.weights_t) {
                 // one contraction over the 2 I columns of [dg | du] against [Wg | Wu]^T [H, 2 I]
                 lp.K = (int)I2; lp.Y = wgut; lp.ldy = I2; lp.rows_y = H;
             } else {
                 // two contractions over I summed in the accumulators, the weights as they are
                 lp.K = I; lp.Y = P.Wg; lp.ldy = H; lp.rows_y = H; lp.y_kmajor = 1;     // Wg [I, H]: k = i
-                lp.X2 = dgu_t + I; lp.Y2 = P.Wu;
+                lp.X2 = dgu_c + I; lp.Y2 = P.Wu;
             }
             lp.D = P.dx + i0 * P.H; lp.ldd = H;
             rc = launch_linear(lp, s);
             if (rc != ALST_OK) return rc;
         }
-        kofs += T_cur;
-        if (slot == L.g - 1 || t == ntiles - 1) {       // the group is complete
-            GradOut out = {nullptr, nullptr, 0, 1.f, t < L.g, t == ntiles - 1, f32, accum};
-            auto into = [&](float* sums, void* dW, int64_t ld) { out.sums = sums; out.out = dW; out.ld = ld; return out; };
-            const uint16_t* x_g = P.x + group_row0 * P.H;
-            const uint16_t* dy_g = P.dy + group_row0 * P.H;
-            WgradParams wp[kMaxBatch] = {};
-            wp[0].K = kofs;
-            wp[0].X = x_g; wp[0].ldx = H; wp[0].rows_x = H;
-            wp[0].Y = dgu; wp[0].ldy = I2; wp[0].rows_y = I;
-            wp[0].out = into(acc_g, P.dWg, H);                                       // dWg[i][h]
-            wp[1] = wp[0];
-            wp[1].Y = dgu + I; wp[1].out = into(acc_u, P.dWu, H);                    // dWu[i][h]
-            wp[2] = wp[0];
-            wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I;
-            wp[2].Y = dy_g; wp[2].ldy = H; wp[2].rows_y = H;
-            wp[2].out = into(acc_d, P.dWd, I);                                       // dWd[h][i]
-            rc = launch_wgrad(wp, 3, s);                                             // one launch
-            if (rc != ALST_OK) return rc;
-        }
+        const int64_t in_group = i0 + rows - group0;
+        if (in_group < L.rows && i0 + rows < P.N) continue;
+        // the group is complete
+        GradOut out = {nullptr, nullptr, 0, 1.f, group0 == 0, i0 + rows == P.N, f32, accum};
+        auto into = [&](float* sums, void* dW, int64_t ld) { out.sums = sums; out.out = dW; out.ld = ld; return out; };
+        WgradParams wp[kMaxBatch] = {};
+        wp[0].K = (int)in_group;
+        wp[0].X = P.x + group0 * H; wp[0].ldx = H; wp[0].rows_x = H;
+        wp[0].Y = dgu; wp[0].ldy = I2; wp[0].rows_y = I;
+        wp[0].out = into(acc_g, P.dWg, H);                                       // dWg[i][h]
+        wp[1] = wp[0];
+        wp[1].Y = dgu + I; wp[1].out = into(acc_u, P.dWu, H);                    // dWu[i][h]
+        wp[2] = wp[0];
+        wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I;
+        wp[2].Y = P.dy + group0 * H; wp[2].ldy = H; wp[2].rows_y = H;
+        wp[2].out = into(acc_d, P.dWd, I);                                       // dWd[h][i]
+        rc = launch_wgrad(wp, 3, s);                                             // one launch
+        if (rc != ALST_OK) return rc;
     }
     return ALST_OK;
 }
@@ -670,9 +677,11 @@ static int run_mlp_backward(const MlpProblem& P) {
 // ---------------------------------------------------------------------------------------------
 // the single tiled linear layer: y = x W^T, dx = dy W, dW = dy^T x
 // ---------------------------------------------------------------------------------------------
+// (its launches read their operand's rows once per 2048 columns of the output)
+static int64_t lin_chunk_rows(int64_t K, int64_t M) { return chunk_rows(K + M); }
+
 struct LinLayout {
     int64_t Tp;
-    int g;                 // tiles per weight-gradient group
     size_t acc, wt, total;
     bool weight_t;         // backward multiplies dy by a transposed copy of W
 };
@@ -682,8 +691,6 @@ static LinLayout make_lin_layout(int64_t N, int64_t K, int64_t M, int64_t tile, 
     LinLayout L = {};
     const int64_t T = tile < N ? tile : N;
     L.Tp = (T + 255) / 256 * 256;
-    int64_t g = kMlpGroupRows / L.Tp;
-    L.g = (int)(g < 1 ? 1 : (g > kMlpGroupMax ? kMlpGroupMax : g));
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     if (backward) {
@@ -733,13 +740,10 @@ static int validate_lin(const LinProblem& P, size_t workspace_bytes, bool backwa
 static int run_lin_forward(const LinProblem& P) {
     int rc = prepare_mlp_kernels();
     if (rc != ALST_OK) return rc;
-    const int64_t T = P.tile < P.N ? P.tile : P.N;
-    const int64_t ntiles = (P.N + T - 1) / T;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int64_t i0 = t * T;
-        const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
+    const int64_t chunk = lin_chunk_rows(P.K, P.M);
+    for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
         LinearParams lp = {};
-        lp.X = P.x + i0 * P.K; lp.ldx = P.K; lp.rows_x = T_cur; lp.K = (int)P.K;
+        lp.X = P.x + i0 * P.K; lp.ldx = P.K; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = (int)P.K;
         lp.Y = P.W; lp.ldy = P.K; lp.rows_y = (int)P.M;
         lp.D = P.y + i0 * P.M; lp.ldd = P.M;
         rc = launch_linear(lp, P.stream);
@@ -766,32 +770,28 @@ static int run_lin_backward(const LinProblem& P) {
                            dim3(256), 0, s, P.W, M, K, (int64_t)K, wt, (int64_t)M);
         ALST_HIP(hipGetLastError());
     }
-    int kofs = 0;                                   // rows of the group so far
-    int64_t group_row0 = 0;
-    for (int64_t t = 0; t < ntiles; ++t) {
-        const int64_t i0 = t * T;
-        const int T_cur = (int)((P.N - i0) < T ? (P.N - i0) : T);
-        const int slot = (int)(t % L.g);
-        if (slot == 0) { kofs = 0; group_row0 = i0; }
+    const int64_t chunk = lin_chunk_rows(P.K, P.M);
+    for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
         LinearParams lp = {};
-        lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = T_cur; lp.K = M;
+        lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = M;
         if (L.weight_t) { lp.Y = wt; lp.ldy = M; lp.rows_y = K; }         // W^T [K, M]
         else { lp.Y = P.W; lp.ldy = K; lp.rows_y = K; lp.y_kmajor = 1; }  // W [M, K]: k = m
         lp.D = P.dx + i0 * P.K; lp.ldd = K;
         rc = launch_linear(lp, s);
         if (rc != ALST_OK) return rc;
-        kofs += T_cur;
-        if (slot == L.g - 1 || t == ntiles - 1) {
-            // dW[m][k] += sum over the group's rows of dy[t][m] x[t][k]: both operands are read
-            // from the caller's arrays as they are
-            WgradParams wp = {};
-            wp.X = P.x + group_row0 * P.K; wp.ldx = K; wp.rows_x = K;
-            wp.Y = P.dy + group_row0 * P.M; wp.ldy = M; wp.rows_y = M;
-            wp.K = kofs;
-            wp.out = {acc, P.dW, K, 1.f, t < L.g, t == ntiles - 1, f32, accum};
-            rc = launch_wgrad(wp, s);
-            if (rc != ALST_OK) return rc;
-        }
+    }
+    const int64_t group = std::max<int64_t>(kMlpGroupRows, L.Tp);
+    for (int64_t i0 = 0; i0 < P.N; i0 += group) {
+        // dW[m][k] += sum over the group's rows of dy[t][m] x[t][k]: both operands are read
+        // from the caller's arrays as they are
+        const int64_t rows = std::min(group, P.N - i0);
+        WgradParams wp = {};
+        wp.X = P.x + i0 * P.K; wp.ldx = K; wp.rows_x = K;
+        wp.Y = P.dy + i0 * P.M; wp.ldy = M; wp.rows_y = M;
+        wp.K = (int)rows;
+        wp.out = {acc, P.dW, K, 1.f, i0 == 0, i0 + rows == P.N, f32, accum};
+        rc = launch_wgrad(wp, s);
+        if (rc != ALST_OK) return rc;
     }
     return ALST_OK;
 }
