@@ -105,6 +105,26 @@ __host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
     return round * kRound + xcd * per + (xcd < more ? xcd : more) + slot;
 }
 
+// The last round, if it fills no more than half of the compute units, is worked on in halves: two
+// workgroups take a block's upper and lower 128 rows (HalfCore; the same k order, so the same
+// results).  numbers: what the launch's workgroups are dealt, blocks below `full` whole, the others
+// as halves.
+struct Halving {
+    int full, numbers;
+    // number -> its block; half: 0, 1 or -1 (whole)
+    __host__ __device__ __forceinline__ int block(int number, int& half) const {
+        half = -1;
+        if (number < full) return number;
+        half = (number - full) & 1;
+        return full + (number - full) / 2;
+    }
+};
+__host__ __device__ __forceinline__ Halving halve_last_round(int blocks) {
+    const int full = blocks / kRound * kRound, left = blocks - full;
+    if (2 * left > kRound) return {blocks, blocks};
+    return {full, full + 2 * left};
+}
+
 // Block (tr, tc) of number i < g.blocks() in the order.
 __host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, int& tr, int& tc) {
     const int column = i / (g.tiles_r * g.PC);               // column of patches
@@ -484,15 +504,17 @@ typedef KMajorDirectT<false> MixedCore;
 // faster (16-row operand reads, half the address arithmetic per k-step; with register-resident
 // operands the two forms are level to 4 % apart).  It is the fastest of the cores, so products
 // over a weight's row index are run on it against a copy of the weight transposed once per call.
-struct DirectCore {
+template <int NT>
+struct DirectCoreT {
     static constexpr int kThreads = 256;
     static constexpr int kMT = 8;     // 16-wide c tiles per wavefront
-    static constexpr int kNT = 8;     // 16-wide r tiles per wavefront
+    static constexpr int kNT = NT;    // 16-wide r tiles per wavefront: 8, or 4 for half a block (128 r)
+    static constexpr int kWaveR = 16 * NT;                 // r one wavefront covers
     typedef f32x4_t acc_t;
     static constexpr int kTile = 16, kRuns = 1, kGroups = 4;
 
     // acc[mt][nt][x]: r = nt * 16 + lane % 16, c = mt * 16 + 4 (lane / 16) + x inside the wavefront's
-    // 128 x 128.
+    // kWaveR x 128.
     struct Lane {
         int lane, grp, lrow, wr, wc;
         __device__ __forceinline__ Lane() {
@@ -504,8 +526,8 @@ struct DirectCore {
             wr = wave & 1;
             wc = wave >> 1;
         }
-        __device__ __forceinline__ int r(int nt) const { return wr * 128 + nt * 16 + lrow; }
-        __device__ __forceinline__ int rbase(int nt) const { return wr * 128 + nt * 16; }
+        __device__ __forceinline__ int r(int nt) const { return wr * kWaveR + nt * 16 + lrow; }
+        __device__ __forceinline__ int rbase(int nt) const { return wr * kWaveR + nt * 16; }
         __device__ __forceinline__ int cw(int mt, int /*q*/) const { return mt * 16 + grp * 4; }
         __device__ __forceinline__ int c(int mt, int q) const { return wc * kGroupC + cw(mt, q); }
     };
@@ -554,13 +576,13 @@ struct DirectCore {
         int rofs[2], xbase, ybase;     // LDS read offsets
         // the block the DMA works for: the lane's sources of k-step 0, the warm-up row, the k-steps
         // and (KTAIL) the k of the last one
-        const uint16_t* xg[8];
+        const uint16_t* xg[NT];
         const uint16_t* yg[8];
         const uint16_t* warm;
         int64_t warm_stride;
         int KT_, klast;
         // MFMA operands of the two k-slices of a step: fy[s][t], fx[s][t] for slice s
-        bf16x8_t fy[2][8], fx[2][8];
+        bf16x8_t fy[2][8], fx[2][NT];
 
         __device__ __forceinline__ explicit Pipe(unsigned char* smem_) : smem(smem_) {
             const int tid = threadIdx.x, lane = tid & 63;
@@ -569,14 +591,15 @@ struct DirectCore {
             const int l15 = lane & 15, g = lane >> 4;
             // One DMA instruction moves 8 rows x 128 bytes: lane -> (row = lane / 8, LDS chunk slot
             // = lane % 8); the lane fetches the global chunk that belongs in its slot.  Wave w owns
-            // rows [64 w, 64 w + 64) of both operand tiles: 8 instructions per operand per k-step.
+            // rows [64 w, 64 w + 64) of an operand tile, 8 instructions per k-step (of the 128 rows of
+            // X of half a block [32 w, 32 w + 32), 4 instructions).
             lr = lane >> 3;
             pc = lane & 7;
             // Operand reads.  A k-step is two slices of 32 k; lane (row l15 of a 16-row tile,
             // k-group g) reads the 16-byte chunk 4 s + g of its row: one read per operand.
 #pragma unroll
             for (int s = 0; s < 2; ++s) rofs[s] = ((4 * s + g) ^ swz(l15)) * 16;
-            xbase = (wr * 128 + l15) * 128;
+            xbase = (wr * kWaveR + l15) * 128;
             ybase = 2 * kTileBytes + (wc * kGroupC + l15) * 128;
         }
         __device__ __forceinline__ void target(const Block& b) {
@@ -588,8 +611,11 @@ struct DirectCore {
             for (int q = 0; q < 8; ++q) {
                 const int row = (w * 8 + q) * 8 + lr;
                 const int kc = pc ^ swz(row);
-                const int xrow = b.r0 + row < b.rows_x ? b.r0 + row : b.rows_x - 1;     // (the clamps: see Block)
-                xg[q] = b.X + (int64_t)xrow * b.ldx + kc * 8;
+                if (q < NT) {                       // (the clamps: see Block)
+                    const int xr = (w * NT + q) * 8 + lr;
+                    const int xrow = b.r0 + xr < b.rows_x ? b.r0 + xr : b.rows_x - 1;
+                    xg[q < NT ? q : 0] = b.X + (int64_t)xrow * b.ldx + kc * 8;
+                }
                 if (b.Y2) {                         // gated pair
                     bool valid;
                     yg[q] = paired_row(b.Y, b.Y2, b.ldy, b.c0, row, b.rows_y, valid) + kc * 8;   // (missing rows: row 0)
@@ -607,24 +633,24 @@ struct DirectCore {
                                                                : reinterpret_cast<const uint16_t*>(zero_chunk);
         }
         __device__ __forceinline__ void issue_loads(int stage, int kt) {
-            unsigned char* xs = smem + stage * kTileBytes + w * 8192;
+            unsigned char* xs = smem + stage * kTileBytes + w * (NT * 1024);
             unsigned char* ys = smem + 2 * kTileBytes + stage * kTileBytes + w * 8192;
             const bool tail = KTAIL && kt == KT_ - 1;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                dma_to_lds<16>(src(xg[q], q, kt, tail), xs + q * 1024);
+                if (q < NT) dma_to_lds<16>(src(xg[q < NT ? q : 0], q, kt, tail), xs + q * 1024);
                 dma_to_lds<16>(src(yg[q], q, kt, tail), ys + q * 1024);
             }
         }
-        // item 0..7: the Y operand of accumulator row t = item, 8..15: the X operand of column t
+        // item 0..7: the Y operand of accumulator row t = item, 8..: the X operand of column item - 8
         __device__ __forceinline__ void read_item(int stage, int s, int item) {
             const unsigned char* base = smem + stage * kTileBytes + rofs[s];
             if (item < 8) fy[s][item] = *reinterpret_cast<const bf16x8_t*>(base + ybase + item * 2048);
             else fx[s][item - 8] = *reinterpret_cast<const bf16x8_t*>(base + xbase + (item - 8) * 2048);
         }
-        // the four MFMAs of slot i (0..15) of a slice
+        // the four MFMAs of slot i (0 .. 2 NT - 1) of a slice
         __device__ __forceinline__ void mfma_quad(acc_t (&acc)[kMT][kNT], int s, int i) {
-            const int mt = i >> 1, n0 = (i & 1) * 4;
+            const int mt = NT == 8 ? i >> 1 : i, n0 = NT == 8 ? (i & 1) * 4 : 0;
 #pragma unroll
             for (int d = 0; d < 4; ++d)
                 acc[mt][n0 + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fy[s][mt], fx[s][n0 + d],
@@ -672,8 +698,13 @@ struct DirectCore {
         __device__ __forceinline__ void kstep(acc_t (&acc)[kMT][kNT], int kt, int dkt, bool behind,
                                               const Block* ahead) {
             const int cur_stage = kt & 1;
-            unsigned char* const xs = smem + cur_stage * kTileBytes + w * 8192;
+            unsigned char* const xs = smem + cur_stage * kTileBytes + w * (NT * 1024);
             unsigned char* const ys = smem + 2 * kTileBytes + cur_stage * kTileBytes + w * 8192;
+            if constexpr (NT == 4) {
+                half_kstep<LOADS, NEXT, TAIL>(acc, cur_stage, xs, ys, dkt, behind);
+                if (LOADS) warm_step(dkt + 2 + kWarmAhead, ahead);
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 mfma_quad(acc, 0, i);
@@ -693,7 +724,7 @@ struct DirectCore {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 mfma_quad(acc, 1, i);
-                if (LOADS) dma_to_lds<16>(src(xg[i], i, dkt + 2, TAIL), xs + i * 1024);
+                if (LOADS) dma_to_lds<16>(src(xg[i % NT], i, dkt + 2, TAIL), xs + i * 1024);
                 if (NEXT) read_item(cur_stage ^ 1, 0, i);
                 __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
                 if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -713,6 +744,55 @@ struct DirectCore {
             if (LOADS) warm_step(dkt + 2 + kWarmAhead, ahead);
         }
 
+        // The k-step of half a block: eight slots per slice, the twelve operand reads of a slice and the
+        // twelve DMA instructions spread over them in the same order.
+        template <bool LOADS, bool NEXT, bool TAIL>
+        __device__ __forceinline__ void half_kstep(acc_t (&acc)[kMT][kNT], int cur_stage, unsigned char* xs,
+                                                   unsigned char* ys, int dkt, bool behind) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                mfma_quad(acc, 0, i);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) read_item(cur_stage, 1, 3 * i + q);
+                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 4; i < 8; ++i) {
+                mfma_quad(acc, 0, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            stage_barrier(behind);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                mfma_quad(acc, 1, i);
+                if (LOADS) {
+                    dma_to_lds<16>(src(xg[i % NT], i, dkt + 2, TAIL), xs + i * 1024);
+                    dma_to_lds<16>(src(yg[i], i, dkt + 2, TAIL), ys + i * 1024);
+                }
+                if (NEXT) {
+                    read_item(cur_stage ^ 1, 0, i);
+                    read_item(cur_stage ^ 1, 0, 8 + i);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+                if (NEXT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 4; i < 8; ++i) {
+                mfma_quad(acc, 1, i);
+                if (LOADS) dma_to_lds<16>(src(yg[i], i, dkt + 2, TAIL), ys + i * 1024);
+                if (NEXT) read_item(cur_stage ^ 1, 0, i);
+                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                if (LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                if (NEXT) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+
         // ---- one block per workgroup
         __device__ __forceinline__ void single(const Block& b, acc_t (&acc)[kMT][kNT]) {
             const int KT = (b.K + kBlockK - 1) / kBlockK;
@@ -722,7 +802,7 @@ struct DirectCore {
             __syncthreads();                   // waits for the DMA (vmcnt) and joins the waves
             if (KT > 1) issue_loads(1, 1);
 #pragma unroll
-            for (int item = 0; item < 16; ++item) read_item(0, 0, item);
+            for (int item = 0; item < 8 + NT; ++item) read_item(0, 0, item);
             // a step's barrier may leave one load in flight iff the step before it had LOADS and warmed
             int kt = 0;
             for (; kt + (KTAIL ? 3 : 2) < KT; ++kt) kstep<true, true>(acc, kt, kt, kt > 0, nullptr);
@@ -755,7 +835,7 @@ struct DirectCore {
             // every wavefront's part of k-step 0 has landed, and all are done with the block before
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-            for (int item = 0; item < 16; ++item) read_item(0, 0, item);
+            for (int item = 0; item < 8 + NT; ++item) read_item(0, 0, item);
             int kt = 0;
             for (; kt + 2 + kWarmAhead < KT; ++kt) kstep<true, true>(acc, kt, kt, kt > 0, nullptr);
             // (the warm-up loads of these steps are for the first steps of `next`)
@@ -769,13 +849,19 @@ struct DirectCore {
         __device__ __forceinline__ void finish() { stage_barrier(false); }
     };
 
-    // One block on its own.
+    // One block (or half of one) on its own.
     template <bool KTAIL>
     static __device__ __forceinline__ void gemm(const Block& b, unsigned char* smem, acc_t (&acc)[kMT][kNT]) {
         Pipe<KTAIL> pipe(smem);
         pipe.single(b, acc);
     }
 };
+typedef DirectCoreT<8> DirectCore;
+// Half a block, for a last round that leaves half of the compute units or more idle.  It reads 384
+// operand rows per k-step where a whole block reads 512 for twice the work, so it takes more than half of
+// a block's time.  linear 10000 x 4096 x 4096 (2.5 rounds): 784 -> 765 us; mlp 6000 x 4096 x 14336:
+// 6327 -> 6082 us; calls of a few blocks gain most (mlp 512 x 256 x 768: 176 -> 126 us).
+typedef DirectCoreT<4> HalfCore;
 
 // ---------------------------------------------------------------------------------------------
 // out[c][r] = in[r][c] (bf16), zeros for rows <= r < the 64 rows of the last piece

@@ -107,7 +107,8 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // dHidden has (rows / 256) * (H / 256) output blocks for a chunk of `rows` dense rows (a multiple
 // of 256).  Picks the number of ranges (1..8) the contraction over V is cut into: the one with the
 // least estimated time, in units of a k-step of one block (1.5 us on gfx950): rounds of the 256
-// compute units times (k-steps per range + about 4 for the block's start and epilogue) and, if cut,
+// compute units (a last one in halves: 5/8) times (k-steps per range + about 4 for the block's start
+// and epilogue) and, if cut,
 // the partial products' way through memory (256 KB per block and range written and read back at
 // about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps at least 16 k-steps.
 // The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
@@ -125,8 +126,9 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int per = (KT + sp - 1) / sp;
         if (sp > 1 && (per < 16 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
-        const int64_t rounds = (blocks * sp + kComputeUnits - 1) / kComputeUnits;
-        const int64_t cost = 16 * rounds * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
+        const int64_t left = blocks * sp % kComputeUnits;
+        const int64_t rounds16 = blocks * sp / kComputeUnits * 16 + (left == 0 ? 0 : 2 * left <= kComputeUnits ? 10 : 16);
+        const int64_t cost = rounds16 * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
         if (cost < best) { best = cost; splits = sp; }
     }
     ksteps = (KT + splits - 1) / splits;
@@ -661,28 +663,22 @@ struct LogitsParams {
 // REDO: the second pass over a chunk, for the rows whose first-pass sums left the safe range; its
 // workgroups leave at once unless row_finish flagged the chunk, and rows that are not marked keep
 // what the first pass wrote.
+// Core: DirectCore for a block, HalfCore for one half of its rows.  r0: the rows' first, tr: the whole
+// block's.
 template <class Core, bool KTAIL, int MODE, bool REDO>
-__global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsParams p) {
+__device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, int Trc, int tr, int tc, int r0,
+                                             unsigned char* smem) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    extern __shared__ __align__(16) unsigned char smem[];
-    int tr, tc;
-    const int T_cur = p.info->Tc, Trc = p.info->Trc;
-    if (T_cur == 0) return;
-    if (REDO && !p.info->redo) return;
-    {
-        const PatchGrid pg = {Trc / kBlockR, p.Vp / kBlockC, p.PR, p.PC};
-        const int i = block_of_workgroup(blockIdx.x, pg.blocks());
-        if (i < 0) return;
-        block_at(pg, i, tr, tc);
-    }
-    const int r0 = tr * kBlockR, c0 = tc * kBlockC;
+    const int c0 = tc * kBlockC;
+    if (r0 >= T_cur) return;        // (a second half of padding rows: the consumers' k-steps end before it)
     constexpr int kRegs = 4 * Core::kRuns;          // accumulator registers of a tile
 
     typename Core::acc_t acc[kMT][kNT];
     zero_acc<Core>(acc);
 
     const uint16_t* const hidden_t = p.hidden_t;
-    const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V);
+    const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, tr * kBlockR, tr, p.W, p.H, c0, tc, nullptr, Trc,
+                                    p.V);
     Core::template gemm<KTAIL>({hidden_t, p.Hk, p.W, p.H, Trc, p.V, p.H, r0, c0, warm, kBlockK, nullptr}, smem,
                                acc);
 
@@ -778,6 +774,22 @@ __global__ __launch_bounds__(Core::kThreads) void logits_kernel(const LogitsPara
     }
 }
 
+template <bool KTAIL, int MODE, bool REDO>
+__global__ __launch_bounds__(DirectCore::kThreads) void logits_kernel(const LogitsParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int T_cur = p.info->Tc, Trc = p.info->Trc;
+    if (T_cur == 0) return;
+    if (REDO && !p.info->redo) return;
+    const PatchGrid pg = {Trc / kBlockR, p.Vp / kBlockC, p.PR, p.PC};
+    const Halving last = halve_last_round(pg.blocks());
+    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    if (number < 0) return;
+    int tr, tc, half;
+    block_at(pg, last.block(number, half), tr, tc);
+    if (half < 0) logits_block<DirectCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR, smem);
+    else logits_block<HalfCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+}
+
 struct DHiddenParams {
     const uint16_t* dz;      // [Rc, Vp]     the chunk's dense rows
     const uint16_t* Wt;      // [H, Vp]      W transposed (k = vocabulary id contiguous), zero beyond V
@@ -802,22 +814,13 @@ struct DHiddenParams {
 // number does not fill the compute units evenly, the contraction is cut into `splits` ranges, each
 // range's blocks write fp32 partial products, and dhidden_reduce_kernel adds them in a fixed
 // order.
+// Core, r0, tr: as in logits_block.
 template <class Core>
-__global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenParams p) {
+__device__ __forceinline__ void dhidden_block(const DHiddenParams& p, int T_cur, int Trc, int splits, int ksteps,
+                                              int split, int tr, int tc, int r0, unsigned char* smem) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    extern __shared__ __align__(16) unsigned char smem[];
-    int tr, tc;
-    const int tiles_c = (p.H + kBlockC - 1) / kBlockC;
-    const int T_cur = p.info->Tc, Trc = p.info->Trc;
-    if (T_cur == 0) return;
-    // the ranges are parts of one launch: their blocks are numbered through
-    const PatchGrid pg = {Trc / kBlockR, tiles_c, p.PR, p.PC};
-    const int splits = p.info->splits, ksteps = p.info->ksteps;
-    const int i = block_of_workgroup(blockIdx.x, pg.blocks() * splits);
-    if (i < 0) return;
-    const int split = i / pg.blocks();
-    block_at(pg, i - split * pg.blocks(), tr, tc);
-    const int r0 = tr * kBlockR, c0 = tc * kBlockC;
+    const int c0 = tc * kBlockC;
+    if (r0 >= T_cur) return;
     // k runs over V rounded up to whole k-steps: dZ and Wt are zero there
     const int k0 = split * ksteps * kBlockK;
     const int klen = min(ksteps * kBlockK, (p.V + kBlockK - 1) / kBlockK * kBlockK - k0);     // > 0
@@ -829,7 +832,7 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
     const uint16_t* const Wk = p.Wt + k0;
     // (a hidden size that ends inside the block: the rows of Wt beyond H are read from its last
     // row, and the epilogue skips those columns)
-    const uint16_t* warm = warm_row(p.PR, p.PC, dz, p.Vp, r0, tr, Wk, p.Vp, c0, tc, nullptr, Trc, p.H);
+    const uint16_t* warm = warm_row(p.PR, p.PC, dz, p.Vp, tr * kBlockR, tr, Wk, p.Vp, c0, tc, nullptr, Trc, p.H);
     Core::template gemm<false>({dz, p.Vp, Wk, p.Vp, Trc, p.H, klen, r0, c0, warm, kBlockK, nullptr}, smem, acc);
 
     const typename Core::Lane lp;
@@ -871,6 +874,23 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_kernel(const DHiddenPa
                 *reinterpret_cast<bf16x4_t*>(row + h) = o;
             }
     }
+}
+
+__global__ __launch_bounds__(DirectCore::kThreads) void dhidden_kernel(const DHiddenParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int T_cur = p.info->Tc, Trc = p.info->Trc;
+    if (T_cur == 0) return;
+    // the ranges are parts of one launch: their blocks are numbered through
+    const PatchGrid pg = {Trc / kBlockR, (p.H + kBlockC - 1) / kBlockC, p.PR, p.PC};
+    const int splits = p.info->splits, ksteps = p.info->ksteps;
+    const Halving last = halve_last_round(pg.blocks() * splits);
+    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    if (number < 0) return;
+    int tr, tc, half;
+    const int i = last.block(number, half), split = i / pg.blocks();
+    block_at(pg, i - split * pg.blocks(), tr, tc);
+    if (half < 0) dhidden_block<DirectCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR, smem);
+    else dhidden_block<HalfCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
 
 // dH[idx[i]] = (g/M) (1/S_i) * sum over the ranges of the partial products of dense row i, in
@@ -947,17 +967,17 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
 static int prepare_kernels_on_current_device() {
     int rc = ALST_OK;
     auto acc = [&](int r) { if (r != ALST_OK) rc = r; };
-    acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_FWD, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_FWD, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_FUSED, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_FUSED, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_BWD, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_BWD, false>));
-    acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_FWD, true>));
-    acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_FWD, true>));
-    acc(allow_big_lds(logits_kernel<DirectCore, false, MODE_FUSED, true>));
-    acc(allow_big_lds(logits_kernel<DirectCore, true, MODE_FUSED, true>));
-    acc(allow_big_lds(dhidden_kernel<DirectCore>));
+    acc(allow_big_lds(logits_kernel<false, MODE_FWD, false>));
+    acc(allow_big_lds(logits_kernel<true, MODE_FWD, false>));
+    acc(allow_big_lds(logits_kernel<false, MODE_FUSED, false>));
+    acc(allow_big_lds(logits_kernel<true, MODE_FUSED, false>));
+    acc(allow_big_lds(logits_kernel<false, MODE_BWD, false>));
+    acc(allow_big_lds(logits_kernel<true, MODE_BWD, false>));
+    acc(allow_big_lds(logits_kernel<false, MODE_FWD, true>));
+    acc(allow_big_lds(logits_kernel<true, MODE_FWD, true>));
+    acc(allow_big_lds(logits_kernel<false, MODE_FUSED, true>));
+    acc(allow_big_lds(logits_kernel<true, MODE_FUSED, true>));
+    acc(allow_big_lds(dhidden_kernel));
     acc(allow_big_lds(dw_kernel<KMajorCore>));
     return rc;
 }
@@ -1027,10 +1047,10 @@ static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
     lp.PR = pg.PR; lp.PC = pg.PC;
     const int grid = grid_for_blocks(pg.blocks());
     if (ktail)
-        hipLaunchKernelGGL((logits_kernel<DirectCore, true, MODE, REDO>), dim3(grid),
+        hipLaunchKernelGGL((logits_kernel<true, MODE, REDO>), dim3(grid),
                            dim3(DirectCore::kThreads), kLdsBytes, s, lp);
     else
-        hipLaunchKernelGGL((logits_kernel<DirectCore, false, MODE, REDO>), dim3(grid),
+        hipLaunchKernelGGL((logits_kernel<false, MODE, REDO>), dim3(grid),
                            dim3(DirectCore::kThreads), kLdsBytes, s, lp);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
@@ -1188,7 +1208,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
             const int grid = grid_for_blocks(L.dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
-            hipLaunchKernelGGL((dhidden_kernel<DirectCore>), dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
+            hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
                                s, dp);
             if (L.dh_cut)
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr), dim3(256), 0, s, dp.part, H, idx_t,

@@ -125,10 +125,13 @@ struct BatchMap {
     PatchGrid g[kMaxBatch];
     int first_block[kMaxBatch + 1];      // first_block[i] .. first_block[i + 1]: blocks of part i
     int n;
-    // which part and which of its blocks a workgroup works on; false for padding workgroups
-    __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC) const {
-        const int i = block_of_workgroup(bid, first_block[n]);
-        if (i < 0) return false;
+    Halving last;                        // (MixedCore and KMajorCore: every block whole)
+    // which part and which of its blocks (or halves, see Halving) a workgroup works on; false for
+    // padding workgroups
+    __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC, int& half) const {
+        const int number = block_of_workgroup(bid, last.numbers);
+        if (number < 0) return false;
+        const int i = last.block(number, half);
         which = 0;
 #pragma unroll
         for (int k = 1; k < kMaxBatch; ++k)
@@ -144,20 +147,34 @@ struct LinearBatch {
     BatchMap map;
 };
 
+// One block, or half of one, of a product of two k-contiguous operands; r0: the rows' first, tr: the
+// whole block's.
+template <class Core, bool KTAIL, bool GUARD>
+__device__ __forceinline__ void linear_block(const LinearParams& p, int PR, int PC, int tr, int tc, int r0,
+                                             unsigned char* smem) {
+    const int c0 = tc * kBlockC;
+    if (r0 >= p.rows_x) return;                    // (the second half of a block that has no such rows)
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    const uint16_t* warm = warm_row(PR, PC, p.X, p.ldx, tr * kBlockR, tr, p.Y, p.ldy, c0, tc, nullptr, p.rows_x,
+                                    p.rows_y);
+    Core::template gemm<KTAIL>({p.X, p.ldx, p.Y, p.ldy, p.rows_x, p.rows_y, p.K, r0, c0, warm, kBlockK, nullptr},
+                               smem, acc);
+    store_block_bf16<Core, GUARD>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
+}
+
 // KTAIL: K is not whole k-steps.
 template <class Core, bool KTAIL>
 __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatch b) {
-    constexpr int kMT = Core::kMT, kNT = Core::kNT;
     extern __shared__ __align__(16) unsigned char smem[];
-    int which, tr, tc, PR, PC;
-    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC)) return;
+    int which, tr, tc, PR, PC, half;
+    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
     const LinearParams& p = b.p[which];
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
 
-    typename Core::acc_t acc[kMT][kNT];
-    zero_acc<Core>(acc);
-
     if constexpr (std::is_same<Core, MixedCore>::value) {
+        typename Core::acc_t acc[Core::kMT][Core::kNT];
+        zero_acc<Core>(acc);
         int64_t step = 0;
         const uint16_t* warm = warm_line_mixed(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc, step, p.rows_x,
                                                p.rows_y, p.K);
@@ -168,20 +185,19 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
             Core::template gemm<KTAIL>(p.X2, p.ldx, p.rows_x, p.Y2, p.ldy, p.rows_y, p.K, r0, c0, smem, acc,
                                        warm, step);
         }
+        store_block_bf16<Core, true>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
     } else {
-        const uint16_t* warm = warm_row(PR, PC, p.X, p.ldx, r0, tr, p.Y, p.ldy, c0, tc, nullptr, p.rows_x, p.rows_y);
-        Core::template gemm<KTAIL>({p.X, p.ldx, p.Y, p.ldy, p.rows_x, p.rows_y, p.K, r0, c0, warm, kBlockK, nullptr},
-                                   smem, acc);
+        if (half < 0) linear_block<Core, KTAIL, true>(p, PR, PC, tr, tc, r0, smem);
+        else linear_block<HalfCore, KTAIL, true>(p, PR, PC, tr, tc, r0 + half * (kBlockR / 2), smem);
     }
-    store_block_bf16<Core, true>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
 }
 
 // The k-contiguous products on persistent workgroups: one workgroup per compute unit walks the
 // launch's blocks bid = blockIdx.x, blockIdx.x + gridDim.x, ... (the same block numbering as
 // linear_kernel, so the 32 workgroups of an XCD still share a patch) and fetches the first two
 // k-steps of its next block while the current block's last two k-steps and epilogue run
-// (DirectCore::Pipe).  total = the launch's block numbers (grid_for_blocks).  Every product of
-// the launch has the same K, a multiple of 128 and >= 256.
+// (DirectCore::Pipe).  total = the workgroup numbers of whole blocks; a last round in halves
+// comes behind the chain.  Every product of the launch has the same K, a multiple of 128 and >= 256.
 // GUARD: some product's rows or columns are not whole blocks.
 template <bool GUARD>
 __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(const LinearBatch b, int total) {
@@ -190,8 +206,8 @@ __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(cons
     // the next block number from `bid` on that is not padding, or -1
     auto next_block = [&](int bid, Core::Block& blk, int& which) {
         for (; bid < total; bid += gridDim.x) {
-            int tr, tc, PR, PC;
-            if (!b.map.locate(bid, which, tr, tc, PR, PC)) continue;
+            int tr, tc, PR, PC, half;
+            if (!b.map.locate(bid, which, tr, tc, PR, PC, half)) continue;
             const LinearParams& p = b.p[which];
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
             blk = {uniform(p.X), uniform(p.ldx), uniform(p.Y), uniform(p.ldy), uniform(p.rows_x), uniform(p.rows_y),
@@ -206,9 +222,9 @@ __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(cons
     Core::Block cur, nxt;
     int which, which_next = 0;
     int bid = next_block(blockIdx.x, cur, which);
-    if (bid < 0) return;
     Core::Pipe<false> pipe(smem);
-    pipe.start(cur);
+    if (bid >= 0) pipe.start(cur);
+    const bool chain = bid >= 0;
     while (bid >= 0) {
         const int nbid = next_block(bid + gridDim.x, nxt, which_next);
         if (nbid < 0) {            // the last block: the chain's fetch goes to this block again, unused
@@ -225,7 +241,13 @@ __global__ __launch_bounds__(DirectCore::kThreads) void linear_chain_kernel(cons
         which = which_next;
         bid = nbid;
     }
-    pipe.finish();
+    if (chain) pipe.finish();
+    for (bid = b.map.last.full + blockIdx.x; bid < b.map.last.numbers + kRound; bid += gridDim.x) {
+        int tr, tc, PR, PC, half;
+        if (!b.map.locate(bid, which, tr, tc, PR, PC, half) || half < 0) continue;
+        __syncthreads();                // LDS is free
+        linear_block<HalfCore, false, GUARD>(b.p[which], PR, PC, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+    }
 }
 
 // Gate and up projections of a tile with the SwiGLU in the epilogue: the block's Y rows are the
@@ -244,6 +266,7 @@ struct GatedParams {
     int64_t ldx, ldw;
     int rows_x, I, K;
     PatchGrid grid;
+    Halving last;
 };
 
 // The SwiGLU epilogue of a block whose accumulators hold g (tiles mt < kMT / 2) and u (tile mt + kMT / 2)
@@ -322,39 +345,44 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
     }
 }
 
+// One block, or half of one; r0: the rows' first, tr: the whole block's.
+template <class Core, bool BWD, bool KTAIL, bool CHECK>
+__device__ __forceinline__ void gated_block(const GatedParams& p, int tr, int tc, int r0, unsigned char* smem) {
+    static_assert(Core::kMT * Core::kTile == kGroupC, "a wavefront's 128 Y rows: 64 of Wg, then the same 64 of Wu");
+    const int c0 = tc * kBlockC;                         // c0 / 2 = first of the block's 128 columns of I
+    if (r0 >= p.rows_x) return;
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    const uint16_t* warm = warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, tr * kBlockR, tr, p.Wg, p.ldw, c0, tc, p.Wu,
+                                    p.rows_x, p.I);
+    Core::template gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, warm, kBlockK, p.Wu}, smem, acc);
+    gated_epilogue<Core, BWD, CHECK>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
+}
+
 // KTAIL: H is not whole k-steps.
 template <bool BWD, bool KTAIL>
 __global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const GatedParams p) {
-    typedef DirectCore Core;
-    static_assert(Core::kMT * Core::kTile == kGroupC, "a wavefront's 128 Y rows: 64 of Wg, then the same 64 of Wu");
     extern __shared__ __align__(16) unsigned char smem[];
-    const int i = block_of_workgroup(blockIdx.x, p.grid.blocks());
-    if (i < 0) return;
-    int tr, tc;
-    block_at(p.grid, i, tr, tc);
-    const int r0 = tr * kBlockR, c0 = tc * kBlockC;      // c0 / 2 = first of the block's 128 columns of I
-
-    Core::acc_t acc[Core::kMT][Core::kNT];
-    zero_acc<Core>(acc);
-
-    const uint16_t* warm = warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x,
-                                    p.I);
-    Core::gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, warm, kBlockK, p.Wu}, smem, acc);
-    gated_epilogue<Core, BWD, true>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
+    const int number = block_of_workgroup(blockIdx.x, p.last.numbers);
+    if (number < 0) return;
+    int tr, tc, half;
+    block_at(p.grid, p.last.block(number, half), tr, tc);
+    if (half < 0) gated_block<DirectCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR, smem);
+    else gated_block<HalfCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
 
 // The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 128 and >= 256.
-// total = the launch's block numbers.  GUARD: rows_x or I is not whole blocks.
+// total = the workgroup numbers of whole blocks.  GUARD: rows_x or I is not whole blocks.
 template <bool BWD, bool GUARD>
 __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const GatedParams p, int total) {
     typedef DirectCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
     auto next_block = [&](int bid, Core::Block& blk) {
         for (; bid < total; bid += gridDim.x) {
-            const int i = block_of_workgroup(bid, p.grid.blocks());
-            if (i < 0) continue;
+            const int number = block_of_workgroup(bid, p.last.numbers);
+            if (number < 0) continue;
             int tr, tc;
-            block_at(p.grid, i, tr, tc);
+            block_at(p.grid, number, tr, tc);
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
             blk = {uniform(p.X), p.ldx, uniform(p.Wg), p.ldw, p.rows_x, p.I, p.K, uniform(r0), uniform(c0),
                    warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x, p.I),
@@ -365,9 +393,9 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
     };
     Core::Block cur, nxt;
     int bid = next_block(blockIdx.x, cur);
-    if (bid < 0) return;
     Core::Pipe<false> pipe(smem);
-    pipe.start(cur);
+    if (bid >= 0) pipe.start(cur);
+    const bool chain = bid >= 0;
     unsigned char* const tw = smem + kChainTurnOffset + (threadIdx.x >> 6) * (Core::kTile * kTurnPitch);
     while (bid >= 0) {
         const int nbid = next_block(bid + gridDim.x, nxt);
@@ -379,7 +407,15 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
         cur = nxt;
         bid = nbid;
     }
-    pipe.finish();
+    if (chain) pipe.finish();
+    for (bid = p.last.full + blockIdx.x; bid < p.last.numbers + kRound; bid += gridDim.x) {
+        const int number = block_of_workgroup(bid, p.last.numbers);
+        if (number < p.last.full) continue;              // (none, or a whole block: the chain's)
+        int tr, tc, half;
+        block_at(p.grid, p.last.block(number, half), tr, tc);
+        __syncthreads();                // LDS is free
+        gated_block<HalfCore, BWD, false, GUARD>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+    }
 }
 
 struct WgradParams {
@@ -400,8 +436,8 @@ template <bool KTAIL>
 __global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const WgradBatch b) {
     typedef KMajorCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
-    int which, tr, tc, PR, PC;
-    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC)) return;
+    int which, tr, tc, PR, PC, half;
+    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
     const WgradParams& p = b.p[which];
     const int r0 = tr * kBlockR, c0 = tc * kBlockC;
 
@@ -468,7 +504,9 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     }
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
+    b.map.last = ps[0].y_kmajor ? Halving{(int)total, (int)total} : halve_last_round((int)total);
     const int blocks = grid_for_blocks(total);
+    const int whole = grid_for_blocks(b.map.last.full);           // the chains' workgroup numbers
     ProfScope pr(PROF_MLP_LINEAR, s);
     const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
     const dim3 threads(DirectCore::kThreads);
@@ -477,9 +515,9 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     else if (ps[0].y_kmajor)
         hipLaunchKernelGGL((linear_kernel<MixedCore, false>), all, threads, kLdsBytes, s, b);
     else if (chain && guard)
-        hipLaunchKernelGGL((linear_chain_kernel<true>), persistent, threads, kChainLdsBytes, s, b, blocks);
+        hipLaunchKernelGGL((linear_chain_kernel<true>), persistent, threads, kChainLdsBytes, s, b, whole);
     else if (chain)
-        hipLaunchKernelGGL((linear_chain_kernel<false>), persistent, threads, kChainLdsBytes, s, b, blocks);
+        hipLaunchKernelGGL((linear_chain_kernel<false>), persistent, threads, kChainLdsBytes, s, b, whole);
     else if (ktail)
         hipLaunchKernelGGL((linear_kernel<DirectCore, true>), all, threads, kLdsBytes, s, b);
     else
@@ -504,6 +542,7 @@ static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
     }
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
+    b.map.last = {(int)total, (int)total};
     const dim3 blocks((unsigned)grid_for_blocks(total)), threads(KMajorCore::kThreads);
     ProfScope pr(PROF_MLP_WGRAD, s);
     if (ps[0].K % kBlockK != 0)
@@ -553,7 +592,8 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
     gp.da = da; gp.a = a; gp.dgu = dgu;
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
-    const int blocks = grid_for_blocks(gp.grid.blocks());
+    gp.last = halve_last_round(gp.grid.blocks());
+    const int blocks = grid_for_blocks(gp.grid.blocks()), whole = grid_for_blocks(gp.last.full);
     const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
     // persistent workgroups that fetch their next block early: whole pairs of k-steps
     const bool chain = P.H % (2 * kBlockK) == 0 && P.H >= 4 * kBlockK;
@@ -561,10 +601,10 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     const dim3 threads(DirectCore::kThreads);
     ProfScope pr(PROF_MLP_LINEAR, s);
     if (chain) {
-        if (guard && da) hipLaunchKernelGGL((gated_chain_kernel<true, true>), persistent, threads, kChainLdsBytes, s, gp, blocks);
-        else if (guard) hipLaunchKernelGGL((gated_chain_kernel<false, true>), persistent, threads, kChainLdsBytes, s, gp, blocks);
-        else if (da) hipLaunchKernelGGL((gated_chain_kernel<true, false>), persistent, threads, kChainLdsBytes, s, gp, blocks);
-        else hipLaunchKernelGGL((gated_chain_kernel<false, false>), persistent, threads, kChainLdsBytes, s, gp, blocks);
+        if (guard && da) hipLaunchKernelGGL((gated_chain_kernel<true, true>), persistent, threads, kChainLdsBytes, s, gp, whole);
+        else if (guard) hipLaunchKernelGGL((gated_chain_kernel<false, true>), persistent, threads, kChainLdsBytes, s, gp, whole);
+        else if (da) hipLaunchKernelGGL((gated_chain_kernel<true, false>), persistent, threads, kChainLdsBytes, s, gp, whole);
+        else hipLaunchKernelGGL((gated_chain_kernel<false, false>), persistent, threads, kChainLdsBytes, s, gp, whole);
     } else if (ktail && da) hipLaunchKernelGGL((gated_kernel<true, true>), all, threads, kLdsBytes, s, gp);
     else if (ktail) hipLaunchKernelGGL((gated_kernel<false, true>), all, threads, kLdsBytes, s, gp);
     else if (da) hipLaunchKernelGGL((gated_kernel<true, false>), all, threads, kLdsBytes, s, gp);

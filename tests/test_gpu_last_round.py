@@ -1,0 +1,64 @@
+"""Launches whose last round of output blocks is worked on in halves of 128 rows: whole rounds in front of
+it and none, halves without rows, extents that end inside a half, chains of blocks and single ones,
+against the fp64 oracle.  Bar as in the other parity tests: 2e-2 of max |ref| per output."""
+import numpy as np
+import pytest
+
+from oracle import tiled_linear_oracle as lorc
+from oracle import tiled_mlp_oracle as morc
+from paper_2506_13996_amd import binding as B
+from paper_2506_13996_amd import synth
+from tests import gpu_util as G
+from tests import test_gpu_linear as TL
+from tests import test_gpu_mlp as TM
+from tests.test_gpu_parity import IGN, _check, _oracle
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+@pytest.mark.parametrize("N,K,M", [
+    (1024, 384, 24576),         # 256 + 128 blocks: as many halves as fit, behind chains
+    (1024, 320, 24584),         # 256 + 132: none
+    (800, 256, 24200),          # 256 + 124, the second halves of the last rows are empty
+    (900, 72, 24320),           # the last half has 4 rows; K is not whole k-steps
+    (129, 64, 256),             # two halves, the second with one row
+    (128, 512, 264),            # second halves empty, 8 columns in the last block
+])
+def test_linear(N, K, M):
+    x, W, dy = TL._inputs(N, K, M, 31)
+    got = TL._run(x, W, dy, 1024)
+    for g, r in zip(got, (lorc.forward(x, W), *lorc.backward(x, W, dy))):
+        assert G.grad_err(g, r) <= TOL
+
+
+@pytest.mark.parametrize("N,H,I", [
+    (1024, 256, 12288),         # gate / up: 256 + 128 blocks
+    (900, 320, 12168),          # the same without chains, rows and columns ragged
+    (140, 256, 640),
+])
+def test_mlp(N, H, I):
+    wl = synth.MlpWorkload("halves", N, H, I, 1024, seed=32)
+    x, Wg, Wu, Wd, dy = synth.make_mlp_inputs(wl)
+    y, dx, gW = TM._run(x, Wg, Wu, Wd, dy, 1024)
+    ref = (morc.forward(x, Wg, Wu, Wd, row_block=256), *morc.backward(x, Wg, Wu, Wd, dy, row_block=256))
+    for g, r in zip((y, dx, *gW), ref):
+        assert G.grad_err(g, r) <= TOL
+
+
+@pytest.mark.parametrize("name,N,H,V,frac", [
+    ("whole_rounds_then_halves", 1024, 64, 24576, 0.0),
+    ("ragged", 1000, 72, 24300, 0.05),
+    ("second_half_without_rows", 600, 64, 33000, 0.15),
+    ("a_last_half_with_one_row", 129, 64, 300, 0.0),
+])
+def test_cross_entropy(name, N, H, V, frac):
+    wl = synth.custom(name, N, H, V, 1024, ignore_frac=frac, seed=33)
+    h, W, y = synth.make_inputs(wl)
+    f, dH, dW = _oracle(h, W, y)
+    r = G.run_fused(h, W, y, 1024)
+    _check(r, f, dH, dW, name, valid=(y != IGN))
+    s = G.run_split(h, W, y, 1024)
+    assert s.status_bwd == B.ALST_OK and s.loss_bits == r.loss_bits
+    _check(s, f, dH, dW, name + " split", valid=(y != IGN))
+    assert (s.lse.view(np.uint32) == r.lse.view(np.uint32)).all()
