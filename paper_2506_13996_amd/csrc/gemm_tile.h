@@ -106,8 +106,8 @@ __host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
 }
 
 // The last round, if it fills no more than half of the compute units, is worked on in halves: two
-// workgroups take a block's upper and lower 128 rows (HalfCore; the same k order, so the same
-// results).  numbers: what the launch's workgroups are dealt, blocks below `full` whole, the others
+// workgroups take a block's upper and lower 128 rows (HalfCore) or, in the weight-gradient products, its
+// left and right 128 columns (KMajorHalfCore); the k order is the same, hence the results.  numbers: what the launch's workgroups are dealt, blocks below `full` whole, the others
 // as halves.
 struct Halving {
     int full, numbers;
@@ -210,13 +210,14 @@ __device__ __forceinline__ int kswz(int k) { return (k & 3) | (((k >> 3) & 1) <<
 // MFMA operand (8 k of one column per lane) from a k-major tile: two transposing reads.  In each,
 // the 16 lanes of a quarter wave address 4 k-rows x 4 pieces of 8 bytes and lane i of the quarter
 // receives the 4 k of column i.  `at`: the lane's address for the first 4 k-rows; the next 4
-// k-rows are 2048 bytes on.
+// k-rows are NEXT4 bytes on (2048 in a tile of 256 columns).
+template <int NEXT4>
 __device__ __forceinline__ bf16x8_t read_kmajor(const unsigned char* at) {
     typedef __attribute__((address_space(3))) i16x4_t* tptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
     unsigned char* const p = const_cast<unsigned char*>(at);
     const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(lptr_t)p);
-    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(lptr_t)(p + 2048));
+    const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tptr_t)(lptr_t)(p + NEXT4));
     return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 // The lane's byte offset inside a k-major tile for granule `gran` (MFMA lane l: column l % 32 of
@@ -225,6 +226,13 @@ __device__ __forceinline__ int kmajor_lane_offset(int lane, int gran) {
     const int sl = lane & 15, b1 = (lane >> 4) & 1, half = lane >> 5;
     const int f = (sl >> 2) | (half << 2);                   // kswz of the lane's k-rows
     return (8 * half + (sl >> 2)) * 512 + ((gran ^ f) * 64) + b1 * 32 + (sl & 3) * 8;
+}
+
+// The same in a tile of 128 columns (LDS rows of 256 bytes, granule slots gran ^ (k & 3); add 4096 per
+// slice).
+__device__ __forceinline__ int kmajor_half_lane_offset(int lane, int gran) {
+    const int sl = lane & 15, b1 = (lane >> 4) & 1, half = lane >> 5;
+    return (8 * half + (sl >> 2)) * 256 + ((gran ^ (sl >> 2)) * 64) + b1 * 32 + (sl & 3) * 8;
 }
 
 // Values that are the same in every lane of a wavefront, said so to the compiler (it then keeps
@@ -271,12 +279,15 @@ __device__ __forceinline__ float groups_sum(float v) {
 // GEMMs the 16 x 16 x 32 form gains nothing over this one when operands come through the
 // transposing reads, and its register allocation breaks down for two k-major operands.
 // XK: X is k-major too.
-template <bool XK>
+// MT: 32-wide c tiles per wavefront: 4, or 2 for half a block (128 c; k-major X only).
+template <bool XK, int MT = 4>
 struct KMajorDirectT {
+    static_assert(MT == 4 || (MT == 2 && XK), "a block or the c half of one");
     static constexpr bool YK = true;
     static constexpr int kThreads = 256;
-    static constexpr int kMT = 4;     // 32-wide c tiles per wavefront
+    static constexpr int kMT = MT;    // 32-wide c tiles per wavefront
     static constexpr int kNT = 4;     // 32-wide r tiles per wavefront
+    static constexpr int kWaveC = 32 * MT;                 // c one wavefront covers
     typedef f32x16_t acc_t;
     static constexpr int kTile = 32, kRuns = 4, kGroups = 2;
 
@@ -294,7 +305,7 @@ struct KMajorDirectT {
         __device__ __forceinline__ int r(int nt) const { return wr * 128 + nt * 32 + lrow; }
         __device__ __forceinline__ int rbase(int nt) const { return wr * 128 + nt * 32; }
         __device__ __forceinline__ int cw(int mt, int q) const { return mt * 32 + q * 8 + grp * 4; }
-        __device__ __forceinline__ int c(int mt, int q) const { return wc * kGroupC + cw(mt, q); }
+        __device__ __forceinline__ int c(int mt, int q) const { return wc * kWaveC + cw(mt, q); }
     };
 
     // LDS row = 128 bytes = 8 chunks of 16 bytes; chunk kc of row `row` lives at slot
@@ -325,9 +336,15 @@ struct KMajorDirectT {
         // [64 w, 64 w + 64) of both operand tiles: 8 instructions per operand per k-step.
         // k-major: one DMA instruction moves 2 k-rows x 512 bytes: lane -> (k-row = lane / 32, chunk
         // slot = lane % 32); wave w owns k-rows [16 w, 16 w + 16) of the tile.
+        // A Y tile of 128 columns: 4 k-rows x 256 bytes, an LDS row is 4 granules and granule g of
+        // k-row k lives at slot g ^ (k & 3) (the 4 k-rows a quarter of a transposing read covers: 4 slots,
+        // all 64 banks).
+        constexpr int kYq = 2 * MT;                          // DMA instructions per wavefront for a Y tile
+        constexpr int kYRow = 128 * MT;                      // bytes of an LDS row of it
         const int lr = lane >> 3, pc = lane & 7;
+        auto ykrow = [&](int q) { return MT == 4 ? w * 16 + q * 2 + (lane >> 5) : w * 16 + q * 4 + (lane >> 4); };
         const uint16_t* xg[8];
-        const uint16_t* yg[8];
+        const uint16_t* yg[kYq];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int krow = w * 16 + q * 2 + (lane >> 5);
@@ -337,7 +354,11 @@ struct KMajorDirectT {
             // (the clamps: see the comment of this function)
             if (XK) xg[q] = X + (int64_t)krow * ldx + (r0 + ch * 8 < rows_x ? r0 + ch * 8 : rows_x - 8);
             else xg[q] = X + (int64_t)(r0 + row < rows_x ? r0 + row : rows_x - 1) * ldx + kc * 8;
-            yg[q] = Y + (int64_t)krow * ldy + (c0 + ch * 8 < rows_y ? c0 + ch * 8 : rows_y - 8);
+            if (q < kYq) {
+                const int yrow = ykrow(q);
+                const int yc = MT == 4 ? ch : (lane & 15) ^ ((yrow & 3) << 2);
+                yg[q % kYq] = Y + (int64_t)yrow * ldy + (c0 + yc * 8 < rows_y ? c0 + yc * 8 : rows_y - 8);
+            }
         }
         // elements from one k-step's tile to the next
         const int64_t xstep = XK ? ldx * kBlockK : kBlockK, ystep = ldy * kBlockK;
@@ -353,16 +374,16 @@ struct KMajorDirectT {
         };
         auto ysrc = [&](int q, int kt, bool tail) -> const uint16_t* {
             const uint16_t* p = yg[q] + kt * ystep;
-            return !tail || krow_in(q) ? p : zeros();
+            return !tail || ykrow(q) < klast ? p : zeros();
         };
         auto issue_loads = [&](int stage, int kt) {
             unsigned char* xs = smem + stage * kTileBytes + w * 8192;
-            unsigned char* ys = smem + 2 * kTileBytes + stage * kTileBytes + w * 8192;
+            unsigned char* ys = smem + 2 * kTileBytes + stage * kTileBytes + w * (kYq * 1024);
             const bool tail = KTAIL && kt == KT - 1;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 dma_to_lds<16>(xsrc(q, kt, tail), xs + q * 1024);
-                dma_to_lds<16>(ysrc(q, kt, tail), ys + q * 1024);
+                if (q < kYq) dma_to_lds<16>(ysrc(q % kYq, kt, tail), ys + q * 1024);
             }
         };
 
@@ -372,23 +393,24 @@ struct KMajorDirectT {
         for (int s = 0; s < 4; ++s) {
             rofs[s] = ((2 * s + half) ^ swz(l31)) * 16;
             xofs[s] = kmajor_lane_offset(lane, wr * 4 + s);      // s = accumulator tile here
-            yofs[s] = 2 * kTileBytes + kmajor_lane_offset(lane, wc * 4 + s);
+            yofs[s] = 2 * kTileBytes + (MT == 4 ? kmajor_lane_offset(lane, wc * 4 + s)
+                                                : kmajor_half_lane_offset(lane, (wc * 2 + s) & 3));
         }
         const int xbase = (wr * 128 + l31) * 128;
 
         // MFMA operands of the four k-slices of a step: fy[s][t], fx[s][t] for slice s.
-        bf16x8_t fy[4][4], fx[4][4];
-        // item 0..3: the Y operand of accumulator row t = item, 4..7: the X operand of column t
+        bf16x8_t fy[4][MT], fx[4][4];
+        // item 0..MT-1: the Y operand of accumulator row t = item, MT..MT+3: the X operand of column item - MT
         auto read_item = [&](int stage, int s, int item) {
             const unsigned char* base = smem + stage * kTileBytes;
-            if (item < 4)
-                fy[s][item] = read_kmajor(base + yofs[item] + s * 8192);
+            if (item < MT)
+                fy[s][item] = read_kmajor<4 * kYRow>(base + yofs[item] + s * (16 * kYRow));
             else
-                fx[s][item - 4] =
-                    XK ? read_kmajor(base + xofs[item - 4] + s * 8192)
-                       : *reinterpret_cast<const bf16x8_t*>(base + xbase + (item - 4) * 4096 + rofs[s]);
+                fx[s][item - MT] =
+                    XK ? read_kmajor<2048>(base + xofs[item - MT] + s * 8192)
+                       : *reinterpret_cast<const bf16x8_t*>(base + xbase + (item - MT) * 4096 + rofs[s]);
         };
-        // the two MFMAs of slot i (0..7) of a quarter step on slice s
+        // the two MFMAs of slot i (0 .. 2 MT - 1) of a quarter step on slice s
         auto mfma_pair = [&](int s, int i) {
             const int mt = i >> 1, n0 = (i & 1) * 2;
             acc[mt][n0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[s][mt], fx[s][n0], acc[mt][n0],
@@ -421,9 +443,9 @@ struct KMajorDirectT {
         __syncthreads();                       // waits for the DMA (vmcnt) and joins the waves
         if (KT > 1) issue_loads(1, 1);
 #pragma unroll
-        for (int item = 0; item < 8; ++item) read_item(0, 0, item);
+        for (int item = 0; item < MT + 4; ++item) read_item(0, 0, item);
 #pragma unroll
-        for (int item = 0; item < 8; ++item) read_item(0, 1, item);
+        for (int item = 0; item < MT + 4; ++item) read_item(0, 1, item);
 
         // One k-step = four quarters of sixteen MFMAs, each quarter eight fenced slots of two MFMAs
         // plus the memory instructions that ride along, in this order:
@@ -444,35 +466,43 @@ struct KMajorDirectT {
             constexpr bool TAIL = decltype(tail)::value;
             const int cur = kt & 1;
             unsigned char* const xs = smem + cur * kTileBytes + w * 8192;
-            unsigned char* const ys = smem + 2 * kTileBytes + cur * kTileBytes + w * 8192;
+            unsigned char* const ys = smem + 2 * kTileBytes + cur * kTileBytes + w * (kYq * 1024);
+            constexpr int kSlots = 2 * MT, kItems = MT + 4;       // (half a block: 4 slots, 6 items)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < kSlots; ++i) {
                 mfma_pair(0, i);
-                read_item(cur, i < 4 ? 2 : 3, (2 * i) & 7);
-                read_item(cur, i < 4 ? 2 : 3, (2 * i + 1) & 7);
+#pragma unroll
+                for (int q = i * 2 * kItems / kSlots; q < (i + 1) * 2 * kItems / kSlots; ++q)
+                    read_item(cur, q < kItems ? 2 : 3, q % kItems);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < kSlots; ++i) {
                 mfma_pair(1, i);
                 __builtin_amdgcn_sched_barrier(0);
             }
             stage_barrier(behind);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < kSlots; ++i) {
                 mfma_pair(2, i);
                 if (LOADS)
-                    dma_to_lds<16>(xsrc(i, kt + 2, TAIL), xs + i * 1024);
-                if (NEXT) read_item(cur ^ 1, 0, i);
+#pragma unroll
+                    for (int q = i * 8 / kSlots; q < (i + 1) * 8 / kSlots; ++q)
+                        dma_to_lds<16>(xsrc(q, kt + 2, TAIL), xs + q * 1024);
+                if (NEXT)
+#pragma unroll
+                    for (int q = i * kItems / kSlots; q < (i + 1) * kItems / kSlots; ++q) read_item(cur ^ 1, 0, q);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < kSlots; ++i) {
                 mfma_pair(3, i);
                 if (LOADS)
-                    dma_to_lds<16>(ysrc(i, kt + 2, TAIL), ys + i * 1024);
-                if (NEXT) read_item(cur ^ 1, 1, i);
+                    dma_to_lds<16>(ysrc(i % kYq, kt + 2, TAIL), ys + i * 1024);
+                if (NEXT)
+#pragma unroll
+                    for (int q = i * kItems / kSlots; q < (i + 1) * kItems / kSlots; ++q) read_item(cur ^ 1, 1, q);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (LOADS && warming) warm_step(kt + 2 + kWarmAhead);
@@ -494,6 +524,7 @@ struct KMajorDirectT {
     }
 };
 typedef KMajorDirectT<true> KMajorCore;
+typedef KMajorDirectT<true, 2> KMajorHalfCore;       // 256 r x 128 c, see HalfCore
 typedef KMajorDirectT<false> MixedCore;
 
 // ---------------------------------------------------------------------------------------------
@@ -1015,7 +1046,7 @@ __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&a
     static_assert(kNT * Core::kTile == 128 && Core::kTile == 32, "a wavefront's r; a turned piece");
     constexpr int kPitch = 128 + 8, kBatch = 8;
     float* const tw = reinterpret_cast<float*>(smem) + (threadIdx.x >> 6) * (32 * kPitch);
-    const int half = lp.lane >> 5, c_first = c0 + lp.wc * kGroupC, rq = (lp.lane & 31) * 4;
+    const int half = lp.lane >> 5, c_first = c0 + lp.wc * Core::kWaveC, rq = (lp.lane & 31) * 4;
     const int r = r0 + lp.wr * 128 + rq;
     const bool rok = r < r_valid;
 #pragma unroll

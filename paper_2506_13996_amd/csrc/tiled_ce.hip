@@ -930,25 +930,12 @@ struct DWParams {
 // r = hidden index (lane dimension), c = vocabulary id (register dimension), k = dense token row:
 // both operands have k as the slow index (k-major cores).  With the hidden index along the lanes
 // the accumulate moves full 128-byte lines of the sums (weight_grad_block).
+// Core: KMajorCore for a block, KMajorHalfCore for half of its columns.
 template <class Core>
-__global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
-    constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    extern __shared__ __align__(16) unsigned char smem[];
-    int tr, tc;
-    const int tiles_r = (p.H + kBlockR - 1) / kBlockR;
-    // k extent of the group (its dense rows are zero padded to whole blocks)
-    const int64_t left = p.hdr->n_valid - p.row0;
-    const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
-    if (Tkc == 0 && !p.out.first) return;
-    {
-        const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
-        const int i = block_of_workgroup(blockIdx.x, pg.blocks());
-        if (i < 0) return;
-        block_at(pg, i, tr, tc);
-    }
-    const int r0 = tr * kBlockR, c0 = tc * kBlockC;
-
-    typename Core::acc_t acc[kMT][kNT];
+__device__ __forceinline__ void dw_block(const DWParams& p, int Tkc, int64_t left, int r0, int c0,
+                                         unsigned char* smem) {
+    if (c0 >= p.V) return;
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
 
     if (Tkc > 0)
@@ -959,6 +946,23 @@ __global__ __launch_bounds__(Core::kThreads) void dw_kernel(const DWParams p) {
     out.scale = p.hdr->inv;
     out.last = left <= p.rows;
     weight_grad_block<Core>(acc, out, r0, c0, p.H, p.V, smem);
+}
+
+__global__ __launch_bounds__(KMajorCore::kThreads) void dw_kernel(const DWParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int tr, tc, half;
+    const int tiles_r = (p.H + kBlockR - 1) / kBlockR;
+    // k extent of the group (its dense rows are zero padded to whole blocks)
+    const int64_t left = p.hdr->n_valid - p.row0;
+    const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
+    if (Tkc == 0 && !p.out.first) return;
+    const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
+    const Halving last = halve_last_round(pg.blocks());
+    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    if (number < 0) return;
+    block_at(pg, last.block(number, half), tr, tc);
+    if (half < 0) dw_block<KMajorCore>(p, Tkc, left, tr * kBlockR, tc * kBlockC, smem);
+    else dw_block<KMajorHalfCore>(p, Tkc, left, tr * kBlockR, tc * kBlockC + half * (kBlockC / 2), smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -978,7 +982,7 @@ static int prepare_kernels_on_current_device() {
     acc(allow_big_lds(logits_kernel<false, MODE_FUSED, true>));
     acc(allow_big_lds(logits_kernel<true, MODE_FUSED, true>));
     acc(allow_big_lds(dhidden_kernel));
-    acc(allow_big_lds(dw_kernel<KMajorCore>));
+    acc(allow_big_lds(dw_kernel));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -1226,7 +1230,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             wp.PR = pg.PR; wp.PC = pg.PC;
             const int grid = grid_for_blocks(pg.blocks());
             ProfScope ps_(PROF_DW, s);
-            hipLaunchKernelGGL((dw_kernel<KMajorCore>), dim3(grid), dim3(KMajorCore::kThreads),
+            hipLaunchKernelGGL(dw_kernel, dim3(grid), dim3(KMajorCore::kThreads),
                                kLdsBytes, s, wp);
             ALST_HIP(hipGetLastError());
         }

@@ -125,7 +125,7 @@ struct BatchMap {
     PatchGrid g[kMaxBatch];
     int first_block[kMaxBatch + 1];      // first_block[i] .. first_block[i + 1]: blocks of part i
     int n;
-    Halving last;                        // (MixedCore and KMajorCore: every block whole)
+    Halving last;                        // (MixedCore: every block whole)
     // which part and which of its blocks (or halves, see Halving) a workgroup works on; false for
     // padding workgroups
     __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC, int& half) const {
@@ -431,20 +431,25 @@ struct WgradBatch {
     BatchMap map;
 };
 
+// One block, or half of one (columns c0 .. c0 + 127).
+template <class Core, bool KTAIL>
+__device__ __forceinline__ void wgrad_block(const WgradParams& p, int r0, int c0, unsigned char* smem) {
+    if (c0 >= p.rows_y) return;
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    Core::template gemm<KTAIL>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, nullptr, 0);
+    weight_grad_block<Core>(acc, p.out, r0, c0, p.rows_x, p.rows_y, smem);
+}
+
 // KTAIL: K is not whole k-steps.
 template <bool KTAIL>
 __global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const WgradBatch b) {
-    typedef KMajorCore Core;
     extern __shared__ __align__(16) unsigned char smem[];
     int which, tr, tc, PR, PC, half;
     if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
     const WgradParams& p = b.p[which];
-    const int r0 = tr * kBlockR, c0 = tc * kBlockC;
-
-    Core::acc_t acc[Core::kMT][Core::kNT];
-    zero_acc<Core>(acc);
-    Core::gemm<KTAIL>(p.X, p.ldx, p.rows_x, p.Y, p.ldy, p.rows_y, p.K, r0, c0, smem, acc, nullptr, 0);
-    weight_grad_block<Core>(acc, p.out, r0, c0, p.rows_x, p.rows_y, smem);
+    if (half < 0) wgrad_block<KMajorCore, KTAIL>(p, tr * kBlockR, tc * kBlockC, smem);
+    else wgrad_block<KMajorHalfCore, KTAIL>(p, tr * kBlockR, tc * kBlockC + half * (kBlockC / 2), smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -542,7 +547,7 @@ static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
     }
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
-    b.map.last = {(int)total, (int)total};
+    b.map.last = halve_last_round((int)total);
     const dim3 blocks((unsigned)grid_for_blocks(total)), threads(KMajorCore::kThreads);
     ProfScope pr(PROF_MLP_WGRAD, s);
     if (ps[0].K % kBlockK != 0)
