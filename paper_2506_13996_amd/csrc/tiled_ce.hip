@@ -95,9 +95,7 @@ struct Layout {
     int64_t Kg;            // dense rows the group's buffers hold: g * Tp
     int64_t Rc;            // most dense rows per chunk of launches, a multiple of 256
     int dh_PR, dh_PC;      // dHidden: patch shape of the block -> tile mapping
-    int64_t dh_blocks;     //          most blocks (over all ranges) a chunk of any number of rows needs
-    int64_t dh_part_rows;  //          most rows of fp32 partial products
-    bool dh_cut;           //          some number of rows has its contraction cut into ranges
+    size_t part_bytes;     //          room for fp32 partial products at `part`
     size_t header, cinfo, loss_rows, lse, idx, block_cnt, block_ofs, zlabel, yc, ref, frow, rowstate,
         rmax, ps, part, hc, stash, wt, acc, total;
 };
@@ -110,7 +108,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // compute units (a last one in halves: 5/8) times (k-steps per range + about 4 for the block's start
 // and epilogue) and, if cut,
 // the partial products' way through memory (256 KB per block and range written and read back at
-// about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps at least 16 k-steps.
+// about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps at least 8 k-steps.
 // The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
 // host evaluates the same function for every possible row count to size the launch.
 constexpr int kComputeUnits = 256;
@@ -125,13 +123,29 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
     const int sp_max = blocks >= 16 * kComputeUnits ? 1 : 8;
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int per = (KT + sp - 1) / sp;
-        if (sp > 1 && (per < 16 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
+        if (sp > 1 && (per < 8 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
         const int64_t left = blocks * sp % kComputeUnits;
         const int64_t rounds16 = blocks * sp / kComputeUnits * 16 + (left == 0 ? 0 : 2 * left <= kComputeUnits ? 10 : 16);
         const int64_t cost = rounds16 * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
         if (cost < best) { best = cost; splits = sp; }
     }
     ksteps = (KT + splits - 1) / splits;
+}
+
+// The most blocks (over all ranges) that dHidden of a chunk of up to `rows` dense rows (a multiple of
+// 256) needs, and whether some number of rows has its contraction cut.  (Beyond 4096 row blocks only the
+// full chunk is looked at; gather_rows_kernel then keeps a smaller chunk's choice within these bounds.)
+static int64_t dhidden_most_blocks(int64_t rows, int64_t H, int64_t V, int64_t part_rows, bool& cut) {
+    const int64_t tiles_c = (H + kBlockC - 1) / kBlockC, rb_max = rows / kBlockR;
+    int64_t most = 0;
+    cut = false;
+    for (int64_t rb = rb_max > 4096 ? rb_max : 1; rb <= rb_max; ++rb) {
+        int sp, ks;
+        dhidden_splits(rb * kBlockR, H, V, part_rows, sp, ks);
+        if (rb * tiles_c * sp > most) most = rb * tiles_c * sp;
+        cut = cut || sp > 1;
+    }
+    return most;
 }
 
 // Ranges of V whose partial products of a full tile the workspace has room for.  The workspace's size is
@@ -197,22 +211,10 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     L.stash = take(fwd_only ? 0 : (size_t)L.Kg * L.Vp * 2);
     // W transposed, [H, Vp] with zeros beyond V: the second operand of dH = dZ W, k-contiguous
     L.wt = take(fwd_only ? 0 : (size_t)H * L.Vp * 2);
-    {   // dHidden: the launch is sized for the worst chunk
+    {
         const PatchGrid pg = choose_patches((int)(L.Rc / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
         L.dh_PR = pg.PR; L.dh_PC = pg.PC;
-        L.dh_part_rows = (int64_t)((at + region - L.part) / ((size_t)H * 4));
-        L.dh_blocks = 0;
-        L.dh_cut = false;
-        // (beyond 4096 row blocks per chunk only the full chunk is looked at; gather_rows_kernel
-        // then keeps a smaller chunk's choice within these bounds)
-        const int64_t rb_max = L.Rc / kBlockR, rb_lo = rb_max > 4096 ? rb_max : 1;
-        for (int64_t rb = rb_lo; rb <= rb_max; ++rb) {
-            int sp, ks;
-            dhidden_splits(rb * kBlockR, H, V, L.dh_part_rows, sp, ks);
-            const int64_t blocks = rb * pg.tiles_c * sp;
-            if (blocks > L.dh_blocks) L.dh_blocks = blocks;
-            L.dh_cut = L.dh_cut || sp > 1;
-        }
+        L.part_bytes = at + region - L.part;
     }
     const bool acc_in_dw = (flags & ALST_FLAG_DW_FP32) && !(flags & ALST_FLAG_DW_ACCUMULATE);
     L.acc = take(acc_in_dw || fwd_only ? 0 : (size_t)V * H * 4);
@@ -1036,7 +1038,7 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
     // every launch must fit a one-dimensional grid
     if (!checked_grid(L.Rc / kBlockR, L.Vp / kBlockC) ||
         !checked_grid((P.H + kBlockR - 1) / kBlockR, L.Vp / kBlockC) ||
-        L.dh_blocks > 0x7fffff00 ||                                        // dHidden
+        L.Rc / kBlockR * ((P.H + kBlockC - 1) / kBlockC) > 0x7fffff00 ||   // dHidden (cut: at most 8 * 4096)
         L.Rc + kZeroBlocksMax > 0x7fffffff)
         return ALST_ERR_SHAPE;
     if (workspace_bytes < L.total) return own_scratch ? ALST_ERR_NOALLOC_LIMIT : ALST_ERR_WORKSPACE;
@@ -1168,6 +1170,24 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
         uint16_t* const hc_t = hc + (do_bwd ? at : 0) * L.Hk;
         uint16_t* const stash_t = stash + (do_bwd ? at : 0) * L.Vp;
 
+        // The partial products of dHidden's ranges: behind the chunk's per-row arrays, or in the rows of
+        // the stash that the group has not reached, if these have more room (the next chunk's logits
+        // are written after they are added up).  A short call has nearly all of the stash: N = 512,
+        // H = 256, V = 4096 takes 8 ranges where the first place holds 1: the call 116 -> 65 us.
+        float* part = reinterpret_cast<float*>(P.ws + L.part);
+        size_t part_bytes = L.part_bytes;
+        bool dh_cut = false;
+        int64_t part_rows = 0, dh_blocks = 0;
+        if (do_bwd) {
+            const size_t behind = (size_t)(L.Kg - at - Tr) * L.Vp * 2;
+            if (behind > part_bytes) {
+                part = reinterpret_cast<float*>(stash + (at + Tr) * L.Vp);
+                part_bytes = behind;
+            }
+            part_rows = (int64_t)(part_bytes / ((size_t)H * 4));
+            dh_blocks = dhidden_most_blocks(Tr, H, V, part_rows, dh_cut);
+        }
+
         {
             ProfScope small_(PROF_OTHER, s);
             GatherParams gp;
@@ -1175,7 +1195,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.hdr = hdr; gp.info = info; gp.Hc = hc_t; gp.yc = yc; gp.ref = ref; gp.rowstate = rowstate;
             gp.rmax = rmax; gp.dHidden = P.dHidden;
             gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
-            gp.dh_blocks = L.dh_blocks; gp.dh_part_rows = L.dh_part_rows;
+            gp.dh_blocks = dh_blocks; gp.dh_part_rows = part_rows;
             gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
             int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
             if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
@@ -1206,15 +1226,15 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             DHiddenParams dp;
             dp.dz = stash_t; dp.Wt = wt; dp.dH_t = P.dHidden; dp.idx = idx_t;
             dp.info = info; dp.hdr = hdr; dp.frow = frow;
-            dp.part = reinterpret_cast<float*>(P.ws + L.part);
+            dp.part = part;
             dp.H = H; dp.V = V; dp.Vp = Vp;
             dp.PR = L.dh_PR; dp.PC = L.dh_PC;
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
-            const int grid = grid_for_blocks(L.dh_blocks);
+            const int grid = grid_for_blocks(dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
             hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
                                s, dp);
-            if (L.dh_cut)
+            if (dh_cut)
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr), dim3(256), 0, s, dp.part, H, idx_t,
                                    info, hdr, frow, P.dHidden);
             ALST_HIP(hipGetLastError());
