@@ -209,7 +209,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     // group's dW product as they are (k = dense row, the slow index)
     L.hc = take((size_t)L.Kg * L.Hk * 2);
     L.stash = take(fwd_only ? 0 : (size_t)L.Kg * L.Vp * 2);
-    // W transposed, [H, Vp] with zeros beyond V: the second operand of dH = dZ W, k-contiguous
+    // W transposed, [H, Vp], zeros from V to whole k-steps: the second operand of dH = dZ W, k-contiguous
     L.wt = take(fwd_only ? 0 : (size_t)H * L.Vp * 2);
     {
         const PatchGrid pg = choose_patches((int)(L.Rc / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(DirectCore::kThreads) void logits_kernel(const Logi
 
 struct DHiddenParams {
     const uint16_t* dz;      // [Rc, Vp]     the chunk's dense rows
-    const uint16_t* Wt;      // [H, Vp]      W transposed (k = vocabulary id contiguous), zero beyond V
+    const uint16_t* Wt;      // [H, Vp]      W transposed (k = vocabulary id contiguous), zero from V to whole k-steps
     uint16_t* dH_t;          // [N, H]       whole dHidden; dense row i goes to row idx[i]
     const int32_t* idx;
     const ChunkInfo* info;
@@ -807,7 +807,7 @@ struct DHiddenParams {
 };
 
 // dH = dZ W runs with both operands k-contiguous (the fastest of the block GEMM's layouts: 9 % on
-// this product): W transposed, [H, Vp] with zeros for V <= v < Vp, is made once per call that
+// this product): W transposed, [H, Vp] with zeros from V to whole k-steps, is made once per call that
 // computes gradients (transpose_bf16_kernel), for the price of reading and writing W once.
 
 // r = token row (lane dimension), c = hidden index (register dimension), k = vocabulary; both
@@ -1145,11 +1145,11 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     // (a hidden size that ends inside a block is handled by the unguarded dHidden and dW kernels:
     // the missing rows of W transposed / columns of the dense hidden rows are read from the last
     // ones and the results discarded; a vocabulary that is not whole k-steps: dZ and W transposed
-    // are zero up to the padded vocabulary)
+    // are zero up to whole k-steps)
     if (do_bwd) {
         ProfScope small_(PROF_OTHER, s);
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)(Vp / 64), (unsigned)((H + 63) / 64)), dim3(256),
-                           0, s, reinterpret_cast<const uint16_t*>(P.W), V, H, (int64_t)H, wt, (int64_t)Vp);
+        const Transposes ts = {{{P.W, V, H, H, wt, Vp}}};
+        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
 

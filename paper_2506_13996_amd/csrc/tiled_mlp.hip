@@ -657,10 +657,8 @@ static int run_mlp_backward(const MlpProblem& P) {
     uint16_t* wgut = reinterpret_cast<uint16_t*>(P.ws + L.wgut);
     if (L.weights_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
-        const dim3 gd((unsigned)((H + 63) / 64), (unsigned)((I + 63) / 64)), gi(gd.y, gd.x);
-        hipLaunchKernelGGL(transpose_bf16_kernel, gd, dim3(256), 0, s, P.Wd, H, I, (int64_t)I, wdt, (int64_t)H);
-        hipLaunchKernelGGL(transpose_bf16_kernel, gi, dim3(256), 0, s, P.Wg, I, H, (int64_t)H, wgut, I2);
-        hipLaunchKernelGGL(transpose_bf16_kernel, gi, dim3(256), 0, s, P.Wu, I, H, (int64_t)H, wgut + I, I2);
+        const Transposes ts = {{{P.Wd, H, I, I, wdt, H}, {P.Wg, I, H, H, wgut, I2}, {P.Wu, I, H, H, wgut + I, I2}}};
+        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
 
@@ -811,8 +809,8 @@ static int run_lin_backward(const LinProblem& P) {
     uint16_t* wt = reinterpret_cast<uint16_t*>(P.ws + L.wt);
     if (L.weight_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)((M + 63) / 64), (unsigned)((K + 63) / 64)),
-                           dim3(256), 0, s, P.W, M, K, (int64_t)K, wt, (int64_t)M);
+        const Transposes ts = {{{P.W, M, K, K, wt, M}}};
+        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
     const int64_t chunk = lin_chunk_rows(P.K, P.M);
