@@ -106,9 +106,11 @@ __host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
 }
 
 // The last round, if it fills no more than half of the compute units, is worked on in halves: two
-// workgroups take a block's upper and lower 128 rows (HalfCore) or, in the weight-gradient products, its
-// left and right 128 columns (KMajorHalfCore); the k order is the same, hence the results.  numbers: what the launch's workgroups are dealt, blocks below `full` whole, the others
-// as halves.
+// workgroups take a block's upper and lower 128 rows (HalfCore) or, in the weight-gradient products,
+// its left and right 128 columns (KMajorHalfCore); the k order is the same, hence the results.  A
+// half takes 0.62 to 0.64 of a block's time (66 against 103 us for 128 and 256 blocks of K = 4096),
+// so beyond 128 blocks, where some unit would get two, whole blocks are the faster ones.
+// numbers: what the launch's workgroups are dealt, blocks below `full` whole, the others as halves.
 struct Halving {
     int full, numbers;
     // number -> its block; half: 0, 1 or -1 (whole)
@@ -524,7 +526,9 @@ struct KMajorDirectT {
     }
 };
 typedef KMajorDirectT<true> KMajorCore;
-typedef KMajorDirectT<true, 2> KMajorHalfCore;       // 256 r x 128 c, see HalfCore
+// 256 r x 128 c, see HalfCore (ce 512 x 256 x 4096: 124 -> 116 us; mlp 512 x 256 x 768: 126 -> 117 us; mlp
+// 256000 x 4096 x 14336: 245.9 -> 245.0 ms).
+typedef KMajorDirectT<true, 2> KMajorHalfCore;
 typedef KMajorDirectT<false> MixedCore;
 
 // ---------------------------------------------------------------------------------------------
@@ -1032,8 +1036,8 @@ struct GradOut {
 // launch; launches on one stream are ordered, so the sums are formed in launch order: deterministic.
 // The last launch's workgroups finish the gradient themselves: a separate pass over the fp32 sums
 // wrote and read 8 bytes per weight more and started only when all of them were done (two
-// micro-batches of 4096 rows on a 128256 x 4096 head, fp32 += : 23.6 -> 21.7 ms).  For that the products are turned around in LDS (`smem`,
-// free once the k-loop is over; each wavefront has its own region), so that sums and results travel
+// micro-batches of 4096 rows on a 128256 x 4096 head, fp32 += : 23.6 -> 21.7 ms).  For that the
+// products are turned around in LDS (`smem`, free once the k-loop is over; each wavefront has its own region), so that sums and results travel
 // as whole row segments of 512 (fp32) or 256 bytes.
 // Rows r >= r_valid (a multiple of 8) and c >= c_valid are skipped.
 template <class Core>

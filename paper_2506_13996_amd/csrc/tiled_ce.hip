@@ -106,9 +106,9 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // of 256).  Picks the number of ranges (1..8) the contraction over V is cut into: the one with the
 // least estimated time, in units of a k-step of one block (1.5 us on gfx950): rounds of the 256
 // compute units (a last one in halves: 5/8) times (k-steps per range + about 4 for the block's start
-// and epilogue) and, if cut,
-// the partial products' way through memory (256 KB per block and range written and read back at
-// about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps at least 8 k-steps.
+// and epilogue) and, if cut, the partial products' way through memory (256 KB per block and range
+// written and read back at about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps
+// at least 8 k-steps.
 // The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
 // host evaluates the same function for every possible row count to size the launch.
 constexpr int kComputeUnits = 256;
@@ -125,7 +125,8 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
         const int per = (KT + sp - 1) / sp;
         if (sp > 1 && (per < 8 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
         const int64_t left = blocks * sp % kComputeUnits;
-        const int64_t rounds16 = blocks * sp / kComputeUnits * 16 + (left == 0 ? 0 : 2 * left <= kComputeUnits ? 10 : 16);
+        const int64_t last16 = left == 0 ? 0 : 2 * left <= kComputeUnits ? 10 : 16;
+        const int64_t rounds16 = blocks * sp / kComputeUnits * 16 + last16;
         const int64_t cost = rounds16 * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
         if (cost < best) { best = cost; splits = sp; }
     }
