@@ -29,10 +29,11 @@ MI355X_BF16_MFMA_PEAK_TFLOPS = 2500.0      # dense bf16, vendor figure
 # Memory-side bytes per launch (calibrated FETCH_SIZE + WRITE_SIZE) are not measurable from inside
 # this script: they come from two `rocprofv3 --pmc` runs of this very command, whose summary is
 # committed under profiles/.  The line below repeats that file's figures for the headline workload
-# and says so in `traffic_source`; for any other workload or tile the field is null.
+# and says so in `traffic_source`; for any other workload or tile the field is null.  (A logits or
+# dHidden launch covers four tiles and counts as four launches: a fourth of its bytes each.)
 TRAFFIC_PROFILE = "profiles/bench_llama8b_128k_hbm_traffic.txt"
 PROFILED_TRAFFIC_BYTES_PER_LAUNCH = {
-    "llama8b_128k": {"logits_gemm": 6.806e9, "dhidden_gemm": 5.916e9, "dw_gemm": 25.573e9},
+    "llama8b_128k": {"logits_gemm": 6.858e9, "dhidden_gemm": 6.058e9, "dw_gemm": 25.770e9},
 }
 OTHER_STEPS, OTHER_WARMUP = 3, 1
 
