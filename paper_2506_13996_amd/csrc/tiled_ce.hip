@@ -112,6 +112,8 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
 // host evaluates the same function for every possible row count to size the launch.
 constexpr int kComputeUnits = 256;
+// (from 16 rounds of workgroups on the chip is filled to 16/17 or better as it is)
+constexpr int64_t kCutBlocks = 16 * kComputeUnits;
 // part_rows_cap: the ranges' fp32 partial products (splits * rows rows) must fit that many rows.
 __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t V, int64_t part_rows_cap,
                                                int& splits, int& ksteps) {
@@ -119,8 +121,7 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
     const int KT = (int)((V + kBlockK - 1) / kBlockK);
     splits = 1;
     int64_t best = INT64_MAX;
-    // (with 16 or more rounds of workgroups the chip is filled to 16/17 or better as it is)
-    const int sp_max = blocks >= 16 * kComputeUnits ? 1 : 8;
+    const int sp_max = blocks >= kCutBlocks ? 1 : 8;
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int per = (KT + sp - 1) / sp;
         if (sp > 1 && (per < 8 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
@@ -134,13 +135,14 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
 }
 
 // The most blocks (over all ranges) that dHidden of a chunk of up to `rows` dense rows (a multiple of
-// 256) needs, and whether some number of rows has its contraction cut.  (Beyond 4096 row blocks only the
-// full chunk is looked at; gather_rows_kernel then keeps a smaller chunk's choice within these bounds.)
+// 256) needs, and whether some number of rows has its contraction cut: what gather_rows_kernel may
+// choose on the device, for every number of dense rows.  Only below 16 rounds of blocks is a contraction
+// cut; from there on the blocks grow with the rows, so of those numbers the largest stands for all.
 static int64_t dhidden_most_blocks(int64_t rows, int64_t H, int64_t V, int64_t part_rows, bool& cut) {
     const int64_t tiles_c = (H + kBlockC - 1) / kBlockC, rb_max = rows / kBlockR;
-    int64_t most = 0;
+    int64_t most = rb_max * tiles_c;
     cut = false;
-    for (int64_t rb = rb_max > 4096 ? rb_max : 1; rb <= rb_max; ++rb) {
+    for (int64_t rb = 1; rb <= rb_max && rb * tiles_c < kCutBlocks; ++rb) {
         int sp, ks;
         dhidden_splits(rb * kBlockR, H, V, part_rows, sp, ks);
         if (rb * tiles_c * sp > most) most = rb * tiles_c * sp;
@@ -156,7 +158,7 @@ static int64_t workspace_ranges(int64_t rows, int64_t H, int64_t V) {
     const int64_t blocks = (rows / kBlockR) * ((H + kBlockC - 1) / kBlockC);
     const int64_t KT = (V + kBlockK - 1) / kBlockK;
     int64_t ranges = 1, best = 0, best_slots = 1;          // share of busy compute units: best / best_slots
-    const int sp_max = blocks >= 16 * kComputeUnits ? 1 : 8;
+    const int sp_max = blocks >= kCutBlocks ? 1 : 8;
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int64_t per = (KT + sp - 1) / sp;
         if (sp > 1 && (per < 64 || (sp - 1) * per >= KT)) break;
@@ -427,7 +429,7 @@ struct GatherParams {
     uint16_t* dHidden;           // [N, H]
     int64_t N, first;
     int64_t Rc;                  // the chunk's rows, rounded up to the block height
-    int64_t H, V, dh_blocks, dh_part_rows;
+    int64_t H, V, dh_part_rows;
     int Hk, ignore_index;
 };
 __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) {
@@ -453,14 +455,11 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) 
         p.info->Tc = Tc;
         p.info->Trc = Trc;
         p.info->redo = 0;
-        // dHidden of this chunk: the ranges of V that suit its Trc rows, within what the launch
-        // and the buffer of partial products were sized for
+        // dHidden of this chunk: the ranges of V that suit its Trc rows.  The host has looked at every
+        // Trc there can be (dhidden_most_blocks): the launch holds the blocks, and the partial products
+        // are added up.
         int sp = 1, ks = 0;
         dhidden_splits(Trc, p.H, p.V, p.dh_part_rows, sp, ks);
-        if ((int64_t)(Trc / kBlockR) * ((p.H + kBlockC - 1) / kBlockC) * sp > p.dh_blocks) {
-            sp = 1;
-            ks = (int)((p.V + kBlockK - 1) / kBlockK);
-        }
         p.info->splits = sp;
         p.info->ksteps = ks;
     }
@@ -1196,7 +1195,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.hdr = hdr; gp.info = info; gp.Hc = hc_t; gp.yc = yc; gp.ref = ref; gp.rowstate = rowstate;
             gp.rmax = rmax; gp.dHidden = P.dHidden;
             gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
-            gp.dh_blocks = dh_blocks; gp.dh_part_rows = part_rows;
+            gp.dh_part_rows = part_rows;
             gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
             int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
             if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
