@@ -1,7 +1,8 @@
 /*
  * alst_debug.h -- benchmarking and testing aids of libalst.  None of them is part of the method
  * (no counterpart in the paper) and no product code needs them: the timers serve the benchmark,
- * the block mapping and the matrix-instruction rate serve the tests and the roofline context.
+ * the block mapping, the chunk lengths and the matrix-instruction rate serve the tests and the roofline
+ * context.
  */
 #ifndef ALST_DEBUG_H
 #define ALST_DEBUG_H
@@ -37,6 +38,14 @@ int alst_profile_read(double* ms_total, int64_t* launches);
  * dealt out as twice as many halves).  A negative return value is minus an alst_status.
  */
 int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* part, int* tr, int* tc);
+
+/*
+ * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched): the rows per
+ * launch that a layer call works in.  op 0: alst_tiled_mlp_forward, 1: alst_tiled_mlp_backward (K = hidden, M =
+ * intermediate size), 2: the y launches of alst_tiled_linear_forward, 3: the dx launches of
+ * alst_tiled_linear_backward.  A negative return value is minus an alst_status.
+ */
+int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t tile);
 
 /*
  * Benchmarking aid (no counterpart in the paper): the sustained rate, in TFLOP/s, of the bf16

@@ -29,7 +29,8 @@ EXPORTS = (
     "alst_tiled_ce_backward", "alst_tiled_ce_forward_backward",
     "alst_tiled_ce_forward_backward_noalloc", "alst_last_device_status",
     "alst_shift_labels", "alst_tiled_ce_token_losses",
-    "alst_profile_enable", "alst_profile_read", "alst_debug_block_tile", "alst_debug_mfma_rate",
+    "alst_profile_enable", "alst_profile_read", "alst_debug_block_tile", "alst_debug_chunk_rows",
+    "alst_debug_mfma_rate",
     "alst_tiled_mlp_workspace_bytes", "alst_tiled_mlp_forward", "alst_tiled_mlp_backward",
     "alst_tiled_linear_workspace_bytes", "alst_tiled_linear_forward", "alst_tiled_linear_backward",
 )
@@ -95,6 +96,8 @@ def load_library() -> ctypes.CDLL:
     lib.alst_debug_mfma_rate.argtypes = [c.c_int, c.c_int, c.c_void_p, c.POINTER(c.c_double), c.c_void_p]
     lib.alst_debug_block_tile.restype = c.c_int
     lib.alst_debug_block_tile.argtypes = [c.c_int] * 4 + [c.POINTER(c.c_int)] * 3
+    lib.alst_debug_chunk_rows.restype = i64
+    lib.alst_debug_chunk_rows.argtypes = [c.c_int, i64, i64, i64, i64]
     _lib = lib
     return lib
 
@@ -368,6 +371,14 @@ def alst_profile_read() -> dict:
     n = (ctypes.c_int64 * 8)()
     _check(load_library().alst_profile_read(ms, n), "alst_profile_read")
     return {k: (ms[i], int(n[i])) for i, k in enumerate(PROFILE_KINDS)}
+
+
+def alst_debug_chunk_rows(op: int, N: int, K: int, M: int, tile: int) -> int:
+    """Rows per launch of a layer call (op: see alst_debug.h).  Host arithmetic only."""
+    n = int(load_library().alst_debug_chunk_rows(op, N, K, M, tile))
+    if n < 0:
+        raise AlstError(-n, "alst_debug_chunk_rows")
+    return n
 
 
 def alst_debug_block_tile(tiles_r: int, tiles_c: int, parts: int, bid: int):

@@ -127,6 +127,13 @@ __host__ __device__ __forceinline__ Halving halve_last_round(int blocks) {
     return {full, full + 2 * left};
 }
 
+// What a launch of `blocks` blocks takes, in 16ths of a round of whole blocks (a last round in halves:
+// 10 / 16, see Halving).
+__host__ __device__ __forceinline__ int64_t rounds16(int64_t blocks, bool halves = true) {
+    const int64_t left = blocks % kRound;
+    return blocks / kRound * 16 + (left == 0 ? 0 : halves && 2 * left <= kRound ? 10 : 16);
+}
+
 // Block (tr, tc) of number i < g.blocks() in the order.
 __host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, int& tr, int& tc) {
     const int column = i / (g.tiles_r * g.PC);               // column of patches

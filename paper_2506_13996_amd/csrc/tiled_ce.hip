@@ -125,10 +125,7 @@ __host__ __device__ inline void dhidden_splits(int64_t rows, int64_t H, int64_t 
     for (int sp = 1; sp <= sp_max; ++sp) {
         const int per = (KT + sp - 1) / sp;
         if (sp > 1 && (per < 8 || (int64_t)(sp - 1) * per >= KT || sp * rows > part_rows_cap)) break;
-        const int64_t left = blocks * sp % kComputeUnits;
-        const int64_t last16 = left == 0 ? 0 : 2 * left <= kComputeUnits ? 10 : 16;
-        const int64_t rounds16 = blocks * sp / kComputeUnits * 16 + last16;
-        const int64_t cost = rounds16 * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
+        const int64_t cost = rounds16(blocks * sp) * (per + 4) + (sp > 1 ? 48 + blocks * sp * 9 / 8 : 0);
         if (cost < best) { best = cost; splits = sp; }
     }
     ksteps = (KT + splits - 1) / splits;

@@ -29,12 +29,14 @@
 // [dg | du] from the group's buffers.
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <initializer_list>
 #include <mutex>
 #include <stdint.h>
 #include <math.h>
 
 #include "../../include/alst_mlp.h"
 #include "../../include/alst_linear.h"
+#include "../../include/alst_debug.h"
 #include "gemm_tile.h"
 #include "common.h"
 
@@ -53,15 +55,53 @@ struct MlpLayout {
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Rows of a chunk with `width` bf16 intermediates (or operand elements) per row: enough to fill the
-// chip, few enough that what one launch of a chunk writes is still in the 256 MB memory-side cache when
-// the next reads it.  4096 rows of a, dg and du of a 14336-wide MLP (352 MB): 244.9 ms for
-// 256000 x 4096; chunks of a whole group (17664 rows) 250.6 ms.  Launches of one 128-row
-// tile of a 256 x 768 MLP took 441 us where chunks take 175 us (N = 512).
-static int64_t chunk_rows(int64_t width) {
-    const int64_t rows = (int64_t)4096 * 3 * 14336 / width / kBlockR * kBlockR;
-    return rows < 4096 ? 4096 : rows > 65536 ? 65536 : rows;
+// A launch of a chunk: columns of output blocks and k-steps per block; halves: a last round of at most
+// half the compute units is worked on in halves (MixedCore has none).
+struct ChunkLaunch { int64_t cols, ksteps; bool halves; };
+static ChunkLaunch chunk_launch(int64_t cols, int64_t k, bool halves = true) {
+    return {(cols + kBlockC - 1) / kBlockC, (k + kBlockK - 1) / kBlockK, halves};
 }
+
+// Rows of a chunk, a multiple of 256 and at most `most`: the number with the least estimated time for all
+// N rows, in units of a k-step of one block: per launch the rounds of the compute units times (k-steps
+// per block + about 4 for its start and epilogue), and about 4 for the launch itself.  (Half of `most` and
+// less is not looked at: two such chunks are one launch each fewer.)  room, group: a weight-gradient
+// group of whole chunks has at most `room` rows and costs `group` 16ths of a unit.
+// What a chunk's length is worth is whole rounds of its narrowest product: 65536 x 4096 x 14336 forward,
+// tile 16384: 18.1 / 17.3 / 16.4 / 16.2 ms in chunks of 2048 / 5120 / 4096 / 16384 rows.  Chunks of as many
+// rows as some bytes allow, whatever the rounds, were up to 6 % slower than one launch per tile of 8192 or
+// more rows: linear 65536 x 4096 x 4096 forward 1.53 against 1.62 ms, MLP 65536 x 1024 x 4096 1.34
+// against 1.43.
+static int64_t chunk_rows(int64_t N, int64_t most, std::initializer_list<ChunkLaunch> launches, int64_t room = 0,
+                          int64_t group = 0) {
+    if (N <= most) return most;
+    auto cost = [&](int64_t row_blocks) {
+        int64_t c = 0;
+        for (const ChunkLaunch& l : launches) c += rounds16(row_blocks * l.cols, l.halves) * (l.ksteps + 4) + 16 * 4;
+        return c;
+    };
+    int64_t best = most, least = INT64_MAX;
+    for (int64_t rows = most; 2 * rows > most; rows -= kBlockR) {
+        const int64_t rest = (N % rows + kBlockR - 1) / kBlockR;
+        int64_t c = N / rows * cost(rows / kBlockR) + (rest ? cost(rest) : 0);
+        if (room) {
+            const int64_t group_rows = room / rows * rows;
+            c += (N + group_rows - 1) / group_rows * group;
+        }
+        if (c < least) { least = c; best = rows; }
+    }
+    return best;
+}
+
+// The most rows of a chunk whose rows are `width` elements wide: 16384, more while they stay below `bytes`
+// (what a launch reads several times over, or the next launch reads again, is then mostly in the memory-side
+// cache).
+static int64_t chunk_rows_max(int64_t width, int64_t bytes, int64_t top) {
+    return std::clamp<int64_t>(bytes / (2 * width) / kBlockR * kBlockR, 16384, top);
+}
+// MLP, width I: a of 16384 / 32768 / 65536 rows 32768 x 4096 x 11008 forward 6.27 / 6.36 ms, 65536 x 1024 x
+// 4096 1.39 / 1.38 / 1.37.
+static int64_t mlp_chunk_rows_max(int64_t I) { return chunk_rows_max(I, (int64_t)512 << 20, 65536); }
 
 static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, bool backward,
                                  uint32_t flags) {
@@ -71,7 +111,8 @@ static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, 
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     if (!backward) {
-        L.chunk = std::min(L.Tp, chunk_rows(3 * I));
+        L.chunk = chunk_rows(N, std::min(L.Tp, mlp_chunk_rows_max(I)),
+                             {chunk_launch(2 * I, H), chunk_launch(H, I)});
         L.a = take((size_t)L.Tp * I * 2);
     } else {
         // a and [dg | du] of a chunk, in the room that those of a group of g tiles and the da of one
@@ -79,7 +120,13 @@ static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, 
         int64_t g = kMlpGroupRows / L.Tp;
         g = g < 1 ? 1 : (g > kMlpGroupMax ? kMlpGroupMax : g);
         const int64_t room = (g * 3 + 1) * L.Tp / 3 / kBlockR * kBlockR;
-        L.chunk = std::min(room, chunk_rows(3 * I));
+        L.weights_t = H % kBlockK == 0 && I % kBlockK == 0;
+        // (a group's three weight gradients: each of its blocks about 4 + 5 k-steps for its start and the
+        // sums' way through memory)
+        const int64_t wgrad_blocks = 3 * ((H + kBlockR - 1) / kBlockR) * ((I + kBlockC - 1) / kBlockC);
+        L.chunk = chunk_rows(N, std::min(room, mlp_chunk_rows_max(I)),
+                             {chunk_launch(I, H, L.weights_t), chunk_launch(2 * I, H), chunk_launch(H, 2 * I, L.weights_t)},
+                             room, rounds16(wgrad_blocks) * 9);
         L.rows = room / L.chunk * L.chunk;
         L.a = take((size_t)(g * 3 + 1) * L.Tp * I * 2);
         L.dgu = L.a + (size_t)L.rows * I * 2;
@@ -87,7 +134,6 @@ static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, 
         // dx = [dg | du] [Wg ; Wu] then read both operands along their rows (the fastest layout
         // of the block GEMM).  For H and I that are whole k-steps; else the weights are read as
         // they are.
-        L.weights_t = H % kBlockK == 0 && I % kBlockK == 0;
         L.wdt = take(L.weights_t ? (size_t)I * H * 2 : 0);
         L.wgut = take(L.weights_t ? (size_t)H * 2 * I * 2 : 0);
         // fp32 overwrite outputs hold the sums themselves
@@ -720,8 +766,15 @@ static int run_mlp_backward(const MlpProblem& P) {
 // ---------------------------------------------------------------------------------------------
 // the single tiled linear layer: y = x W^T, dx = dy W, dW = dy^T x
 // ---------------------------------------------------------------------------------------------
-// (its launches read their operand's rows once per 2048 columns of the output)
-static int64_t lin_chunk_rows(int64_t K, int64_t M) { return chunk_rows(K + M); }
+// Rows of a launch of D [N, M] = X [N, K] Y.  One launch for all rows if a row of X is read once (an output of
+// at most 8 columns of blocks, a patch's width: 131072 x 1024 x 1024 forward 223 us, in two launches 230;
+// 4 M rows are 64 whole rounds and more, far from the limit of a grid); else 16384, more while a chunk of X stays below 128 MB: 32768 x 5120 x 16384 forward 3.80 / 3.92 ms with
+// 16384 / 32768 rows.
+static int64_t lin_chunk_rows(int64_t N, int64_t K, int64_t M, bool halves = true) {
+    const int64_t all = (N + kBlockR - 1) / kBlockR * kBlockR;
+    if (M <= 8 * kBlockC) return std::min(all, (int64_t)1 << 22);
+    return chunk_rows(N, std::min(all, chunk_rows_max(K, (int64_t)128 << 20, 262144)), {chunk_launch(M, K, halves)});
+}
 
 struct LinLayout {
     int64_t Tp;
@@ -783,7 +836,7 @@ static int validate_lin(const LinProblem& P, size_t workspace_bytes, bool backwa
 static int run_lin_forward(const LinProblem& P) {
     int rc = prepare_mlp_kernels();
     if (rc != ALST_OK) return rc;
-    const int64_t chunk = lin_chunk_rows(P.K, P.M);
+    const int64_t chunk = lin_chunk_rows(P.N, P.K, P.M);
     for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
         LinearParams lp = {};
         lp.X = P.x + i0 * P.K; lp.ldx = P.K; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = (int)P.K;
@@ -813,7 +866,7 @@ static int run_lin_backward(const LinProblem& P) {
         hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
-    const int64_t chunk = lin_chunk_rows(P.K, P.M);
+    const int64_t chunk = lin_chunk_rows(P.N, P.M, P.K, L.weight_t);
     for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
         LinearParams lp = {};
         lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = M;
@@ -912,5 +965,13 @@ int alst_tiled_linear_backward(const void* x, const void* W, const void* dy, int
     return run_lin_backward(P);
 }
 
-}  // extern "C"
+int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t tile) {
+    if (op < 0 || op > 3 || N < 1 || K < 1 || M < 1 || tile < 1 || N > (int64_t)1 << 30 || K > (int64_t)1 << 20 ||
+        M > (int64_t)1 << (op < 2 ? 20 : 24))
+        return -ALST_ERR_SHAPE;
+    if (op < 2) return make_mlp_layout(N, K, M, tile, op == 1, 0).chunk;
+    if (op == 2) return lin_chunk_rows(N, K, M);
+    return lin_chunk_rows(N, M, K, make_lin_layout(N, K, M, tile, true, 0).weight_t);
+}
 
+}  // extern "C"

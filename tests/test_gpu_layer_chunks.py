@@ -40,7 +40,7 @@ def test_mlp_chunks(N, H, I, tile, flags):
 
 @pytest.mark.parametrize("N,K,M,tile", [
     (16385, 64, 72, 128),       # one row in the second weight-gradient group
-    (66000, 8, 16, 300),        # two launches of y and dx
+    (66000, 8, 16, 300),        # 220 tiles in one launch of y and of dx
     (17000, 16, 64, 16640),     # a tile longer than a group
 ])
 def test_linear_chunks(N, K, M, tile):
@@ -48,6 +48,26 @@ def test_linear_chunks(N, K, M, tile):
     got = TL._run(x, W, dy, tile)
     for g, r in zip(got, (lorc.forward(x, W), *lorc.backward(x, W, dy))):
         assert G.grad_err(g, r) <= TOL
+
+
+def test_several_launches_of_y_and_dx():
+    """Rows of more than 128 MB of either operand: y and dx in several launches, the last of them short.  Rows on
+    both sides of every seam and a sample of the others against float64 on the same device."""
+    N, K, M = 33_000, 4104, 2184
+    chunks = [B.alst_debug_chunk_rows(op, N, K, M, 4096) for op in (2, 3)]
+    assert all(N // 3 < c < N for c in chunks)
+    g = torch.Generator(device="cuda").manual_seed(24)
+    x, W, dy = (torch.randn(s, device="cuda", generator=g).to(torch.bfloat16) for s in ((N, K), (M, K), (N, M)))
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    dW = torch.empty_like(W)
+    B.alst_tiled_linear_forward(x, W, 4096, y=y)
+    ws = torch.empty(B.alst_tiled_linear_workspace_bytes(N, K, M, 4096, True), dtype=torch.uint8, device="cuda")
+    B.alst_tiled_linear_backward(x, W, dy, 4096, dx=dx, dW=dW, workspace=ws)
+    assert torch.isfinite(y).all() and torch.isfinite(dx).all()
+    seams = [r for c in chunks for at in range(c, N, c) for r in (at - 2, at - 1, at, at + 1)]
+    rows = torch.tensor(sorted({0, 1, N - 2, N - 1, *seams, *range(7, N, 997)}), device="cuda")
+    for got, ref in ((y, x[rows].double() @ W.double().t()), (dx, dy[rows].double() @ W.double())):
+        assert float((got[rows].double() - ref).abs().max() / ref.abs().max()) <= TOL
 
 
 def test_tile_size_does_not_reach_rows():
