@@ -92,6 +92,8 @@ inline PatchGrid choose_patches(int tiles_r, int tiles_c) {
     return best;
 }
 
+// A launch has fewer than 2^32 threads (more are not refused: their number wraps): workgroups of 256.
+constexpr int64_t kGridBlocks = ((int64_t)1 << 24) - kRound;
 inline int grid_for_blocks(int64_t blocks) { return (int)((blocks + kRound - 1) / kRound * kRound); }
 
 // Workgroup -> number of its block among the launch's `total`, or -1.

@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/alst.h"
@@ -87,6 +88,8 @@ constexpr uint32_t kKnownFlags = ALST_FLAG_DW_FP32 | ALST_FLAG_DW_ACCUMULATE | A
                                  ALST_FLAG_TILE_SCRATCH | ALST_FLAG_FORWARD_ONLY;
 
 constexpr int kScanThreads = 1024;   // rows per block of the compaction kernels
+// gather_rows_kernel: rows of the sequence a workgroup looks for ignored tokens at a time, workgroups that do so
+constexpr int kZeroRows = 16, kZeroBlocksMax = 32768;
 
 struct Layout {
     int64_t Tp, Vp, ng;    // padded tile rows, padded vocabulary, 128-column groups
@@ -188,7 +191,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     L.block_ofs = take(nblocks * 8);
     // Per-row arrays, softmax partials and partial dHidden products of one chunk.  The region is
     // sized for one tile (20 bytes per row, 8 per row and 128-column group, the partial products a
-    // full tile needs); a chunk then takes as many rows of the dW group as fit it with 24 bytes
+    // full tile needs); a chunk then takes as many rows of the dW group as fit it (and a grid) with 24 bytes
     // per row and 4 per row and group (the partial products of dHidden reuse the softmax partials'
     // place, which row_finish has consumed by then).
     const size_t region = (size_t)L.Tp * (20 + 8 * (size_t)L.ng) +
@@ -196,8 +199,11 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     const size_t at = take(region);
     const int64_t fit = (int64_t)(region / (24 + 4 * (size_t)L.ng)) / kBlockR * kBlockR;
     const int64_t rows = (N + kBlockR - 1) / kBlockR * kBlockR, Kn = L.Kg < rows ? L.Kg : rows;
-    const int64_t parts = (Kn + fit - 1) / fit;
-    L.Rc = ((Kn + parts - 1) / parts + kBlockR - 1) / kBlockR * kBlockR;     // <= fit, a multiple of 256
+    // (a launch has a workgroup of 256 per row and those of the zeroing, or per output block of the chunk)
+    const int64_t cols = std::max((L.Vp + kBlockC - 1) / kBlockC, (H + kBlockC - 1) / kBlockC);
+    const int64_t grid = std::min(kGridBlocks - kZeroBlocksMax, kGridBlocks / cols * kBlockR) / kBlockR * kBlockR;
+    const int64_t most = std::min(fit, grid), parts = (Kn + most - 1) / most;
+    L.Rc = ((Kn + parts - 1) / parts + kBlockR - 1) / kBlockR * kBlockR;     // <= most, a multiple of 256
     L.zlabel = at;
     L.yc = L.zlabel + (size_t)L.Rc * 4;
     L.ref = L.yc + (size_t)L.Rc * 4;
@@ -411,7 +417,6 @@ __device__ __forceinline__ float from_ordered_int(int k) {
 // row as taking part in that pass.  Workgroup 0 leaves the chunk's counts and its dHidden ranges.
 // Workgroups from Rc on (first chunk, if a gradient is wanted) take kZeroRows rows of the sequence at a
 // time; the dHidden rows of ignored tokens become zeros.
-constexpr int kZeroRows = 16, kZeroBlocksMax = 32768;
 struct GatherParams {
     const uint16_t* hidden;      // [N, H]
     const int32_t* labels;       // [N]
@@ -1032,11 +1037,11 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
         return ALST_ERR_ALIGN;
     if (need_bwd_out && (!aligned16(P.dHidden) || !aligned16(P.dW))) return ALST_ERR_ALIGN;
     const Layout L = make_layout(P.N, P.H, P.V, P.tile, P.flags);
-    // every launch must fit a one-dimensional grid
-    if (!checked_grid(L.Rc / kBlockR, L.Vp / kBlockC) ||
+    // tiles beyond these many blocks are refused (what a launch holds, make_layout sees to)
+    if (!checked_grid(L.Tp / kBlockR, L.Vp / kBlockC) ||
         !checked_grid((P.H + kBlockR - 1) / kBlockR, L.Vp / kBlockC) ||
-        L.Rc / kBlockR * ((P.H + kBlockC - 1) / kBlockC) > 0x7fffff00 ||   // dHidden (cut: at most 8 * 4096)
-        L.Rc + kZeroBlocksMax > 0x7fffffff)
+        L.Tp / kBlockR * ((P.H + kBlockC - 1) / kBlockC) > 0x7fffff00 ||
+        (L.Vp / 256) * (L.Tp / 64) > 0x7fffffff)
         return ALST_ERR_SHAPE;
     if (workspace_bytes < L.total) return own_scratch ? ALST_ERR_NOALLOC_LIMIT : ALST_ERR_WORKSPACE;
     return ALST_OK;
