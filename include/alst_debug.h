@@ -1,8 +1,7 @@
 /*
  * alst_debug.h -- benchmarking and testing aids of libalst.  None of them is part of the method
  * (no counterpart in the paper) and no product code needs them: the timers serve the benchmark,
- * the block mapping, the chunk lengths and the matrix-instruction rate serve the tests and the roofline
- * context.
+ * the block mapping, the chunks and the matrix-instruction rate serve the tests and the roofline context.
  */
 #ifndef ALST_DEBUG_H
 #define ALST_DEBUG_H
@@ -46,6 +45,24 @@ int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* par
  * alst_tiled_linear_backward.  A negative return value is minus an alst_status.
  */
 int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t tile);
+
+/*
+ * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched): chunk number
+ * `chunk` of the launches of a cross-entropy call that computes gradients, and what the device makes of it if
+ * `dense` of its rows are there (rows with a valid label, numbered densely through the sequence).
+ */
+typedef struct {
+    int64_t first, rows;             /* dense rows first .. first + rows - 1, as far as they exist */
+    int64_t group0;                  /* first dense row of its dW group */
+    int64_t dhidden_blocks;          /* output blocks of dHidden over all ranges, for `dense` rows */
+    int64_t dhidden_grid;            /* workgroups of the dHidden launch */
+    int64_t largest_grid;            /* workgroups of the chunk's largest launch */
+    int ranges;                      /* ranges dHidden's contraction is cut into, for `dense` rows */
+    int added_up;                    /* whether the launch that adds partial products up is made */
+    int in_stash;                    /* the partial products lie in stash rows not reached yet */
+} alst_debug_ce_chunk_info;
+int alst_debug_ce_chunk(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags, int64_t chunk, int64_t dense,
+                        alst_debug_ce_chunk_info* info);
 
 /*
  * Benchmarking aid (no counterpart in the paper): the sustained rate, in TFLOP/s, of the bf16

@@ -30,10 +30,18 @@ EXPORTS = (
     "alst_tiled_ce_forward_backward_noalloc", "alst_last_device_status",
     "alst_shift_labels", "alst_tiled_ce_token_losses",
     "alst_profile_enable", "alst_profile_read", "alst_debug_block_tile", "alst_debug_chunk_rows",
-    "alst_debug_mfma_rate",
+    "alst_debug_ce_chunk", "alst_debug_mfma_rate",
     "alst_tiled_mlp_workspace_bytes", "alst_tiled_mlp_forward", "alst_tiled_mlp_backward",
     "alst_tiled_linear_workspace_bytes", "alst_tiled_linear_forward", "alst_tiled_linear_backward",
 )
+
+
+class CeChunkInfo(ctypes.Structure):
+    """alst_debug_ce_chunk_info (alst_debug.h)."""
+    _fields_ = [(n, ctypes.c_int64) for n in ("first", "rows", "group0", "dhidden_blocks", "dhidden_grid",
+                                              "largest_grid")] + \
+               [(n, ctypes.c_int) for n in ("ranges", "added_up", "in_stash")]
+
 
 _lib = None
 
@@ -98,6 +106,8 @@ def load_library() -> ctypes.CDLL:
     lib.alst_debug_block_tile.argtypes = [c.c_int] * 4 + [c.POINTER(c.c_int)] * 3
     lib.alst_debug_chunk_rows.restype = i64
     lib.alst_debug_chunk_rows.argtypes = [c.c_int, i64, i64, i64, i64]
+    lib.alst_debug_ce_chunk.restype = c.c_int
+    lib.alst_debug_ce_chunk.argtypes = [i64, i64, i64, i64, u32, i64, i64, c.POINTER(CeChunkInfo)]
     _lib = lib
     return lib
 
@@ -379,6 +389,14 @@ def alst_debug_chunk_rows(op: int, N: int, K: int, M: int, tile: int) -> int:
     if n < 0:
         raise AlstError(-n, "alst_debug_chunk_rows")
     return n
+
+
+def alst_debug_ce_chunk(N: int, H: int, V: int, tile: int, flags: int, chunk: int, dense: int) -> CeChunkInfo:
+    """A chunk of a cross-entropy call's launches (alst_debug.h).  Host arithmetic only."""
+    info = CeChunkInfo()
+    _check(load_library().alst_debug_ce_chunk(N, H, V, tile, flags, chunk, dense, ctypes.byref(info)),
+           "alst_debug_ce_chunk")
+    return info
 
 
 def alst_debug_block_tile(tiles_r: int, tiles_c: int, parts: int, bid: int):

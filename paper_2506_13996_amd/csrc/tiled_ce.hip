@@ -44,6 +44,7 @@
 #include <mutex>
 
 #include "../../include/alst.h"
+#include "../../include/alst_debug.h"
 #include "gemm_tile.h"
 #include "common.h"
 
@@ -999,6 +1000,43 @@ static int prepare_kernels() {
     return results[dev];
 }
 
+// A chunk of launches as the host sees it, which knows N only: dense rows first .. first + rows - 1, as far as
+// they exist.
+struct ChunkPlan {
+    int64_t group0;            // first dense row of the chunk's dW group
+    int64_t at, rows;          // the chunk's place in the group and length
+    int Tr;                    // rows rounded up to the block height
+    bool group_done;           // the group's last chunk
+    // dHidden: where the fp32 partial products of its ranges go (a place in the workspace) and how many
+    // rows of them fit; the most blocks, and whether they may have to be added up
+    size_t part;
+    int64_t part_rows, dh_blocks;
+    bool dh_cut;
+};
+static ChunkPlan chunk_plan(const Layout& L, int64_t N, int64_t H, int64_t V, int64_t first, bool do_bwd) {
+    ChunkPlan c = {};
+    c.group0 = first / L.Kg * L.Kg;
+    c.at = first - c.group0;
+    c.rows = std::min(std::min(L.Rc, L.Kg - c.at), N - first);
+    c.Tr = (int)((c.rows + kBlockR - 1) / kBlockR * kBlockR);
+    c.group_done = c.at + c.rows == L.Kg || first + c.rows == N;
+    if (!do_bwd) return c;
+    // The partial products: behind the chunk's per-row arrays, or in the rows of the stash that the group
+    // has not reached, if these have more room (the next chunk's logits are written after they are added
+    // up).  A short call has nearly all of the stash: N = 512, H = 256, V = 4096 takes 8 ranges where the
+    // first place holds 1: the call 116 -> 65 us.
+    c.part = L.part;
+    size_t bytes = L.part_bytes;
+    const size_t behind = (size_t)(L.Kg - c.at - c.Tr) * L.Vp * 2;
+    if (behind > bytes) {
+        c.part = L.stash + (size_t)(c.at + c.Tr) * L.Vp * 2;
+        bytes = behind;
+    }
+    c.part_rows = (int64_t)(bytes / ((size_t)H * 4));
+    c.dh_blocks = dhidden_most_blocks(c.Tr, H, V, c.part_rows, c.dh_cut);
+    return c;
+}
+
 struct Problem {
     const uint16_t* hidden;
     const uint16_t* W;
@@ -1157,38 +1195,17 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
 
     // The host does not know M: it walks the chunks of N rows, the most there can be; the kernels of
     // a chunk beyond the dense rows find Tc = 0 on the device and leave at once.
-    int64_t group0 = 0;                                 // first dense row of the dW group
     for (int64_t first = 0, rows = 0; first < P.N; first += rows) {
-        if (first - group0 == L.Kg) group0 = first;
-        const int64_t at = first - group0;              // the chunk's rows inside the group
-        rows = L.Rc < L.Kg - at ? L.Rc : L.Kg - at;
-        if (rows > P.N - first) rows = P.N - first;
-        const int Tr = (int)((rows + kBlockR - 1) / kBlockR * kBlockR);
-        const bool group_done = at + rows == L.Kg || first + rows == P.N;
+        const ChunkPlan c = chunk_plan(L, P.N, P.H, P.V, first, do_bwd);
+        rows = c.rows;
+        const int Tr = c.Tr;
         const int32_t* idx_t = idx + first;             // the chunk's dense rows -> sequence rows
         // the caller's tiles that begin in this chunk, for the timers
         const int tiles = (int)((first + rows + T - 1) / T - (first + T - 1) / T);
         // (the forward-only layout has the rows of one chunk)
-        uint16_t* const hc_t = hc + (do_bwd ? at : 0) * L.Hk;
-        uint16_t* const stash_t = stash + (do_bwd ? at : 0) * L.Vp;
-
-        // The partial products of dHidden's ranges: behind the chunk's per-row arrays, or in the rows of
-        // the stash that the group has not reached, if these have more room (the next chunk's logits
-        // are written after they are added up).  A short call has nearly all of the stash: N = 512,
-        // H = 256, V = 4096 takes 8 ranges where the first place holds 1: the call 116 -> 65 us.
-        float* part = reinterpret_cast<float*>(P.ws + L.part);
-        size_t part_bytes = L.part_bytes;
-        bool dh_cut = false;
-        int64_t part_rows = 0, dh_blocks = 0;
-        if (do_bwd) {
-            const size_t behind = (size_t)(L.Kg - at - Tr) * L.Vp * 2;
-            if (behind > part_bytes) {
-                part = reinterpret_cast<float*>(stash + (at + Tr) * L.Vp);
-                part_bytes = behind;
-            }
-            part_rows = (int64_t)(part_bytes / ((size_t)H * 4));
-            dh_blocks = dhidden_most_blocks(Tr, H, V, part_rows, dh_cut);
-        }
+        uint16_t* const hc_t = hc + (do_bwd ? c.at : 0) * L.Hk;
+        uint16_t* const stash_t = stash + (do_bwd ? c.at : 0) * L.Vp;
+        float* const part = reinterpret_cast<float*>(P.ws + c.part);
 
         {
             ProfScope small_(PROF_OTHER, s);
@@ -1197,7 +1214,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.hdr = hdr; gp.info = info; gp.Hc = hc_t; gp.yc = yc; gp.ref = ref; gp.rowstate = rowstate;
             gp.rmax = rmax; gp.dHidden = P.dHidden;
             gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
-            gp.dh_part_rows = part_rows;
+            gp.dh_part_rows = c.part_rows;
             gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
             int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
             if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
@@ -1232,21 +1249,21 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             dp.H = H; dp.V = V; dp.Vp = Vp;
             dp.PR = L.dh_PR; dp.PC = L.dh_PC;
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
-            const int grid = grid_for_blocks(dh_blocks);
+            const int grid = grid_for_blocks(c.dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
             hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
                                s, dp);
-            if (dh_cut)
+            if (c.dh_cut)
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr), dim3(256), 0, s, dp.part, H, idx_t,
                                    info, hdr, frow, P.dHidden);
             ALST_HIP(hipGetLastError());
         }
-        if (group_done) {
+        if (c.group_done) {
             DWParams wp;
             wp.hg = hc; wp.dzg = stash; wp.hdr = hdr;
-            wp.out = {acc, P.dW, P.H, 0.f, group0 == 0, 0, (P.flags & ALST_FLAG_DW_FP32) != 0,
+            wp.out = {acc, P.dW, P.H, 0.f, c.group0 == 0, 0, (P.flags & ALST_FLAG_DW_FP32) != 0,
                       (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
-            wp.row0 = group0; wp.rows = L.Kg;
+            wp.row0 = c.group0; wp.rows = L.Kg;
             wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
             const PatchGrid pg = choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
             wp.PR = pg.PR; wp.PC = pg.PC;
@@ -1435,6 +1452,36 @@ int alst_tiled_ce_token_losses(const void* workspace, size_t workspace_bytes, in
     hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, rows,
                        token_loss_out, N);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
+int alst_debug_ce_chunk(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags, int64_t chunk, int64_t dense,
+                        alst_debug_ce_chunk_info* info) {
+    if (!info) return ALST_ERR_NULL;
+    if ((flags & ~kKnownFlags) || (flags & ALST_FLAG_FORWARD_ONLY)) return ALST_ERR_UNSUPPORTED;
+    if (N < 1 || H < 1 || V < 1 || tile < 1 || chunk < 0) return ALST_ERR_SHAPE;
+    if (N > (int64_t)1 << 30 || H > (int64_t)1 << 20 || V > (int64_t)1 << 24) return ALST_ERR_SHAPE;
+    const Layout L = make_layout(N, H, V, tile, flags);
+    ChunkPlan c = {};
+    int64_t first = 0;
+    for (int64_t k = 0; k <= chunk; ++k, first += c.rows) {
+        if (first >= N) return ALST_ERR_SHAPE;
+        c = chunk_plan(L, N, H, V, first, true);
+    }
+    if (dense < 0 || dense > c.rows) return ALST_ERR_SHAPE;
+    const int64_t Trc = (dense + kBlockR - 1) / kBlockR * kBlockR;
+    int ranges, ksteps;
+    dhidden_splits(Trc, H, V, c.part_rows, ranges, ksteps);          // as gather_rows_kernel
+    info->first = first - c.rows;
+    info->rows = c.rows;
+    info->group0 = c.group0;
+    info->ranges = ranges;
+    info->added_up = c.dh_cut;
+    info->dhidden_blocks = Trc / kBlockR * ((H + kBlockC - 1) / kBlockC) * ranges;
+    info->dhidden_grid = grid_for_blocks(c.dh_blocks);
+    info->largest_grid = std::max<int64_t>({c.Tr + kZeroBlocksMax, info->dhidden_grid,
+                                            grid_for_blocks(c.Tr / kBlockR * (L.Vp / kBlockC))});
+    info->in_stash = c.part != L.part;
+    return ALST_OK;
 }
 
 int alst_shift_labels(const int32_t* labels, int32_t* shift_labels, int64_t N, int32_t ignore_index,

@@ -15,6 +15,18 @@ def bf16_dev_to_f64(t: torch.Tensor) -> np.ndarray:
     return t.float().cpu().numpy().astype(np.float64)
 
 
+def ce_chunks(N, H, V, tile, flags, n_valid):
+    """The chunks of a cross-entropy call with gradients, with n_valid dense rows in all (host arithmetic)."""
+    out, at = [], 0
+    while at < N:
+        whole = B.alst_debug_ce_chunk(N, H, V, tile, flags, len(out), 0)
+        here = max(0, min(n_valid - whole.first, whole.rows))
+        out.append(B.alst_debug_ce_chunk(N, H, V, tile, flags, len(out), here))
+        assert whole.first == at and whole.rows > 0
+        at += whole.rows
+    return out
+
+
 class Result:
     pass
 
