@@ -46,15 +46,20 @@ def test_mlp(N, H, I):
         assert G.grad_err(g, r) <= TOL
 
 
-@pytest.mark.parametrize("name,N,H,V,frac", [
-    ("whole_rounds_then_halves", 1024, 64, 24576, 0.0),
-    ("ragged", 1000, 72, 24300, 0.05),
-    ("second_half_without_rows", 600, 64, 33000, 0.15),
-    ("a_last_half_with_one_row", 129, 64, 300, 0.0),
+@pytest.mark.parametrize("name,N,H,V,n_valid,left,empty_half", [
+    # left: output blocks of the logits in the last round; empty_half: its last row block's second half has no row
+    ("whole_rounds_then_halves", 1024, 64, 24576, 1024, 128, False),
+    ("ragged", 1000, 72, 24300, 950, 124, False),
+    ("more_than_halves_take", 600, 64, 33000, 517, 131, True),
+    ("second_half_without_rows", 600, 64, 33000, 350, 2, True),
+    ("a_last_half_with_one_row", 129, 64, 300, 129, 2, False),
 ])
-def test_cross_entropy(name, N, H, V, frac):
-    wl = synth.custom(name, N, H, V, 1024, ignore_frac=frac, seed=33)
+def test_cross_entropy(name, N, H, V, n_valid, left, empty_half):
+    row_blocks, columns = -(-n_valid // 256), -(-V // 256)
+    assert row_blocks * columns % 256 == left and ((n_valid - 1) % 256 < 128) == empty_half
+    wl = synth.custom(name, N, H, V, 1024, ignore_frac=0.0, seed=33)
     h, W, y = synth.make_inputs(wl)
+    y[np.random.default_rng(34).choice(N, N - n_valid, replace=False)] = IGN
     f, dH, dW = _oracle(h, W, y)
     r = G.run_fused(h, W, y, 1024)
     _check(r, f, dH, dW, name, valid=(y != IGN))
