@@ -18,13 +18,18 @@ FORMS = [0, B.ALST_FLAG_DW_FP32, B.ALST_FLAG_DW_ACCUMULATE, B.ALST_FLAG_DW_FP32 
 
 
 @pytest.mark.parametrize("flags", FORMS)
-@pytest.mark.parametrize("name,N,H,V,tile,ignored", [
-    ("one_group", 300, 72, 520, 100, 0),
-    ("three_groups", 1200, 264, 328, 256, 0),
-    ("dense_rows_end_in_the_second_group", 1200, 72, 264, 256, 700),
-    ("no_dense_row", 600, 72, 264, 256, 600),
+@pytest.mark.parametrize("name,N,H,V,tile,ignored,groups", [
+    # groups: dW groups (of one tile rounded up to 256) with dense rows, of all
+    ("one_group", 200, 72, 520, 100, 0, (1, 1)),
+    ("two_groups", 300, 72, 520, 100, 0, (2, 2)),
+    ("three_groups", 700, 264, 328, 256, 0, (3, 3)),
+    ("five_groups", 1200, 264, 328, 256, 0, (5, 5)),
+    ("dense_rows_end_in_the_second_group", 1200, 72, 264, 256, 700, (2, 5)),
+    ("no_dense_row", 600, 72, 264, 256, 600, (0, 3)),
 ])
-def test_dw_forms(name, N, H, V, tile, ignored, flags):
+def test_dw_forms(name, N, H, V, tile, ignored, groups, flags):
+    chunks = G.ce_chunks(N, H, V, tile, flags | B.ALST_FLAG_TILE_SCRATCH, N - ignored)
+    assert groups == (len({c.group0 for c in chunks if c.first < N - ignored}), len({c.group0 for c in chunks}))
     wl = synth.custom(name, N, H, V, tile, ignore_frac=0.0, seed=62)
     h, W, y = synth.make_inputs(wl)
     y = y.copy()
