@@ -59,6 +59,14 @@ int main() {
                                 V, T, -100, 1.f, static_cast<float*>(fake(0x40000)), nullptr, nullptr,
                                 fake(0x60000), fake(0x70000), fake(0x50000), w - 1, f, nullptr);
                             EXPECT(rb == rc);
+                            alst_debug_ce_chunk_info i;
+                            EXPECT(alst_debug_ce_chunk(N, H, V, T, f, 0, 0, &i) == ALST_OK);
+                            const int64_t rows = i.rows;
+                            EXPECT(rows >= 1 && rows <= N && i.largest_grid < (1 << 24));
+                            for (int64_t dense : {(int64_t)1, rows / 2, rows}) {
+                                EXPECT(alst_debug_ce_chunk(N, H, V, T, f, 0, dense, &i) == ALST_OK);
+                                EXPECT(i.dhidden_blocks <= i.dhidden_grid && (i.ranges == 1 || i.added_up));
+                            }
                         }
                         const int rt = alst_tiled_ce_token_losses(fake(0x50000), w - 1, N, H, V, T, f,
                                                                   static_cast<float*>(fake(0x80000)), nullptr);
@@ -81,6 +89,10 @@ int main() {
                         const size_t wb = alst_tiled_mlp_workspace_bytes(N, H, I, T, 1, f);
                         EXPECT(wf > 0 && wb > wf);
                         calls += 2;
+                        for (int op = 0; op < 4; ++op) {
+                            const int64_t rows = alst_debug_chunk_rows(op, N, H, I, T);
+                            EXPECT(rows >= 256 && rows % 256 == 0);
+                        }
                         EXPECT(alst_tiled_mlp_forward(fake(0x10000), fake(0x20000), fake(0x30000),
                                                       fake(0x40000), N, H, I, T, fake(0x50000), fake(0x60000),
                                                       wf - 1, f, nullptr) == ALST_ERR_WORKSPACE);
