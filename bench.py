@@ -26,13 +26,13 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 MI355X_BF16_MFMA_PEAK_TFLOPS = 2500.0      # dense bf16, vendor figure
-# Memory-side bytes per launch (calibrated FETCH_SIZE + WRITE_SIZE) are not measurable from inside
+# Memory-side bytes per span of the per-kernel timer (calibrated FETCH_SIZE + WRITE_SIZE) are not measurable from inside
 # this script: they come from two `rocprofv3 --pmc` runs of this very command, whose summary is
 # committed under profiles/.  The line below repeats that file's figures for the headline workload
-# and says so in `traffic_source`; for any other workload or tile the field is null.  (A logits or
-# dHidden launch covers four tiles and counts as four launches: a fourth of its bytes each.)
+# and says so in `traffic_source`; for any other workload or tile the field is null.  A logits or
+# dHidden launch counts as one span per tile that it covers, here four with a fourth of its bytes each.
 TRAFFIC_PROFILE = "profiles/bench_llama8b_128k_hbm_traffic.txt"
-PROFILED_TRAFFIC_BYTES_PER_LAUNCH = {
+PROFILED_TRAFFIC_BYTES_PER_SPAN = {
     "llama8b_128k": {"logits_gemm": 6.858e9, "dhidden_gemm": 6.058e9, "dw_gemm": 25.770e9},
 }
 OTHER_STEPS, OTHER_WARMUP = 3, 1
@@ -166,14 +166,14 @@ class CeRun:
         tflops_useful = 6.0 * N * H * V / sec / 1e12
         tflops_exec = (8.0 if split else 6.0) * M * H * V / sec / 1e12
         # dominant kernel = the block GEMM kind with the largest summed time.  Over one step the
-        # launches of a kind together contract 2 M H V flop (each launch its tile's, or its group
-        # of tiles', valid rows), so the mean algorithmic flop per launch are 2 M H V * steps / launches.
+        # spans of a kind together contract 2 M H V flop, so the mean algorithmic flop per span are
+        # 2 M H V * steps / spans.
         gemm = {k: v for k, v in prof.items() if k.endswith("_gemm") and v[1] > 0}
         dom = max(gemm, key=lambda k: gemm[k][0])
         dom_ms, dom_n = gemm[dom]
-        flop_per_launch = (4.0 if split and dom == "logits_gemm" else 2.0) * M * H * V * prof_steps / dom_n
-        achieved = flop_per_launch / (dom_ms / dom_n * 1e-3) / 1e12
-        known = PROFILED_TRAFFIC_BYTES_PER_LAUNCH.get(wl.name, {}).get(dom)
+        flop_per_span = (4.0 if split and dom == "logits_gemm" else 2.0) * M * H * V * prof_steps / dom_n
+        achieved = flop_per_span / (dom_ms / dom_n * 1e-3) / 1e12
+        known = PROFILED_TRAFFIC_BYTES_PER_SPAN.get(wl.name, {}).get(dom)
         profiled = known is not None and self.tile == wl.tile and not split and self.flags == 0
         roofline = {"bound": "mfma", "kernel": dom, "achieved": achieved,
                     "peak": MI355X_BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -181,8 +181,8 @@ class CeRun:
                     "traffic": known if profiled else None,
                     "traffic_source": (TRAFFIC_PROFILE + " (rocprofv3 --pmc runs of this command; "
                                        "not measured in this run)") if profiled else None,
-                    "avg_launch_ms": dom_ms / dom_n, "launches": dom_n,
-                    "flop_per_launch": flop_per_launch,
+                    "span": "one launch" if dom == "dw_gemm" else "one tile (a launch covers several)",
+                    "spans": dom_n, "avg_span_ms": dom_ms / dom_n, "flop_per_span": flop_per_span,
                     "per_kind_ms_per_step": {k: v[0] / prof_steps for k, v in prof.items() if v[1]},
                     "per_kind_frac": {k: (4.0 if split and k == "logits_gemm" else 2.0) * M * H * V * prof_steps
                                       / (v[0] * 1e-3) / 1e12 / MI355X_BF16_MFMA_PEAK_TFLOPS
@@ -288,8 +288,8 @@ def bench_mlp(args, torch=None, B=None, synth=None, steps=None, warmup=None, wit
     gemm = {k: v for k, v in prof.items() if k in kind_flop and v[1] > 0}
     dom = max(gemm, key=lambda k: gemm[k][0])
     dom_ms, dom_n = gemm[dom]
-    flop_per_launch = kind_flop[dom] * steps / dom_n
-    achieved = flop_per_launch / (dom_ms / dom_n * 1e-3) / 1e12
+    flop_per_span = kind_flop[dom] * steps / dom_n
+    achieved = flop_per_span / (dom_ms / dom_n * 1e-3) / 1e12
     out = {
         "metric": "tokens/sec, tiled MLP fwd+bwd, H=%d I=%d" % (H, I),
         "value": N / (ms_per_step * 1e-3), "unit": "tokens/s", "n_gpus": 1, "steps": steps,
@@ -305,8 +305,8 @@ def bench_mlp(args, torch=None, B=None, synth=None, steps=None, warmup=None, wit
         "roofline": {"bound": "mfma", "kernel": dom, "achieved": achieved,
                      "peak": MI355X_BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MI355X_BF16_MFMA_PEAK_TFLOPS, "traffic": None,
-                     "avg_launch_ms": dom_ms / dom_n, "launches": dom_n,
-                     "flop_per_launch": flop_per_launch,
+                     "span": "one launch", "spans": dom_n, "avg_span_ms": dom_ms / dom_n,
+                     "flop_per_span": flop_per_span,
                      "per_kind_ms_per_step": {k: v[0] / steps for k, v in prof.items() if v[1]},
                      "per_kind_frac": {k: kind_flop[k] * steps / (v[0] * 1e-3) / 1e12
                                        / MI355X_BF16_MFMA_PEAK_TFLOPS for k, v in gemm.items()}},

@@ -16,15 +16,15 @@ extern "C" {
  * Benchmarking aid (no counterpart in the paper).  While enabled, every launch of a block GEMM and
  * each group of small kernels between them is bracketed by a pair of HIP events on the launch
  * stream.  alst_profile_read() waits for the recorded events, writes per kind the summed
- * milliseconds and the number of spans into the HOST arrays ms_total[8] and launches[8], and
- * forgets the spans.  A logits or dHidden launch may cover several of the caller's tiles; its span
- * counts as that many, so ms_total / launches is the time per tile.  Kinds: 0 logits GEMM, 1 dHidden GEMM, 2 dW GEMM, 3 the small kernels of a
- * cross-entropy tile; 4 the projection GEMMs of the tiled MLP (alst_mlp.h), 5 its weight-gradient
+ * milliseconds and the number of spans into the HOST arrays ms_total[8] and spans[8], and
+ * forgets the spans.  A logits or dHidden launch may cover several of the caller's tiles and counts as
+ * that many spans, so for these ms_total / spans is the time per tile.  Kinds: 0 logits GEMM, 1 dHidden
+ * GEMM, 2 dW GEMM, 3 the small kernels of a cross-entropy chunk; 4 the projection GEMMs of the tiled MLP (alst_mlp.h), 5 its weight-gradient
  * GEMMs, 6 its small kernels; 7 unused.  The recorded spans are process-wide state behind a lock:
  * calls from several host threads are safe, and their spans land in one list.
  */
 int alst_profile_enable(int on);
-int alst_profile_read(double* ms_total, int64_t* launches);
+int alst_profile_read(double* ms_total, int64_t* spans);
 
 /*
  * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched).  The block

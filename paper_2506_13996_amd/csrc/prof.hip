@@ -118,24 +118,24 @@ int alst_profile_enable(int on) {
     return ALST_OK;
 }
 
-int alst_profile_read(double* ms_total, int64_t* launches) {
-    if (!ms_total || !launches) return ALST_ERR_NULL;
-    for (int k = 0; k < PROF_KINDS; ++k) { ms_total[k] = 0.0; launches[k] = 0; }
+int alst_profile_read(double* ms_total, int64_t* spans) {
+    if (!ms_total || !spans) return ALST_ERR_NULL;
+    for (int k = 0; k < PROF_KINDS; ++k) { ms_total[k] = 0.0; spans[k] = 0; }
     int rc = ALST_OK;
-    std::vector<ProfSpan> spans;
+    std::vector<ProfSpan> done;
     {
         std::lock_guard<std::mutex> hold(g_prof_lock);
-        spans.swap(g_prof_spans);
+        done.swap(g_prof_spans);
     }
-    for (const ProfSpan& sp : spans) {              // waits for the GPU: outside the lock
+    for (const ProfSpan& sp : done) {              // waits for the GPU: outside the lock
         float ms = 0.f;
         if (hipEventSynchronize(sp.b) != hipSuccess ||
             hipEventElapsedTime(&ms, sp.a, sp.b) != hipSuccess) rc = ALST_ERR_HIP;
         ms_total[sp.kind] += ms;
-        launches[sp.kind] += sp.count;
+        spans[sp.kind] += sp.count;
     }
     std::lock_guard<std::mutex> hold(g_prof_lock);
-    for (const ProfSpan& sp : spans) {
+    for (const ProfSpan& sp : done) {
         g_prof_pool.push_back(sp.a);
         g_prof_pool.push_back(sp.b);
     }
