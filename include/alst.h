@@ -22,10 +22,9 @@
  *     passed as void* (NULL = the default stream).
  *   - Layout: dense row-major, no strides: hidden[N,H], W[V,H], dHidden[N,H], dW[V,H].
  *     bf16 = bfloat16 (upper half of an IEEE binary32).  H must be a multiple of 8 and every
- *     base pointer 16-byte aligned, else ALST_ERR_ALIGN.  Any V >= 1 is accepted.  The fastest
- *     kernels are used for every V and every H that is a multiple of 64 (neither has to be a
- *     multiple of the 256-wide blocks the kernels work in); with another H the logits run on a
- *     slower, bounds-checked kernel.
+ *     base pointer 16-byte aligned, else ALST_ERR_ALIGN.  Any V >= 1 is accepted.  The same
+ *     kernels serve every V and H (neither has to be a multiple of the 256-wide blocks or the
+ *     64-wide steps they work in).
  *   - Ownership: the caller owns every buffer, including `workspace`; the library allocates and
  *     frees no device memory and keeps no state between calls, so peak device memory is
  *     inputs + outputs + alst_tiled_ce_workspace_bytes().  Calls that share a workspace must be
@@ -41,9 +40,9 @@
  *     workspace, read with alst_last_device_status().  A row with an out-of-range label is
  *     treated as ignored, so nothing is read or written out of bounds.
  *   - Rows of ignored tokens are left out of all three contractions: the rows with a valid label
- *     are numbered densely in sequence order and the tiles are cut from that dense numbering
- *     (tile t = valid rows t*tile .. t*tile+tile-1, gathered into a dense matrix), so the executed
- *     work is 6 * M * H * V flop for M valid tokens, not 6 * N * H * V.
+ *     are numbered densely in sequence order and the launches work on chunks of that numbering
+ *     (as many consecutive valid rows as the workspace holds, gathered into a dense matrix), so the
+ *     executed work is 6 * M * H * V flop for M valid tokens, not 6 * N * H * V.
  *   - tile: any value >= 1; a tile larger than N is clamped; N need not be a multiple of tile.
  *     The tile size changes scheduling and memory only: the loss bits do not depend on it.
  */
@@ -109,8 +108,10 @@ int alst_version(void);
  *   4 * V * H           fp32 dW sums (absent for fp32 overwrite output, whose sums live in dW)
  *   2 * Vp * H          bf16 copy of W transposed, made once per call that computes gradients (the
  *                       dHidden product then reads both its operands along their rows)
- *   8 * (Vp / 128) * Tp   softmax partials of one tile
- * and with ALST_FLAG_FORWARD_ONLY only the last one and 2 * Tp * H remain.
+ *   8 * (Vp / 128) * Tp + 4 * (1 to 8) * Tp * H   per-row state and softmax partials of a chunk, then the
+ *                       partial products of its dHidden (the second term not with
+ *                       ALST_FLAG_FORWARD_ONLY)
+ * and with ALST_FLAG_FORWARD_ONLY only the last one's first term and 2 * Tp * H remain.
  */
 size_t alst_tiled_ce_workspace_bytes(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags);
 

@@ -47,7 +47,7 @@ size_t alst_tiled_mlp_workspace_bytes(int64_t N, int64_t H, int64_t I, int64_t t
                                       uint32_t flags);
 
 /*
- * y = (silu(x Wg^T) * (x Wu^T)) Wd^T, tile by tile (6 N H I flop).
+ * y = (silu(x Wg^T) * (x Wu^T)) Wd^T, in chunks of at most a tile's rows rounded up to 256 (6 N H I flop).
  *   x [N,H], Wg [I,H], Wu [I,H], Wd [H,I] bf16     inputs, not modified
  *   y [N,H] bf16                                   overwritten
  */
@@ -56,7 +56,8 @@ int alst_tiled_mlp_forward(const void* x, const void* Wg, const void* Wu, const 
                            void* workspace, size_t workspace_bytes, uint32_t flags, void* stream);
 
 /*
- * Gradients for upstream dy [N,H] bf16; each tile's g and u are recomputed (16 N H I flop).
+ * Gradients for upstream dy [N,H] bf16, in chunks of rows that the workspace of the tile holds; each
+ * chunk's g and u are recomputed (16 N H I flop).
  *   dx [N,H] bf16                        overwritten
  *   dWg, dWu [I,H], dWd [H,I]            bf16 (fp32 with ALST_FLAG_DW_FP32); overwritten, or += with
  *                                        ALST_FLAG_DW_ACCUMULATE

@@ -14,12 +14,15 @@
 //
 // An operand is either k-contiguous (a matrix [rows][k]) or k-major (a matrix [k][columns], the
 // block taking 256 of its columns).  Three combinations occur:
-//     D[r][c] = sum_k X[r][k] * Y[c][k]     both k-contiguous: logits, forward projections
-//     D[r][c] = sum_k X[r][k] * Y[k][c]     "mixed": a product with a weight matrix over its row
-//                                           index (dH = dZ W, da = dy Wd, dx = dg Wg + du Wu)
+//     D[r][c] = sum_k X[r][k] * Y[c][k]     both k-contiguous: logits, forward projections, and the products
+//                                           with a weight matrix over its row index (dH = dZ W, da = dy Wd,
+//                                           dx = dg Wg + du Wu, dx = dy W) against a copy of the weight
+//                                           transposed once per call (transpose_bf16_kernel)
+//     D[r][c] = sum_k X[r][k] * Y[k][c]     "mixed": those products of the MLP and the linear layer with the
+//                                           weight as it is, where an extent is not whole k-steps
 //     D[r][c] = sum_k X[k][r] * Y[k][c]     both k-major: the weight-gradient products, whose k is
 //                                           the token row
-// so that every operand is read from memory as it is and nothing is ever transposed.
+// Activations and what is made of them are read as they lie; only weights are ever transposed.
 //
 // Three cores with the same accumulator interface, one per layout: DirectCore, MixedCore, KMajorCore.
 // 4 wavefronts (one per SIMD), 128 x 128 per wavefront, operands DMA'd straight from global memory
@@ -535,14 +538,13 @@ struct KMajorDirectT {
     }
 };
 typedef KMajorDirectT<true> KMajorCore;
-// 256 r x 128 c, see HalfCore (ce 512 x 256 x 4096: 124 -> 116 us; mlp 512 x 256 x 768: 126 -> 117 us; mlp
-// 256000 x 4096 x 14336: 245.9 -> 245.0 ms).
+// 256 r x 128 c, see HalfCore (ce 512 x 256 x 4096: 124 -> 116 us; mlp 512 x 256 x 768: 126 -> 117 us; no
+// difference beyond the spread in calls of many rounds).
 typedef KMajorDirectT<true, 2> KMajorHalfCore;
 typedef KMajorDirectT<false> MixedCore;
 
 // ---------------------------------------------------------------------------------------------
-// DirectCore: 4 wavefronts, global -> LDS DMA, aligned shapes only, both operands k-contiguous,
-// v_mfma_f32_16x16x32_bf16
+// DirectCore: 4 wavefronts, global -> LDS DMA, both operands k-contiguous, v_mfma_f32_16x16x32_bf16
 // ---------------------------------------------------------------------------------------------
 // Against the same pipeline on the 32 x 32 x 16 form a plain product of the logits shape is 8 %
 // faster (16-row operand reads, half the address arithmetic per k-step; with register-resident
@@ -970,7 +972,7 @@ static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transp
 // Epilogues shared by the kernels built on the cores (written against the cores' layout traits)
 // ---------------------------------------------------------------------------------------------
 constexpr int kTurnPitch = 272;     // bytes per row of the LDS turn-around area: 256 + 16 of padding
-// LDS of a kernel whose workgroups run chains of blocks on DirectCore (gemm_chain): the epilogue's
+// LDS of a kernel whose workgroups run chains of blocks (DirectCore::Pipe): the epilogue's
 // turn-around area (4 wavefronts x 16 rows) lies behind the stages and the warm-up landing area,
 // which belong to the next block's DMA while the epilogue runs.
 constexpr int kChainTurnOffset = kLdsBytes;

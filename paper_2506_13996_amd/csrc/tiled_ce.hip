@@ -1,6 +1,6 @@
 // Sequence-tiled LM-head projection + cross-entropy for gfx950: kernels and the C ABI (alst.h).
 //
-// Per sequence tile of T rows (paper, section "Sequence Tiling for Reducing Activation Memory
+// Per shard of the sequence (paper, section "Sequence Tiling for Reducing Activation Memory
 // Footprint": forward and backward of each logits shard are done together and the shard's
 // intermediates are dropped before the next shard):
 //
@@ -28,14 +28,14 @@
 //                        conditional launch of 1. and 2. whose workgroups leave at once when no
 //                        row of the chunk asked for it.
 //   3. dhidden_kernel    dH_i = (g/M) (1/S_i) e'_i W   (contraction over V), rows scattered back
-//   4. dw_kernel         acc += (H_c / S)^T e'         once per group of tiles (contraction over
+//   4. dw_kernel         acc += (H_c / S)^T e'         once per group of rows (contraction over
 //                        the group's dense rows, fp32)
 //
-// After the last tile: loss = sum(per-row loss) / M in a fixed order.  The last group's dw_kernel writes
+// After the last chunk: loss = sum(per-row loss) / M in a fixed order.  The last group's dw_kernel writes
 // dW = (g/M) acc.
 // The contractions share the block GEMM of gemm_tile.h: logits and dHidden with both operands
 // k-contiguous (dHidden against a copy of W transposed once per call), dW with both operands
-// k-major (the group's dense hidden rows and dZ rows as they are).  No per-tile array is
+// k-major (the group's dense hidden rows and dZ rows as they are).  No array of rows is
 // transposed.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -72,11 +72,10 @@ struct ChunkInfo {
     int pad[3];
 };
 
-// dW is accumulated into the fp32 [V, H] sums once per GROUP of consecutive tiles: the dense
-// hidden rows and dZ rows of the group's tiles are kept one behind the other and one dW GEMM
-// contracts over all of them, so the read-modify-write of the 4*V*H-byte accumulator and the
-// GEMM's epilogue are paid once per group instead of once per tile.  The group spans about
-// kDwGroupRows rows.
+// dW is accumulated into the fp32 [V, H] sums once per GROUP of consecutive dense rows, as many as
+// some number of tiles has (about kDwGroupRows): the hidden rows and dZ rows of the group's chunks are
+// kept one behind the other and one dW GEMM contracts over all of them, so the read-modify-write of
+// the 4*V*H-byte accumulator and the GEMM's epilogue are paid once per group instead of once per chunk.
 constexpr int kDwGroupRows = 16384;
 constexpr int kDwGroupMax = 8;
 // ALST_FLAG_TILE_SCRATCH (and the forward-only layout, which keeps no dZ at all): groups of one tile.
@@ -412,8 +411,7 @@ __device__ __forceinline__ float from_ordered_int(int k) {
 
 // Workgroup b < Rc: dense row b of the chunk that starts at dense row `first`.  Copies the hidden
 // row of its token into the dense matrix Hc (the chunk's rows; row pitch Hk = H rounded up to whole
-// k-steps, zeros behind the H elements: the logits GEMM contracts over Hk) and its label into yc;
-// rows Tc <= b < Trc are zero padding.  Also sets the row's softmax reference for the first logits
+// k-steps, zeros behind the H elements) and its label into yc; rows Tc <= b < Trc are zero padding.  Also sets the row's softmax reference for the first logits
 // pass (0; backward from a saved lse: that lse, so that e is the probability itself) and marks the
 // row as taking part in that pass.  Workgroup 0 leaves the chunk's counts and its dHidden ranges.
 // Workgroups from Rc on (first chunk, if a gradient is wanted) take kZeroRows rows of the sequence at a
@@ -1176,16 +1174,14 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     }
     ALST_HIP(hipGetLastError());
 
-    // The GEMM cores without bounds checks serve every shape.  The row extent of a chunk is always
-    // block-aligned (dense rows are zero padded to a multiple of the block height).
-    // (a vocabulary that ends inside a column block: the logits kernel reads the last row of W
-    // in place of the missing ones and masks those columns; a hidden size that is not whole
-    // k-steps: the chunks of W's rows and of the dense hidden rows beyond H are zeros)
+    // The row extent of a chunk is always block-aligned (dense rows are zero padded to a multiple of the
+    // block height).  A vocabulary that ends inside a column block: the logits kernel reads the last
+    // row of W in place of the missing ones and masks those columns; a hidden size that is not whole
+    // k-steps: what W's rows and the dense hidden rows have beyond H in the last one is read as zeros.
     const bool ktail_logits = (H % kBlockK) != 0;
-    // (a hidden size that ends inside a block is handled by the unguarded dHidden and dW kernels:
-    // the missing rows of W transposed / columns of the dense hidden rows are read from the last
-    // ones and the results discarded; a vocabulary that is not whole k-steps: dZ and W transposed
-    // are zero up to whole k-steps)
+    // A hidden size that ends inside a block: dHidden and dW read the last rows of W transposed / columns
+    // of the dense hidden rows in place of the missing ones and discard the results; a vocabulary that
+    // is not whole k-steps: dZ and W transposed are zero up to whole k-steps.
     if (do_bwd) {
         ProfScope small_(PROF_OTHER, s);
         const Transposes ts = {{{P.W, V, H, H, wt, Vp}}};

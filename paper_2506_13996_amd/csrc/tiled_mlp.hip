@@ -3,7 +3,7 @@
 //
 // Paper, subsection "TiledMLP": forward and backward of the MLP are run on tiles of the sequence,
 // the [tile, intermediate] activations exist only for the tile in flight and backward recomputes
-// them.  Per tile of T rows, all contractions on the block GEMM of gemm_tile.h (operands with the
+// them.  Per chunk of rows (below), all contractions on the block GEMM of gemm_tile.h (operands with the
 // contraction index contiguous):
 //
 //   forward    a  = silu(x Wg^T) * (x Wu^T)   gated_kernel: both products in one block, SwiGLU in
@@ -11,11 +11,12 @@
 //              y  = a Wd^T
 //   backward   da = dy Wd                     against Wd^T, transposed once per call
 //              a, [dg | du]                   gated_kernel again (g and u recomputed), its epilogue
-//                                             reads da; written into the rows of the tile's group
+//                                             reads da; written into the rows of the chunk's group
 //              dx = dg Wg + du Wu             one contraction over the 2 I columns of [dg | du]
 //                                             against [Wg | Wu]^T, transposed once per call
 //                                             (H or I not a multiple of 64: the weights as they are,
-//                                             k-major operands, dx as two contractions over I)
+//                                             k-major operands on MixedCore, which has no halves for a
+//                                             short last round; dx as two contractions over I)
 //   per group  dWg += dg^T x, dWu += du^T x, dWd += dy^T a   (fp32, contraction over the group's rows)
 //
 // The launches work on CHUNKS of consecutive rows whose length is chosen for the hardware
@@ -857,8 +858,6 @@ static int run_lin_backward(const LinProblem& P) {
     const bool in_out = f32 && !accum;
     float* acc = in_out ? reinterpret_cast<float*>(P.dW) : reinterpret_cast<float*>(P.ws + L.acc);
     const int K = (int)P.K, M = (int)P.M;
-    const int64_t T = P.tile < P.N ? P.tile : P.N;
-    const int64_t ntiles = (P.N + T - 1) / T;
     uint16_t* wt = reinterpret_cast<uint16_t*>(P.ws + L.wt);
     if (L.weight_t) {
         ProfScope ps(PROF_MLP_OTHER, s);

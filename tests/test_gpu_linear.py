@@ -43,8 +43,7 @@ CASES = [
     ("ragged", 700, 136, 200, 300),
     ("tile_gt_n", 130, 64, 72, 4096),
     ("wide_output", 512, 256, 4096, 512),       # an LM-head-like projection
-    # block-aligned K and M, rows not a whole number of k-steps: dW = whole k-steps on the
-    # unguarded core + the 12 rows left over on the guarded one
+    # block-aligned K and M, rows not a whole number of k-steps: dW's last k-step has 12 rows
     ("aligned_ragged_rows", 1100, 256, 512, 512),
     ("aligned_few_rows", 40, 256, 256, 64),
     # 4 x 97 output blocks on 256 persistent workgroups: chains of two blocks (the second fetched
@@ -86,7 +85,7 @@ def test_linear_flags_and_workspace_contract():
 
 
 def test_linear_random_shapes_against_oracle():
-    """A seeded sweep of odd and block-aligned shapes (guarded and unguarded kernels, ragged tiles,
+    """A seeded sweep of odd and block-aligned shapes (ragged extents of every kind, ragged tiles,
     row counts that are not whole k-steps)."""
     g = np.random.default_rng(78)
     for case in range(10):

@@ -43,12 +43,12 @@ CASES = [
     ("ragged", 700, 136, 200, 300),               # H % 64 != 0, I % 256 != 0, ragged tiles
     ("tile_gt_n", 200, 64, 96, 4096),
     ("one_row_tiles", 5, 64, 64, 1),
-    # block-aligned H and I, a row count that is not a whole number of k-steps: the weight
-    # gradients take the whole k-steps on the unguarded core and the 12 rows left over on the other
+    # block-aligned H and I, a row count that is not a whole number of k-steps: the last k-step of the
+    # weight gradients has 12 rows
     ("aligned_ragged_rows", 1100, 256, 512, 512),
     ("aligned_few_rows", 40, 256, 256, 64),       # fewer rows than one k-step
     # whole blocks of rows and whole k-steps of H, but I ends inside a block's 128 columns (and is
-    # not whole k-steps): gate/up on the unguarded core with the column guard in its epilogue
+    # not whole k-steps): the column guard in the gate/up epilogue
     ("intermediate_ends_inside_a_block", 768, 256, 328, 256),
     ("intermediate_192", 512, 128, 192, 256),     # I a multiple of 64: the transposed-weight products too
 ]
@@ -213,8 +213,8 @@ def test_mlp_hip_graph_replays_match_eager():
 
 
 def test_mlp_random_shapes_against_oracle():
-    """A seeded sweep of odd and block-aligned shapes: every combination of guarded and unguarded
-    kernels, ragged tiles and row counts that are not whole k-steps."""
+    """A seeded sweep of odd and block-aligned shapes: chains of blocks and single ones, weights
+    transposed and as they are, ragged tiles and row counts that are not whole k-steps."""
     g = np.random.default_rng(77)
     for case in range(10):
         N = int(g.integers(1, 800))

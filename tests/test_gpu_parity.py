@@ -50,7 +50,7 @@ def _check(r, f, dH, dW, tag="", valid=None):
 CASES = [
     # name, N, H, V, tile, ignore_frac
     ("tiny", 512, 256, 4096, 128, 0.05),            # the Tiny workload itself
-    ("aligned", 1024, 256, 1024, 512, 0.05),        # every extent block-aligned: unguarded kernels
+    ("aligned", 1024, 256, 1024, 512, 0.05),        # every extent block-aligned
     ("aligned_3tiles_ragged_last", 1280, 512, 768, 512, 0.1),
     ("ragged", 700, 136, 1000, 300, 0.1),           # H % 64 != 0, V % 256 != 0, ragged tiles
     ("tile_gt_n", 200, 64, 300, 4096, 0.0),
@@ -62,14 +62,13 @@ CASES = [
     # a full tile of 64 output blocks is cut into 4 ranges, the last tile (2 row blocks) into 8: the
     # number of ranges is chosen per tile on the device
     ("split_v_last_tile_differs", 8500, 512, 33280, 8192, 0.0),
-    # block-aligned H, a vocabulary that ends inside a column block: unguarded logits and dW kernels
-    # (the missing rows of W are masked); dHidden unguarded too, a vocabulary that is not whole
-    # k-steps taking the kernel variant that clamps the last k-step's rows of W
+    # block-aligned H, a vocabulary that ends inside a column block (the columns of the missing rows of W
+    # are masked), and inside a k-step of dHidden (zeros there)
     ("ragged_v_whole_ksteps", 600, 256, 1088, 256, 0.1),
     ("ragged_v", 600, 256, 1000, 256, 0.1),
     ("ragged_v_below_one_block", 300, 256, 72, 128, 0.1),
     # hidden sizes that are not whole k-steps of 64 (below one step, just above one, odd multiples
-    # of 8): the dense hidden rows are zero padded, W's rows are read clamped in the last k-step
+    # of 8): what both operands of the logits lack in the last k-step is read as zeros
     ("h_below_one_kstep", 300, 8, 500, 128, 0.1),
     ("h_72", 520, 72, 700, 256, 0.1),
     ("h_1000", 300, 1000, 520, 256, 0.1),
@@ -359,9 +358,8 @@ def test_random_shapes_against_oracle():
 
 
 def test_random_shapes_with_block_aligned_hidden_size():
-    """The same sweep with H a multiple of the block width, so that the unguarded kernels meet
-    vocabularies, row counts and tiles of every alignment (V a multiple of 64 in half the cases,
-    which also takes dHidden off the guarded core)."""
+    """The same sweep with H a multiple of the block width, so that whole blocks of it meet
+    vocabularies, row counts and tiles of every alignment (V a multiple of 64 in half the cases)."""
     g = np.random.default_rng(2025)
     for case in range(10):
         N = int(g.integers(1, 1200))
