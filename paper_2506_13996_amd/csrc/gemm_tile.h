@@ -64,12 +64,16 @@ static __device__ __align__(16) uint32_t zero_chunk[4];
 
 // XCD-aware block numbering.  Workgroups are dealt round-robin to the 8 XCDs (each with its own L2);
 // the 32 workgroups that are resident together on one XCD get a run of 32 consecutive blocks of an
-// order that walks the output in PR x PC patches (patches down the rows first, a patch's rows
-// fastest), so that they share operand tiles through that L2.  The order has no holes: an output
-// that is not whole patches has narrower ones at its edges, a run may straddle two, and a launch
-// of several products ("parts") numbers their blocks through.  The blocks that do not fill a round
-// of 256 are spread evenly over the XCDs.  (Numbering padded patches instead, patch P on XCD P % 8, left
-// an XCD with a second patch while others had none: 9 patches took the time of 16.)
+// order that walks the output in columns PC blocks wide, so that a run is a patch of PR x PC blocks that
+// share operand tiles through that L2.  The order has no holes: a last column may be narrower, a launch
+// of several products ("parts") numbers their blocks through, and the blocks that do not fill a round of
+// 256 are spread evenly over the XCDs.  (Numbering padded patches instead, patch P on XCD P % 8, left an
+// XCD with a second patch while others had none: 9 patches took the time of 16.)
+// Inside a column the blocks go by patches, a patch's rows fastest, if its rows are whole patches, else
+// row by row: a run is whole rows either way.  By patches alone a run was parts of two patches behind the
+// first partial one, whose sharers do not cover each other's warm-up lines (63 instead of 64 row blocks:
+// cross-entropy step 16384 x 5120 x 200064, 3 % ignored, 81.2 -> 76.9 ms, 16384 x 2560 x 128256 27.0 -> 25.2);
+// row by row alone dW of 16 row blocks takes 1 % longer.
 constexpr int kXcds = 8, kPerXcd = 32, kRound = kXcds * kPerXcd;
 struct PatchGrid {
     int tiles_r, tiles_c;      // output blocks of one part
@@ -141,13 +145,14 @@ __host__ __device__ __forceinline__ int64_t rounds16(int64_t blocks, bool halves
 
 // Block (tr, tc) of number i < g.blocks() in the order.
 __host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, int& tr, int& tc) {
-    const int column = i / (g.tiles_r * g.PC);               // column of patches
+    const int column = i / (g.tiles_r * g.PC);
     i -= column * g.tiles_r * g.PC;
     const int c0 = column * g.PC, cols = g.tiles_c - c0 < g.PC ? g.tiles_c - c0 : g.PC;
-    const int r0 = i / (g.PR * cols) * g.PR, rows = g.tiles_r - r0 < g.PR ? g.tiles_r - r0 : g.PR;
+    const int rows = g.tiles_r % g.PR == 0 ? g.PR : 1;       // rows at a time
+    const int r0 = i / (rows * cols) * rows;
     i -= r0 * cols;
-    tr = r0 + i % rows;
-    tc = c0 + i / rows;
+    tr = r0 + (i & (rows - 1));
+    tc = c0 + (rows == 1 ? i : i / rows);
 }
 
 // Gated pair of Y operands: with Y2 given, the 256 Y rows of the block at c0 are four runs of 64
