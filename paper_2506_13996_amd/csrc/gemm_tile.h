@@ -109,9 +109,14 @@ __host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
     const int left = total - round * kRound;
     if (left >= kRound) return round * kRound + xcd * kPerXcd + slot;
     if (left <= 0) return -1;
-    const int per = left / kXcds, more = left % kXcds;       // the first `more` XCDs have per + 1
-    if (slot >= per + (xcd < more ? 1 : 0)) return -1;
-    return round * kRound + xcd * per + (xcd < more ? xcd : more) + slot;
+    // Half a round and more in units of 8, the row of a patch, whose sharers stay together; fewer one by one.
+    // (One by one, 248 blocks were 31 an XCD, parts of rows at both ends: cross-entropy step 16384 x 5120 x
+    // 128256, 3 % ignored, 49.3 -> 47.8 ms.)  The first `more` XCDs have a unit more.
+    const int unit = 2 * left >= kRound ? 8 : 1, units = (left + unit - 1) / unit;
+    const int per = units / kXcds, more = units % kXcds;
+    if (slot >= (per + (xcd < more ? 1 : 0)) * unit) return -1;
+    const int number = (xcd * per + (xcd < more ? xcd : more)) * unit + slot;
+    return number < left ? round * kRound + number : -1;
 }
 
 // The last round, if it fills no more than half of the compute units, is worked on in halves: two

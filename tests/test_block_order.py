@@ -32,3 +32,21 @@ def test_runs_are_patches(tiles_r, tiles_c):
     for r in full:
         if r not in wide:                    # the sharers of a tile are all there: rows x columns
             assert len({tr for tr, _ in r}) * len({tc for _, tc in r}) == 32
+
+
+@pytest.mark.parametrize("tiles_r,tiles_c", [(63, 16), (62, 24), (61, 16), (31, 8), (17, 8)])
+def test_a_last_round_is_dealt_in_whole_rows(tiles_r, tiles_c):
+    """Half a round and more: an XCD gets whole rows of a patch (8 blocks), so that their sharers stay
+    together, and the XCDs differ by one row at most."""
+    left = tiles_r * tiles_c % 256
+    assert left >= 128
+    n = B.alst_debug_block_tile(tiles_r, tiles_c, 1, 0)[0]
+    per_xcd = [[] for _ in range(8)]
+    for bid in range(n - 256, n):
+        _, part, tr, tc = B.alst_debug_block_tile(tiles_r, tiles_c, 1, bid)
+        if part >= 0:
+            per_xcd[bid % 8].append((tr, tc // 8))
+    assert sum(map(len, per_xcd)) == left
+    assert max(map(len, per_xcd)) - min(map(len, per_xcd)) <= 8
+    for blocks in per_xcd:
+        assert all(blocks.count(row) == 8 for row in set(blocks))
