@@ -97,6 +97,7 @@ struct Layout {
     int g;                 // the caller's tiles per dW group
     int64_t Kg;            // dense rows the group's buffers hold: g * Tp
     int64_t Rc;            // most dense rows per chunk of launches, a multiple of 256
+    int64_t step;          // dense rows of a chunk behind which more than Rc follow
     int dh_PR, dh_PC;      // dHidden: patch shape of the block -> tile mapping
     size_t part_bytes;     //          room for fp32 partial products at `part`
     size_t header, cinfo, loss_rows, lse, idx, block_cnt, block_ofs, zlabel, yc, ref, frow, rowstate,
@@ -168,6 +169,11 @@ static int64_t workspace_ranges(int64_t rows, int64_t H, int64_t V) {
     return ranges;
 }
 
+// From about here on (k-steps: 1536) calls gain by chunks of one round of dHidden: at 128256 words and more up to
+// 1.7 % for H = 2048 to 8192 and none loses (131072 x 4096 276.0 -> 274.8 ms, 32768 x 5120 x 152064 82.0 -> 80.8,
+// 32768 x 8192 x 128256 150.9 -> 148.4), at 65536 words between level and 1.6 % slower (H = 1024 to 7168).
+constexpr int64_t kLongVocabulary = 98304;
+
 static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags) {
     Layout L;
     const int64_t T = tile < N ? tile : N;
@@ -204,6 +210,15 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     const int64_t grid = std::min(kGridBlocks - kZeroBlocksMax, kGridBlocks / cols * kBlockR) / kBlockR * kBlockR;
     const int64_t most = std::min(fit, grid), parts = (Kn + most - 1) / most;
     L.Rc = ((Kn + parts - 1) / parts + kBlockR - 1) / kBlockR * kBlockR;     // <= most, a multiple of 256
+    // A long vocabulary makes dHidden's blocks long, and over several rounds of them in one launch the
+    // workgroups of an XCD no longer walk k together: chunks of about one round then, and not less than
+    // 4096 rows (a last one up to a quarter longer: each chunk reads W again).
+    L.step = L.Rc;
+    const int64_t round_rows = std::max<int64_t>(4096, kRound * (int64_t)kBlockR * kBlockC / H / 4096 * 4096);
+    if (!fwd_only && V >= kLongVocabulary && L.Rc > round_rows + round_rows / 4) {
+        L.step = round_rows;
+        L.Rc = round_rows + round_rows / 4;
+    }
     L.zlabel = at;
     L.yc = L.zlabel + (size_t)L.Rc * 4;
     L.ref = L.yc + (size_t)L.Rc * 4;
@@ -218,7 +233,7 @@ static Layout make_layout(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_
     // W transposed, [H, Vp], zeros from V to whole k-steps: the second operand of dH = dZ W, k-contiguous
     L.wt = take(fwd_only ? 0 : (size_t)H * L.Vp * 2);
     {
-        const PatchGrid pg = choose_patches((int)(L.Rc / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
+        const PatchGrid pg = choose_patches((int)(L.step / kBlockR), (int)((H + kBlockC - 1) / kBlockC));
         L.dh_PR = pg.PR; L.dh_PC = pg.PC;
         L.part_bytes = at + region - L.part;
     }
@@ -1015,7 +1030,8 @@ static ChunkPlan chunk_plan(const Layout& L, int64_t N, int64_t H, int64_t V, in
     ChunkPlan c = {};
     c.group0 = first / L.Kg * L.Kg;
     c.at = first - c.group0;
-    c.rows = std::min(std::min(L.Rc, L.Kg - c.at), N - first);
+    const int64_t left = std::min(L.Kg - c.at, N - first);
+    c.rows = left <= L.Rc ? left : L.step;
     c.Tr = (int)((c.rows + kBlockR - 1) / kBlockR * kBlockR);
     c.group_done = c.at + c.rows == L.Kg || first + c.rows == N;
     if (!do_bwd) return c;

@@ -51,6 +51,25 @@ def test_random_shapes():
             _check(N, H, V, tile, flags, 1, rng.randint(0, second.rows))
 
 
+@pytest.mark.parametrize("N,H,V,tile,rows", [
+    (131072, 4096, 128256, 4096, 4096), (131072, 1024, 200064, 4096, 16384), (131072, 4096, 65536, 4096, 16384),
+    (20000, 8192, 128256, 2048, 4096), (20000, 2048, 128256, 8192, 8192), (12000, 4096, 98304, 300, 4096),
+    (5000, 4096, 128256, 2048, 5000), (9300, 4096, 128256, 2048, 4096),
+])
+def test_chunks_of_a_long_vocabulary(N, H, V, tile, rows):
+    """About one round of dHidden's 256 x 256 blocks; a last chunk up to a quarter longer."""
+    at, k, lengths = 0, 0, []
+    while at < N:
+        i = _check(N, H, V, tile, 0, k, 0)
+        assert i.first == at and i.group0 <= at
+        _check(N, H, V, tile, 0, k, i.rows)
+        lengths.append((i.group0, i.rows))
+        at, k = at + i.rows, k + 1
+    assert at == N and lengths[0][1] == rows
+    for (group, n), (after, _) in zip(lengths, lengths[1:] + [(-1, 0)]):
+        assert n == rows if group == after else n <= rows + rows // 4      # (a group's last chunk)
+
+
 def test_bad_arguments_are_rejected():
     for a in [(0, 8, 8, 1, 0, 0, 0), (10, 8, 8, 1, 0, 5, 0), (10, 8, 8, 1, 0, 0, 11), (10, 8, 8, 1, 0, -1, 0),
               (10, 8, 8, 1, B.ALST_FLAG_FORWARD_ONLY, 0, 0), (10, 8, 8, 1, 1 << 20, 0, 0)]:
