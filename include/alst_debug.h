@@ -33,7 +33,8 @@ int alst_profile_read(double* ms_total, int64_t* spans);
  * products ("parts") whose blocks are numbered through.  For a launch of `parts` products of
  * tiles_r x tiles_c blocks this returns the number of workgroups and writes, for workgroup `bid`,
  * the part and block it computes (part = -1: the workgroup leaves at once), evaluated with the
- * same functions the kernels use (for a launch of whole blocks; a last round of at most 128 blocks is
+ * same functions the kernels use (one part: in the order for a long contraction, several: in
+ * that for weight gradients; for a launch of whole blocks; a last round of at most 128 blocks is
  * dealt out as twice as many halves).  A negative return value is minus an alst_status.
  */
 int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* part, int* tr, int* tc);

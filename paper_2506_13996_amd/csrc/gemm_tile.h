@@ -69,11 +69,7 @@ static __device__ __align__(16) uint32_t zero_chunk[4];
 // of several products ("parts") numbers their blocks through, and the blocks that do not fill a round of
 // 256 are spread evenly over the XCDs.  (Numbering padded patches instead, patch P on XCD P % 8, left an
 // XCD with a second patch while others had none: 9 patches took the time of 16.)
-// Inside a column the blocks go by patches, a patch's rows fastest, if its rows are whole patches, else
-// row by row: a run is whole rows either way.  By patches alone a run was parts of two patches behind the
-// first partial one, whose sharers do not cover each other's warm-up lines (63 instead of 64 row blocks:
-// cross-entropy step 16384 x 5120 x 200064, 3 % ignored, 81.2 -> 76.9 ms, 16384 x 2560 x 128256 27.0 -> 25.2);
-// row by row alone dW of 16 row blocks takes 1 % longer.
+// Inside a column the blocks go by patches, a patch's rows fastest, or row by row (by_rows).
 constexpr int kXcds = 8, kPerXcd = 32, kRound = kXcds * kPerXcd;
 struct PatchGrid {
     int tiles_r, tiles_c;      // output blocks of one part
@@ -103,17 +99,29 @@ inline PatchGrid choose_patches(int tiles_r, int tiles_c) {
 constexpr int64_t kGridBlocks = ((int64_t)1 << 24) - kRound;
 inline int grid_for_blocks(int64_t blocks) { return (int)((blocks + kRound - 1) / kRound * kRound); }
 
+// Row by row: for a long contraction over rows that are not whole patches.  By patches a run there is parts of two
+// behind the first partial one, whose sharers do not cover each other's warm-up lines; row by row it is
+// whole rows (63 instead of 64 row blocks: cross-entropy step 16384 x 5120 x 200064, 3 % ignored, 81.2 ->
+// 76.9 ms, 16384 x 2560 x 128256 27.0 -> 25.2).  By patches are faster: rows of whole patches (dW of 16 row blocks
+// 1 %), short contractions (MLP 192512 x 512 x 1536: 3 % of its projections), and the weight gradients,
+// which do without the warm-up (12288 x 2304 x 2816: 3 %).
+__host__ __device__ __forceinline__ bool by_rows(const PatchGrid& g, int K) {
+    return K >= 1024 && g.tiles_r % g.PR != 0;
+}
+
 // Workgroup -> number of its block among the launch's `total`, or -1.
-__host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total) {
+__host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total, bool rows) {
     const int round = bid / kRound, xcd = bid % kXcds, slot = (bid / kXcds) % kPerXcd;
     const int left = total - round * kRound;
     if (left >= kRound) return round * kRound + xcd * kPerXcd + slot;
     if (left <= 0) return -1;
-    // Half a round and more in units of 8, the row of a patch, whose sharers stay together; fewer one by one.
-    // (One by one, 248 blocks were 31 an XCD, parts of rows at both ends: cross-entropy step 16384 x 5120 x
-    // 128256, 3 % ignored, 49.3 -> 47.8 ms.)  The first `more` XCDs have a unit more.
-    const int unit = 2 * left >= kRound ? 8 : 1, units = (left + unit - 1) / unit;
-    const int per = units / kXcds, more = units % kXcds;
+    // The last round is spread evenly, one by one: the first `more` XCDs have one more.  Row by row, half
+    // a round and more is dealt in units of 8, the row of a patch, whose sharers then stay together, if the fullest XCD gets no more
+    // than a tenth above the mean (one by one, 236 blocks were parts of rows at both ends of every XCD's share:
+    // cross-entropy step 16384 x 5120 x 128256, 3 % ignored, 49.3 -> 47.8 ms; but 207 blocks of a weight
+    // gradient as 32 and 24 an XCD instead of 26: 283 -> 316 us).
+    const int units8 = (left + 7) / 8, unit = rows && 2 * left >= kRound && (units8 + 7) / 8 * 640 <= left * 11 ? 8 : 1;
+    const int units = unit == 8 ? units8 : left, per = units / kXcds, more = units % kXcds;
     if (slot >= (per + (xcd < more ? 1 : 0)) * unit) return -1;
     const int number = (xcd * per + (xcd < more ? xcd : more)) * unit + slot;
     return number < left ? round * kRound + number : -1;
@@ -149,15 +157,19 @@ __host__ __device__ __forceinline__ int64_t rounds16(int64_t blocks, bool halves
 }
 
 // Block (tr, tc) of number i < g.blocks() in the order.
-__host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, int& tr, int& tc) {
+__host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, bool rows, int& tr, int& tc) {
     const int column = i / (g.tiles_r * g.PC);
     i -= column * g.tiles_r * g.PC;
     const int c0 = column * g.PC, cols = g.tiles_c - c0 < g.PC ? g.tiles_c - c0 : g.PC;
-    const int rows = g.tiles_r % g.PR == 0 ? g.PR : 1;       // rows at a time
-    const int r0 = i / (rows * cols) * rows;
+    if (rows) {
+        tr = i / cols;
+        tc = c0 + i - tr * cols;
+        return;
+    }
+    const int r0 = i / (g.PR * cols) * g.PR, in = g.tiles_r - r0 < g.PR ? g.tiles_r - r0 : g.PR;
     i -= r0 * cols;
-    tr = r0 + (i & (rows - 1));
-    tc = c0 + (rows == 1 ? i : i / rows);
+    tr = r0 + i % in;
+    tc = c0 + i / in;
 }
 
 // Gated pair of Y operands: with Y2 given, the 256 Y rows of the block at c0 are four runs of 64

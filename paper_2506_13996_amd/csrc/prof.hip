@@ -153,10 +153,11 @@ int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* par
     const int64_t total = (int64_t)tiles_r * tiles_c * parts;
     if (total > 0x7fffff00) return -ALST_ERR_SHAPE;
     *part = -1; *tr = 0; *tc = 0;
-    const int i = block_of_workgroup(bid, (int)total);
+    const bool rows = parts == 1 && by_rows(g, 1 << 16);
+    const int i = block_of_workgroup(bid, (int)total, rows);
     if (i >= 0) {
         *part = i / g.blocks();
-        block_at(g, i % g.blocks(), *tr, *tc);
+        block_at(g, i % g.blocks(), rows, *tr, *tc);
     }
     return grid_for_blocks(total);
 }

@@ -114,7 +114,7 @@ static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; 
 // written and read back at about 5 TB/s: 0.07 units) and the launch that adds them.  A range keeps
 // at least 8 k-steps.
 // The chunk's row count is known on the device only, so gather_rows_kernel makes the choice; the
-// host evaluates the same function for every possible row count to size the launch.
+// host evaluates the same function for every row count that can be cut (dhidden_most_blocks).
 constexpr int kComputeUnits = 256;
 // (from 16 rounds of workgroups on the chip is filled to 16/17 or better as it is)
 constexpr int64_t kCutBlocks = 16 * kComputeUnits;
@@ -800,10 +800,11 @@ __global__ __launch_bounds__(DirectCore::kThreads) void logits_kernel(const Logi
     if (REDO && !p.info->redo) return;
     const PatchGrid pg = {Trc / kBlockR, p.Vp / kBlockC, p.PR, p.PC};
     const Halving last = halve_last_round(pg.blocks());
-    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    const bool rows = by_rows(pg, p.H);
+    const int number = block_of_workgroup(blockIdx.x, last.numbers, rows);
     if (number < 0) return;
     int tr, tc, half;
-    block_at(pg, last.block(number, half), tr, tc);
+    block_at(pg, last.block(number, half), rows, tr, tc);
     if (half < 0) logits_block<DirectCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR, smem);
     else logits_block<HalfCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
@@ -902,11 +903,12 @@ __global__ __launch_bounds__(DirectCore::kThreads) void dhidden_kernel(const DHi
     const PatchGrid pg = {Trc / kBlockR, (p.H + kBlockC - 1) / kBlockC, p.PR, p.PC};
     const int splits = p.info->splits, ksteps = p.info->ksteps;
     const Halving last = halve_last_round(pg.blocks() * splits);
-    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    const bool rows = by_rows(pg, ksteps * kBlockK);
+    const int number = block_of_workgroup(blockIdx.x, last.numbers, rows);
     if (number < 0) return;
     int tr, tc, half;
     const int i = last.block(number, half), split = i / pg.blocks();
-    block_at(pg, i - split * pg.blocks(), tr, tc);
+    block_at(pg, i - split * pg.blocks(), rows, tr, tc);
     if (half < 0) dhidden_block<DirectCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR, smem);
     else dhidden_block<HalfCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
@@ -976,9 +978,9 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void dw_kernel(const DWParams
     if (Tkc == 0 && !p.out.first) return;
     const PatchGrid pg = {tiles_r, p.Vp / kBlockC, p.PR, p.PC};
     const Halving last = halve_last_round(pg.blocks());
-    const int number = block_of_workgroup(blockIdx.x, last.numbers);
+    const int number = block_of_workgroup(blockIdx.x, last.numbers, false);
     if (number < 0) return;
-    block_at(pg, last.block(number, half), tr, tc);
+    block_at(pg, last.block(number, half), false, tr, tc);
     if (half < 0) dw_block<KMajorCore>(p, Tkc, left, tr * kBlockR, tc * kBlockC, smem);
     else dw_block<KMajorHalfCore>(p, Tkc, left, tr * kBlockR, tc * kBlockC + half * (kBlockC / 2), smem);
 }

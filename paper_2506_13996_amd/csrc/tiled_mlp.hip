@@ -173,10 +173,11 @@ struct BatchMap {
     int first_block[kMaxBatch + 1];      // first_block[i] .. first_block[i + 1]: blocks of part i
     int n;
     Halving last;                        // (MixedCore: every block whole)
+    bool rows;                           // the order of the blocks (by_rows; one product only)
     // which part and which of its blocks (or halves, see Halving) a workgroup works on; false for
     // padding workgroups
     __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC, int& half) const {
-        const int number = block_of_workgroup(bid, last.numbers);
+        const int number = block_of_workgroup(bid, last.numbers, rows);
         if (number < 0) return false;
         const int i = last.block(number, half);
         which = 0;
@@ -185,7 +186,7 @@ struct BatchMap {
             if (k < n && i >= first_block[k]) which = k;
         PR = g[which].PR;
         PC = g[which].PC;
-        block_at(g[which], i - first_block[which], tr, tc);
+        block_at(g[which], i - first_block[which], rows, tr, tc);
         return true;
     }
 };
@@ -316,6 +317,7 @@ struct GatedParams {
     int rows_x, I, K;
     PatchGrid grid;
     Halving last;
+    bool rows;               // the order of the blocks (by_rows)
 };
 
 // The SwiGLU epilogue of a block whose accumulators hold g (tiles mt < kMT / 2) and u (tile mt + kMT / 2)
@@ -412,10 +414,10 @@ __device__ __forceinline__ void gated_block(const GatedParams& p, int tr, int tc
 template <bool BWD, bool KTAIL>
 __global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const GatedParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int number = block_of_workgroup(blockIdx.x, p.last.numbers);
+    const int number = block_of_workgroup(blockIdx.x, p.last.numbers, p.rows);
     if (number < 0) return;
     int tr, tc, half;
-    block_at(p.grid, p.last.block(number, half), tr, tc);
+    block_at(p.grid, p.last.block(number, half), p.rows, tr, tc);
     if (half < 0) gated_block<DirectCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR, smem);
     else gated_block<HalfCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
@@ -428,10 +430,10 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
     extern __shared__ __align__(16) unsigned char smem[];
     auto next_block = [&](int bid, Core::Block& blk) {
         for (; bid < total; bid += gridDim.x) {
-            const int number = block_of_workgroup(bid, p.last.numbers);
+            const int number = block_of_workgroup(bid, p.last.numbers, p.rows);
             if (number < 0) continue;
             int tr, tc;
-            block_at(p.grid, number, tr, tc);
+            block_at(p.grid, number, p.rows, tr, tc);
             const int r0 = tr * kBlockR, c0 = tc * kBlockC;
             blk = {uniform(p.X), p.ldx, uniform(p.Wg), p.ldw, p.rows_x, p.I, p.K, uniform(r0), uniform(c0),
                    warm_row(p.grid.PR, p.grid.PC, p.X, p.ldx, r0, tr, p.Wg, p.ldw, c0, tc, p.Wu, p.rows_x, p.I),
@@ -458,10 +460,10 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const
     }
     if (chain) pipe.finish();
     for (bid = p.last.full + blockIdx.x; bid < p.last.numbers + kRound; bid += gridDim.x) {
-        const int number = block_of_workgroup(bid, p.last.numbers);
+        const int number = block_of_workgroup(bid, p.last.numbers, p.rows);
         if (number < p.last.full) continue;              // (none, or a whole block: the chain's)
         int tr, tc, half;
-        block_at(p.grid, p.last.block(number, half), tr, tc);
+        block_at(p.grid, p.last.block(number, half), p.rows, tr, tc);
         __syncthreads();                // LDS is free
         gated_block<HalfCore, BWD, false, GUARD>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
     }
@@ -561,6 +563,7 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
     b.map.last = ps[0].y_kmajor ? Halving{(int)total, (int)total} : halve_last_round((int)total);
+    b.map.rows = n == 1 && !ps[0].y_kmajor && by_rows(b.map.g[0], ps[0].K);
     const int blocks = grid_for_blocks(total);
     const int whole = grid_for_blocks(b.map.last.full);           // the chains' workgroup numbers
     ProfScope pr(PROF_MLP_LINEAR, s);
@@ -652,6 +655,7 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.da = da; gp.a = a; gp.dgu = dgu;
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
     gp.last = halve_last_round(gp.grid.blocks());
+    gp.rows = by_rows(gp.grid, gp.K);
     const int blocks = grid_for_blocks(gp.grid.blocks()), whole = grid_for_blocks(gp.last.full);
     const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
     // persistent workgroups that fetch their next block early: whole pairs of k-steps
