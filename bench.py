@@ -30,10 +30,10 @@ MI355X_BF16_MFMA_PEAK_TFLOPS = 2500.0      # dense bf16, vendor figure
 # this script: they come from two `rocprofv3 --pmc` runs of this very command, whose summary is
 # committed under profiles/.  The line below repeats that file's figures for the headline workload
 # and says so in `traffic_source`; for any other workload or tile the field is null.  A logits or
-# dHidden launch counts as one span per tile that it covers, here four with a fourth of its bytes each.
+# dHidden launch counts as one span per tile that it covers, here one.
 TRAFFIC_PROFILE = "profiles/bench_llama8b_128k_hbm_traffic.txt"
 PROFILED_TRAFFIC_BYTES_PER_SPAN = {
-    "llama8b_128k": {"logits_gemm": 6.858e9, "dhidden_gemm": 6.058e9, "dw_gemm": 25.770e9},
+    "llama8b_128k": {"logits_gemm": 6.855e9, "dhidden_gemm": 5.916e9, "dw_gemm": 25.618e9},
 }
 OTHER_STEPS, OTHER_WARMUP = 3, 1
 
@@ -181,7 +181,7 @@ class CeRun:
                     "traffic": known if profiled else None,
                     "traffic_source": (TRAFFIC_PROFILE + " (rocprofv3 --pmc runs of this command; "
                                        "not measured in this run)") if profiled else None,
-                    "span": "one launch" if dom == "dw_gemm" else "one tile (a launch covers several)",
+                    "span": "one launch" if dom == "dw_gemm" else "one tile (a launch may cover several)",
                     "spans": dom_n, "avg_span_ms": dom_ms / dom_n, "flop_per_span": flop_per_span,
                     "per_kind_ms_per_step": {k: v[0] / prof_steps for k, v in prof.items() if v[1]},
                     "per_kind_frac": {k: (4.0 if split and k == "logits_gemm" else 2.0) * M * H * V * prof_steps
