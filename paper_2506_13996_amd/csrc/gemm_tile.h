@@ -120,11 +120,11 @@ __host__ __device__ __forceinline__ int block_of_workgroup(int bid, int total, b
     // than a tenth above the mean (one by one, 236 blocks were parts of rows at both ends of every XCD's share:
     // cross-entropy step 16384 x 5120 x 128256, 3 % ignored, 49.3 -> 47.8 ms; but 207 blocks of a weight
     // gradient as 32 and 24 an XCD instead of 26: 283 -> 316 us).
-    const int units8 = (left + 7) / 8, unit = rows && 2 * left >= kRound && (units8 + 7) / 8 * 640 <= left * 11 ? 8 : 1;
-    const int units = unit == 8 ? units8 : left, per = units / kXcds, more = units % kXcds;
-    if (slot >= (per + (xcd < more ? 1 : 0)) * unit) return -1;
-    const int number = (xcd * per + (xcd < more ? xcd : more)) * unit + slot;
-    return number < left ? round * kRound + number : -1;
+    const int units8 = (left + 7) / 8;
+    const int shift = rows && 2 * left >= kRound && (units8 + 7) / 8 * 640 <= left * 11 ? 3 : 0;
+    const int units = shift ? units8 : left, per = units / kXcds, more = units % kXcds;
+    const int number = ((xcd * per + (xcd < more ? xcd : more)) << shift) + slot;
+    return slot < (per + (xcd < more ? 1 : 0)) << shift && number < left ? round * kRound + number : -1;
 }
 
 // The last round, if it fills no more than half of the compute units, is worked on in halves: two
@@ -161,12 +161,8 @@ __host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, boo
     const int column = i / (g.tiles_r * g.PC);
     i -= column * g.tiles_r * g.PC;
     const int c0 = column * g.PC, cols = g.tiles_c - c0 < g.PC ? g.tiles_c - c0 : g.PC;
-    if (rows) {
-        tr = i / cols;
-        tc = c0 + i - tr * cols;
-        return;
-    }
-    const int r0 = i / (g.PR * cols) * g.PR, in = g.tiles_r - r0 < g.PR ? g.tiles_r - r0 : g.PR;
+    const int PR = rows ? 1 : g.PR;
+    const int r0 = i / (PR * cols) * PR, in = g.tiles_r - r0 < PR ? g.tiles_r - r0 : PR;
     i -= r0 * cols;
     tr = r0 + i % in;
     tc = c0 + i / in;
