@@ -168,17 +168,17 @@ __host__ __device__ __forceinline__ void block_at(const PatchGrid& g, int i, boo
     tc = c0 + i / in;
 }
 
-// Gated pair of Y operands: with Y2 given, the 256 Y rows of the block at c0 are four runs of 64
-// rows, run q = rows c0 / 2 + (q / 2) * 64 .. + 63 of Y (q even) or of Y2 (q odd): the 128 rows of
-// a wavefront are 64 rows of Y followed by the same 64 rows of Y2, so a lane that holds the
-// product with row j of Y in accumulator tile mt holds the one with row j of Y2 in the tile 64 rows on
-// (mt + 2 for 32-row tiles, mt + 4 for 16-row tiles).
+// Gated pair of Y operands: with Y2 given, the Y rows of the block at c0 are runs of RUN = 64 (32)
+// rows, run q = rows c0 / 2 + (q / 2) * RUN .. + RUN - 1 of Y (q even) or of Y2 (q odd): the 2 RUN rows of
+// a wavefront are RUN rows of Y followed by the same rows of Y2, so a lane that holds the
+// product with row j of Y in accumulator tile mt holds the one with row j of Y2 in the tile RUN rows on.
 // br = row inside the block; valid = the source row exists (the pointer is then usable anyway).
+template <int RUN = 64>
 __device__ __forceinline__ const uint16_t* paired_row(const uint16_t* Y, const uint16_t* Y2,
                                                       int64_t ldy, int c0, int br, int rows_y,
                                                       bool& valid) {
-    const int run = br >> 6;
-    const int src = (c0 >> 1) + (run >> 1) * 64 + (br & 63);
+    const int run = br >> (RUN == 64 ? 6 : 5);
+    const int src = (c0 >> 1) + (run >> 1) * RUN + (br & (RUN - 1));
     valid = src < rows_y;
     return ((run & 1) ? Y2 : Y) + (int64_t)(valid ? src : 0) * ldy;
 }
@@ -265,6 +265,18 @@ __device__ __forceinline__ int kmajor_lane_offset(int lane, int gran) {
 __device__ __forceinline__ int kmajor_half_lane_offset(int lane, int gran) {
     const int sl = lane & 15, b1 = (lane >> 4) & 1, half = lane >> 5;
     return (8 * half + (sl >> 2)) * 256 + ((gran ^ (sl >> 2)) * 64) + b1 * 32 + (sl & 3) * 8;
+}
+
+// Between LDS accesses of different lanes of one wavefront: LDS serves them in program order, but the compiler may
+// order them anew along the branches of lanes that skip a guarded store (it sees one lane), and let those lanes write
+// the next piece before the others have read this one.  No instruction.
+template <bool DIVERGENT>
+__device__ __forceinline__ void wave_sync() {
+    if constexpr (DIVERGENT) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
 }
 
 // Values that are the same in every lane of a wavefront, said so to the compiler (it then keeps
@@ -574,6 +586,7 @@ struct DirectCoreT {
     static constexpr int kMT = 8;     // 16-wide c tiles per wavefront
     static constexpr int kNT = NT;    // 16-wide r tiles per wavefront: 8, or 4 for half a block (128 r)
     static constexpr int kWaveR = 16 * NT;                 // r one wavefront covers
+    static constexpr int kWaveC = kGroupC;
     typedef f32x4_t acc_t;
     static constexpr int kTile = 16, kRuns = 1, kGroups = 4;
 
@@ -928,6 +941,304 @@ typedef DirectCoreT<8> DirectCore;
 typedef DirectCoreT<4> HalfCore;
 
 // ---------------------------------------------------------------------------------------------
+// Small blocks
+// ---------------------------------------------------------------------------------------------
+// For launches whose 256 x 256 blocks would leave most compute units idle.  What bounds such a launch is how fast
+// one compute unit gets operands that are not in its L2: about 57 GB/s, whatever is requested ahead (some
+// 45 KB in flight at the latency of the memory-side cache; from L2 it is 150 GB/s).  So the blocks are small: 8 or
+// 16 times as many workgroups each fetch a half to a third of what a 128 x 256 half block does, through a
+// ring of LDS stages with all the steps ahead in flight that fit.  Same interfaces as the large cores.
+
+// Columns of a launch's small blocks, 64 or 128, or 0: large ones.  Small while they are at most one round, as
+// narrow as that allows.  us per product of 64 x 64 / 64 x 128 / large blocks, captured in a graph:
+//   512 x 1024 (8 large blocks), K = 256: 4.5 / 5.4 / 7.7, 768: 7.0 / 8.7 / 12.4, 8192: 41 / 58 / 97
+//   1024 x 2048 (32), K = 256: 7.5 / 5.7 / 8.1, 768: 13.0 / 9.4 / 12.8, 8192: 81 / 61 / 90
+//   2048 x 2048 (64), K = 256: 13.4 / 9.8 / 8.6, 768: 24 / 17 / 13.8, 8192: 152 / 116 / 90
+// Weight gradients (whole linear backward calls): 512 x 1024 (8), 2048 rows: 29.9 / 34.0 / 47.6;
+// 1024 x 2048 (32), 8192 rows: 94 / 80 / 131.
+// count(c): the launch's blocks of 64 x c.
+constexpr int kSmallRows = 64;
+inline int64_t small_blocks(int64_t rows, int64_t cols, int64_t c) {
+    return ((rows + kSmallRows - 1) / kSmallRows) * ((cols + c - 1) / c);
+}
+template <class Count>
+inline int small_block_columns(Count count) {
+    return count(64) <= kRound ? 64 : count(128) <= kRound ? 128 : 0;
+}
+
+// Waits until at most `steps` (no more than MOST) steps' DMA of PER instructions each is in flight for this wavefront,
+// and for its LDS reads, then joins the wavefronts of the workgroup.
+template <int PER, int MOST>
+__device__ __forceinline__ void ring_barrier(int steps) {
+    static_assert(PER * MOST < 64, "vmcnt has six bits");
+    if constexpr (MOST == 0) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    } else {
+        if (steps >= MOST) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(MOST * PER) : "memory");
+        else ring_barrier<PER, MOST - 1>(steps);
+    }
+}
+
+// Both operands k-contiguous, 64 (r) x 16 MT (c).  The four wavefronts lie along r, 16 rows each.
+template <int MT>
+struct RingCoreT {
+    static_assert(MT == 4 || MT == 8, "64 or 128 c");
+    static constexpr int kThreads = 256;
+    static constexpr int kMT = MT, kNT = 1;
+    static constexpr int kWaveR = 16, kWaveC = 16 * MT, kRows = 4 * kWaveR, kCols = kWaveC;
+    typedef f32x4_t acc_t;
+    static constexpr int kTile = 16, kRuns = 1, kGroups = 4;
+    static constexpr int kXBytes = kRows * 128, kStage = kXBytes + kCols * 128;
+    static constexpr int kStages = MT == 4 ? 8 : 5, kLds = kStages * kStage;      // 128 KB, 120 KB
+    typedef typename DirectCoreT<8>::Block Block;
+
+    struct Lane {
+        int lane, grp, lrow, wr;
+        static constexpr int wc = 0;
+        __device__ __forceinline__ Lane() {
+            lane = threadIdx.x & 63;
+            grp = lane >> 4;
+            lrow = lane & 15;
+            wr = threadIdx.x >> 6;
+        }
+        __device__ __forceinline__ int r(int) const { return wr * kWaveR + lrow; }
+        __device__ __forceinline__ int rbase(int) const { return wr * kWaveR; }
+        __device__ __forceinline__ int cw(int mt, int /*q*/) const { return mt * 16 + grp * 4; }
+        __device__ __forceinline__ int c(int mt, int q) const { return cw(mt, q); }
+    };
+
+    // As DirectCore's Block says (without the warm-up).
+    template <bool KTAIL>
+    static __device__ __forceinline__ void gemm(const Block& b, unsigned char* smem, acc_t (&acc)[kMT][kNT]) {
+        constexpr int kXq = 2, kYq = MT / 2, kPer = kXq + kYq;    // DMA instructions per wavefront and k-step
+        const int lane = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6));
+        const int lr = lane >> 3, pc = lane & 7, l15 = lane & 15, g = lane >> 4;
+        auto swz = [](int row) { return (row >> 1) & 7; };
+        const int KT = uniform((b.K + kBlockK - 1) / kBlockK), klast = b.K - (KT - 1) * kBlockK;
+        const uint16_t* xg[kXq];
+        const uint16_t* yg[kYq];
+        int kx[kXq], ky[kYq];                                     // the lane's k inside a step
+#pragma unroll
+        for (int q = 0; q < kXq; ++q) {
+            const int row = (w * kXq + q) * 8 + lr;
+            kx[q] = (pc ^ swz(row)) * 8;
+            xg[q] = b.X + (int64_t)(b.r0 + row < b.rows_x ? b.r0 + row : b.rows_x - 1) * b.ldx + kx[q];
+        }
+#pragma unroll
+        for (int q = 0; q < kYq; ++q) {
+            const int row = (w * kYq + q) * 8 + lr;
+            ky[q] = (pc ^ swz(row)) * 8;
+            if (b.Y2) {
+                bool valid;
+                yg[q] = paired_row<kWaveC / 2>(b.Y, b.Y2, b.ldy, b.c0, row, b.rows_y, valid) + ky[q];
+            } else {
+                yg[q] = b.Y + (int64_t)(b.c0 + row < b.rows_y ? b.c0 + row : b.rows_y - 1) * b.ldy + ky[q];
+            }
+        }
+        auto issue = [&](int kt, int stage) {
+            const bool tail = KTAIL && kt == KT - 1;
+            auto src = [&](const uint16_t* p, int k) {
+                return !tail || k < klast ? p + kt * kBlockK : reinterpret_cast<const uint16_t*>(zero_chunk);
+            };
+#pragma unroll
+            for (int q = 0; q < kXq; ++q) dma_to_lds<16>(src(xg[q], kx[q]), smem + stage + (w * kXq + q) * 1024);
+#pragma unroll
+            for (int q = 0; q < kYq; ++q) dma_to_lds<16>(src(yg[q], ky[q]), smem + stage + kXBytes + (w * kYq + q) * 1024);
+        };
+        int rofs[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) rofs[s] = ((4 * s + g) ^ swz(l15)) * 16 + l15 * 128;
+
+#pragma unroll
+        for (int kt = 0; kt < kStages - 1; ++kt)
+            if (kt < KT) issue(kt, kt * kStage);
+        int cur = 0, free = (kStages - 1) * kStage;               // stages, as byte offsets
+        auto next = [](int at) { return at == (kStages - 1) * kStage ? 0 : at + kStage; };
+        for (int kt = 0; kt < KT; ++kt) {
+            // step kt has landed, and every wavefront has read the stage of step kt - 1
+            ring_barrier<kPer, kStages - 2>(KT - 1 - kt);
+            if (kt + kStages - 1 < KT) issue(kt + kStages - 1, free);
+            const unsigned char* const st = smem + cur;
+            bf16x8_t fy[2][kMT], fx[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                fx[s] = *reinterpret_cast<const bf16x8_t*>(st + w * (kWaveR * 128) + rofs[s]);
+#pragma unroll
+                for (int t = 0; t < kMT; ++t)
+                    fy[s][t] = *reinterpret_cast<const bf16x8_t*>(st + kXBytes + t * 2048 + rofs[s]);
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int m = 0; m < kMT; ++m)
+                    acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fy[s][m], fx[s], acc[m][0], 0, 0, 0);
+            cur = next(cur);
+            free = next(free);
+        }
+        __syncthreads();               // the epilogue turns its data around in the stages
+    }
+};
+
+// Both operands k-major, 64 (r) x 32 CT (c).  The wavefronts share the block by k (wavefront w: the steps of 32 k w,
+// w + 4, ...), which takes a third of the transposing reads that a share by columns takes, and needs no barrier in the loop:
+// each has a ring of LDS stages of its own.  The partial sums are added in LDS at the end in wavefront order;
+// after that a wavefront holds 32 c x 32 CT / 2 r.
+template <int CT>
+struct KMajorSplitT {
+    static_assert(CT == 4 || CT == 2, "128 or 64 c");
+    static constexpr int kThreads = 256, kWaves = 4;
+    static constexpr int kRT = 2;                                 // 32-wide r tiles of the block
+    static constexpr int kMT = 1, kNT = CT * kRT / kWaves;        // a wavefront's tiles of the summed block
+    static constexpr int kWaveC = 32, kRows = 32 * kRT, kCols = 32 * CT;
+    typedef f32x16_t acc_t;
+    static constexpr int kTile = 32, kRuns = 4, kGroups = 2;
+    static constexpr int kStepK = 32, kXBytes = kStepK * kRows * 2, kYRow = 64 * CT, kStage = kXBytes + kStepK * kYRow;
+    static constexpr int kStages = CT == 4 ? 3 : 4, kLds = kWaves * kStages * kStage;      // 144 KB, 128 KB
+
+    struct Lane {
+        int lane, grp, lrow, wr, wc;
+        __device__ __forceinline__ Lane() {
+            lane = threadIdx.x & 63;
+            grp = lane >> 5;
+            lrow = lane & 31;
+            const int wave = threadIdx.x >> 6;
+            wr = wave % (kRT / kNT);
+            wc = wave / (kRT / kNT);
+        }
+        __device__ __forceinline__ int r(int nt) const { return (wr * kNT + nt) * 32 + lrow; }
+        __device__ __forceinline__ int rbase(int nt) const { return (wr * kNT + nt) * 32; }
+        __device__ __forceinline__ int cw(int mt, int q) const { return mt * 32 + q * 8 + grp * 4; }
+        __device__ __forceinline__ int c(int mt, int q) const { return wc * kWaveC + cw(mt, q); }
+    };
+
+    // As KMajorCore's gemm.
+    template <bool KTAIL>
+    static __device__ __forceinline__ void gemm(const uint16_t* __restrict__ X, int64_t ldx, int rows_x,
+                                                const uint16_t* __restrict__ Y, int64_t ldy, int rows_y, int K, int r0,
+                                                int c0, unsigned char* smem, acc_t (&out)[kMT][kNT],
+                                                const uint16_t* /*warm*/, int64_t /*warm_stride*/) {
+        const int lane = threadIdx.x & 63, w = uniform((int)(threadIdx.x >> 6));
+        const int KT = uniform((K + kStepK - 1) / kStepK), klast = K - (KT - 1) * kStepK;
+        const int steps = (KT - w + kWaves - 1) / kWaves;
+        // LDS rows (k) of 128 bytes (64 columns), 8 per DMA instruction: granule (32 columns) g of k-row k at slot
+        // g ^ (k / 2 & 1).  Of 256 bytes (128 columns), 4 per instruction: slot g ^ (k & 3).  The 4 k-rows that a
+        // quarter of a transposing read covers then fall into different 64 bytes of the 256 that the banks span.
+        constexpr int kXq = 4, kYq = 2 * CT, kPer = kXq + kYq, kYk = 16 / CT;    // kYk: k-rows of Y per instruction
+        auto slot_x = [](int g, int k) { return g ^ ((k >> 1) & 1); };
+        auto slot_y = [](int g, int k) { return CT == 4 ? g ^ (k & 3) : g ^ ((k >> 1) & 1); };
+        const uint16_t* xg[kXq];
+        const uint16_t* yg[kYq];
+        const int xk = lane >> 3, yk = lane / (64 / kYk), ya = lane % (64 / kYk);     // (+ 8 q, + kYk q: the same slots)
+        const int xc = r0 + (slot_x((lane & 7) >> 2, xk) * 4 + (lane & 3)) * 8;
+        const int yc = c0 + (slot_y(ya >> 2, yk) * 4 + (ya & 3)) * 8;
+#pragma unroll
+        for (int q = 0; q < kXq; ++q) xg[q] = X + (int64_t)(xk + 8 * q) * ldx + (xc < rows_x ? xc : rows_x - 8);
+#pragma unroll
+        for (int q = 0; q < kYq; ++q) yg[q] = Y + (int64_t)(yk + kYk * q) * ldy + (yc < rows_y ? yc : rows_y - 8);
+        unsigned char* const ring = smem + w * (kStages * kStage);
+        auto issue = [&](int i, int stage) {
+            const int kt = w + kWaves * i;
+            const bool tail = KTAIL && kt == KT - 1;
+            const uint16_t* const zeros = reinterpret_cast<const uint16_t*>(zero_chunk);
+            const int64_t xs = (int64_t)kt * kStepK * ldx, ys = (int64_t)kt * kStepK * ldy;
+#pragma unroll
+            for (int q = 0; q < kXq; ++q)
+                dma_to_lds<16>(!tail || xk + 8 * q < klast ? xg[q] + xs : zeros, ring + stage + q * 1024);
+#pragma unroll
+            for (int q = 0; q < kYq; ++q)
+                dma_to_lds<16>(!tail || yk + kYk * q < klast ? yg[q] + ys : zeros, ring + stage + kXBytes + q * 1024);
+        };
+        // a lane's place in a transposing read of a 16-row slice: k-row 8 half + sl / 4 (see kmajor_lane_offset)
+        const int sl = lane & 15, kr = 8 * (lane >> 5) + (sl >> 2), within = ((lane >> 4) & 1) * 32 + (sl & 3) * 8;
+        int xofs[kRT], yofs[CT];
+#pragma unroll
+        for (int t = 0; t < kRT; ++t) xofs[t] = kr * 128 + slot_x(t, kr) * 64 + within;
+#pragma unroll
+        for (int t = 0; t < CT; ++t) yofs[t] = kXBytes + kr * kYRow + slot_y(t, kr) * 64 + within;
+
+        acc_t acc[CT][kRT];
+#pragma unroll
+        for (int m = 0; m < CT; ++m)
+#pragma unroll
+            for (int n = 0; n < kRT; ++n)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc[m][n][j] = 0.f;
+
+        int cur = 0, free = (kStages - 1) * kStage;               // stages, as byte offsets
+        auto next = [](int at) { return at == (kStages - 1) * kStage ? 0 : at + kStage; };
+#pragma unroll
+        for (int i = 0; i < kStages - 1; ++i)
+            if (i < steps) issue(i, i * kStage);
+        for (int i = 0; i < steps; ++i) {
+            // this wavefront's reads of the stage that is filled next are done; then its step i has landed
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (i + kStages - 1 < steps) issue(i + kStages - 1, free);
+            const int behind = steps - 1 - i;
+            if (behind >= kStages - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * kPer) : "memory");
+            else if (kStages == 4 && behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kPer) : "memory");
+            else if (behind >= 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kPer) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const unsigned char* const st = ring + cur;
+            bf16x8_t fy[2][CT], fx[2][kRT];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int t = 0; t < kRT; ++t) fx[s][t] = read_kmajor<4 * 128>(st + xofs[t] + s * (16 * 128));
+#pragma unroll
+                for (int t = 0; t < CT; ++t) fy[s][t] = read_kmajor<4 * kYRow>(st + yofs[t] + s * (16 * kYRow));
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int m = 0; m < CT; ++m)
+#pragma unroll
+                    for (int n = 0; n < kRT; ++n)
+                        acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[s][m], fx[s][n], acc[m][n], 0, 0, 0);
+            cur = next(cur);
+            free = next(free);
+        }
+        __syncthreads();               // the rings become the place of the partial sums
+        // wavefront d gets the kNT tiles d kNT .. of the block, counted r first: c tile d kNT / kRT
+        constexpr int kPiece = kNT * 4096;
+        auto tile = [&](int d, int n) -> acc_t& { return acc[(d * kNT + n) / kRT][(d * kNT + n) % kRT]; };
+#pragma unroll
+        for (int d = 0; d < kWaves; ++d) {
+            if (d == w) continue;
+            unsigned char* const to = smem + (d * 3 + (w < d ? w : w - 1)) * kPiece + lane * 16;
+#pragma unroll
+            for (int n = 0; n < kNT; ++n)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const acc_t& t = tile(d, n);
+                    *reinterpret_cast<f32x4_t*>(to + (n * 4 + j) * 1024) = f32x4_t{t[4 * j], t[4 * j + 1], t[4 * j + 2], t[4 * j + 3]};
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < kWaves; ++d) {
+            if (d != w) continue;
+            const unsigned char* const from = smem + d * 3 * kPiece + lane * 16;
+#pragma unroll
+            for (int n = 0; n < kNT; ++n)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int o = 0; o < kWaves; ++o) {
+                        const acc_t& t = tile(d, n);
+                        const f32x4_t v = o == d ? f32x4_t{t[4 * j], t[4 * j + 1], t[4 * j + 2], t[4 * j + 3]}
+                                                 : *reinterpret_cast<const f32x4_t*>(from + (o < d ? o : o - 1) * kPiece + (n * 4 + j) * 1024);
+                        sum = o == 0 ? v : sum + v;
+                    }
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) out[0][n][4 * j + x] = sum[x];
+                }
+        }
+        __syncthreads();
+    }
+};
+
+// ---------------------------------------------------------------------------------------------
 // out[c][r] = in[r][c] (bf16), zeros for rows <= r < the 64 rows of the last piece
 // ---------------------------------------------------------------------------------------------
 // Weights that a product contracts over their row index are transposed once per call, so that
@@ -947,22 +1258,19 @@ struct Transposes {
     Transpose m[3];            // (rows = 0: none)
     int64_t pieces() const { return m[0].pieces() + m[1].pieces() + m[2].pieces(); }
 };
-static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transposes ts) {
-    int64_t i = blockIdx.x;
-    int k = 0;
-    for (; k < 2 && i >= ts.m[k].pieces(); ++k) i -= ts.m[k].pieces();
-    const uint16_t* __restrict__ const in = ts.m[k].in;
-    uint16_t* __restrict__ const out = ts.m[k].out;
-    const int rows = ts.m[k].rows, cols = ts.m[k].cols;
-    const int64_t ld_in = ts.m[k].ld_in, ld_out = ts.m[k].ld_out;
+__device__ __forceinline__ void transpose_piece(const Transpose& t, int64_t i) {
+    const uint16_t* __restrict__ const in = t.in;
+    uint16_t* __restrict__ const out = t.out;
+    const int rows = t.rows, cols = t.cols;
+    const int64_t ld_in = t.ld_in, ld_out = t.ld_out;
     const int across = (rows + 63) / 64;
     __shared__ uint16_t piece[64][64 + 2];
     const int r0 = (int)(i % across) * 64, c0 = (int)(i / across) * 64;
-    const int t = threadIdx.x;
-    // in: 64 rows x 8 chunks of 8 columns; thread -> (row t / 8 + 32 j, chunk t % 8)
+    const int tid = threadIdx.x;
+    // in: 64 rows x 8 chunks of 8 columns; thread -> (row tid / 8 + 32 j, chunk tid % 8)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int r = t / 8 + 32 * j, cc = (t % 8) * 8;
+        const int r = tid / 8 + 32 * j, cc = (tid % 8) * 8;
         u32x4_t x = {0u, 0u, 0u, 0u};
         if (r0 + r < rows && c0 + cc < cols)
             x = *reinterpret_cast<const u32x4_t*>(in + (int64_t)(r0 + r) * ld_in + c0 + cc);
@@ -976,7 +1284,7 @@ static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transp
     // out: 64 rows (columns of in) x 8 chunks of 8
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int c = t / 8 + 32 * j, rc = (t % 8) * 8;
+        const int c = tid / 8 + 32 * j, rc = (tid % 8) * 8;
         if (c0 + c >= cols) continue;
         u32x4_t y;
 #pragma unroll
@@ -984,6 +1292,12 @@ static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transp
             y[q] = (uint32_t)piece[rc + 2 * q][c] | ((uint32_t)piece[rc + 2 * q + 1][c] << 16);
         *reinterpret_cast<u32x4_t*>(out + (int64_t)(c0 + c) * ld_out + r0 + rc) = y;
     }
+}
+static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transposes ts) {
+    int64_t i = blockIdx.x;
+    int k = 0;
+    for (; k < 2 && i >= ts.m[k].pieces(); ++k) i -= ts.m[k].pieces();
+    transpose_piece(ts.m[k], i);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1022,8 +1336,9 @@ __device__ __forceinline__ void store_block_bf16(const typename Core::acc_t (&ac
                                                  unsigned char* smem) {
     const typename Core::Lane lp;
     unsigned char* const tw = smem + (threadIdx.x >> 6) * (Core::kTile * kTurnPitch);
-    const int lrow = lp.lane >> 4, lcol = lp.lane & 15;            // 4 rows x 16 chunks of 16 B
-    const int gc = c0 + lp.wc * kGroupC + lcol * 8;
+    constexpr int kChunks = Core::kWaveC / 8, kRowsAtOnce = 64 / kChunks;
+    const int lrow = lp.lane / kChunks, lcol = lp.lane % kChunks;            // 4 (8) rows x 16 (8) chunks of 16 B
+    const int gc = c0 + lp.wc * Core::kWaveC + lcol * 8;
 #pragma unroll
     for (int nt = 0; nt < Core::kNT; ++nt) {
 #pragma unroll
@@ -1035,14 +1350,16 @@ __device__ __forceinline__ void store_block_bf16(const typename Core::acc_t (&ac
                 for (int x = 0; x < 4; ++x) o[x] = (__bf16)acc[mt][nt][q * 4 + x];
                 *reinterpret_cast<bf16x4_t*>(tw + lp.lrow * kTurnPitch + lp.cw(mt, q) * 2) = o;
             }
+        wave_sync<GUARD>();
 #pragma unroll
-        for (int it = 0; it < Core::kTile / 4; ++it) {
-            const int row = it * 4 + lrow;
+        for (int it = 0; it < Core::kTile / kRowsAtOnce; ++it) {
+            const int row = it * kRowsAtOnce + lrow;
             const int gr = r0 + lp.rbase(nt) + row;
             const u32x4_t v = *reinterpret_cast<const u32x4_t*>(tw + row * kTurnPitch + lcol * 16);
             if (!GUARD || (gr < rows_out && gc + 8 <= cols_out))
                 __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(D + (int64_t)gr * ldd + gc));
         }
+        wave_sync<GUARD>();
     }
 }
 
@@ -1093,13 +1410,14 @@ __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&a
         }
         return;
     }
-    // one row of accumulator tiles at a time: 32 c x 128 r as fp32 (row pitch: two rows 4 apart, which
+    // one row of accumulator tiles at a time: 32 c x kR r as fp32 (row pitch: two rows 4 apart, which
     // one store writes, fall into different halves of the banks), then as whole rows, 4 r per lane
-    static_assert(kNT * Core::kTile == 128 && Core::kTile == 32, "a wavefront's r; a turned piece");
-    constexpr int kPitch = 128 + 8, kBatch = 8;
+    constexpr int kR = kNT * Core::kTile, kRowLanes = kR / 4, kRowsAtOnce = 64 / kRowLanes;
+    static_assert((kR == 128 || kR == 64 || kR == 32) && Core::kTile == 32, "a wavefront's r; a turned piece");
+    constexpr int kPitch = kR + 8, kBatch = kR == 32 ? 4 : 8;
     float* const tw = reinterpret_cast<float*>(smem) + (threadIdx.x >> 6) * (32 * kPitch);
-    const int half = lp.lane >> 5, c_first = c0 + lp.wc * Core::kWaveC, rq = (lp.lane & 31) * 4;
-    const int r = r0 + lp.wr * 128 + rq;
+    const int sub = lp.lane / kRowLanes, c_first = c0 + lp.wc * Core::kWaveC, rq = lp.lane % kRowLanes * 4;
+    const int r = r0 + lp.wr * kR + rq;
     const bool rok = r < r_valid;
 #pragma unroll
     for (int mt = 0; mt < kMT; ++mt) {
@@ -1108,14 +1426,15 @@ __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&a
 #pragma unroll
             for (int j = 0; j < kRegs; ++j)
                 tw[(lp.cw(0, j >> 2) + (j & 3)) * kPitch + nt * 32 + lp.lrow] = acc[mt][nt][j];
+        wave_sync<true>();
 #pragma unroll 1
-        for (int row0 = 0; row0 < 32; row0 += 2 * kBatch) {
+        for (int row0 = 0; row0 < 32; row0 += kRowsAtOnce * kBatch) {
             f32x4_t v[kBatch];
             bool ok[kBatch];
             int64_t at[kBatch];
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                const int c = c_first + mt * 32 + row0 + 2 * b + half;
+                const int c = c_first + mt * 32 + row0 + kRowsAtOnce * b + sub;
                 ok[b] = rok && c < c_valid;
                 at[b] = ok[b] ? (int64_t)c * g.ld + r : 0;
             }
@@ -1129,7 +1448,7 @@ __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&a
             }
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
-                v[b] += *reinterpret_cast<const f32x4_t*>(tw + (row0 + 2 * b + half) * kPitch + rq);
+                v[b] += *reinterpret_cast<const f32x4_t*>(tw + (row0 + kRowsAtOnce * b + sub) * kPitch + rq);
                 v[b] *= g.scale;
             }
             if (g.f32) {
@@ -1166,6 +1485,7 @@ __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&a
                 }
             }
         }
+        wave_sync<true>();
     }
 }
 

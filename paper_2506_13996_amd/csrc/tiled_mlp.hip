@@ -240,6 +240,20 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
     }
 }
 
+// The same in small blocks (SplitCoreT); the map's numbers are those of blocks of Core's size.
+template <class Core, bool KTAIL>
+__global__ __launch_bounds__(Core::kThreads) void linear_small_kernel(const LinearBatch b) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int which, tr, tc, PR, PC, half;
+    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
+    const LinearParams& p = b.p[which];
+    const int r0 = tr * Core::kRows, c0 = tc * Core::kCols;
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    Core::template gemm<KTAIL>({p.X, p.ldx, p.Y, p.ldy, p.rows_x, p.rows_y, p.K, r0, c0, nullptr, 0, nullptr}, smem, acc);
+    store_block_bf16<Core, true>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
+}
+
 // The k-contiguous products on persistent workgroups: one workgroup per compute unit walks the
 // launch's blocks bid = blockIdx.x, blockIdx.x + gridDim.x, ... (the same block numbering as
 // linear_kernel, so the 32 workgroups of an XCD still share a patch) and fetches the first two
@@ -329,13 +343,14 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
                                                int r0, int c0, unsigned char* tw) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     constexpr int kHalfMT = kMT / 2;
-    // Per wavefront and accumulator column nt: kTile rows x 64 columns of I.  Everything that goes
+    // Per wavefront and accumulator column nt: kTile rows x 64 (32) columns of I.  Everything that goes
     // to or comes from memory is turned around in the wavefront's own LDS region (as in
     // store_block_bf16) so that global accesses are whole 128-byte row segments.
     const typename Core::Lane lp;
     constexpr int kRuns = Core::kRuns, kTile = Core::kTile;
-    const int lrow = lp.lane >> 3, lcol = lp.lane & 7;             // 8 rows x 8 chunks of 16 B
-    const int gc = (c0 >> 1) + lp.wc * 64 + lcol * 8;              // this lane's 8 columns of I
+    constexpr int kCols = Core::kWaveC / 2, kChunks = kCols / 8, kRowsAtOnce = 64 / kChunks;
+    const int lrow = lp.lane / kChunks, lcol = lp.lane % kChunks;  // 8 (16) rows x 8 (4) chunks of 16 B
+    const int gc = (c0 >> 1) + lp.wc * kCols + lcol * 8;           // this lane's 8 columns of I
     const bool col_ok = !CHECK || gc + 8 <= p.I;
     const u32x4_t zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -348,28 +363,32 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
             for (int mt = 0; mt < kHalfMT; ++mt)
 #pragma unroll
                 for (int q = 0; q < kRuns; ++q) *reinterpret_cast<bf16x4_t*>(own(mt, q)) = v[mt][q];
+            wave_sync<CHECK>();
 #pragma unroll
-            for (int it = 0; it < kTile / 8; ++it) {
-                const int row = it * 8 + lrow;
+            for (int it = 0; it < kTile / kRowsAtOnce; ++it) {
+                const int row = it * kRowsAtOnce + lrow;
                 const u32x4_t val = *reinterpret_cast<const u32x4_t*>(tw + row * kTurnPitch + lcol * 16);
                 if (!CHECK || (row0 + row < p.rows_x && col_ok))
                     *reinterpret_cast<u32x4_t*>(dst + (int64_t)(row0 + row) * ld + gc) = val;
             }
+            wave_sync<CHECK>();
         };
         bf16x4_t d[kHalfMT][kRuns];
         if (BWD) {
 #pragma unroll
-            for (int it = 0; it < kTile / 8; ++it) {
-                const int row = it * 8 + lrow;
+            for (int it = 0; it < kTile / kRowsAtOnce; ++it) {
+                const int row = it * kRowsAtOnce + lrow;
                 const bool ok = !CHECK || (row0 + row < p.rows_x && col_ok);
                 const u32x4_t val = ok ? *reinterpret_cast<const u32x4_t*>(p.da + (int64_t)(row0 + row) * p.I + gc)
                                        : zero4;
                 *reinterpret_cast<u32x4_t*>(tw + row * kTurnPitch + lcol * 16) = val;
             }
+            wave_sync<CHECK>();
 #pragma unroll
             for (int mt = 0; mt < kHalfMT; ++mt)
 #pragma unroll
                 for (int q = 0; q < kRuns; ++q) d[mt][q] = *reinterpret_cast<const bf16x4_t*>(own(mt, q));
+            wave_sync<CHECK>();
         }
         bf16x4_t oa[kHalfMT][kRuns], og[kHalfMT][kRuns], ou[kHalfMT][kRuns];
 #pragma unroll
@@ -420,6 +439,21 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const Gated
     block_at(p.grid, p.last.block(number, half), p.rows, tr, tc);
     if (half < 0) gated_block<DirectCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR, smem);
     else gated_block<HalfCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+}
+
+// The same in small blocks.
+template <class Core, bool BWD, bool KTAIL>
+__global__ __launch_bounds__(Core::kThreads) void gated_small_kernel(const GatedParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int number = block_of_workgroup(blockIdx.x, p.last.numbers, false);
+    if (number < 0) return;
+    int tr, tc;
+    block_at(p.grid, number, false, tr, tc);
+    const int r0 = tr * Core::kRows, c0 = tc * Core::kCols;          // c0 / 2 = first of the block's 64 columns of I
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    Core::template gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, nullptr, 0, p.Wu}, smem, acc);
+    gated_epilogue<Core, BWD, true>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
 }
 
 // The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 128 and >= 256.
@@ -503,6 +537,16 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const Wgrad
     else wgrad_block<KMajorHalfCore, KTAIL>(p, tr * kBlockR, tc * kBlockC + half * (kBlockC / 2), smem);
 }
 
+// The same in small blocks.
+template <class Core, bool KTAIL>
+__global__ __launch_bounds__(Core::kThreads) void wgrad_small_kernel(const WgradBatch b) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    int which, tr, tc, PR, PC, half;
+    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
+    const WgradParams& p = b.p[which];
+    wgrad_block<Core, KTAIL>(p, tr * Core::kRows, tc * Core::kCols, smem);
+}
+
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
@@ -527,6 +571,22 @@ static int prepare_mlp_kernels_on_current_device() {
     acc(allow_big_lds(gated_chain_kernel<true, true>, kChainLdsBytes));
     acc(allow_big_lds(wgrad_kernel<false>));
     acc(allow_big_lds(wgrad_kernel<true>));
+    acc(allow_big_lds(linear_small_kernel<RingCoreT<4>, false>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(linear_small_kernel<RingCoreT<4>, true>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(linear_small_kernel<RingCoreT<8>, false>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(linear_small_kernel<RingCoreT<8>, true>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, false>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, true>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, false>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, true>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, false>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, true>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, false>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, true>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<2>, false>, KMajorSplitT<2>::kLds));
+    acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<2>, true>, KMajorSplitT<2>::kLds));
+    acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<4>, false>, KMajorSplitT<4>::kLds));
+    acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<4>, true>, KMajorSplitT<4>::kLds));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -541,28 +601,67 @@ static int prepare_mlp_kernels() {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Numbers the blocks of block_r x block_c of n products through; returns their number (may be beyond a launch).
+template <class Batch, class Params>
+static int64_t number_blocks(Batch& b, const Params* ps, int n, int block_r, int block_c) {
+    b.map.n = n;
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const Params& p = ps[i];
+        b.p[i] = p;
+        b.map.first_block[i] = (int)total;
+        const int tiles_r = (p.rows_x + block_r - 1) / block_r, tiles_c = (p.rows_y + block_c - 1) / block_c;
+        b.map.g[i] = choose_patches(tiles_r, tiles_c);
+        total += (int64_t)tiles_r * tiles_c;
+    }
+    for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
+    b.map.last = Halving{(int)total, (int)total};
+    b.map.rows = false;
+    return total;
+}
+// Columns of small blocks for the n products (small_block_columns), or 0: large ones.
+template <class Params>
+static int small_columns(const Params* ps, int n) {
+    return small_block_columns([&](int64_t c) {
+        int64_t total = 0;
+        for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
+        return total;
+    });
+}
+
+template <class Core>
+static int launch_linear_small(const LinearParams* ps, int n, hipStream_t s) {
+    LinearBatch b = {};
+    const int64_t total = number_blocks(b, ps, n, Core::kRows, Core::kCols);
+    bool ktail = false;
+    for (int i = 0; i < n; ++i) ktail = ktail || ps[i].K % kBlockK != 0;
+    const dim3 blocks((unsigned)grid_for_blocks(total)), threads(Core::kThreads);
+    ProfScope pr(PROF_MLP_LINEAR, s);
+    if (ktail) hipLaunchKernelGGL((linear_small_kernel<Core, true>), blocks, threads, Core::kLds, s, b);
+    else hipLaunchKernelGGL((linear_small_kernel<Core, false>), blocks, threads, Core::kLds, s, b);
+    return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
 // One launch for the n products (n <= kMaxBatch), all of one kind (y_kmajor).
 static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
+    if (!ps[0].y_kmajor) {
+        const int columns = small_columns(ps, n);
+        if (columns == 64) return launch_linear_small<RingCoreT<4>>(ps, n, s);
+        if (columns == 128) return launch_linear_small<RingCoreT<8>>(ps, n, s);
+    }
     LinearBatch b = {};
-    b.map.n = n;
+    const int64_t total = number_blocks(b, ps, n, kBlockR, kBlockC);
+    if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     bool guard = false, ktail = false;
     // persistent workgroups that fetch their next block early: one K, whole pairs of k-steps
     bool chain = !ps[0].y_kmajor && ps[0].K % (2 * kBlockK) == 0 && ps[0].K >= 4 * kBlockK;
-    int64_t total = 0;
     for (int i = 0; i < n; ++i) {
         const LinearParams& p = ps[i];
-        b.p[i] = p;
-        b.map.first_block[i] = (int)total;
-        const int tiles_r = (p.rows_x + kBlockR - 1) / kBlockR, tiles_c = (p.rows_y + kBlockC - 1) / kBlockC;
-        b.map.g[i] = choose_patches(tiles_r, tiles_c);
-        total += (int64_t)tiles_r * tiles_c;
         guard = guard || p.rows_x % kBlockR != 0 || p.rows_y % kBlockC != 0;
         ktail = ktail || p.K % kBlockK != 0;
         chain = chain && p.K == ps[0].K;
     }
-    if (total > 0x7fffff00) return ALST_ERR_SHAPE;
-    for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
-    b.map.last = ps[0].y_kmajor ? Halving{(int)total, (int)total} : halve_last_round((int)total);
+    if (!ps[0].y_kmajor) b.map.last = halve_last_round((int)total);
     b.map.rows = n == 1 && !ps[0].y_kmajor && by_rows(b.map.g[0], ps[0].K);
     const int blocks = grid_for_blocks(total);
     const int whole = grid_for_blocks(b.map.last.full);           // the chains' workgroup numbers
@@ -589,21 +688,25 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
 
 static int launch_linear(const LinearParams& p, hipStream_t s) { return launch_linear(&p, 1, s); }
 
+template <class Core>
+static int launch_wgrad_small(const WgradParams* ps, int n, hipStream_t s) {
+    WgradBatch b = {};
+    const int64_t total = number_blocks(b, ps, n, Core::kRows, Core::kCols);
+    const dim3 blocks((unsigned)grid_for_blocks(total)), threads(Core::kThreads);
+    ProfScope pr(PROF_MLP_WGRAD, s);
+    if (ps[0].K % kBlockK != 0) hipLaunchKernelGGL((wgrad_small_kernel<Core, true>), blocks, threads, Core::kLds, s, b);
+    else hipLaunchKernelGGL((wgrad_small_kernel<Core, false>), blocks, threads, Core::kLds, s, b);
+    return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
 // The n weight-gradient products (n <= kMaxBatch, all with the same K) in one launch.
 static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
+    const int columns = small_columns(ps, n);
+    if (columns == 64) return launch_wgrad_small<KMajorSplitT<2>>(ps, n, s);
+    if (columns == 128) return launch_wgrad_small<KMajorSplitT<4>>(ps, n, s);
     WgradBatch b = {};
-    b.map.n = n;
-    int64_t total = 0;
-    for (int i = 0; i < n; ++i) {
-        const WgradParams& p = ps[i];
-        b.p[i] = p;
-        b.map.first_block[i] = (int)total;
-        const int tiles_r = (p.rows_x + kBlockR - 1) / kBlockR, tiles_c = (p.rows_y + kBlockC - 1) / kBlockC;
-        b.map.g[i] = choose_patches(tiles_r, tiles_c);
-        total += (int64_t)tiles_r * tiles_c;
-    }
+    const int64_t total = number_blocks(b, ps, n, kBlockR, kBlockC);
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
-    for (int i = n; i <= kMaxBatch; ++i) b.map.first_block[i] = (int)total;
     b.map.last = halve_last_round((int)total);
     const dim3 blocks((unsigned)grid_for_blocks(total)), threads(KMajorCore::kThreads);
     ProfScope pr(PROF_MLP_WGRAD, s);
@@ -646,6 +749,21 @@ static int validate_mlp(const MlpProblem& P, size_t workspace_bytes, bool backwa
     return ALST_OK;
 }
 
+template <class Core>
+static int launch_gated_small(GatedParams gp, bool bwd, hipStream_t s) {
+    gp.grid = choose_patches((gp.rows_x + Core::kRows - 1) / Core::kRows, (2 * gp.I + Core::kCols - 1) / Core::kCols);
+    gp.last = {gp.grid.blocks(), gp.grid.blocks()};
+    const dim3 blocks((unsigned)grid_for_blocks(gp.grid.blocks())), threads(Core::kThreads);
+    const bool ktail = gp.K % kBlockK != 0;
+    ProfScope pr(PROF_MLP_LINEAR, s);
+    constexpr int lds = Core::kLds;
+    if (ktail && bwd) hipLaunchKernelGGL((gated_small_kernel<Core, true, true>), blocks, threads, lds, s, gp);
+    else if (ktail) hipLaunchKernelGGL((gated_small_kernel<Core, false, true>), blocks, threads, lds, s, gp);
+    else if (bwd) hipLaunchKernelGGL((gated_small_kernel<Core, true, false>), blocks, threads, lds, s, gp);
+    else hipLaunchKernelGGL((gated_small_kernel<Core, false, false>), blocks, threads, lds, s, gp);
+    return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
 // a = silu(x_t Wg^T) * (x_t Wu^T) for `rows` rows of x; backward (da given): also [dg | du].
 static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, const uint16_t* da, uint16_t* a,
                         uint16_t* dgu, hipStream_t s) {
@@ -653,6 +771,9 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.X = x_t; gp.ldx = P.H; gp.rows_x = rows; gp.K = (int)P.H;
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
     gp.da = da; gp.a = a; gp.dgu = dgu;
+    const int columns = small_block_columns([&](int64_t c) { return small_blocks(rows, 2 * P.I, c); });
+    if (columns == 64) return launch_gated_small<RingCoreT<4>>(gp, da != nullptr, s);
+    if (columns == 128) return launch_gated_small<RingCoreT<8>>(gp, da != nullptr, s);
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
     gp.last = halve_last_round(gp.grid.blocks());
     gp.rows = by_rows(gp.grid, gp.K);
