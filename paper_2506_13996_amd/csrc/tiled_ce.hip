@@ -430,7 +430,11 @@ __device__ __forceinline__ float from_ordered_int(int k) {
 // pass (0; backward from a saved lse: that lse, so that e is the probability itself) and marks the
 // row as taking part in that pass.  Workgroup 0 leaves the chunk's counts and its dHidden ranges.
 // Workgroups from Rc on (first chunk, if a gradient is wanted) take kZeroRows rows of the sequence at a
-// time; the dHidden rows of ignored tokens become zeros.
+// time; the dHidden rows of ignored tokens become zeros.  The workgroups behind those transpose W (first chunk, if
+// a gradient is wanted: a launch of its own took 3 us more of the smallest calls).
+// INDEX (N <= kGatherIndexRows, one chunk): there was no launch that numbers the rows; every workgroup counts the valid labels
+// itself, and workgroup 0 leaves the header (512 x 256 x 4096: two launches of 3.8 and 3.4 us become one).
+constexpr int kGatherIndexRows = 1024;
 struct GatherParams {
     const uint16_t* hidden;      // [N, H]
     const int32_t* labels;       // [N]
@@ -446,15 +450,28 @@ struct GatherParams {
     int64_t N, first;
     int64_t Rc;                  // the chunk's rows, rounded up to the block height
     int64_t H, V, dh_part_rows;
+    int64_t zero_blocks;
     int Hk, ignore_index;
+    // INDEX: what index_rows_kernel writes
+    Header* hdr_out;
+    int32_t* idx_out;
+    float *lse, *loss_rows;      // may be null
+    int64_t* n_valid_out;
+    float grad_loss;
+    int sum_mode;
 };
-__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) {
+template <bool INDEX>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p, const Transpose t) {
     const int64_t b = blockIdx.x;
+    if (b >= p.Rc + p.zero_blocks) {
+        transpose_piece(t, b - p.Rc - p.zero_blocks);
+        return;
+    }
     const u32x4_t zero4 = {0u, 0u, 0u, 0u};
     const int src_chunks = (int)(p.H / 8);
     if (b >= p.Rc) {
         const int lane = threadIdx.x & 63;
-        for (int64_t row0 = (b - p.Rc) * kZeroRows; row0 < p.N; row0 += (gridDim.x - p.Rc) * kZeroRows) {
+        for (int64_t row0 = (b - p.Rc) * kZeroRows; row0 < p.N; row0 += p.zero_blocks * kZeroRows) {
             const int64_t i = row0 + lane;
             const bool ignored = lane < kZeroRows && i < p.N && !label_valid(p.labels[i], p.ignore_index, (int)p.V);
             for (unsigned long long mask = __ballot(ignored); mask; mask &= mask - 1) {
@@ -464,7 +481,64 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) 
         }
         return;
     }
-    const long long left = p.hdr->n_valid - p.first;
+    long long n_valid = 0;
+    int my_row = 0;                // INDEX: the token of dense row b
+    if constexpr (INDEX) {
+        constexpr int kPer = kGatherIndexRows / 256;
+        __shared__ int count[kPer][4];
+        __shared__ int row_of_b;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        unsigned long long mask[kPer];
+        bool bad = false;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int i = j * 256 + threadIdx.x;
+            const int y = i < p.N ? p.labels[i] : p.ignore_index;
+            const bool valid = i < p.N && label_valid(y, p.ignore_index, (int)p.V);
+            bad |= y != p.ignore_index && !valid;
+            mask[j] = __ballot(valid);
+            if (lane == 0) count[j][wave] = __popcll(mask[j]);
+        }
+        const int any_bad = __syncthreads_or(bad);
+        int total = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if (w == wave) {
+                    const int rank = total + __builtin_amdgcn_mbcnt_hi((unsigned)(mask[j] >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((unsigned)mask[j], 0));
+                    if ((mask[j] >> lane & 1) && rank == b) row_of_b = j * 256 + threadIdx.x;
+                }
+                total += count[j][w];
+            }
+        n_valid = total;
+        if (b == 0) {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                const int i = j * 256 + threadIdx.x;
+                if (i < p.N && !(mask[j] >> lane & 1)) {
+                    if (p.lse) p.lse[i] = 0.f;
+                    if (p.loss_rows) p.loss_rows[i] = 0.f;
+                }
+            }
+            if (threadIdx.x == 0) {
+                p.hdr_out->status = any_bad ? (int)ALST_ERR_LABEL_RANGE : 0;
+                p.hdr_out->n_valid = total;
+                p.hdr_out->inv = total > 0 ? (p.sum_mode ? p.grad_loss : p.grad_loss / (float)total) : 0.f;
+                p.hdr_out->loss_sum = 0.0;
+                if (p.n_valid_out) *p.n_valid_out = total;
+            }
+        }
+        __syncthreads();
+        if (b < total) {
+            my_row = row_of_b;
+            if (threadIdx.x == 0) p.idx_out[b] = my_row;
+        }
+    } else {
+        n_valid = p.hdr->n_valid;
+    }
+    const long long left = n_valid - p.first;
     const int Tc = (int)(left < 0 ? 0 : (left > p.Rc ? p.Rc : left));
     const int Trc = (Tc + kBlockR - 1) / kBlockR * kBlockR;
     if (b == 0 && threadIdx.x == 0) {
@@ -485,7 +559,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherParams p) 
     int y = -1;
     float ref = 0.f;
     if (b < Tc) {
-        const int64_t row = p.idx[p.first + b];
+        const int64_t row = INDEX ? my_row : p.idx[p.first + b];
         const u32x4_t* src = reinterpret_cast<const u32x4_t*>(p.hidden + row * p.H);
         for (int c = threadIdx.x; c < chunks; c += 256) dst[c] = c < src_chunks ? src[c] : zero4;
         if (threadIdx.x == 0) {
@@ -621,28 +695,35 @@ __global__ __launch_bounds__(kCombineRows * kCombineLanes) void row_finish_kerne
     }
 }
 
-// loss = (sum of the per-row terms in a fixed order) / M, or the sum itself.  One block.
-__global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restrict__ loss_rows,
-                                                           int64_t N, Header* h, int sum_mode,
-                                                           float* __restrict__ loss_out) {
-    __shared__ double part[1024];
+// loss = (sum of the per-row terms in a fixed order) / M, or the sum itself.  One workgroup of THREADS.
+struct LossParams {
+    const float* loss_rows;
+    int64_t N;
+    Header* h;
+    int sum_mode;
+    float* loss_out;
+};
+template <int THREADS>
+__device__ __forceinline__ void loss_reduce(const LossParams& p) {
+    __shared__ double part[THREADS];
     double s = 0.0;
 #pragma unroll 8
-    for (int64_t i = threadIdx.x; i < N; i += 1024) s += (double)loss_rows[i];
+    for (int64_t i = threadIdx.x; i < p.N; i += THREADS) s += (double)p.loss_rows[i];
     part[threadIdx.x] = s;
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    for (int w = THREADS / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const long long M = h->n_valid;
-        const double L = M > 0 ? (sum_mode ? part[0] : part[0] / (double)M) : 0.0;
-        h->loss_sum = part[0];
-        *loss_out = (float)L;
-        if (!isfinite(L)) atomicMax(&h->status, (int)ALST_ERR_NONFINITE);
+        const long long M = p.h->n_valid;
+        const double L = M > 0 ? (p.sum_mode ? part[0] : part[0] / (double)M) : 0.0;
+        p.h->loss_sum = part[0];
+        *p.loss_out = (float)L;
+        if (!isfinite(L)) atomicMax(&p.h->status, (int)ALST_ERR_NONFINITE);
     }
 }
+__global__ __launch_bounds__(1024) void loss_reduce_kernel(const LossParams p) { loss_reduce<1024>(p); }
 
 __global__ void copy_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -681,13 +762,13 @@ struct LogitsParams {
 // REDO: the second pass over a chunk, for the rows whose first-pass sums left the safe range; its
 // workgroups leave at once unless row_finish flagged the chunk, and rows that are not marked keep
 // what the first pass wrote.
-// Core: DirectCore for a block, HalfCore for one half of its rows.  r0: the rows' first, tr: the whole
-// block's.
+// Core: DirectCore for a block, HalfCore for one half of its rows, RingCoreT<8> for a small one.
+// warm: the block's warm-up row (large blocks).
 template <class Core, bool KTAIL, int MODE, bool REDO>
-__device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, int Trc, int tr, int tc, int r0,
-                                             unsigned char* smem) {
+__device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, int Trc, int r0, int c0,
+                                             const uint16_t* warm, unsigned char* smem) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    const int c0 = tc * kBlockC;
+    static_assert(Core::kWaveC == kGroupC, "a wavefront's c are one group of the softmax partials");
     if (r0 >= T_cur) return;        // (a second half of padding rows: the consumers' k-steps end before it)
     constexpr int kRegs = 4 * Core::kRuns;          // accumulator registers of a tile
 
@@ -695,8 +776,6 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
     zero_acc<Core>(acc);
 
     const uint16_t* const hidden_t = p.hidden_t;
-    const uint16_t* warm = warm_row(p.PR, p.PC, hidden_t, p.Hk, tr * kBlockR, tr, p.W, p.H, c0, tc, nullptr, Trc,
-                                    p.V);
     Core::template gemm<KTAIL>({hidden_t, p.Hk, p.W, p.H, Trc, p.V, p.H, r0, c0, warm, kBlockK, nullptr}, smem,
                                acc);
 
@@ -759,6 +838,7 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
                     *reinterpret_cast<bf16x4_t*>(tw + lp.lrow * kTurnPitch + lp.cw(mt, q) * 2) = o;
             }
         if (MODE != MODE_FWD) {
+            wave_sync<REDO>();
             const int lrow = lp.lane >> 4, lcol = lp.lane & 15;        // 4 rows x 16 chunks of 16 B
             const int rb = r0 + lp.rbase(nt);
             uint16_t* const out = p.stash + (int64_t)rb * p.Vp + c0 + lp.wc * kGroupC + lcol * 8;
@@ -769,6 +849,7 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
                 if (!REDO || p.rowstate[rb + row] != 0)
                     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(out + (int64_t)row * p.Vp));
             }
+            wave_sync<REDO>();
         }
         if (MODE != MODE_BWD) {
             s = groups_sum<Core::kGroups>(s);
@@ -805,8 +886,27 @@ __global__ __launch_bounds__(DirectCore::kThreads) void logits_kernel(const Logi
     if (number < 0) return;
     int tr, tc, half;
     block_at(pg, last.block(number, half), rows, tr, tc);
-    if (half < 0) logits_block<DirectCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR, smem);
-    else logits_block<HalfCore, KTAIL, MODE, REDO>(p, T_cur, Trc, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+    const int r0 = tr * kBlockR, c0 = tc * kBlockC;
+    const uint16_t* warm = warm_row(p.PR, p.PC, p.hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V);
+    if (half < 0) logits_block<DirectCore, KTAIL, MODE, REDO>(p, T_cur, Trc, r0, c0, warm, smem);
+    else logits_block<HalfCore, KTAIL, MODE, REDO>(p, T_cur, Trc, r0 + half * (kBlockR / 2), c0, warm, smem);
+}
+
+// The same in small blocks.
+typedef RingCoreT<8> LogitsSmallCore;
+template <bool KTAIL, int MODE, bool REDO>
+__global__ __launch_bounds__(LogitsSmallCore::kThreads) void logits_small_kernel(const LogitsParams p) {
+    typedef LogitsSmallCore Core;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int T_cur = p.info->Tc, Trc = p.info->Trc;
+    if (T_cur == 0) return;
+    if (REDO && !p.info->redo) return;
+    const PatchGrid pg = {Trc / Core::kRows, p.Vp / Core::kCols, p.PR, p.PC};
+    const int number = block_of_workgroup(blockIdx.x, pg.blocks(), false);
+    if (number < 0) return;
+    int tr, tc;
+    block_at(pg, number, false, tr, tc);
+    logits_block<Core, KTAIL, MODE, REDO>(p, T_cur, Trc, tr * Core::kRows, tc * Core::kCols, nullptr, smem);
 }
 
 struct DHiddenParams {
@@ -833,12 +933,11 @@ struct DHiddenParams {
 // number does not fill the compute units evenly, the contraction is cut into `splits` ranges, each
 // range's blocks write fp32 partial products, and dhidden_reduce_kernel adds them in a fixed
 // order.
-// Core, r0, tr: as in logits_block.
+// warm: the block's warm-up row for k = 0 (large blocks).
 template <class Core>
 __device__ __forceinline__ void dhidden_block(const DHiddenParams& p, int T_cur, int Trc, int splits, int ksteps,
-                                              int split, int tr, int tc, int r0, unsigned char* smem) {
+                                              int split, int r0, int c0, const uint16_t* warm, unsigned char* smem) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
-    const int c0 = tc * kBlockC;
     if (r0 >= T_cur) return;
     // k runs over V rounded up to whole k-steps: dZ and Wt are zero there
     const int k0 = split * ksteps * kBlockK;
@@ -851,7 +950,6 @@ __device__ __forceinline__ void dhidden_block(const DHiddenParams& p, int T_cur,
     const uint16_t* const Wk = p.Wt + k0;
     // (a hidden size that ends inside the block: the rows of Wt beyond H are read from its last
     // row, and the epilogue skips those columns)
-    const uint16_t* warm = warm_row(p.PR, p.PC, dz, p.Vp, tr * kBlockR, tr, Wk, p.Vp, c0, tc, nullptr, Trc, p.H);
     Core::template gemm<false>({dz, p.Vp, Wk, p.Vp, Trc, p.H, klen, r0, c0, warm, kBlockK, nullptr}, smem, acc);
 
     const typename Core::Lane lp;
@@ -909,19 +1007,43 @@ __global__ __launch_bounds__(DirectCore::kThreads) void dhidden_kernel(const DHi
     int tr, tc, half;
     const int i = last.block(number, half), split = i / pg.blocks();
     block_at(pg, i - split * pg.blocks(), rows, tr, tc);
-    if (half < 0) dhidden_block<DirectCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR, smem);
-    else dhidden_block<HalfCore>(p, T_cur, Trc, splits, ksteps, split, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
+    const int r0 = tr * kBlockR, c0 = tc * kBlockC, k0 = split * ksteps * kBlockK;
+    const uint16_t* warm = warm_row(p.PR, p.PC, p.dz + k0, p.Vp, r0, tr, p.Wt + k0, p.Vp, c0, tc, nullptr, Trc, p.H);
+    if (half < 0) dhidden_block<DirectCore>(p, T_cur, Trc, splits, ksteps, split, r0, c0, warm, smem);
+    else dhidden_block<HalfCore>(p, T_cur, Trc, splits, ksteps, split, r0 + half * (kBlockR / 2), c0, warm, smem);
+}
+
+// The same in small blocks (the ranges are chosen as for the large ones).
+template <class Core>
+__global__ __launch_bounds__(Core::kThreads) void dhidden_small_kernel(const DHiddenParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int T_cur = p.info->Tc, Trc = p.info->Trc;
+    if (T_cur == 0) return;
+    const PatchGrid pg = {Trc / Core::kRows, (p.H + Core::kCols - 1) / Core::kCols, p.PR, p.PC};
+    const int splits = p.info->splits, ksteps = p.info->ksteps;
+    const int number = block_of_workgroup(blockIdx.x, pg.blocks() * splits, false);
+    if (number < 0) return;
+    int tr, tc;
+    const int split = number / pg.blocks();
+    block_at(pg, number - split * pg.blocks(), false, tr, tc);
+    dhidden_block<Core>(p, T_cur, Trc, splits, ksteps, split, tr * Core::kRows, tc * Core::kCols, nullptr, smem);
 }
 
 // dH[idx[i]] = (g/M) (1/S_i) * sum over the ranges of the partial products of dense row i, in
 // range order.  Chunks whose contraction was not cut were written by dhidden_kernel itself.
+// loss (the last chunk of a call that wants it): the workgroup behind the `rows` makes the loss, which costs a call of
+// one chunk nothing here and 4 us as a launch.
 __global__ __launch_bounds__(256) void dhidden_reduce_kernel(const float* __restrict__ part, int H,
                                                              const int32_t* __restrict__ idx,
                                                              const ChunkInfo* __restrict__ info,
                                                              const Header* __restrict__ hdr,
                                                              const float* __restrict__ frow,
-                                                             uint16_t* __restrict__ dH) {
+                                                             uint16_t* __restrict__ dH, int rows, const LossParams loss) {
     const int i = blockIdx.x;
+    if (i == rows) {
+        loss_reduce<256>(loss);
+        return;
+    }
     const int splits = info->splits, Trc = info->Trc;
     if (i >= info->Tc || splits <= 1) return;
     const float inv = hdr->inv * frow[i];
@@ -985,6 +1107,21 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void dw_kernel(const DWParams
     else dw_block<KMajorHalfCore>(p, Tkc, left, tr * kBlockR, tc * kBlockC + half * (kBlockC / 2), smem);
 }
 
+// The same in small blocks.
+template <class Core>
+__global__ __launch_bounds__(Core::kThreads) void dw_small_kernel(const DWParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t left = p.hdr->n_valid - p.row0;
+    const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
+    if (Tkc == 0 && !p.out.first) return;
+    const PatchGrid pg = {(p.H + Core::kRows - 1) / Core::kRows, (p.V + Core::kCols - 1) / Core::kCols, p.PR, p.PC};
+    const int number = block_of_workgroup(blockIdx.x, pg.blocks(), false);
+    if (number < 0) return;
+    int tr, tc;
+    block_at(pg, number, false, tr, tc);
+    dw_block<Core>(p, Tkc, left, tr * Core::kRows, tc * Core::kCols, smem);
+}
+
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
@@ -1001,8 +1138,22 @@ static int prepare_kernels_on_current_device() {
     acc(allow_big_lds(logits_kernel<true, MODE_FWD, true>));
     acc(allow_big_lds(logits_kernel<false, MODE_FUSED, true>));
     acc(allow_big_lds(logits_kernel<true, MODE_FUSED, true>));
+    acc(allow_big_lds(logits_small_kernel<false, MODE_FWD, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<true, MODE_FWD, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<false, MODE_FUSED, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<true, MODE_FUSED, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<false, MODE_BWD, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<true, MODE_BWD, false>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<false, MODE_FWD, true>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<true, MODE_FWD, true>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<false, MODE_FUSED, true>, LogitsSmallCore::kLds));
+    acc(allow_big_lds(logits_small_kernel<true, MODE_FUSED, true>, LogitsSmallCore::kLds));
     acc(allow_big_lds(dhidden_kernel));
+    acc(allow_big_lds(dhidden_small_kernel<RingCoreT<4>>, RingCoreT<4>::kLds));
+    acc(allow_big_lds(dhidden_small_kernel<RingCoreT<8>>, RingCoreT<8>::kLds));
     acc(allow_big_lds(dw_kernel));
+    acc(allow_big_lds(dw_small_kernel<KMajorSplitT<2>>, KMajorSplitT<2>::kLds));
+    acc(allow_big_lds(dw_small_kernel<KMajorSplitT<4>>, KMajorSplitT<4>::kLds));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -1105,6 +1256,16 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
 // number of rows that take part from the device and surplus blocks leave at once.
 template <int MODE, bool REDO>
 static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
+    // (small blocks: 128 columns only, a group of the softmax partials)
+    if (small_blocks(Tr, lp.Vp, LogitsSmallCore::kCols) <= kRound) {
+        const PatchGrid pg = choose_patches(Tr / LogitsSmallCore::kRows, lp.Vp / LogitsSmallCore::kCols);
+        lp.PR = pg.PR; lp.PC = pg.PC;
+        const dim3 grid((unsigned)grid_for_blocks(pg.blocks())), threads(LogitsSmallCore::kThreads);
+        constexpr int lds = LogitsSmallCore::kLds;
+        if (ktail) hipLaunchKernelGGL((logits_small_kernel<true, MODE, REDO>), grid, threads, lds, s, lp);
+        else hipLaunchKernelGGL((logits_small_kernel<false, MODE, REDO>), grid, threads, lds, s, lp);
+        return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+    }
     const PatchGrid pg = choose_patches(Tr / kBlockR, lp.Vp / kBlockC);
     lp.PR = pg.PR; lp.PC = pg.PC;
     const int grid = grid_for_blocks(pg.blocks());
@@ -1175,7 +1336,10 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     const int64_t T = P.tile < P.N ? P.tile : P.N;
     const int sum_mode = (P.flags & ALST_FLAG_REDUCE_SUM) ? 1 : 0;
 
-    if (P.N <= kIndexRows) {
+    const bool gather_indexes = P.N <= kGatherIndexRows && chunk_plan(L, P.N, P.H, P.V, 0, false).rows == P.N;
+    if (gather_indexes) {
+        // (gather_rows_kernel numbers the rows)
+    } else if (P.N <= kIndexRows) {
         hipLaunchKernelGGL(index_rows_kernel, dim3(1), dim3(kScanThreads), 0, s, P.labels, (int)P.N,
                            P.ignore_index, V, P.grad_loss, sum_mode, idx, do_fwd ? lse_buf : nullptr,
                            do_fwd ? loss_rows : nullptr, hdr, P.n_valid_out);
@@ -1200,12 +1364,9 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     // A hidden size that ends inside a block: dHidden and dW read the last rows of W transposed / columns
     // of the dense hidden rows in place of the missing ones and discard the results; a vocabulary that
     // is not whole k-steps: dZ and W transposed are zero up to whole k-steps.
-    if (do_bwd) {
-        ProfScope small_(PROF_OTHER, s);
-        const Transposes ts = {{{P.W, V, H, H, wt, Vp}}};
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
-        ALST_HIP(hipGetLastError());
-    }
+    const Transpose transpose = {P.W, do_bwd ? V : 0, do_bwd ? H : 0, H, wt, Vp};
+    const LossParams loss = {loss_rows, P.N, hdr, sum_mode, P.loss_out};
+    bool loss_made = false;
 
     // The host does not know M: it walks the chunks of N rows, the most there can be; the kernels of
     // a chunk beyond the dense rows find Tc = 0 on the device and leave at once.
@@ -1232,7 +1393,19 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
             int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
             if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
-            hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(Tr + zero_blocks)), dim3(256), 0, s, gp);
+            gp.zero_blocks = zero_blocks;
+            gp.hdr_out = hdr; gp.idx_out = idx; gp.lse = do_fwd ? lse_buf : nullptr;
+            gp.loss_rows = do_fwd ? loss_rows : nullptr; gp.n_valid_out = P.n_valid_out;
+            gp.grad_loss = P.grad_loss; gp.sum_mode = sum_mode;
+            int64_t pieces = first == 0 ? transpose.pieces() : 0;
+            if (pieces > kGridBlocks - Tr - zero_blocks) {         // more than a launch holds: one of its own
+                hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)pieces), dim3(256), 0, s, Transposes{{transpose}});
+                ALST_HIP(hipGetLastError());
+                pieces = 0;
+            }
+            const dim3 grid((unsigned)(Tr + zero_blocks + pieces));
+            if (gather_indexes) hipLaunchKernelGGL(gather_rows_kernel<true>, grid, dim3(256), 0, s, gp, transpose);
+            else hipLaunchKernelGGL(gather_rows_kernel<false>, grid, dim3(256), 0, s, gp, transpose);
             ALST_HIP(hipGetLastError());
         }
 
@@ -1265,11 +1438,21 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
             const int grid = grid_for_blocks(c.dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
-            hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes,
-                               s, dp);
-            if (c.dh_cut)
-                hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr), dim3(256), 0, s, dp.part, H, idx_t,
-                                   info, hdr, frow, P.dHidden);
+            // (a block is 16 small ones of 64 columns or fewer)
+            const int columns = small_block_columns([&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); });
+            if (columns == 64)
+                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<4>>, dim3(kRound), dim3(RingCoreT<4>::kThreads),
+                                   RingCoreT<4>::kLds, s, dp);
+            else if (columns == 128)
+                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<8>>, dim3(kRound), dim3(RingCoreT<8>::kThreads),
+                                   RingCoreT<8>::kLds, s, dp);
+            else
+                hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes, s, dp);
+            if (c.dh_cut) {
+                loss_made = do_fwd && first + rows == P.N;
+                hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr + loss_made), dim3(256), 0, s, dp.part, H, idx_t,
+                                   info, hdr, frow, P.dHidden, Tr, loss);
+            }
             ALST_HIP(hipGetLastError());
         }
         if (c.group_done) {
@@ -1279,19 +1462,21 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
                       (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
             wp.row0 = c.group0; wp.rows = L.Kg;
             wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
-            const PatchGrid pg = choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
+            const int columns = small_block_columns([&](int64_t cols) { return small_blocks(H, V, cols); });
+            const int block_r = columns ? kSmallRows : kBlockR, block_c = columns ? columns : kBlockC;
+            const PatchGrid pg = choose_patches((H + block_r - 1) / block_r, columns ? (V + columns - 1) / columns : Vp / block_c);
             wp.PR = pg.PR; wp.PC = pg.PC;
-            const int grid = grid_for_blocks(pg.blocks());
+            const dim3 grid((unsigned)grid_for_blocks(pg.blocks())), threads(KMajorCore::kThreads);
             ProfScope ps_(PROF_DW, s);
-            hipLaunchKernelGGL(dw_kernel, dim3(grid), dim3(KMajorCore::kThreads),
-                               kLdsBytes, s, wp);
+            if (columns == 64) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<2>>, grid, threads, KMajorSplitT<2>::kLds, s, wp);
+            else if (columns == 128) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<4>>, grid, threads, KMajorSplitT<4>::kLds, s, wp);
+            else hipLaunchKernelGGL(dw_kernel, grid, threads, kLdsBytes, s, wp);
             ALST_HIP(hipGetLastError());
         }
     }
 
-    if (do_fwd) {
-        hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, loss_rows, P.N, hdr,
-                           sum_mode, P.loss_out);
+    if (do_fwd && !loss_made) {
+        hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(1024), 0, s, loss);
         ALST_HIP(hipGetLastError());
     }
     return ALST_OK;

@@ -1,15 +1,20 @@
 """Launches in small blocks of 64 x 64 or 64 x 128: the counts at which they begin and end, extents that end inside a
-block, contractions shorter and longer than the ring of stages, and ranges of k that leave a wavefront without steps; next to them, ragged launches just large enough for 256 x 256 blocks.  Against the fp64
+block, contractions shorter and longer than the ring of stages, ranges of k that leave a wavefront without steps, and
+row numbering inside the gather launch; next to them, ragged launches just large enough for 256 x 256 blocks.  Against the fp64
 oracle, bar as in the other parity tests: 2e-2 of max |ref| per output (bf16 rounding of intermediates and
 outputs, 2^-9 relative each; the order of the fp32 sums is far below that)."""
+import numpy as np
 import pytest
 
+from oracle import tiled_ce_oracle as orc
 from oracle import tiled_linear_oracle as lorc
 from oracle import tiled_mlp_oracle as morc
+from paper_2506_13996_amd import binding as B
 from paper_2506_13996_amd import synth
 from tests import gpu_util as G
 from tests import test_gpu_linear as TL
 from tests import test_gpu_mlp as TM
+from tests.test_gpu_parity import IGN, _check, _oracle, _redo_case
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
@@ -54,3 +59,56 @@ def test_mlp(N, H, I, gated):
     ref = (morc.forward(x, Wg, Wu, Wd, row_block=256), *morc.backward(x, Wg, Wu, Wd, dy, row_block=256))
     for g, r in zip((y, dx, *gW), ref):
         assert G.grad_err(g, r) <= TOL
+
+
+@pytest.mark.parametrize("name,N,H,V,tile,n_valid", [
+    ("gather_numbers_1024_rows", 1024, 256, 2048, 1024, 1000),        # logits: 256 blocks of 64 x 128
+    ("one_row_more", 1025, 256, 2048, 2048, 1000),                    # a launch of its own numbers the rows
+    ("every_row_valid", 1024, 72, 500, 1024, 1024),
+    ("no_row_valid", 700, 64, 300, 1024, 0),
+    ("one_row_valid", 64, 64, 300, 64, 1),
+    ("two_chunks", 1000, 64, 3000, 128, 900),                         # dense rows beyond one chunk
+    ("large_logits_small_gradients", 1000, 136, 6000, 1024, 960),     # dHidden and dW are small ones
+    ("small_logits_large_dw", 128, 2304, 2304, 128, 120),
+    ("vocabulary_ends_before_the_last_small_block", 200, 64, 4097, 256, 200),
+])
+def test_cross_entropy(name, N, H, V, tile, n_valid):
+    wl = synth.custom(name, N, H, V, tile, ignore_frac=0.0, seed=53)
+    h, W, y = synth.make_inputs(wl)
+    y[np.random.default_rng(54).choice(N, N - n_valid, replace=False)] = IGN
+    r = G.run_fused(h, W, y, tile)
+    assert r.n_valid == n_valid and r.status == B.ALST_OK
+    if n_valid == 0:
+        assert r.loss == 0.0 and not r.dH.any() and not r.dW.any() and not r.lse.any()
+        return
+    f, dH, dW = _oracle(h, W, y)
+    _check(r, f, dH, dW, name, valid=(y != IGN))
+    s = G.run_split(h, W, y, tile)
+    assert s.status_bwd == B.ALST_OK and s.loss_bits == r.loss_bits
+    _check(s, f, dH, dW, name + " split", valid=(y != IGN))
+
+
+def test_a_label_out_of_range_is_reported_where_the_gather_numbers_the_rows():
+    wl = synth.custom("bad", 300, 64, 500, 512, ignore_frac=0.1, seed=55)
+    h, W, y = synth.make_inputs(wl)
+    ok = y.copy()
+    ok[137] = IGN
+    y[137] = 500
+    r = G.run_fused(h, W, y, 512)
+    assert r.status == B.ALST_ERR_LABEL_RANGE and r.n_valid == int((ok != IGN).sum())
+    f, dH, dW = _oracle(h, W, ok)
+    r.status = B.ALST_OK
+    _check(r, f, dH, dW, "label out of range", valid=(ok != IGN))
+
+
+def test_second_pass_in_large_blocks():
+    """The second logits pass for some rows of a chunk, at a size beyond the small blocks."""
+    N, H, V = 640, 64, 6000
+    assert small_columns(768, 6144) == 0
+    wl = synth.custom("redo", N, H, V, 1024, ignore_frac=0.1, seed=56)
+    h, _, y = synth.make_inputs(wl)
+    W = synth.normal_bf16(V, H, 0.2, 57, synth.STREAM_W)
+    hm = orc.bf16_bits_to_f64(h).copy()
+    hm[::3] *= 40.0
+    f = _redo_case("mixed, large blocks", synth.f32_to_bf16_bits(hm.astype(np.float32)), W, y, 1024)
+    assert (np.abs(f["lse"]) > 90.0)[::3][(y != IGN)[::3]].all()
