@@ -758,61 +758,39 @@ struct LogitsParams {
 };
 
 // r = token row of the chunk (MFMA lane dimension), c = vocabulary id (register dimension).
-// KTAIL: the hidden size is not whole k-steps.
 // REDO: the second pass over a chunk, for the rows whose first-pass sums left the safe range; its
 // workgroups leave at once unless row_finish flagged the chunk, and rows that are not marked keep
 // what the first pass wrote.
-// Core: DirectCore for a block, HalfCore for one half of its rows, RingCoreT<8> for a small one.
-// warm: the block's warm-up row (large blocks).
-template <class Core, bool KTAIL, int MODE, bool REDO>
-__device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, int Trc, int r0, int c0,
-                                             const uint16_t* warm, unsigned char* smem) {
+// tw: the wavefront's LDS turn-around area, kTile rows.
+template <class Core, int MODE, bool REDO>
+__device__ __forceinline__ void logits_epilogue(const LogitsParams& p, typename Core::acc_t (&acc)[Core::kMT][Core::kNT],
+                                                int T_cur, int r0, int c0, unsigned char* tw) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     static_assert(Core::kWaveC == kGroupC, "a wavefront's c are one group of the softmax partials");
-    if (r0 >= T_cur) return;        // (a second half of padding rows: the consumers' k-steps end before it)
     constexpr int kRegs = 4 * Core::kRuns;          // accumulator registers of a tile
-
-    typename Core::acc_t acc[kMT][kNT];
-    zero_acc<Core>(acc);
-
-    const uint16_t* const hidden_t = p.hidden_t;
-    Core::template gemm<KTAIL>({hidden_t, p.Hk, p.W, p.H, Trc, p.V, p.H, r0, c0, warm, kBlockK, nullptr}, smem,
-                               acc);
-
     const typename Core::Lane lp;
+    // What the rows need from memory is asked for at once: tile by tile, behind the tile's stores, it was eight
+    // times a load's latency (5 % of the kernel at H = 1600, 2.5 % at 4096).  The first pass of the forward modes
+    // has ref = 0 everywhere.
+    constexpr bool kRef = MODE == MODE_BWD || REDO;
+    int y[kNT];
+    float ref[kNT];
+    bool act[kNT];                                        // this pass writes the row's results
 #pragma unroll
     for (int nt = 0; nt < kNT; ++nt) {
         const int i = r0 + lp.r(nt);
-        const bool rowok = i < T_cur;
-        const bool act = !REDO || p.rowstate[i] != 0;     // this pass writes row i's results
-        {                               // columns beyond the vocabulary (last column block)
-            if (c0 + kBlockC > p.V) {
+        y[nt] = p.labels_t[i];                            // (padding rows: -1)
+        ref[nt] = kRef ? p.ref[i] : 0.f;
+        act[nt] = !REDO || p.rowstate[i] != 0;
+    }
 #pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
+    for (int nt = 0; nt < kNT; ++nt) {
+        if (c0 + kBlockC > p.V) {                         // columns beyond the vocabulary (last column block)
 #pragma unroll
-                    for (int j = 0; j < kRegs; ++j)
-                        if (c0 + lp.c(mt, j >> 2) + (j & 3) >= p.V) acc[mt][nt][j] = -INFINITY;
-            }
-        }
-        const float ref = p.ref[i];
-        {
-            // label logit: exactly one lane of one block holds column y of row i.  Few wavefronts
-            // hold any (a tile's rows x 128 of V columns), so the search sits behind a uniform branch.
-            const int y = rowok && act ? p.labels_t[i] : -1;
-            const unsigned d = (unsigned)(y - (c0 + lp.wc * kGroupC));
-            const bool mine = y >= 0 && d < (unsigned)kGroupC &&
-                              ((d >> 2) & (unsigned)(Core::kGroups - 1)) == (unsigned)lp.grp;
-            if (__ballot(mine) != 0ull) {
-                if (mine) {
-                    float zl = 0.f;
+            for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll
-                    for (int mt = 0; mt < kMT; ++mt)
-#pragma unroll
-                        for (int j = 0; j < kRegs; ++j)
-                            if (d == (unsigned)(lp.cw(mt, j >> 2) + (j & 3))) zl = acc[mt][nt][j];
-                    p.zlabel[i] = zl;
-                }
-            }
+                for (int j = 0; j < kRegs; ++j)
+                    if (c0 + lp.c(mt, j >> 2) + (j & 3) >= p.V) acc[mt][nt][j] = -INFINITY;
         }
         // e = exp(z - ref) as exp2(z * log2(e) - ref * log2(e)); summed in fp32, stored as bf16.
         // In the accumulators a lane holds 4 consecutive columns of one row, so a direct store
@@ -820,8 +798,7 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
         // its kTile x 128 piece around in LDS (free once the k-loop is over; each wavefront has its
         // own region and LDS serves a wavefront's accesses in order, so no barrier is needed) and
         // stores whole 256-byte row segments.
-        const float ref2 = ref * kLog2e;
-        unsigned char* const tw = smem + (threadIdx.x >> 6) * (32 * kTurnPitch);
+        const float ref2 = ref[nt] * kLog2e;
         float s = 0.f;
 #pragma unroll
         for (int mt = 0; mt < kMT; ++mt)
@@ -830,7 +807,8 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
                 bf16x4_t o;
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    const float e = __builtin_amdgcn_exp2f(fmaf(acc[mt][nt][q * 4 + x], kLog2e, -ref2));
+                    const float z = acc[mt][nt][q * 4 + x];
+                    const float e = __builtin_amdgcn_exp2f(kRef ? fmaf(z, kLog2e, -ref2) : z * kLog2e);
                     s += e;
                     o[x] = (__bf16)e;
                 }
@@ -851,9 +829,26 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
             }
             wave_sync<REDO>();
         }
+        // label logit: exactly one lane of one block holds column y of row i.  Few wavefronts
+        // hold any (a tile's rows x 128 of V columns), so the search sits behind a uniform branch.
+        const unsigned d = (unsigned)(y[nt] - (c0 + lp.wc * kGroupC));
+        const bool mine = act[nt] && y[nt] >= 0 && d < (unsigned)kGroupC &&
+                          ((d >> 2) & (unsigned)(Core::kGroups - 1)) == (unsigned)lp.grp;
+        if (__ballot(mine) != 0ull) {
+            if (mine) {
+                float zl = 0.f;
+#pragma unroll
+                for (int mt = 0; mt < kMT; ++mt)
+#pragma unroll
+                    for (int j = 0; j < kRegs; ++j)
+                        if (d == (unsigned)(lp.cw(mt, j >> 2) + (j & 3))) zl = acc[mt][nt][j];
+                p.zlabel[r0 + lp.r(nt)] = zl;
+            }
+        }
         if (MODE != MODE_BWD) {
+            const int i = r0 + lp.r(nt);
             s = groups_sum<Core::kGroups>(s);
-            if (lp.grp == 0 && act) p.ps[((c0 + lp.wc * kGroupC) >> 7) * p.Rc + i] = s;
+            if (lp.grp == 0 && act[nt]) p.ps[((c0 + lp.wc * kGroupC) >> 7) * p.Rc + i] = s;
             if (!REDO) {
                 // A row whose total will leave [kSumLo, kSumHi] needs its exact maximum for the second
                 // pass.  The group that holds it then has s > kSumHi / 2^17 groups / 128 columns, or
@@ -871,6 +866,19 @@ __device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, i
             }
         }
     }
+}
+
+// One block.  KTAIL: the hidden size is not whole k-steps.
+// Core: DirectCore for a block, HalfCore for one half of its rows, RingCoreT<8> for a small one.
+// warm: the block's warm-up row (large blocks).
+template <class Core, bool KTAIL, int MODE, bool REDO>
+__device__ __forceinline__ void logits_block(const LogitsParams& p, int T_cur, int Trc, int r0, int c0,
+                                             const uint16_t* warm, unsigned char* smem) {
+    if (r0 >= T_cur) return;        // (a second half of padding rows: the consumers' k-steps end before it)
+    typename Core::acc_t acc[Core::kMT][Core::kNT];
+    zero_acc<Core>(acc);
+    Core::template gemm<KTAIL>({p.hidden_t, p.Hk, p.W, p.H, Trc, p.V, p.H, r0, c0, warm, kBlockK, nullptr}, smem, acc);
+    logits_epilogue<Core, MODE, REDO>(p, acc, T_cur, r0, c0, smem + (threadIdx.x >> 6) * (Core::kTile * kTurnPitch));
 }
 
 template <bool KTAIL, int MODE, bool REDO>
@@ -973,12 +981,20 @@ __device__ __forceinline__ void dhidden_block(const DHiddenParams& p, int T_cur,
         return;
     }
     const float inv = p.hdr->inv;
+    float frow[kNT];                                // (all asked for at once, see logits_epilogue)
+    int token[kNT];
+#pragma unroll
+    for (int nt = 0; nt < kNT; ++nt) {
+        const int i = r0 + lp.r(nt) < T_cur ? r0 + lp.r(nt) : T_cur - 1;
+        frow[nt] = p.frow[i];
+        token[nt] = p.idx[i];
+    }
 #pragma unroll
     for (int nt = 0; nt < kNT; ++nt) {
         const int i = r0 + lp.r(nt);
         if (i >= T_cur) continue;
-        const float sc = inv * p.frow[i];
-        uint16_t* row = p.dH_t + (int64_t)p.idx[i] * p.H;
+        const float sc = inv * frow[nt];
+        uint16_t* row = p.dH_t + (int64_t)token[nt] * p.H;
 #pragma unroll
         for (int mt = 0; mt < kMT; ++mt)
 #pragma unroll

@@ -353,6 +353,18 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
     const int gc = (c0 >> 1) + lp.wc * kCols + lcol * 8;           // this lane's 8 columns of I
     const bool col_ok = !CHECK || gc + 8 <= p.I;
     const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+    // (da is asked for at once: tile by tile, behind the tile's stores, it was eight times a load's latency)
+    u32x4_t da[BWD ? kNT : 1][kTile / kRowsAtOnce];
+    if (BWD) {
+#pragma unroll
+        for (int nt = 0; nt < kNT; ++nt)
+#pragma unroll
+            for (int it = 0; it < kTile / kRowsAtOnce; ++it) {
+                const int row = r0 + lp.rbase(nt) + it * kRowsAtOnce + lrow;
+                const bool ok = !CHECK || (row < p.rows_x && col_ok);
+                da[BWD ? nt : 0][it] = ok ? *reinterpret_cast<const u32x4_t*>(p.da + (int64_t)row * p.I + gc) : zero4;
+            }
+    }
 #pragma unroll
     for (int nt = 0; nt < kNT; ++nt) {
         const int row0 = r0 + lp.rbase(nt);
@@ -378,10 +390,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
 #pragma unroll
             for (int it = 0; it < kTile / kRowsAtOnce; ++it) {
                 const int row = it * kRowsAtOnce + lrow;
-                const bool ok = !CHECK || (row0 + row < p.rows_x && col_ok);
-                const u32x4_t val = ok ? *reinterpret_cast<const u32x4_t*>(p.da + (int64_t)(row0 + row) * p.I + gc)
-                                       : zero4;
-                *reinterpret_cast<u32x4_t*>(tw + row * kTurnPitch + lcol * 16) = val;
+                *reinterpret_cast<u32x4_t*>(tw + row * kTurnPitch + lcol * 16) = da[BWD ? nt : 0][it];
             }
             wave_sync<CHECK>();
 #pragma unroll
@@ -398,7 +407,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const float g = acc[mt][nt][q * 4 + x], u = acc[mt + kHalfMT][nt][q * 4 + x];
-                    const float sg = 1.f / (1.f + __expf(-g));
+                    const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-g));      // (1 ulp; 0 behind an infinity)
                     const float silu = g * sg;
                     oa[mt][q][x] = (__bf16)(silu * u);
                     if (BWD) {
