@@ -149,6 +149,21 @@ __host__ __device__ __forceinline__ Halving halve_last_round(int blocks) {
     return {full, full + 2 * left};
 }
 
+// Whether a launch of k-contiguous products runs on persistent workgroups that fetch their next block early
+// (DirectCore::Pipe).  K: whole k-steps, at least the 4 that a chain needs.  A chain's start, its larger LDS and its last,
+// unused fetch cost a launch of one or two rounds more than they save, unless the contraction is long; us of a
+// product without / with:
+//   K = 256: 128 blocks 9.5 / 9.8, 256: 14.6 / 15.5, 384: 22.0 / 22.4, 576: 38.8 / 37.6, 2048: 101 / 85
+//   K = 1024: 128 blocks 18.6 / 19.1, 256: 31.2 / 30.6, 384: 49.2 / 49.1, 576: 78.0 / 77.7, 2048: 234 / 220
+//   K = 4096: 128 blocks 59.2 / 59.3, 256: 97.2 / 95.2, 576: 232 / 229, 2048: 749 / 740
+// Kernels with a long epilogue (softmax, SwiGLU) need more rounds: MLP forward 4096 x 2048 x 2048 (256 gate / up blocks)
+// 84.4 / 86.9, 3000 x 2048 x 4096 (384) 138 / 140, 10000 x 2048 x 8192 (2560) 821 / 815, x 256 x 8192 255 / 247;
+// cross-entropy steps 8000 x 512 x 5000 (640) 272 / 277, 3001 x 1600 x 50257 (2167) 1796 / 1764.
+inline bool chain_pays(int64_t blocks, int64_t K, bool long_epilogue) {
+    if (K % kBlockK != 0 || K < 4 * kBlockK) return false;
+    return long_epilogue ? blocks > 4 * kRound : blocks > 2 * kRound || (blocks >= kRound && K >= 1024);
+}
+
 // What a launch of `blocks` blocks takes, in 16ths of a round of whole blocks (a last round in halves:
 // 10 / 16, see Halving).
 __host__ __device__ __forceinline__ int64_t rounds16(int64_t blocks, bool halves = true) {
@@ -594,8 +609,8 @@ struct DirectCoreT {
     // kWaveR x 128.
     struct Lane {
         int lane, grp, lrow, wr, wc;
-        __device__ __forceinline__ Lane() {
-            const int tid = threadIdx.x;
+        // tid: threadIdx.x
+        __device__ __forceinline__ Lane(int tid = threadIdx.x) {
             lane = tid & 63;
             grp = lane >> 4;
             lrow = lane & 15;
@@ -642,8 +657,7 @@ struct DirectCoreT {
     //    operands travel while the epilogue runs and no block but the first waits for a
     //    prologue.  The last block of a chain names itself as the block after it (the fetch is
     //    then wasted; finish() waits for it so that nothing is in flight when the workgroup
-    //    ends).  Every block of a chain must have the same K, a multiple of 128 (the stages
-    //    alternate: a block's step 0 must meet stage 0) and >= 256.  Between start() and
+    //    ends).  Every block of a chain must have the same K, a multiple of 64 and >= 256.  Between start() and
     //    finish() the first kLdsBytes of LDS belong to the chain: an epilogue that turns data
     //    around in LDS does it behind them.
     template <bool KTAIL>
@@ -658,12 +672,14 @@ struct DirectCoreT {
         const uint16_t* warm;
         int64_t warm_stride;
         int KT_, klast;
+        int base;                      // the stage of the block's k-step 0 (0, but for chains of an odd number of k-steps)
         // MFMA operands of the two k-slices of a step: fy[s][t], fx[s][t] for slice s
         bf16x8_t fy[2][8], fx[2][NT];
 
         __device__ __forceinline__ explicit Pipe(unsigned char* smem_) : smem(smem_) {
             const int tid = threadIdx.x, lane = tid & 63;
             w = uniform(tid >> 6);
+            base = 0;
             const int wr = w & 1, wc = w >> 1;
             const int l15 = lane & 15, g = lane >> 4;
             // One DMA instruction moves 8 rows x 128 bytes: lane -> (row = lane / 8, LDS chunk slot
@@ -766,7 +782,7 @@ struct DirectCoreT {
         // back to back and the matrix pipe idles behind their issue).  Inside a slot the MFMAs
         // go first (the sched_group_barrier calls): the wait the compiler puts before a slot's
         // first MFMA then covers reads issued long ago, not the slot's own (1.5 % of the kernel).
-        // kt: the step computed (its stage is kt & 1).  LOADS: the DMA of step dkt + 2 of the
+        // kt: the step computed (its stage is (kt + base) & 1).  LOADS: the DMA of step dkt + 2 of the
         // targeted block is issued (dkt = kt, or kt - KT when the target is the next block of a
         // chain; TAIL: that is the block's last step).  NEXT: step kt + 1 exists.  Steps without LOADS
         // leave no DMA in flight.
@@ -774,7 +790,7 @@ struct DirectCoreT {
         template <bool LOADS, bool NEXT, bool TAIL = false>
         __device__ __forceinline__ void kstep(acc_t (&acc)[kMT][kNT], int kt, int dkt, bool behind,
                                               const Block* ahead) {
-            const int cur_stage = kt & 1;
+            const int cur_stage = (kt + base) & 1;
             unsigned char* const xs = smem + cur_stage * kTileBytes + w * (NT * 1024);
             unsigned char* const ys = smem + 2 * kTileBytes + cur_stage * kTileBytes + w * 8192;
             if constexpr (NT == 4) {
@@ -912,7 +928,7 @@ struct DirectCoreT {
             // every wavefront's part of k-step 0 has landed, and all are done with the block before
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-            for (int item = 0; item < 8 + NT; ++item) read_item(0, 0, item);
+            for (int item = 0; item < 8 + NT; ++item) read_item(base, 0, item);
             int kt = 0;
             for (; kt + 2 + kWarmAhead < KT; ++kt) kstep<true, true>(acc, kt, kt, kt > 0, nullptr);
             // (the warm-up loads of these steps are for the first steps of `next`)
@@ -922,6 +938,7 @@ struct DirectCoreT {
             kstep<true, false>(acc, kt + 1, -1, true, nullptr);
             // all but the 16 DMA instructions of the last half step and the warm-up load behind them
             asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
+            base ^= KT & 1;
         }
         __device__ __forceinline__ void finish() { stage_barrier(false); }
     };
@@ -995,11 +1012,11 @@ struct RingCoreT {
     struct Lane {
         int lane, grp, lrow, wr;
         static constexpr int wc = 0;
-        __device__ __forceinline__ Lane() {
-            lane = threadIdx.x & 63;
+        __device__ __forceinline__ Lane(int tid = threadIdx.x) {
+            lane = tid & 63;
             grp = lane >> 4;
             lrow = lane & 15;
-            wr = threadIdx.x >> 6;
+            wr = tid >> 6;
         }
         __device__ __forceinline__ int r(int) const { return wr * kWaveR + lrow; }
         __device__ __forceinline__ int rbase(int) const { return wr * kWaveR; }

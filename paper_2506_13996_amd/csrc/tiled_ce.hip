@@ -764,11 +764,11 @@ struct LogitsParams {
 // tw: the wavefront's LDS turn-around area, kTile rows.
 template <class Core, int MODE, bool REDO>
 __device__ __forceinline__ void logits_epilogue(const LogitsParams& p, typename Core::acc_t (&acc)[Core::kMT][Core::kNT],
-                                                int T_cur, int r0, int c0, unsigned char* tw) {
+                                                int T_cur, int r0, int c0, unsigned char* tw, int tid = threadIdx.x) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     static_assert(Core::kWaveC == kGroupC, "a wavefront's c are one group of the softmax partials");
     constexpr int kRegs = 4 * Core::kRuns;          // accumulator registers of a tile
-    const typename Core::Lane lp;
+    const typename Core::Lane lp(tid);
     // What the rows need from memory is asked for at once: tile by tile, behind the tile's stores, it was eight
     // times a load's latency (5 % of the kernel at H = 1600, 2.5 % at 4096).  The first pass of the forward modes
     // has ref = 0 everywhere.
@@ -898,6 +898,64 @@ __global__ __launch_bounds__(DirectCore::kThreads) void logits_kernel(const Logi
     const uint16_t* warm = warm_row(p.PR, p.PC, p.hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V);
     if (half < 0) logits_block<DirectCore, KTAIL, MODE, REDO>(p, T_cur, Trc, r0, c0, warm, smem);
     else logits_block<HalfCore, KTAIL, MODE, REDO>(p, T_cur, Trc, r0 + half * (kBlockR / 2), c0, warm, smem);
+}
+
+// The first pass on persistent workgroups that fetch their next block's first two k-steps while the current block's
+// last two and its epilogue run (DirectCore::Pipe); a last round in halves comes behind the chain.  The
+// hidden size is whole k-steps and at least 4 of them.
+template <int MODE>
+__global__ __launch_bounds__(DirectCore::kThreads) void logits_chain_kernel(const LogitsParams p) {
+    typedef DirectCore Core;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int T_cur = uniform(p.info->Tc), Trc = uniform(p.info->Trc);
+    if (T_cur == 0) return;
+    const PatchGrid pg = {Trc / kBlockR, p.Vp / kBlockC, p.PR, p.PC};
+    const Halving last = halve_last_round(pg.blocks());
+    const bool rows = by_rows(pg, p.H);
+    const int whole = (last.full + kRound - 1) / kRound * kRound;          // the chains' workgroup numbers
+    auto next_block = [&](int bid, Core::Block& blk) {
+        for (; bid < whole; bid += gridDim.x) {
+            const int number = block_of_workgroup(bid, last.numbers, rows);
+            if (number < 0) continue;
+            int tr, tc;
+            block_at(pg, number, rows, tr, tc);
+            const int r0 = tr * kBlockR, c0 = tc * kBlockC;
+            blk = {uniform(p.hidden_t), p.Hk, uniform(p.W), p.H, Trc, p.V, p.H, uniform(r0), uniform(c0),
+                   warm_row(p.PR, p.PC, p.hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V), kBlockK, nullptr};
+            return uniform(bid);
+        }
+        return -1;
+    };
+    Core::Block cur, nxt;
+    int bid = next_block(blockIdx.x, cur);
+    Core::Pipe<false> pipe(smem);
+    if (bid >= 0) pipe.start(cur);
+    const bool chain = bid >= 0;
+    while (bid >= 0) {
+        const int nbid = next_block(bid + gridDim.x, nxt);
+        if (nbid < 0) nxt = cur;        // the last block: the chain's fetch goes to this block again, unused
+        typename Core::acc_t acc[Core::kMT][Core::kNT];
+        zero_acc<Core>(acc);
+        pipe.run(cur, nxt, acc);
+        // (what depends on the lane alone is worked out again for every block: kept over the blocks it is spilled)
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        logits_epilogue<Core, MODE, false>(p, acc, T_cur, cur.r0, cur.c0,
+                                           smem + kChainTurnOffset + (tid >> 6) * (Core::kTile * kTurnPitch), tid);
+        cur = nxt;
+        bid = nbid;
+    }
+    if (chain) pipe.finish();
+    for (bid = last.full + blockIdx.x; bid < last.numbers + kRound; bid += gridDim.x) {
+        const int number = block_of_workgroup(bid, last.numbers, rows);
+        if (number < last.full) continue;              // (none, or a whole block: the chain's)
+        int tr, tc, half;
+        block_at(pg, last.block(number, half), rows, tr, tc);
+        const int r0 = tr * kBlockR, c0 = tc * kBlockC;
+        const uint16_t* warm = warm_row(p.PR, p.PC, p.hidden_t, p.Hk, r0, tr, p.W, p.H, c0, tc, nullptr, Trc, p.V);
+        __syncthreads();                // LDS is free
+        logits_block<HalfCore, false, MODE, false>(p, T_cur, Trc, r0 + half * (kBlockR / 2), c0, warm, smem);
+    }
 }
 
 // The same in small blocks.
@@ -1154,6 +1212,9 @@ static int prepare_kernels_on_current_device() {
     acc(allow_big_lds(logits_kernel<true, MODE_FWD, true>));
     acc(allow_big_lds(logits_kernel<false, MODE_FUSED, true>));
     acc(allow_big_lds(logits_kernel<true, MODE_FUSED, true>));
+    acc(allow_big_lds(logits_chain_kernel<MODE_FWD>, kChainLdsBytes));
+    acc(allow_big_lds(logits_chain_kernel<MODE_FUSED>, kChainLdsBytes));
+    acc(allow_big_lds(logits_chain_kernel<MODE_BWD>, kChainLdsBytes));
     acc(allow_big_lds(logits_small_kernel<false, MODE_FWD, false>, LogitsSmallCore::kLds));
     acc(allow_big_lds(logits_small_kernel<true, MODE_FWD, false>, LogitsSmallCore::kLds));
     acc(allow_big_lds(logits_small_kernel<false, MODE_FUSED, false>, LogitsSmallCore::kLds));
@@ -1285,7 +1346,10 @@ static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
     const PatchGrid pg = choose_patches(Tr / kBlockR, lp.Vp / kBlockC);
     lp.PR = pg.PR; lp.PC = pg.PC;
     const int grid = grid_for_blocks(pg.blocks());
-    if (ktail)
+    if (!REDO && chain_pays(pg.blocks(), lp.H, true))
+        hipLaunchKernelGGL((logits_chain_kernel<MODE>), dim3((unsigned)std::min(grid, persistent_grid())),
+                           dim3(DirectCore::kThreads), kChainLdsBytes, s, lp);
+    else if (ktail)
         hipLaunchKernelGGL((logits_kernel<true, MODE, REDO>), dim3(grid),
                            dim3(DirectCore::kThreads), kLdsBytes, s, lp);
     else

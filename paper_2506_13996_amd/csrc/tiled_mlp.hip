@@ -259,7 +259,7 @@ __global__ __launch_bounds__(Core::kThreads) void linear_small_kernel(const Line
 // linear_kernel, so the 32 workgroups of an XCD still share a patch) and fetches the first two
 // k-steps of its next block while the current block's last two k-steps and epilogue run
 // (DirectCore::Pipe).  total = the workgroup numbers of whole blocks; a last round in halves
-// comes behind the chain.  Every product of the launch has the same K, a multiple of 128 and >= 256.
+// comes behind the chain.  Every product of the launch has the same K, a multiple of 64 and >= 256.
 // GUARD: some product's rows or columns are not whole blocks.  HALVES: there is a last round in halves; a launch
 // of whole rounds is 0.3 to 0.7 % faster without that code in it (98304 x 2048 x 8192: 2409 -> 2393 us).
 template <bool GUARD, bool HALVES>
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(Core::kThreads) void gated_small_kernel(const Gated
     gated_epilogue<Core, BWD, true>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
 }
 
-// The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 128 and >= 256.
+// The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 64 and >= 256.
 // total = the workgroup numbers of whole blocks.  GUARD: rows_x or I is not whole blocks.
 template <bool BWD, bool GUARD>
 __global__ __launch_bounds__(DirectCore::kThreads) void gated_chain_kernel(const GatedParams p, int total) {
@@ -662,8 +662,7 @@ static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
     const int64_t total = number_blocks(b, ps, n, kBlockR, kBlockC);
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     bool guard = false, ktail = false;
-    // persistent workgroups that fetch their next block early: one K, whole pairs of k-steps
-    bool chain = !ps[0].y_kmajor && ps[0].K % (2 * kBlockK) == 0 && ps[0].K >= 4 * kBlockK;
+    bool chain = !ps[0].y_kmajor && chain_pays(total, ps[0].K, false);          // (of one K)
     for (int i = 0; i < n; ++i) {
         const LinearParams& p = ps[i];
         guard = guard || p.rows_x % kBlockR != 0 || p.rows_y % kBlockC != 0;
@@ -788,8 +787,7 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.rows = by_rows(gp.grid, gp.K);
     const int blocks = grid_for_blocks(gp.grid.blocks()), whole = grid_for_blocks(gp.last.full);
     const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
-    // persistent workgroups that fetch their next block early: whole pairs of k-steps
-    const bool chain = P.H % (2 * kBlockK) == 0 && P.H >= 4 * kBlockK;
+    const bool chain = chain_pays(gp.grid.blocks(), P.H, true);
     const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
     const dim3 threads(DirectCore::kThreads);
     ProfScope pr(PROF_MLP_LINEAR, s);
