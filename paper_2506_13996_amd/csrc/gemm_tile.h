@@ -999,14 +999,14 @@ __device__ __forceinline__ void ring_barrier(int steps) {
 // Both operands k-contiguous, 64 (r) x 16 MT (c).  The four wavefronts lie along r, 16 rows each.
 template <int MT>
 struct RingCoreT {
-    static_assert(MT == 4 || MT == 8, "64 or 128 c");
+    static_assert(MT == 2 || MT == 4 || MT == 8, "32, 64 or 128 c");
     static constexpr int kThreads = 256;
     static constexpr int kMT = MT, kNT = 1;
     static constexpr int kWaveR = 16, kWaveC = 16 * MT, kRows = 4 * kWaveR, kCols = kWaveC;
     typedef f32x4_t acc_t;
     static constexpr int kTile = 16, kRuns = 1, kGroups = 4;
     static constexpr int kXBytes = kRows * 128, kStage = kXBytes + kCols * 128;
-    static constexpr int kStages = MT == 4 ? 8 : 5, kLds = kStages * kStage;      // 128 KB, 120 KB
+    static constexpr int kStages = MT == 8 ? 5 : 8, kLds = kStages * kStage;      // 96, 128, 120 KB
     typedef typename DirectCoreT<8>::Block Block;
 
     struct Lane {

@@ -324,7 +324,9 @@ struct GatedParams {
     const uint16_t* X;       // [rows_x, ldx]   the tile's rows of x
     const uint16_t* Wg;      // [I, ldw]
     const uint16_t* Wu;      // [I, ldw]
-    const uint16_t* da;      // [rows_x, I]     backward; may be `a`
+    const uint16_t* da;      // [rows_x, I]     backward; may be `a`; or null (small blocks):
+    const uint16_t* dy;      // [rows_x, ldx]   da = dy Wdt^T is made here
+    const uint16_t* Wdt;     // [I, ldw]        Wd transposed
     uint16_t* a;             // [rows_x, I]
     uint16_t* dgu;           // [rows_x, 2I]    backward
     int64_t ldx, ldw;
@@ -337,10 +339,12 @@ struct GatedParams {
 // The SwiGLU epilogue of a block whose accumulators hold g (tiles mt < kMT / 2) and u (tile mt + kMT / 2)
 // of the same elements.  CHECK: rows >= rows_x and 8-column chunks beyond I are neither read nor
 // written.  tw: this wavefront's LDS turn-around region (kTile rows of kTurnPitch bytes).
-template <class Core, bool BWD, bool CHECK>
+// OWN_DA: da is the lane's, in dacc (rounded to bf16 here, as it is on its way through memory), not in memory.
+template <class Core, bool BWD, bool CHECK, bool OWN_DA = false>
 __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
                                                const typename Core::acc_t (&acc)[Core::kMT][Core::kNT],
-                                               int r0, int c0, unsigned char* tw) {
+                                               int r0, int c0, unsigned char* tw,
+                                               const typename Core::acc_t (*dacc)[Core::kNT] = nullptr) {
     constexpr int kMT = Core::kMT, kNT = Core::kNT;
     constexpr int kHalfMT = kMT / 2;
     // Per wavefront and accumulator column nt: kTile rows x 64 (32) columns of I.  Everything that goes
@@ -355,7 +359,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
     const u32x4_t zero4 = {0u, 0u, 0u, 0u};
     // (da is asked for at once: tile by tile, behind the tile's stores, it was eight times a load's latency)
     u32x4_t da[BWD ? kNT : 1][kTile / kRowsAtOnce];
-    if (BWD) {
+    if (BWD && !OWN_DA) {
 #pragma unroll
         for (int nt = 0; nt < kNT; ++nt)
 #pragma unroll
@@ -386,7 +390,14 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
             wave_sync<CHECK>();
         };
         bf16x4_t d[kHalfMT][kRuns];
-        if (BWD) {
+        if (BWD && OWN_DA) {
+#pragma unroll
+            for (int mt = 0; mt < kHalfMT; ++mt)
+#pragma unroll
+                for (int q = 0; q < kRuns; ++q)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) d[mt][q][x] = (__bf16)dacc[mt][nt][q * 4 + x];
+        } else if (BWD) {
 #pragma unroll
             for (int it = 0; it < kTile / kRowsAtOnce; ++it) {
                 const int row = it * kRowsAtOnce + lrow;
@@ -459,10 +470,24 @@ __global__ __launch_bounds__(Core::kThreads) void gated_small_kernel(const Gated
     int tr, tc;
     block_at(p.grid, number, false, tr, tc);
     const int r0 = tr * Core::kRows, c0 = tc * Core::kCols;          // c0 / 2 = first of the block's 64 columns of I
+    unsigned char* const tw = smem + (threadIdx.x >> 6) * (Core::kTile * kTurnPitch);
     typename Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
+    if constexpr (BWD) {
+        if (p.dy) {
+            // da of the block's rows and columns of I first: as a launch of its own it was 4 - 5 us more, most of them not
+            // its loads (512 x 256 x 768 forward and backward: 52.4 -> 48.4 us)
+            typedef RingCoreT<Core::kMT / 2> Half;
+            typename Core::acc_t dacc[Half::kMT][Half::kNT];
+            zero_acc<Half>(dacc);
+            Half::template gemm<KTAIL>({p.dy, p.ldx, p.Wdt, p.ldw, p.rows_x, p.I, p.K, r0, c0 / 2, nullptr, 0, nullptr}, smem, dacc);
+            Core::template gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, nullptr, 0, p.Wu}, smem, acc);
+            gated_epilogue<Core, BWD, true, true>(p, acc, r0, c0, tw, dacc);
+            return;
+        }
+    }
     Core::template gemm<KTAIL>({p.X, p.ldx, p.Wg, p.ldw, p.rows_x, p.I, p.K, r0, c0, nullptr, 0, p.Wu}, smem, acc);
-    gated_epilogue<Core, BWD, true>(p, acc, r0, c0, smem + (threadIdx.x >> 6) * (32 * kTurnPitch));
+    gated_epilogue<Core, BWD, true>(p, acc, r0, c0, tw);
 }
 
 // The same on persistent workgroups (see linear_chain_kernel): K = H a multiple of 64 and >= 256.
@@ -772,16 +797,21 @@ static int launch_gated_small(GatedParams gp, bool bwd, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
-// a = silu(x_t Wg^T) * (x_t Wu^T) for `rows` rows of x; backward (da given): also [dg | du].
+static int gated_small_columns(int rows, int64_t I) {
+    return small_block_columns([&](int64_t c) { return small_blocks(rows, 2 * I, c); });
+}
+// a = silu(x_t Wg^T) * (x_t Wu^T) for `rows` rows of x; backward (da given, or dy_t and Wd transposed to make it from
+// if the blocks are small): also [dg | du].
 static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, const uint16_t* da, uint16_t* a,
-                        uint16_t* dgu, hipStream_t s) {
+                        uint16_t* dgu, hipStream_t s, const uint16_t* dy_t = nullptr, const uint16_t* wdt = nullptr) {
     GatedParams gp = {};
+    gp.dy = dy_t; gp.Wdt = wdt;
     gp.X = x_t; gp.ldx = P.H; gp.rows_x = rows; gp.K = (int)P.H;
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
     gp.da = da; gp.a = a; gp.dgu = dgu;
-    const int columns = small_block_columns([&](int64_t c) { return small_blocks(rows, 2 * P.I, c); });
-    if (columns == 64) return launch_gated_small<RingCoreT<4>>(gp, da != nullptr, s);
-    if (columns == 128) return launch_gated_small<RingCoreT<8>>(gp, da != nullptr, s);
+    const int columns = gated_small_columns(rows, P.I);
+    if (columns == 64) return launch_gated_small<RingCoreT<4>>(gp, dgu != nullptr, s);
+    if (columns == 128) return launch_gated_small<RingCoreT<8>>(gp, dgu != nullptr, s);
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
     gp.last = halve_last_round(gp.grid.blocks());
     gp.rows = by_rows(gp.grid, gp.K);
@@ -856,7 +886,10 @@ static int run_mlp_backward(const MlpProblem& P) {
         const uint16_t* x_c = P.x + i0 * P.H;
         const uint16_t* dy_c = P.dy + i0 * P.H;
 
-        {   // da = dy Wd (contraction over H), then g and u again with a, dg, du made in the epilogue
+        if (L.weights_t && gated_small_columns(rows, I)) {
+            rc = launch_gated(P, x_c, rows, nullptr, a_c, dgu_c, s, dy_c, wdt);
+            if (rc != ALST_OK) return rc;
+        } else {   // da = dy Wd (contraction over H), then g and u again with a, dg, du made in the epilogue
             LinearParams lp = {};
             lp.X = dy_c; lp.ldx = H; lp.rows_x = rows; lp.K = H;
             if (L.weights_t) { lp.Y = wdt; lp.ldy = H; lp.rows_y = I; }            // Wd^T [I, H]

@@ -50,6 +50,8 @@ def test_linear(N, K, M, forward, wgrad):
     (300, 64, 1720, 128),
     (1000, 320, 1000, 128),
     (1032, 72, 1032, 0),               # large blocks
+    (500, 320, 448, 64),               # whole k-steps: da is made in the gated launch
+    (1000, 256, 832, 128),
 ])
 def test_mlp(N, H, I, gated):
     assert small_columns(N, 2 * I) == gated
