@@ -1256,11 +1256,11 @@ struct KMajorSplitT {
 };
 
 // ---------------------------------------------------------------------------------------------
-// out[c][r] = in[r][c] (bf16), zeros for rows <= r < the 64 rows of the last piece
+// out[c][r] = in[r][c] (bf16), zeros for rows <= r < fill
 // ---------------------------------------------------------------------------------------------
 // Weights that a product contracts over their row index are transposed once per call, so that
 // the product reads both operands along their rows (DirectCore).  in: [rows, ld_in], cols a
-// multiple of 8, 16-byte aligned rows; out: [cols, ld_out], ld_out >= rows rounded up to 64.  One
+// multiple of 8, 16-byte aligned rows; out: [cols, ld_out], fill >= rows a multiple of 8, at most rows rounded up to 64.  One
 // workgroup of 256 turns a 64 x 64 piece around in LDS; the pieces of the matrices are numbered through
 // (one launch for all: each costs 4.6 us at the smallest sizes).
 struct Transpose {
@@ -1269,6 +1269,7 @@ struct Transpose {
     int64_t ld_in;
     uint16_t* out;
     int64_t ld_out;
+    int fill;
     __host__ __device__ int64_t pieces() const { return (int64_t)((rows + 63) / 64) * ((cols + 63) / 64); }
 };
 struct Transposes {
@@ -1302,7 +1303,7 @@ __device__ __forceinline__ void transpose_piece(const Transpose& t, int64_t i) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int c = tid / 8 + 32 * j, rc = (tid % 8) * 8;
-        if (c0 + c >= cols) continue;
+        if (c0 + c >= cols || r0 + rc >= t.fill) continue;
         u32x4_t y;
 #pragma unroll
         for (int q = 0; q < 4; ++q)

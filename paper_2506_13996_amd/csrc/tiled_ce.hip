@@ -1444,7 +1444,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     // A hidden size that ends inside a block: dHidden and dW read the last rows of W transposed / columns
     // of the dense hidden rows in place of the missing ones and discard the results; a vocabulary that
     // is not whole k-steps: dZ and W transposed are zero up to whole k-steps.
-    const Transpose transpose = {P.W, do_bwd ? V : 0, do_bwd ? H : 0, H, wt, Vp};
+    const Transpose transpose = {P.W, do_bwd ? V : 0, do_bwd ? H : 0, H, wt, Vp, (V + kBlockK - 1) / kBlockK * kBlockK};
     const LossParams loss = {loss_rows, P.N, hdr, sum_mode, P.loss_out};
     bool loss_made = false;
 

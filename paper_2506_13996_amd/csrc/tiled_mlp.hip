@@ -14,9 +14,9 @@
 //                                             reads da; written into the rows of the chunk's group
 //              dx = dg Wg + du Wu             one contraction over the 2 I columns of [dg | du]
 //                                             against [Wg | Wu]^T, transposed once per call
-//                                             (H or I not a multiple of 64: the weights as they are,
-//                                             k-major operands on MixedCore, which has no halves for a
-//                                             short last round; dx as two contractions over I)
+//                                             (H or I not a multiple of 64, several groups: the weights as
+//                                             they are, k-major operands on MixedCore, which has no halves for
+//                                             a short last round; dx as two contractions over I)
 //   per group  dWg += dg^T x, dWu += du^T x, dWd += dy^T a   (fp32, contraction over the group's rows)
 //
 // The launches work on CHUNKS of consecutive rows whose length is chosen for the hardware
@@ -121,7 +121,11 @@ static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, 
         int64_t g = kMlpGroupRows / L.Tp;
         g = g < 1 ? 1 : (g > kMlpGroupMax ? kMlpGroupMax : g);
         const int64_t room = (g * 3 + 1) * L.Tp / 3 / kBlockR * kBlockR;
-        L.weights_t = H % kBlockK == 0 && I % kBlockK == 0;
+        // fp32 overwrite outputs hold the sums themselves
+        const bool in_out = (flags & ALST_FLAG_DW_FP32) && !(flags & ALST_FLAG_DW_ACCUMULATE);
+        const bool whole = H % kBlockK == 0 && I % kBlockK == 0;
+        // H or I that are not whole k-steps: no room of their own, but a call of one group leaves that of the sums unused
+        L.weights_t = whole || (!in_out && N <= std::min(room, mlp_chunk_rows_max(I)));
         // (a group's three weight gradients: each of its blocks about 4 + 5 k-steps for its start and the
         // sums' way through memory)
         const int64_t wgrad_blocks = 3 * ((H + kBlockR - 1) / kBlockR) * ((I + kBlockC - 1) / kBlockC);
@@ -133,15 +137,16 @@ static MlpLayout make_mlp_layout(int64_t N, int64_t H, int64_t I, int64_t tile, 
         L.dgu = L.a + (size_t)L.rows * I * 2;
         // Wd transposed [I, H] and [Wg | Wu] transposed [H, 2 I], made once per call: da = dy Wd and
         // dx = [dg | du] [Wg ; Wu] then read both operands along their rows (the fastest layout
-        // of the block GEMM).  For H and I that are whole k-steps; else the weights are read as
-        // they are.
-        L.wdt = take(L.weights_t ? (size_t)I * H * 2 : 0);
-        L.wgut = take(L.weights_t ? (size_t)H * 2 * I * 2 : 0);
-        // fp32 overwrite outputs hold the sums themselves
-        const bool in_out = (flags & ALST_FLAG_DW_FP32) && !(flags & ALST_FLAG_DW_ACCUMULATE);
+        // of the block GEMM).
+        L.wdt = take(whole ? (size_t)I * H * 2 : 0);
+        L.wgut = take(whole ? (size_t)H * 2 * I * 2 : 0);
         L.acc_g = take(in_out ? 0 : (size_t)I * H * 4);
         L.acc_u = take(in_out ? 0 : (size_t)I * H * 4);
         L.acc_d = take(in_out ? 0 : (size_t)H * I * 4);
+        if (L.weights_t && !whole) {
+            L.wdt = L.acc_g;
+            L.wgut = L.acc_u;
+        }
     }
     L.total = o;
     return L;
@@ -873,7 +878,7 @@ static int run_mlp_backward(const MlpProblem& P) {
     uint16_t* wgut = reinterpret_cast<uint16_t*>(P.ws + L.wgut);
     if (L.weights_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
-        const Transposes ts = {{{P.Wd, H, I, I, wdt, H}, {P.Wg, I, H, H, wgut, I2}, {P.Wu, I, H, H, wgut + I, I2}}};
+        const Transposes ts = {{{P.Wd, H, I, I, wdt, H, H}, {P.Wg, I, H, H, wgut, I2, I}, {P.Wu, I, H, H, wgut + I, I2, I}}};
         hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
@@ -966,10 +971,12 @@ static LinLayout make_lin_layout(int64_t N, int64_t K, int64_t M, int64_t tile, 
         const bool in_out = (flags & ALST_FLAG_DW_FP32) && !(flags & ALST_FLAG_DW_ACCUMULATE);
         L.acc = take(in_out ? 0 : (size_t)M * K * 4);
         // W transposed [K, M], made once per call: dx = dy W then reads both operands along their
-        // rows (the fastest layout of the block GEMM).  For M a multiple of 64; else W is read
-        // as it is.
-        L.weight_t = M % kBlockK == 0;
-        L.wt = take(L.weight_t ? (size_t)K * M * 2 : 0);
+        // rows (the fastest layout of the block GEMM).  M that is not whole k-steps: no room of its own, but a call of one
+        // group leaves that of the sums unused; else W is read as it is.
+        const bool whole = M % kBlockK == 0;
+        L.weight_t = whole || (!in_out && N <= std::max<int64_t>(kMlpGroupRows, L.Tp));
+        L.wt = take(whole ? (size_t)K * M * 2 : 0);
+        if (!whole) L.wt = L.acc;
     }
     L.total = o;
     return L;
@@ -1033,7 +1040,7 @@ static int run_lin_backward(const LinProblem& P) {
     uint16_t* wt = reinterpret_cast<uint16_t*>(P.ws + L.wt);
     if (L.weight_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
-        const Transposes ts = {{{P.W, M, K, K, wt, M}}};
+        const Transposes ts = {{{P.W, M, K, K, wt, M, M}}};
         hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
         ALST_HIP(hipGetLastError());
     }
