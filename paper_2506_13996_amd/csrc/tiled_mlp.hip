@@ -423,7 +423,7 @@ __device__ __forceinline__ void gated_epilogue(const GatedParams& p,
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const float g = acc[mt][nt][q * 4 + x], u = acc[mt + kHalfMT][nt][q * 4 + x];
-                    const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-g));      // (1 ulp; 0 behind an infinity)
+                    const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-g));      // (1 ulp; 0 below g = -87.3, a quotient: -88.7)
                     const float silu = g * sg;
                     oa[mt][q][x] = (__bf16)(silu * u);
                     if (BWD) {
@@ -466,7 +466,12 @@ __global__ __launch_bounds__(DirectCore::kThreads) void gated_kernel(const Gated
     else gated_block<HalfCore, BWD, KTAIL, true>(p, tr, tc, tr * kBlockR + half * (kBlockR / 2), smem);
 }
 
-// The same in small blocks.
+// The same in small blocks.  LDS: that of the rings of both products (the narrower one has more stages).
+template <class Core, bool BWD>
+constexpr int gated_small_lds() {
+    constexpr int da = RingCoreT<Core::kMT / 2>::kLds;
+    return BWD && da > Core::kLds ? da : Core::kLds;
+}
 template <class Core, bool BWD, bool KTAIL>
 __global__ __launch_bounds__(Core::kThreads) void gated_small_kernel(const GatedParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -614,14 +619,14 @@ static int prepare_mlp_kernels_on_current_device() {
     acc(allow_big_lds(linear_small_kernel<RingCoreT<4>, true>, RingCoreT<4>::kLds));
     acc(allow_big_lds(linear_small_kernel<RingCoreT<8>, false>, RingCoreT<8>::kLds));
     acc(allow_big_lds(linear_small_kernel<RingCoreT<8>, true>, RingCoreT<8>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, false>, RingCoreT<4>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, true>, RingCoreT<4>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, false>, RingCoreT<4>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, true>, RingCoreT<4>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, false>, RingCoreT<8>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, true>, RingCoreT<8>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, false>, RingCoreT<8>::kLds));
-    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, true>, RingCoreT<8>::kLds));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, false>, gated_small_lds<RingCoreT<4>, false>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, false, true>, gated_small_lds<RingCoreT<4>, false>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, false>, gated_small_lds<RingCoreT<4>, true>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<4>, true, true>, gated_small_lds<RingCoreT<4>, true>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, false>, gated_small_lds<RingCoreT<8>, false>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, false, true>, gated_small_lds<RingCoreT<8>, false>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, false>, gated_small_lds<RingCoreT<8>, true>()));
+    acc(allow_big_lds(gated_small_kernel<RingCoreT<8>, true, true>, gated_small_lds<RingCoreT<8>, true>()));
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<2>, false>, KMajorSplitT<2>::kLds));
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<2>, true>, KMajorSplitT<2>::kLds));
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<4>, false>, KMajorSplitT<4>::kLds));
@@ -794,7 +799,7 @@ static int launch_gated_small(GatedParams gp, bool bwd, hipStream_t s) {
     const dim3 blocks((unsigned)grid_for_blocks(gp.grid.blocks())), threads(Core::kThreads);
     const bool ktail = gp.K % kBlockK != 0;
     ProfScope pr(PROF_MLP_LINEAR, s);
-    constexpr int lds = Core::kLds;
+    const int lds = bwd ? gated_small_lds<Core, true>() : gated_small_lds<Core, false>();
     if (ktail && bwd) hipLaunchKernelGGL((gated_small_kernel<Core, true, true>), blocks, threads, lds, s, gp);
     else if (ktail) hipLaunchKernelGGL((gated_small_kernel<Core, false, true>), blocks, threads, lds, s, gp);
     else if (bwd) hipLaunchKernelGGL((gated_small_kernel<Core, true, false>), blocks, threads, lds, s, gp);

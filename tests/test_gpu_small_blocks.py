@@ -52,6 +52,8 @@ def test_linear(N, K, M, forward, wgrad):
     (1032, 72, 1032, 0),               # large blocks
     (500, 320, 448, 64),               # whole k-steps: da is made in the gated launch
     (1000, 256, 832, 128),
+    (1000, 1024, 832, 128),            # 16 k-steps: every stage of the rings of da and of g and u is used
+    (500, 1096, 448, 64),
 ])
 def test_mlp(N, H, I, gated):
     assert small_columns(N, 2 * I) == gated
