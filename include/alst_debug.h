@@ -20,7 +20,8 @@ extern "C" {
  * forgets the spans.  A logits or dHidden launch may cover several of the caller's tiles and counts as
  * that many spans, so for these ms_total / spans is the time per tile.  Kinds: 0 logits GEMM, 1 dHidden
  * GEMM, 2 dW GEMM, 3 the small kernels of a cross-entropy chunk; 4 the projection GEMMs of the tiled MLP (alst_mlp.h), 5 its weight-gradient
- * GEMMs, 6 its small kernels; 7 unused.  The recorded spans are process-wide state behind a lock:
+ * GEMMs, 6 its small kernels; 7 unused.  Short calls make both kinds of
+ * gradients in one launch, which counts as dHidden (kind 1), or as weight gradients (kind 5).  The recorded spans are process-wide state behind a lock:
  * calls from several host threads are safe, and their spans land in one list.
  */
 int alst_profile_enable(int on);

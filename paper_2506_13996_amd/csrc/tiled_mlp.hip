@@ -184,6 +184,10 @@ struct BatchMap {
     __device__ __forceinline__ bool locate(int bid, int& which, int& tr, int& tc, int& PR, int& PC, int& half) const {
         const int number = block_of_workgroup(bid, last.numbers, rows);
         if (number < 0) return false;
+        find(number, which, tr, tc, PR, PC, half);
+        return true;
+    }
+    __device__ __forceinline__ void find(int number, int& which, int& tr, int& tc, int& PR, int& PC, int& half) const {
         const int i = last.block(number, half);
         which = 0;
 #pragma unroll
@@ -192,7 +196,6 @@ struct BatchMap {
         PR = g[which].PR;
         PC = g[which].PC;
         block_at(g[which], i - first_block[which], rows, tr, tc);
-        return true;
     }
 };
 struct LinearBatch {
@@ -245,18 +248,23 @@ __global__ __launch_bounds__(Core::kThreads) void linear_kernel(const LinearBatc
     }
 }
 
-// The same in small blocks (SplitCoreT); the map's numbers are those of blocks of Core's size.
+// The same in small blocks (RingCoreT); the map's numbers are those of blocks of Core's size.
 template <class Core, bool KTAIL>
-__global__ __launch_bounds__(Core::kThreads) void linear_small_kernel(const LinearBatch b) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void linear_small_block(const LinearBatch& b, int number, unsigned char* smem) {
     int which, tr, tc, PR, PC, half;
-    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
+    b.map.find(number, which, tr, tc, PR, PC, half);
     const LinearParams& p = b.p[which];
     const int r0 = tr * Core::kRows, c0 = tc * Core::kCols;
     typename Core::acc_t acc[Core::kMT][Core::kNT];
     zero_acc<Core>(acc);
     Core::template gemm<KTAIL>({p.X, p.ldx, p.Y, p.ldy, p.rows_x, p.rows_y, p.K, r0, c0, nullptr, 0, nullptr}, smem, acc);
     store_block_bf16<Core, true>(acc, p.D, p.ldd, r0, c0, p.rows_x, p.rows_y, smem);
+}
+template <class Core, bool KTAIL>
+__global__ __launch_bounds__(Core::kThreads) void linear_small_kernel(const LinearBatch b) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int number = block_of_workgroup(blockIdx.x, b.map.last.numbers, false);
+    if (number >= 0) linear_small_block<Core, KTAIL>(b, number, smem);
 }
 
 // The k-contiguous products on persistent workgroups: one workgroup per compute unit walks the
@@ -583,17 +591,38 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void wgrad_kernel(const Wgrad
 
 // The same in small blocks.
 template <class Core, bool KTAIL>
+__device__ __forceinline__ void wgrad_small_block(const WgradBatch& b, int number, unsigned char* smem) {
+    int which, tr, tc, PR, PC, half;
+    b.map.find(number, which, tr, tc, PR, PC, half);
+    wgrad_block<Core, KTAIL>(b.p[which], tr * Core::kRows, tc * Core::kCols, smem);
+}
+template <class Core, bool KTAIL>
 __global__ __launch_bounds__(Core::kThreads) void wgrad_small_kernel(const WgradBatch b) {
     extern __shared__ __align__(16) unsigned char smem[];
-    int which, tr, tc, PR, PC, half;
-    if (!b.map.locate(blockIdx.x, which, tr, tc, PR, PC, half)) return;
-    const WgradParams& p = b.p[which];
-    wgrad_block<Core, KTAIL>(p, tr * Core::kRows, tc * Core::kCols, smem);
+    const int number = block_of_workgroup(blockIdx.x, b.map.last.numbers, false);
+    if (number >= 0) wgrad_small_block<Core, KTAIL>(b, number, smem);
+}
+
+// dx and the weight gradients of one group in one launch, both in small blocks: neither reads what the other writes, and
+// with at most one round of blocks in all, each has a compute unit of its own.  Core, WgradCore: blocks of the same size.
+template <class Core, class WgradCore, bool KTAIL>
+__global__ __launch_bounds__(Core::kThreads) void backward_small_kernel(const LinearBatch dx, const WgradBatch dw) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    static_assert(Core::kRows == WgradCore::kRows && Core::kCols == WgradCore::kCols && Core::kThreads == WgradCore::kThreads,
+                  "one numbering of blocks");
+    const int first = dx.map.last.numbers;
+    const int number = block_of_workgroup(blockIdx.x, first + dw.map.last.numbers, false);
+    if (number < 0) return;
+    if (number < first) linear_small_block<Core, KTAIL>(dx, number, smem);
+    else wgrad_small_block<WgradCore, KTAIL>(dw, number - first, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
+template <class Core, class WgradCore>
+constexpr int backward_small_lds() { return Core::kLds > WgradCore::kLds ? Core::kLds : WgradCore::kLds; }
+
 static int prepare_mlp_kernels_on_current_device() {
     int rc = ALST_OK;
     auto acc = [&](int r) { if (r != ALST_OK) rc = r; };
@@ -631,6 +660,10 @@ static int prepare_mlp_kernels_on_current_device() {
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<2>, true>, KMajorSplitT<2>::kLds));
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<4>, false>, KMajorSplitT<4>::kLds));
     acc(allow_big_lds(wgrad_small_kernel<KMajorSplitT<4>, true>, KMajorSplitT<4>::kLds));
+    acc(allow_big_lds(backward_small_kernel<RingCoreT<4>, KMajorSplitT<2>, false>, backward_small_lds<RingCoreT<4>, KMajorSplitT<2>>()));
+    acc(allow_big_lds(backward_small_kernel<RingCoreT<4>, KMajorSplitT<2>, true>, backward_small_lds<RingCoreT<4>, KMajorSplitT<2>>()));
+    acc(allow_big_lds(backward_small_kernel<RingCoreT<8>, KMajorSplitT<4>, false>, backward_small_lds<RingCoreT<8>, KMajorSplitT<4>>()));
+    acc(allow_big_lds(backward_small_kernel<RingCoreT<8>, KMajorSplitT<4>, true>, backward_small_lds<RingCoreT<8>, KMajorSplitT<4>>()));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -761,6 +794,38 @@ static int launch_wgrad(const WgradParams* ps, int n, hipStream_t s) {
 }
 
 static int launch_wgrad(const WgradParams& p, hipStream_t s) { return launch_wgrad(&p, 1, s); }
+
+template <class Core, class WgradCore>
+static int launch_backward_small(const LinearParams& lp, const WgradParams* ps, int n, hipStream_t s) {
+    LinearBatch dx = {};
+    WgradBatch dw = {};
+    const int64_t total = number_blocks(dx, &lp, 1, Core::kRows, Core::kCols) +
+                          number_blocks(dw, ps, n, WgradCore::kRows, WgradCore::kCols);
+    const dim3 blocks((unsigned)grid_for_blocks(total)), threads(Core::kThreads);
+    constexpr int lds = backward_small_lds<Core, WgradCore>();
+    ProfScope pr(PROF_MLP_WGRAD, s);
+    if (lp.K % kBlockK != 0 || ps[0].K % kBlockK != 0)
+        hipLaunchKernelGGL((backward_small_kernel<Core, WgradCore, true>), blocks, threads, lds, s, dx, dw);
+    else hipLaunchKernelGGL((backward_small_kernel<Core, WgradCore, false>), blocks, threads, lds, s, dx, dw);
+    return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
+// dx (lp) and the n weight gradients of the group that it completes.  One launch while the small blocks of all are at most
+// one round, two otherwise (blocks beyond a round wait for a compute unit, which costs more than the launch:
+// small_block_columns).  The launch and the shorter product cost nothing then; us of a forward and backward call, two launches / one:
+// MLP 512 x 256 x 768 40.8 / 34.3, 1024 x 256 x 512 39.4 / 31.0, 512 x 512 x 1024 51.5 / 47.7; linear 512 x 1024 x 1024, whose
+// blocks become 64 x 128 where two launches had 64 x 64, 27.4 / 24.1.
+static int launch_backward(const LinearParams& lp, const WgradParams* ps, int n, hipStream_t s) {
+    const int columns = lp.y_kmajor ? 0 : small_block_columns([&](int64_t c) {
+        int64_t total = small_blocks(lp.rows_x, lp.rows_y, c);
+        for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
+        return total;
+    });
+    if (columns == 64) return launch_backward_small<RingCoreT<4>, KMajorSplitT<2>>(lp, ps, n, s);
+    if (columns == 128) return launch_backward_small<RingCoreT<8>, KMajorSplitT<4>>(lp, ps, n, s);
+    const int rc = launch_linear(lp, s);
+    return rc == ALST_OK ? launch_wgrad(ps, n, s) : rc;
+}
 
 struct MlpProblem {
     const uint16_t *x, *Wg, *Wu, *Wd, *dy;
@@ -909,8 +974,8 @@ static int run_mlp_backward(const MlpProblem& P) {
             if (rc == ALST_OK) rc = launch_gated(P, x_c, rows, a_c, a_c, dgu_c, s);
             if (rc != ALST_OK) return rc;
         }
+        LinearParams lp = {};
         {   // dx = dg Wg + du Wu
-            LinearParams lp = {};
             lp.X = dgu_c; lp.ldx = I2; lp.rows_x = rows;
             if (L.weights_t) {
                 // one contraction over the 2 I columns of [dg | du] against [Wg | Wu]^T [H, 2 I]
@@ -921,11 +986,13 @@ static int run_mlp_backward(const MlpProblem& P) {
                 lp.X2 = dgu_c + I; lp.Y2 = P.Wu;
             }
             lp.D = P.dx + i0 * P.H; lp.ldd = H;
-            rc = launch_linear(lp, s);
-            if (rc != ALST_OK) return rc;
         }
         const int64_t in_group = i0 + rows - group0;
-        if (in_group < L.rows && i0 + rows < P.N) continue;
+        if (in_group < L.rows && i0 + rows < P.N) {
+            rc = launch_linear(lp, s);
+            if (rc != ALST_OK) return rc;
+            continue;
+        }
         // the group is complete
         GradOut out = {nullptr, nullptr, 0, 1.f, group0 == 0, i0 + rows == P.N, f32, accum};
         auto into = [&](float* sums, void* dW, int64_t ld) { out.sums = sums; out.out = dW; out.ld = ld; return out; };
@@ -940,7 +1007,8 @@ static int run_mlp_backward(const MlpProblem& P) {
         wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I;
         wp[2].Y = P.dy + group0 * H; wp[2].ldy = H; wp[2].rows_y = H;
         wp[2].out = into(acc_d, P.dWd, I);                                       // dWd[h][i]
-        rc = launch_wgrad(wp, 3, s);                                             // one launch
+        // (weights transposed into the room of the sums: a call of one group, whose gradients don't touch the sums)
+        rc = launch_backward(lp, wp, 3, s);
         if (rc != ALST_OK) return rc;
     }
     return ALST_OK;
@@ -1050,12 +1118,13 @@ static int run_lin_backward(const LinProblem& P) {
         ALST_HIP(hipGetLastError());
     }
     const int64_t chunk = lin_chunk_rows(P.N, P.M, P.K, L.weight_t);
+    LinearParams lp = {};
     for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
-        LinearParams lp = {};
         lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = M;
         if (L.weight_t) { lp.Y = wt; lp.ldy = M; lp.rows_y = K; }         // W^T [K, M]
         else { lp.Y = P.W; lp.ldy = K; lp.rows_y = K; lp.y_kmajor = 1; }  // W [M, K]: k = m
         lp.D = P.dx + i0 * P.K; lp.ldd = K;
+        if (i0 + chunk >= P.N) break;                                     // (the last one: with the first group)
         rc = launch_linear(lp, s);
         if (rc != ALST_OK) return rc;
     }
@@ -1069,7 +1138,7 @@ static int run_lin_backward(const LinProblem& P) {
         wp.Y = P.dy + i0 * P.M; wp.ldy = M; wp.rows_y = M;
         wp.K = (int)rows;
         wp.out = {acc, P.dW, K, 1.f, i0 == 0, i0 + rows == P.N, f32, accum};
-        rc = launch_wgrad(wp, s);
+        rc = i0 == 0 ? launch_backward(lp, &wp, 1, s) : launch_wgrad(wp, s);
         if (rc != ALST_OK) return rc;
     }
     return ALST_OK;

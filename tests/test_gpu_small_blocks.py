@@ -92,6 +92,54 @@ def test_cross_entropy(name, N, H, V, tile, n_valid):
     _check(s, f, dH, dW, name + " split", valid=(y != IGN))
 
 
+def joint_columns(*products):
+    """Which blocks a launch of several products takes, or 0: a launch for each kind."""
+    return next((c for c in (64, 128) if sum(-(-r // 64) * -(-k // c) for r, k in products) <= 256), 0)
+
+
+@pytest.mark.parametrize("N,K,M,joint", [
+    (512, 512, 1536, 64),              # 64 blocks of dx and 192 of dW: one round
+    (520, 512, 1536, 128),             # a row of blocks more
+    (1000, 1000, 904, 128),            # ragged in every extent; one round, 15 k-steps
+    (1024, 1024, 2048, 0),             # 128 + 256 blocks of 64 x 128: two launches, both small
+    (5, 8, 16, 64),
+])
+def test_linear_backward_in_one_launch(N, K, M, joint):
+    assert joint_columns((N, K), (K, M)) == joint
+    x, W, dy = TL._inputs(N, K, M, 58)
+    got = TL._run(x, W, dy, 4096)
+    for g, r in zip(got, (lorc.forward(x, W), *lorc.backward(x, W, dy))):
+        assert G.grad_err(g, r) <= TOL
+
+
+@pytest.mark.parametrize("N,H,I,joint", [
+    (512, 256, 1024, 64),              # 32 blocks of dx and 3 x 64 of the weights' gradients
+    (1000, 256, 1024, 64),             # 64: one round
+    (1032, 256, 1024, 128),
+    (300, 520, 1000, 128),             # ragged: transposed weights lie where the sums would
+    (600, 384, 2048, 0),
+])
+def test_mlp_backward_in_one_launch(N, H, I, joint):
+    assert joint_columns((N, H), (H, I), (H, I), (I, H)) == joint
+    wl = synth.MlpWorkload("joint", N, H, I, 2048, seed=59)
+    x, Wg, Wu, Wd, dy = synth.make_mlp_inputs(wl)
+    y, dx, gW = TM._run(x, Wg, Wu, Wd, dy, 2048)
+    ref = (morc.forward(x, Wg, Wu, Wd, row_block=256), *morc.backward(x, Wg, Wu, Wd, dy, row_block=256))
+    for g, r in zip((y, dx, *gW), ref):
+        assert G.grad_err(g, r) <= TOL
+
+
+@pytest.mark.parametrize("name,N,H,V,tile,n_valid", [
+    ("one_round_of_both", 512, 256, 4096, 512, 486),
+    ("fewer_rows_than_the_chunk", 512, 256, 4096, 512, 100),
+    ("no_row_valid", 512, 256, 4096, 512, 0),
+    ("last_chunk_without_rows", 1000, 64, 3000, 128, 120),
+    ("two_launches", 512, 512, 4096, 512, 486),
+])
+def test_cross_entropy_gradients_in_one_launch(name, N, H, V, tile, n_valid):
+    test_cross_entropy(name, N, H, V, tile, n_valid)
+
+
 def test_a_label_out_of_range_is_reported_where_the_gather_numbers_the_rows():
     wl = synth.custom("bad", 300, 64, 500, 512, ignore_frac=0.1, seed=55)
     h, W, y = synth.make_inputs(wl)
