@@ -1089,18 +1089,27 @@ __global__ __launch_bounds__(DirectCore::kThreads) void dhidden_kernel(const DHi
 
 // The same in small blocks (the ranges are chosen as for the large ones).
 template <class Core>
+struct DHiddenSmall {
+    const DHiddenParams& p;
+    int T_cur, Trc, splits;
+    PatchGrid pg;
+    __device__ __forceinline__ explicit DHiddenSmall(const DHiddenParams& p_)
+        : p(p_), T_cur(p_.info->Tc), Trc(p_.info->Trc), splits(p_.info->splits),
+          pg{Trc / Core::kRows, (p_.H + Core::kCols - 1) / Core::kCols, p_.PR, p_.PC} {}
+    __device__ __forceinline__ int blocks() const { return T_cur == 0 ? 0 : pg.blocks() * splits; }
+    __device__ __forceinline__ void run(int number, unsigned char* smem) const {
+        int tr, tc;
+        const int split = number / pg.blocks();
+        block_at(pg, number - split * pg.blocks(), false, tr, tc);
+        dhidden_block<Core>(p, T_cur, Trc, splits, p.info->ksteps, split, tr * Core::kRows, tc * Core::kCols, nullptr, smem);
+    }
+};
+template <class Core>
 __global__ __launch_bounds__(Core::kThreads) void dhidden_small_kernel(const DHiddenParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int T_cur = p.info->Tc, Trc = p.info->Trc;
-    if (T_cur == 0) return;
-    const PatchGrid pg = {Trc / Core::kRows, (p.H + Core::kCols - 1) / Core::kCols, p.PR, p.PC};
-    const int splits = p.info->splits, ksteps = p.info->ksteps;
-    const int number = block_of_workgroup(blockIdx.x, pg.blocks() * splits, false);
-    if (number < 0) return;
-    int tr, tc;
-    const int split = number / pg.blocks();
-    block_at(pg, number - split * pg.blocks(), false, tr, tc);
-    dhidden_block<Core>(p, T_cur, Trc, splits, ksteps, split, tr * Core::kRows, tc * Core::kCols, nullptr, smem);
+    const DHiddenSmall<Core> dh(p);
+    const int number = block_of_workgroup(blockIdx.x, dh.blocks(), false);
+    if (number >= 0) dh.run(number, smem);
 }
 
 // dH[idx[i]] = (g/M) (1/S_i) * sum over the ranges of the partial products of dense row i, in
@@ -1183,18 +1192,47 @@ __global__ __launch_bounds__(KMajorCore::kThreads) void dw_kernel(const DWParams
 
 // The same in small blocks.
 template <class Core>
+struct DWSmall {
+    const DWParams& p;
+    int64_t left;
+    int Tkc;
+    PatchGrid pg;
+    __device__ __forceinline__ explicit DWSmall(const DWParams& p_)
+        : p(p_), left(p_.hdr->n_valid - p_.row0),
+          Tkc(left <= 0 ? 0 : (int)(((left < p_.rows ? left : p_.rows) + kBlockK - 1) / kBlockK * kBlockK)),
+          pg{(p_.H + Core::kRows - 1) / Core::kRows, (p_.V + Core::kCols - 1) / Core::kCols, p_.PR, p_.PC} {}
+    __device__ __forceinline__ int blocks() const { return Tkc == 0 && !p.out.first ? 0 : pg.blocks(); }
+    __device__ __forceinline__ void run(int number, unsigned char* smem) const {
+        int tr, tc;
+        block_at(pg, number, false, tr, tc);
+        dw_block<Core>(p, Tkc, left, tr * Core::kRows, tc * Core::kCols, smem);
+    }
+};
+template <class Core>
 __global__ __launch_bounds__(Core::kThreads) void dw_small_kernel(const DWParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int64_t left = p.hdr->n_valid - p.row0;
-    const int Tkc = left <= 0 ? 0 : (int)(((left < p.rows ? left : p.rows) + kBlockK - 1) / kBlockK * kBlockK);
-    if (Tkc == 0 && !p.out.first) return;
-    const PatchGrid pg = {(p.H + Core::kRows - 1) / Core::kRows, (p.V + Core::kCols - 1) / Core::kCols, p.PR, p.PC};
-    const int number = block_of_workgroup(blockIdx.x, pg.blocks(), false);
-    if (number < 0) return;
-    int tr, tc;
-    block_at(pg, number, false, tr, tc);
-    dw_block<Core>(p, Tkc, left, tr * Core::kRows, tc * Core::kCols, smem);
+    const DWSmall<Core> dw(p);
+    const int number = block_of_workgroup(blockIdx.x, dw.blocks(), false);
+    if (number >= 0) dw.run(number, smem);
 }
+
+// dHidden of a group's last chunk and the group's dW in one launch, both in small blocks: neither reads what the other
+// writes (dHidden's partial products lie behind the rows that dW reads), and with at most one round of blocks in all, each
+// has a compute unit of its own.
+template <class Core, class DWCore>
+__global__ __launch_bounds__(Core::kThreads) void gradients_small_kernel(const DHiddenParams hp, const DWParams wp) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    static_assert(Core::kThreads == DWCore::kThreads, "one launch");
+    const DHiddenSmall<Core> dh(hp);
+    const DWSmall<DWCore> dw(wp);
+    const int first = dh.blocks();
+    const int number = block_of_workgroup(blockIdx.x, first + dw.blocks(), false);
+    if (number < 0) return;
+    if (number < first) dh.run(number, smem);
+    else dw.run(number - first, smem);
+}
+template <class Core, class DWCore>
+constexpr int gradients_small_lds() { return Core::kLds > DWCore::kLds ? Core::kLds : DWCore::kLds; }
 
 // ---------------------------------------------------------------------------------------------
 // host side
@@ -1231,6 +1269,8 @@ static int prepare_kernels_on_current_device() {
     acc(allow_big_lds(dw_kernel));
     acc(allow_big_lds(dw_small_kernel<KMajorSplitT<2>>, KMajorSplitT<2>::kLds));
     acc(allow_big_lds(dw_small_kernel<KMajorSplitT<4>>, KMajorSplitT<4>::kLds));
+    acc(allow_big_lds(gradients_small_kernel<RingCoreT<4>, KMajorSplitT<2>>, gradients_small_lds<RingCoreT<4>, KMajorSplitT<2>>()));
+    acc(allow_big_lds(gradients_small_kernel<RingCoreT<8>, KMajorSplitT<4>>, gradients_small_lds<RingCoreT<8>, KMajorSplitT<4>>()));
     return rc;
 }
 // Once per device, whatever the number of host threads that make their first call together.
@@ -1508,6 +1548,27 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
         if (rc != ALST_OK) return rc;
         if (!do_bwd) continue;
 
+        // dHidden in small blocks (a block is 16 of 64 columns or fewer), and dW, which joins its launch while both together are
+        // at most one round; us of a call, two launches / one: 512 x 256 x 4096 39.0 / 35.0, 512 x 1024 x 1024 43.8 / 39.3, 300 x
+        // 256 x 1000 35.2 / 27.7
+        auto dh_small = [&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); };
+        auto dw_small = [&](int64_t cols) { return small_blocks(H, V, cols); };
+        auto dw_grid = [&](int columns) {
+            return columns ? choose_patches((H + kSmallRows - 1) / kSmallRows, (V + columns - 1) / columns)
+                           : choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
+        };
+        const int dh_columns = small_block_columns(dh_small);
+        const int both = !c.group_done ? 0 : small_block_columns([&](int64_t cols) { return dh_small(cols) + dw_small(cols); });
+        DWParams wp = {};
+        if (c.group_done) {
+            wp.hg = hc; wp.dzg = stash; wp.hdr = hdr;
+            wp.out = {acc, P.dW, P.H, 0.f, c.group0 == 0, 0, (P.flags & ALST_FLAG_DW_FP32) != 0,
+                      (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
+            wp.row0 = c.group0; wp.rows = L.Kg;
+            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
+            const PatchGrid pg = dw_grid(both);
+            wp.PR = pg.PR; wp.PC = pg.PC;
+        }
         {
             DHiddenParams dp;
             dp.dz = stash_t; dp.Wt = wt; dp.dH_t = P.dHidden; dp.idx = idx_t;
@@ -1518,12 +1579,16 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             // enough workgroups for whatever number of rows and ranges the chunk turns out to have
             const int grid = grid_for_blocks(c.dh_blocks);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
-            // (a block is 16 small ones of 64 columns or fewer)
-            const int columns = small_block_columns([&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); });
-            if (columns == 64)
+            if (both == 64)
+                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<4>, KMajorSplitT<2>>), dim3(kRound), dim3(RingCoreT<4>::kThreads),
+                                   (gradients_small_lds<RingCoreT<4>, KMajorSplitT<2>>()), s, dp, wp);
+            else if (both == 128)
+                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<8>, KMajorSplitT<4>>), dim3(kRound), dim3(RingCoreT<8>::kThreads),
+                                   (gradients_small_lds<RingCoreT<8>, KMajorSplitT<4>>()), s, dp, wp);
+            else if (dh_columns == 64)
                 hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<4>>, dim3(kRound), dim3(RingCoreT<4>::kThreads),
                                    RingCoreT<4>::kLds, s, dp);
-            else if (columns == 128)
+            else if (dh_columns == 128)
                 hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<8>>, dim3(kRound), dim3(RingCoreT<8>::kThreads),
                                    RingCoreT<8>::kLds, s, dp);
             else
@@ -1535,16 +1600,9 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             }
             ALST_HIP(hipGetLastError());
         }
-        if (c.group_done) {
-            DWParams wp;
-            wp.hg = hc; wp.dzg = stash; wp.hdr = hdr;
-            wp.out = {acc, P.dW, P.H, 0.f, c.group0 == 0, 0, (P.flags & ALST_FLAG_DW_FP32) != 0,
-                      (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
-            wp.row0 = c.group0; wp.rows = L.Kg;
-            wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
-            const int columns = small_block_columns([&](int64_t cols) { return small_blocks(H, V, cols); });
-            const int block_r = columns ? kSmallRows : kBlockR, block_c = columns ? columns : kBlockC;
-            const PatchGrid pg = choose_patches((H + block_r - 1) / block_r, columns ? (V + columns - 1) / columns : Vp / block_c);
+        if (c.group_done && !both) {
+            const int columns = small_block_columns(dw_small);
+            const PatchGrid pg = dw_grid(columns);
             wp.PR = pg.PR; wp.PC = pg.PC;
             const dim3 grid((unsigned)grid_for_blocks(pg.blocks())), threads(KMajorCore::kThreads);
             ProfScope ps_(PROF_DW, s);
