@@ -695,7 +695,9 @@ __global__ __launch_bounds__(kCombineRows * kCombineLanes) void row_finish_kerne
     }
 }
 
-// loss = (sum of the per-row terms in a fixed order) / M, or the sum itself.  One workgroup of THREADS.
+// loss = (sum of the per-row terms in a fixed order) / M, or the sum itself.  One workgroup of THREADS; the order is
+// the same for every number of threads: kLossSums sums of every kLossSums-th term, added up pairwise.  Which launch makes the loss
+// depends on the tile and the entry point, the bits of the loss do not.
 struct LossParams {
     const float* loss_rows;
     int64_t N;
@@ -703,16 +705,29 @@ struct LossParams {
     int sum_mode;
     float* loss_out;
 };
+constexpr int kLossSums = 1024;
 template <int THREADS>
 __device__ __forceinline__ void loss_reduce(const LossParams& p) {
-    __shared__ double part[THREADS];
-    double s = 0.0;
+    constexpr int kPer = kLossSums / THREADS;
+    __shared__ double part[kLossSums];
+    double s[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) s[q] = 0.0;
+    const float* at = p.loss_rows + threadIdx.x;
+    const int64_t whole = p.N / kLossSums;
+    const int rest = (int)(p.N % kLossSums);
 #pragma unroll 8
-    for (int64_t i = threadIdx.x; i < p.N; i += THREADS) s += (double)p.loss_rows[i];
-    part[threadIdx.x] = s;
+    for (int64_t k = 0; k < whole; ++k, at += kLossSums)
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) s[q] += (double)at[q * THREADS];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if ((int)threadIdx.x + q * THREADS < rest) s[q] += (double)at[q * THREADS];
+        part[threadIdx.x + q * THREADS] = s[q];
+    }
     __syncthreads();
-    for (int w = THREADS / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    for (int w = kLossSums / 2; w > 0; w >>= 1) {
+        for (int t = threadIdx.x; t < w; t += THREADS) part[t] += part[t + w];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
@@ -1114,16 +1129,19 @@ __global__ __launch_bounds__(Core::kThreads) void dhidden_small_kernel(const DHi
 
 // dH[idx[i]] = (g/M) (1/S_i) * sum over the ranges of the partial products of dense row i, in
 // range order.  Chunks whose contraction was not cut were written by dhidden_kernel itself.
-// loss (the last chunk of a call that wants it): the workgroup behind the `rows` makes the loss, which costs a call of
-// one chunk nothing here and 4 us as a launch.
+// make_loss (the last chunk of a call of up to kLossInReduceRows rows that wants it): workgroup 0 makes the loss and the
+// rows come behind it.  That saves a launch where one workgroup of 256 has added up the terms before the rows are done, and is
+// a tail behind them where it hasn't; us of a call, a launch of its own / in this one: 512 x 256 x 4096 40.4 / 38.2, 4096 x 256 x
+// 4096 90.8 / 87.5, 16384 241.7 / 239.0, 400000 5535 / 5553; 32768 x 64 x 512 227.5 / 229.2, 131072 x 64 x 512 850.9 / 872.4.
+constexpr int64_t kLossInReduceRows = 16384;
 __global__ __launch_bounds__(256) void dhidden_reduce_kernel(const float* __restrict__ part, int H,
                                                              const int32_t* __restrict__ idx,
                                                              const ChunkInfo* __restrict__ info,
                                                              const Header* __restrict__ hdr,
                                                              const float* __restrict__ frow,
-                                                             uint16_t* __restrict__ dH, int rows, const LossParams loss) {
-    const int i = blockIdx.x;
-    if (i == rows) {
+                                                             uint16_t* __restrict__ dH, int make_loss, const LossParams loss) {
+    const int i = (int)blockIdx.x - make_loss;
+    if (i < 0) {
         loss_reduce<256>(loss);
         return;
     }
@@ -1594,9 +1612,9 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             else
                 hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes, s, dp);
             if (c.dh_cut) {
-                loss_made = do_fwd && first + rows == P.N;
+                loss_made = do_fwd && first + rows == P.N && P.N <= kLossInReduceRows;
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr + loss_made), dim3(256), 0, s, dp.part, H, idx_t,
-                                   info, hdr, frow, P.dHidden, Tr, loss);
+                                   info, hdr, frow, P.dHidden, (int)loss_made, loss);
             }
             ALST_HIP(hipGetLastError());
         }
