@@ -51,17 +51,26 @@ int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t t
 /*
  * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched): chunk number
  * `chunk` of the launches of a cross-entropy call that computes gradients, and what the device makes of it if
- * `dense` of its rows are there (rows with a valid label, numbered densely through the sequence).
+ * `dense` of its rows are there (rows with a valid label, numbered densely through the sequence).  The library
+ * chooses its launches with the same functions.
  */
 typedef struct {
     int64_t first, rows;             /* dense rows first .. first + rows - 1, as far as they exist */
     int64_t group0;                  /* first dense row of its dW group */
     int64_t dhidden_blocks;          /* output blocks of dHidden over all ranges, for `dense` rows */
     int64_t dhidden_grid;            /* workgroups of the dHidden launch */
+    int64_t dw_blocks;               /* output blocks of dW (0: the chunk does not complete its group) */
+    int64_t dw_grid;                 /* workgroups of the dW launch (0: none, or its blocks are in the dHidden launch) */
+    int64_t gather_grid;             /* workgroups of the launch that gathers the rows (first chunk: zeroes, transposes W) */
     int64_t largest_grid;            /* workgroups of the chunk's largest launch */
     int ranges;                      /* ranges dHidden's contraction is cut into, for `dense` rows */
     int added_up;                    /* whether the launch that adds partial products up is made */
     int in_stash;                    /* the partial products lie in stash rows not reached yet */
+    int logits_columns, dhidden_columns, dw_columns;      /* of the small blocks (64 rows) a product runs on, 0: 256 x 256 */
+    int logits_chained;              /* the logits run on persistent workgroups that walk chains of blocks */
+    int together;                    /* dHidden and dW are one launch */
+    int numbered_by_gather;          /* the gathering launch numbers the rows too */
+    int transposed_apart;            /* W is transposed by launches of its own (first chunk) */
 } alst_debug_ce_chunk_info;
 int alst_debug_ce_chunk(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t flags, int64_t chunk, int64_t dense,
                         alst_debug_ce_chunk_info* info);

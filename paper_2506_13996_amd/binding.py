@@ -39,8 +39,10 @@ EXPORTS = (
 class CeChunkInfo(ctypes.Structure):
     """alst_debug_ce_chunk_info (alst_debug.h)."""
     _fields_ = [(n, ctypes.c_int64) for n in ("first", "rows", "group0", "dhidden_blocks", "dhidden_grid",
-                                              "largest_grid")] + \
-               [(n, ctypes.c_int) for n in ("ranges", "added_up", "in_stash")]
+                                              "dw_blocks", "dw_grid", "gather_grid", "largest_grid")] + \
+               [(n, ctypes.c_int) for n in ("ranges", "added_up", "in_stash", "logits_columns", "dhidden_columns",
+                                            "dw_columns", "logits_chained", "together", "numbered_by_gather",
+                                            "transposed_apart")]
 
 
 _lib = None

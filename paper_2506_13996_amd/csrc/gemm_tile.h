@@ -1311,11 +1311,19 @@ __device__ __forceinline__ void transpose_piece(const Transpose& t, int64_t i) {
         *reinterpret_cast<u32x4_t*>(out + (int64_t)(c0 + c) * ld_out + r0 + rc) = y;
     }
 }
-static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transposes ts) {
-    int64_t i = blockIdx.x;
+static __global__ __launch_bounds__(256) void transpose_bf16_kernel(const Transposes ts, int64_t first) {
+    int64_t i = first + blockIdx.x;
     int k = 0;
     for (; k < 2 && i >= ts.m[k].pieces(); ++k) i -= ts.m[k].pieces();
     transpose_piece(ts.m[k], i);
+}
+// (more pieces than a launch holds: several)
+static inline bool launch_transposes(const Transposes& ts, hipStream_t s) {
+    const int64_t pieces = ts.pieces();
+    for (int64_t first = 0; first < pieces; first += kGridBlocks)
+        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)(pieces - first < kGridBlocks ? pieces - first : kGridBlocks)),
+                           dim3(256), 0, s, ts, first);
+    return hipGetLastError() == hipSuccess;
 }
 
 // ---------------------------------------------------------------------------------------------

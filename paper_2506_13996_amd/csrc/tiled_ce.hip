@@ -1389,31 +1389,88 @@ static int validate(const Problem& P, size_t workspace_bytes, bool need_fwd_out,
 
 // Grids are sized for Tr (the chunk's rows rounded up to the block height); the kernels read the
 // number of rows that take part from the device and surplus blocks leave at once.
+struct LogitsLaunch {
+    int columns;               // of small blocks, or 0: large ones
+    bool chain;                // the first pass runs on chains of blocks
+    PatchGrid pg;
+    int grid;                  // workgroups (a chain has no more than there are compute units)
+};
+static LogitsLaunch choose_logits(int Tr, int Vp, int64_t H) {
+    LogitsLaunch l = {};
+    // (small blocks: 128 columns only, a group of the softmax partials)
+    if (small_blocks(Tr, Vp, LogitsSmallCore::kCols) <= kRound) {
+        l.columns = LogitsSmallCore::kCols;
+        l.pg = choose_patches(Tr / LogitsSmallCore::kRows, Vp / LogitsSmallCore::kCols);
+    } else {
+        l.pg = choose_patches(Tr / kBlockR, Vp / kBlockC);
+        l.chain = chain_pays(l.pg.blocks(), H, true);
+    }
+    l.grid = grid_for_blocks(l.pg.blocks());
+    return l;
+}
 template <int MODE, bool REDO>
 static int launch_logits(LogitsParams lp, int Tr, bool ktail, hipStream_t s) {
-    // (small blocks: 128 columns only, a group of the softmax partials)
-    if (small_blocks(Tr, lp.Vp, LogitsSmallCore::kCols) <= kRound) {
-        const PatchGrid pg = choose_patches(Tr / LogitsSmallCore::kRows, lp.Vp / LogitsSmallCore::kCols);
-        lp.PR = pg.PR; lp.PC = pg.PC;
-        const dim3 grid((unsigned)grid_for_blocks(pg.blocks())), threads(LogitsSmallCore::kThreads);
-        constexpr int lds = LogitsSmallCore::kLds;
-        if (ktail) hipLaunchKernelGGL((logits_small_kernel<true, MODE, REDO>), grid, threads, lds, s, lp);
-        else hipLaunchKernelGGL((logits_small_kernel<false, MODE, REDO>), grid, threads, lds, s, lp);
-        return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
-    }
-    const PatchGrid pg = choose_patches(Tr / kBlockR, lp.Vp / kBlockC);
-    lp.PR = pg.PR; lp.PC = pg.PC;
-    const int grid = grid_for_blocks(pg.blocks());
-    if (!REDO && chain_pays(pg.blocks(), lp.H, true))
-        hipLaunchKernelGGL((logits_chain_kernel<MODE>), dim3((unsigned)std::min(grid, persistent_grid())),
-                           dim3(DirectCore::kThreads), kChainLdsBytes, s, lp);
-    else if (ktail)
-        hipLaunchKernelGGL((logits_kernel<true, MODE, REDO>), dim3(grid),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, lp);
-    else
-        hipLaunchKernelGGL((logits_kernel<false, MODE, REDO>), dim3(grid),
-                           dim3(DirectCore::kThreads), kLdsBytes, s, lp);
+    const LogitsLaunch l = choose_logits(Tr, lp.Vp, lp.H);
+    lp.PR = l.pg.PR; lp.PC = l.pg.PC;
+    const dim3 grid((unsigned)l.grid), threads(DirectCore::kThreads);
+    constexpr int lds = LogitsSmallCore::kLds;
+    if (l.columns && ktail) hipLaunchKernelGGL((logits_small_kernel<true, MODE, REDO>), grid, threads, lds, s, lp);
+    else if (l.columns) hipLaunchKernelGGL((logits_small_kernel<false, MODE, REDO>), grid, threads, lds, s, lp);
+    else if (!REDO && l.chain)
+        hipLaunchKernelGGL((logits_chain_kernel<MODE>), dim3((unsigned)std::min(l.grid, persistent_grid())), threads,
+                           kChainLdsBytes, s, lp);
+    else if (ktail) hipLaunchKernelGGL((logits_kernel<true, MODE, REDO>), grid, threads, kLdsBytes, s, lp);
+    else hipLaunchKernelGGL((logits_kernel<false, MODE, REDO>), grid, threads, kLdsBytes, s, lp);
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
+}
+
+// W transposed for the call's dHidden (nothing to transpose: forward only).
+static Transpose weight_transpose(const Layout& L, const uint16_t* W, uint16_t* wt, int64_t H, int64_t V, bool do_bwd) {
+    return {W, do_bwd ? (int)V : 0, do_bwd ? (int)H : 0, H, wt, L.Vp, (int)((V + kBlockK - 1) / kBlockK * kBlockK)};
+}
+// The launch that gathers the rows of the chunk that begins at dense row `first`.
+struct GatherLaunch {
+    bool numbers;              // it numbers the rows too
+    int64_t zero_blocks;       // workgroups that look for ignored tokens
+    int64_t pieces;            // workgroups that transpose W
+    bool transposes_apart;     // W is transposed by a launch of its own: this one would be more than a grid
+};
+static GatherLaunch choose_gather(const Layout& L, const Transpose& t, int64_t N, int64_t H, int64_t V, int64_t first, int Tr,
+                                  bool do_bwd) {
+    GatherLaunch g = {};
+    g.numbers = N <= kGatherIndexRows && chunk_plan(L, N, H, V, 0, false).rows == N;
+    g.zero_blocks = do_bwd && first == 0 ? std::min<int64_t>((N + kZeroRows - 1) / kZeroRows, kZeroBlocksMax) : 0;
+    g.pieces = first == 0 ? t.pieces() : 0;
+    g.transposes_apart = g.pieces > kGridBlocks - Tr - g.zero_blocks;
+    if (g.transposes_apart) g.pieces = 0;
+    return g;
+}
+
+// The launches of a chunk's gradients.
+struct GradientLaunches {
+    int dh_columns, dw_columns;        // of small blocks, or 0: large ones (dw_columns: the group is complete)
+    bool together;                     // dHidden and dW in one launch, both in small blocks of dh_columns
+    PatchGrid dw;
+    int dh_grid, dw_grid;
+};
+// dHidden in small blocks (a block is 16 of 64 columns or fewer), and dW, which joins its launch while both together are
+// at most one round; us of a call, two launches / one: 512 x 256 x 4096 39.0 / 35.0, 512 x 1024 x 1024 43.8 / 39.3, 300 x
+// 256 x 1000 35.2 / 27.7
+static GradientLaunches choose_gradients(const ChunkPlan& c, int64_t H, int64_t V, int64_t Vp) {
+    GradientLaunches g = {};
+    auto dh_small = [&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); };
+    auto dw_small = [&](int64_t cols) { return small_blocks(H, V, cols); };
+    const int both = !c.group_done ? 0 : small_block_columns([&](int64_t cols) { return dh_small(cols) + dw_small(cols); });
+    g.together = both != 0;
+    g.dh_columns = both ? both : small_block_columns(dh_small);
+    // (enough workgroups for whatever number of rows and ranges the chunk turns out to have)
+    g.dh_grid = g.dh_columns ? kRound : grid_for_blocks(c.dh_blocks);
+    if (!c.group_done) return g;
+    g.dw_columns = both ? both : small_block_columns(dw_small);
+    g.dw = g.dw_columns ? choose_patches((int)((H + kSmallRows - 1) / kSmallRows), (int)((V + g.dw_columns - 1) / g.dw_columns))
+                        : choose_patches((int)((H + kBlockR - 1) / kBlockR), (int)(Vp / kBlockC));
+    g.dw_grid = both ? 0 : grid_for_blocks(g.dw.blocks());
+    return g;
 }
 
 // The logits pass of a chunk and the per-row work behind it; for the modes that form the softmax
@@ -1474,8 +1531,8 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     const int64_t T = P.tile < P.N ? P.tile : P.N;
     const int sum_mode = (P.flags & ALST_FLAG_REDUCE_SUM) ? 1 : 0;
 
-    const bool gather_indexes = P.N <= kGatherIndexRows && chunk_plan(L, P.N, P.H, P.V, 0, false).rows == P.N;
-    if (gather_indexes) {
+    const Transpose transpose = weight_transpose(L, P.W, wt, P.H, P.V, do_bwd);
+    if (choose_gather(L, transpose, P.N, P.H, P.V, 0, 0, do_bwd).numbers) {
         // (gather_rows_kernel numbers the rows)
     } else if (P.N <= kIndexRows) {
         hipLaunchKernelGGL(index_rows_kernel, dim3(1), dim3(kScanThreads), 0, s, P.labels, (int)P.N,
@@ -1502,7 +1559,6 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
     // A hidden size that ends inside a block: dHidden and dW read the last rows of W transposed / columns
     // of the dense hidden rows in place of the missing ones and discard the results; a vocabulary that
     // is not whole k-steps: dZ and W transposed are zero up to whole k-steps.
-    const Transpose transpose = {P.W, do_bwd ? V : 0, do_bwd ? H : 0, H, wt, Vp, (V + kBlockK - 1) / kBlockK * kBlockK};
     const LossParams loss = {loss_rows, P.N, hdr, sum_mode, P.loss_out};
     bool loss_made = false;
 
@@ -1529,20 +1585,14 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             gp.N = P.N; gp.first = first; gp.Rc = Tr; gp.H = P.H; gp.V = P.V;
             gp.dh_part_rows = c.part_rows;
             gp.Hk = (int)L.Hk; gp.ignore_index = P.ignore_index;
-            int64_t zero_blocks = do_bwd && first == 0 ? (P.N + kZeroRows - 1) / kZeroRows : 0;
-            if (zero_blocks > kZeroBlocksMax) zero_blocks = kZeroBlocksMax;
-            gp.zero_blocks = zero_blocks;
+            const GatherLaunch g = choose_gather(L, transpose, P.N, P.H, P.V, first, Tr, do_bwd);
+            gp.zero_blocks = g.zero_blocks;
             gp.hdr_out = hdr; gp.idx_out = idx; gp.lse = do_fwd ? lse_buf : nullptr;
             gp.loss_rows = do_fwd ? loss_rows : nullptr; gp.n_valid_out = P.n_valid_out;
             gp.grad_loss = P.grad_loss; gp.sum_mode = sum_mode;
-            int64_t pieces = first == 0 ? transpose.pieces() : 0;
-            if (pieces > kGridBlocks - Tr - zero_blocks) {         // more than a launch holds: one of its own
-                hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)pieces), dim3(256), 0, s, Transposes{{transpose}});
-                ALST_HIP(hipGetLastError());
-                pieces = 0;
-            }
-            const dim3 grid((unsigned)(Tr + zero_blocks + pieces));
-            if (gather_indexes) hipLaunchKernelGGL(gather_rows_kernel<true>, grid, dim3(256), 0, s, gp, transpose);
+            if (g.transposes_apart && !launch_transposes(Transposes{{transpose}}, s)) return ALST_ERR_HIP;
+            const dim3 grid((unsigned)(Tr + g.zero_blocks + g.pieces));
+            if (g.numbers) hipLaunchKernelGGL(gather_rows_kernel<true>, grid, dim3(256), 0, s, gp, transpose);
             else hipLaunchKernelGGL(gather_rows_kernel<false>, grid, dim3(256), 0, s, gp, transpose);
             ALST_HIP(hipGetLastError());
         }
@@ -1566,17 +1616,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
         if (rc != ALST_OK) return rc;
         if (!do_bwd) continue;
 
-        // dHidden in small blocks (a block is 16 of 64 columns or fewer), and dW, which joins its launch while both together are
-        // at most one round; us of a call, two launches / one: 512 x 256 x 4096 39.0 / 35.0, 512 x 1024 x 1024 43.8 / 39.3, 300 x
-        // 256 x 1000 35.2 / 27.7
-        auto dh_small = [&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); };
-        auto dw_small = [&](int64_t cols) { return small_blocks(H, V, cols); };
-        auto dw_grid = [&](int columns) {
-            return columns ? choose_patches((H + kSmallRows - 1) / kSmallRows, (V + columns - 1) / columns)
-                           : choose_patches((H + kBlockR - 1) / kBlockR, Vp / kBlockC);
-        };
-        const int dh_columns = small_block_columns(dh_small);
-        const int both = !c.group_done ? 0 : small_block_columns([&](int64_t cols) { return dh_small(cols) + dw_small(cols); });
+        const GradientLaunches gl = choose_gradients(c, P.H, P.V, L.Vp);
         DWParams wp = {};
         if (c.group_done) {
             wp.hg = hc; wp.dzg = stash; wp.hdr = hdr;
@@ -1584,8 +1624,7 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
                       (P.flags & ALST_FLAG_DW_ACCUMULATE) != 0};
             wp.row0 = c.group0; wp.rows = L.Kg;
             wp.H = H; wp.Hk = (int)L.Hk; wp.V = V; wp.Vp = Vp;
-            const PatchGrid pg = dw_grid(both);
-            wp.PR = pg.PR; wp.PC = pg.PC;
+            wp.PR = gl.dw.PR; wp.PC = gl.dw.PC;
         }
         {
             DHiddenParams dp;
@@ -1594,23 +1633,20 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             dp.part = part;
             dp.H = H; dp.V = V; dp.Vp = Vp;
             dp.PR = L.dh_PR; dp.PC = L.dh_PC;
-            // enough workgroups for whatever number of rows and ranges the chunk turns out to have
-            const int grid = grid_for_blocks(c.dh_blocks);
+            const dim3 grid((unsigned)gl.dh_grid), threads(DirectCore::kThreads);
             ProfScope ps_(PROF_DHIDDEN, s, tiles);
-            if (both == 64)
-                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<4>, KMajorSplitT<2>>), dim3(kRound), dim3(RingCoreT<4>::kThreads),
+            if (gl.together && gl.dh_columns == 64)
+                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<4>, KMajorSplitT<2>>), grid, threads,
                                    (gradients_small_lds<RingCoreT<4>, KMajorSplitT<2>>()), s, dp, wp);
-            else if (both == 128)
-                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<8>, KMajorSplitT<4>>), dim3(kRound), dim3(RingCoreT<8>::kThreads),
+            else if (gl.together)
+                hipLaunchKernelGGL((gradients_small_kernel<RingCoreT<8>, KMajorSplitT<4>>), grid, threads,
                                    (gradients_small_lds<RingCoreT<8>, KMajorSplitT<4>>()), s, dp, wp);
-            else if (dh_columns == 64)
-                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<4>>, dim3(kRound), dim3(RingCoreT<4>::kThreads),
-                                   RingCoreT<4>::kLds, s, dp);
-            else if (dh_columns == 128)
-                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<8>>, dim3(kRound), dim3(RingCoreT<8>::kThreads),
-                                   RingCoreT<8>::kLds, s, dp);
+            else if (gl.dh_columns == 64)
+                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<4>>, grid, threads, RingCoreT<4>::kLds, s, dp);
+            else if (gl.dh_columns == 128)
+                hipLaunchKernelGGL(dhidden_small_kernel<RingCoreT<8>>, grid, threads, RingCoreT<8>::kLds, s, dp);
             else
-                hipLaunchKernelGGL(dhidden_kernel, dim3(grid), dim3(DirectCore::kThreads), kLdsBytes, s, dp);
+                hipLaunchKernelGGL(dhidden_kernel, grid, threads, kLdsBytes, s, dp);
             if (c.dh_cut) {
                 loss_made = do_fwd && first + rows == P.N && P.N <= kLossInReduceRows;
                 hipLaunchKernelGGL(dhidden_reduce_kernel, dim3(Tr + loss_made), dim3(256), 0, s, dp.part, H, idx_t,
@@ -1618,14 +1654,11 @@ static int run(const Problem& P, bool do_fwd, bool do_bwd) {
             }
             ALST_HIP(hipGetLastError());
         }
-        if (c.group_done && !both) {
-            const int columns = small_block_columns(dw_small);
-            const PatchGrid pg = dw_grid(columns);
-            wp.PR = pg.PR; wp.PC = pg.PC;
-            const dim3 grid((unsigned)grid_for_blocks(pg.blocks())), threads(KMajorCore::kThreads);
+        if (c.group_done && !gl.together) {
+            const dim3 grid((unsigned)gl.dw_grid), threads(KMajorCore::kThreads);
             ProfScope ps_(PROF_DW, s);
-            if (columns == 64) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<2>>, grid, threads, KMajorSplitT<2>::kLds, s, wp);
-            else if (columns == 128) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<4>>, grid, threads, KMajorSplitT<4>::kLds, s, wp);
+            if (gl.dw_columns == 64) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<2>>, grid, threads, KMajorSplitT<2>::kLds, s, wp);
+            else if (gl.dw_columns) hipLaunchKernelGGL(dw_small_kernel<KMajorSplitT<4>>, grid, threads, KMajorSplitT<4>::kLds, s, wp);
             else hipLaunchKernelGGL(dw_kernel, grid, threads, kLdsBytes, s, wp);
             ALST_HIP(hipGetLastError());
         }
@@ -1831,10 +1864,25 @@ int alst_debug_ce_chunk(int64_t N, int64_t H, int64_t V, int64_t tile, uint32_t 
     info->group0 = c.group0;
     info->ranges = ranges;
     info->added_up = c.dh_cut;
-    info->dhidden_blocks = Trc / kBlockR * ((H + kBlockC - 1) / kBlockC) * ranges;
-    info->dhidden_grid = grid_for_blocks(c.dh_blocks);
-    info->largest_grid = std::max<int64_t>({c.Tr + kZeroBlocksMax, info->dhidden_grid,
-                                            grid_for_blocks(c.Tr / kBlockR * (L.Vp / kBlockC))});
+    const int64_t at = first - c.rows;
+    const GatherLaunch g = choose_gather(L, weight_transpose(L, nullptr, nullptr, H, V, true), N, H, V, at, c.Tr, true);
+    const LogitsLaunch l = choose_logits(c.Tr, (int)L.Vp, H);
+    const GradientLaunches gl = choose_gradients(c, H, V, L.Vp);
+    info->dhidden_blocks = (gl.dh_columns ? Trc / kSmallRows * ((H + gl.dh_columns - 1) / gl.dh_columns)
+                                          : Trc / kBlockR * ((H + kBlockC - 1) / kBlockC)) * ranges;
+    info->dhidden_grid = gl.dh_grid;
+    info->dw_blocks = c.group_done ? gl.dw.blocks() : 0;
+    info->dw_grid = gl.dw_grid;
+    info->gather_grid = c.Tr + g.zero_blocks + g.pieces;
+    info->largest_grid = std::max<int64_t>({info->gather_grid, (int64_t)gl.dh_grid, (int64_t)gl.dw_grid, (int64_t)l.grid,
+                                            (int64_t)c.Tr + 1});
+    info->logits_columns = l.columns;
+    info->logits_chained = l.chain;
+    info->dhidden_columns = gl.dh_columns;
+    info->dw_columns = gl.dw_columns;
+    info->together = gl.together;
+    info->numbered_by_gather = g.numbers;
+    info->transposed_apart = g.transposes_apart;
     info->in_stash = c.part != L.part;
     return ALST_OK;
 }

@@ -961,8 +961,7 @@ static int run_mlp_backward(const MlpProblem& P) {
     if (L.weights_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
         const Transposes ts = {{{P.Wd, H, I, I, wdt, H, H}, {P.Wg, I, H, H, wgut, I2, I}, {P.Wu, I, H, H, wgut + I, I2, I}}};
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
-        ALST_HIP(hipGetLastError());
+        if (!launch_transposes(ts, s)) return ALST_ERR_HIP;
     }
 
     for (int64_t i0 = 0; i0 < P.N; i0 += L.chunk) {
@@ -1126,8 +1125,7 @@ static int run_lin_backward(const LinProblem& P) {
     if (L.weight_t) {
         ProfScope ps(PROF_MLP_OTHER, s);
         const Transposes ts = {{{P.W, M, K, K, wt, M, M}}};
-        hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)ts.pieces()), dim3(256), 0, s, ts);
-        ALST_HIP(hipGetLastError());
+        if (!launch_transposes(ts, s)) return ALST_ERR_HIP;
     }
     const int64_t chunk = lin_chunk_rows(P.N, P.M, P.K, L.weight_t);
     LinearParams lp = {};

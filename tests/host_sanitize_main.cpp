@@ -62,10 +62,14 @@ int main() {
                             alst_debug_ce_chunk_info i;
                             EXPECT(alst_debug_ce_chunk(N, H, V, T, f, 0, 0, &i) == ALST_OK);
                             const int64_t rows = i.rows;
-                            EXPECT(rows >= 1 && rows <= N && i.largest_grid < (1 << 24));
+                            EXPECT(rows >= 1 && rows <= N && i.gather_grid < (1 << 24));
+                            // (dW of more blocks than a grid holds: a weight of 2^41 bytes)
+                            EXPECT(i.largest_grid < (1 << 24) || H * V >= (int64_t)1 << 39);
                             for (int64_t dense : {(int64_t)1, rows / 2, rows}) {
                                 EXPECT(alst_debug_ce_chunk(N, H, V, T, f, 0, dense, &i) == ALST_OK);
-                                EXPECT(i.dhidden_blocks <= i.dhidden_grid && (i.ranges == 1 || i.added_up));
+                                EXPECT(i.dhidden_blocks + (i.together ? i.dw_blocks : 0) <= i.dhidden_grid);
+                                EXPECT(i.ranges == 1 || i.added_up);
+                                EXPECT(i.together || i.dw_blocks <= i.dw_grid);
                             }
                         }
                         const int rt = alst_tiled_ce_token_losses(fake(0x50000), w - 1, N, H, V, T, f,

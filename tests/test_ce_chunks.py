@@ -23,6 +23,20 @@ def _check(N, H, V, tile, flags, chunk, dense):
     assert i.ranges == 1 or i.added_up, case
     assert i.dhidden_blocks <= i.dhidden_grid, case
     assert i.largest_grid < 1 << 24, case              # workgroups of 256, fewer than 2^32 threads
+    assert i.largest_grid >= max(i.gather_grid, i.dhidden_grid, i.dw_grid), case
+    # the gathering launch: the rows, those who look for ignored tokens and, unless that is too many, those who transpose W
+    rows, zeroes = -(-i.rows // 256) * 256, min(-(-N // 16), 32768) if chunk == 0 else 0
+    pieces = -(-V // 64) * -(-H // 64) if chunk == 0 else 0
+    assert i.transposed_apart == (rows + zeroes + pieces > (1 << 24) - 256), case
+    assert i.gather_grid == rows + zeroes + (0 if i.transposed_apart else pieces), case
+    # small blocks are at most one round of the compute units, with dW's if these are in the same launch
+    if i.dhidden_columns:
+        assert i.dhidden_grid == 256 and i.dhidden_blocks + (i.dw_blocks if i.together else 0) <= 256, case
+    if i.dw_columns:
+        assert i.dw_blocks <= 256, case
+    assert i.dw_blocks <= i.dw_grid or i.together or i.dw_blocks == 0, case
+    if i.together:
+        assert i.dhidden_columns == i.dw_columns != 0 and i.dw_grid == 0, case
     return i
 
 
@@ -68,6 +82,30 @@ def test_chunks_of_a_long_vocabulary(N, H, V, tile, rows):
     assert at == N and lengths[0][1] == rows
     for (group, n), (after, _) in zip(lengths, lengths[1:] + [(-1, 0)]):
         assert n == rows if group == after else n <= rows + rows // 4      # (a group's last chunk)
+
+
+@pytest.mark.parametrize("N,H,V,apart", [(4096, 4096, 128256, 0), (8192, 8192, 8380000, 0), (4096, 8192, 8388608, 1)])
+def test_the_transposition_is_a_launch_of_its_own_where_a_grid_ends(N, H, V, apart):
+    assert _check(N, H, V, 2048, 0, 0, 0).transposed_apart == apart
+    if N > 4096:
+        assert _check(N, H, V, 2048, 0, 1, 0).transposed_apart == 0
+
+
+def test_small_blocks_for_every_number_of_rows():
+    """Every number of dense rows of short calls around the ends of the rules, where the ranges change with the rows."""
+    seen = set()
+    for N, H, V in [(512, 256, 4096), (512, 512, 4096), (1024, 256, 2048), (1024, 72, 500), (300, 520, 1000), (2048, 256, 1000),
+                    (256, 64, 20000), (700, 2304, 2304), (1000, 64, 3000), (200, 512, 4000), (1024, 512, 2048), (100, 2304, 2304),
+                    (3000, 256, 1500)]:
+        for tile in (128, N):
+            at, k = 0, 0
+            while at < N:
+                rows = B.alst_debug_ce_chunk(N, H, V, tile, 0, k, 0).rows
+                for dense in range(0, rows + 1, 1 if rows < 400 else 7):
+                    i = _check(N, H, V, tile, 0, k, dense)
+                    seen.add((i.dhidden_columns, i.dw_columns, i.together))
+                at, k = at + rows, k + 1
+    assert seen >= {(64, 64, 1), (128, 128, 1), (64, 128, 0), (128, 64, 0), (128, 0, 0), (0, 64, 0), (0, 0, 0)}, seen
 
 
 def test_bad_arguments_are_rejected():
