@@ -1,7 +1,7 @@
 /*
  * alst_debug.h -- benchmarking and testing aids of libalst.  None of them is part of the method
  * (no counterpart in the paper) and no product code needs them: the timers serve the benchmark,
- * the block mapping, the chunks and the matrix-instruction rate serve the tests and the roofline context.
+ * the block mapping, the chunks, the choice of launches and the matrix-instruction rate serve the tests and the roofline context.
  */
 #ifndef ALST_DEBUG_H
 #define ALST_DEBUG_H
@@ -47,6 +47,21 @@ int alst_debug_block_tile(int tiles_r, int tiles_c, int parts, int bid, int* par
  * alst_tiled_linear_backward.  A negative return value is minus an alst_status.
  */
 int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t tile);
+
+/*
+ * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched): what the launches of a layer
+ * call's last chunk of rows run on (op, K, M: as above).  The library chooses its launches with the same functions.
+ */
+typedef struct {
+    int64_t rows;                        /* of the chunk */
+    int transposed;                      /* backward: against the weights transposed, not as they are */
+    int gated_columns, gated_chained;    /* MLP, gate and up: columns of the small blocks (64 rows), 0: 256 x 256, one a
+                                            workgroup or (chained) on persistent workgroups that walk chains of them */
+    int product_columns, product_chained;        /* y; backward: dx */
+    int wgrad_columns;                   /* the weight gradients of the group (linear layer: the first) */
+    int together;                        /* dx and they are one launch */
+} alst_debug_layer_info;
+int alst_debug_layer(int op, int64_t N, int64_t K, int64_t M, int64_t tile, uint32_t flags, alst_debug_layer_info* info);
 
 /*
  * Testing aid (no counterpart in the paper; host arithmetic only, no device is touched): chunk number

@@ -30,7 +30,7 @@ EXPORTS = (
     "alst_tiled_ce_forward_backward_noalloc", "alst_last_device_status",
     "alst_shift_labels", "alst_tiled_ce_token_losses",
     "alst_profile_enable", "alst_profile_read", "alst_debug_block_tile", "alst_debug_chunk_rows",
-    "alst_debug_ce_chunk", "alst_debug_mfma_rate",
+    "alst_debug_layer", "alst_debug_ce_chunk", "alst_debug_mfma_rate",
     "alst_tiled_mlp_workspace_bytes", "alst_tiled_mlp_forward", "alst_tiled_mlp_backward",
     "alst_tiled_linear_workspace_bytes", "alst_tiled_linear_forward", "alst_tiled_linear_backward",
 )
@@ -43,6 +43,13 @@ class CeChunkInfo(ctypes.Structure):
                [(n, ctypes.c_int) for n in ("ranges", "added_up", "in_stash", "logits_columns", "dhidden_columns",
                                             "dw_columns", "logits_chained", "together", "numbered_by_gather",
                                             "transposed_apart")]
+
+
+class LayerInfo(ctypes.Structure):
+    """alst_debug_layer_info (alst_debug.h)."""
+    _fields_ = [("rows", ctypes.c_int64)] + \
+               [(n, ctypes.c_int) for n in ("transposed", "gated_columns", "gated_chained", "product_columns",
+                                            "product_chained", "wgrad_columns", "together")]
 
 
 _lib = None
@@ -108,6 +115,8 @@ def load_library() -> ctypes.CDLL:
     lib.alst_debug_block_tile.argtypes = [c.c_int] * 4 + [c.POINTER(c.c_int)] * 3
     lib.alst_debug_chunk_rows.restype = i64
     lib.alst_debug_chunk_rows.argtypes = [c.c_int, i64, i64, i64, i64]
+    lib.alst_debug_layer.restype = c.c_int
+    lib.alst_debug_layer.argtypes = [c.c_int, i64, i64, i64, i64, u32, c.POINTER(LayerInfo)]
     lib.alst_debug_ce_chunk.restype = c.c_int
     lib.alst_debug_ce_chunk.argtypes = [i64, i64, i64, i64, u32, i64, i64, c.POINTER(CeChunkInfo)]
     _lib = lib
@@ -391,6 +400,13 @@ def alst_debug_chunk_rows(op: int, N: int, K: int, M: int, tile: int) -> int:
     if n < 0:
         raise AlstError(-n, "alst_debug_chunk_rows")
     return n
+
+
+def alst_debug_layer(op: int, N: int, K: int, M: int, tile: int, flags: int = 0) -> LayerInfo:
+    """What a layer call's launches run on (op: see alst_debug.h).  Host arithmetic only."""
+    info = LayerInfo()
+    _check(load_library().alst_debug_layer(op, N, K, M, tile, flags, ctypes.byref(info)), "alst_debug_layer")
+    return info
 
 
 def alst_debug_ce_chunk(N: int, H: int, V: int, tile: int, flags: int, chunk: int, dense: int) -> CeChunkInfo:

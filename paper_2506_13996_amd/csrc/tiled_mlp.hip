@@ -731,23 +731,39 @@ static int launch_linear_small(const LinearParams* ps, int n, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
+// What a launch runs on: small blocks of that many columns, or (0) large ones, one a workgroup or in chains.
+struct BlockChoice {
+    int columns;
+    bool chain;
+};
+static BlockChoice choose_linear(const LinearParams* ps, int n) {
+    BlockChoice c = {};
+    if (ps[0].y_kmajor) return c;
+    c.columns = small_columns(ps, n);
+    if (c.columns) return c;
+    int64_t total = 0;
+    bool one_k = true;                                            // (a chain is of one K)
+    for (int i = 0; i < n; ++i) {
+        total += (int64_t)((ps[i].rows_x + kBlockR - 1) / kBlockR) * ((ps[i].rows_y + kBlockC - 1) / kBlockC);
+        one_k = one_k && ps[i].K == ps[0].K;
+    }
+    c.chain = one_k && chain_pays(total, ps[0].K, false);
+    return c;
+}
+
 // One launch for the n products (n <= kMaxBatch), all of one kind (y_kmajor).
 static int launch_linear(const LinearParams* ps, int n, hipStream_t s) {
-    if (!ps[0].y_kmajor) {
-        const int columns = small_columns(ps, n);
-        if (columns == 64) return launch_linear_small<RingCoreT<4>>(ps, n, s);
-        if (columns == 128) return launch_linear_small<RingCoreT<8>>(ps, n, s);
-    }
+    const auto [columns, chain] = choose_linear(ps, n);
+    if (columns == 64) return launch_linear_small<RingCoreT<4>>(ps, n, s);
+    if (columns == 128) return launch_linear_small<RingCoreT<8>>(ps, n, s);
     LinearBatch b = {};
     const int64_t total = number_blocks(b, ps, n, kBlockR, kBlockC);
     if (total > 0x7fffff00) return ALST_ERR_SHAPE;
     bool guard = false, ktail = false;
-    bool chain = !ps[0].y_kmajor && chain_pays(total, ps[0].K, false);          // (of one K)
     for (int i = 0; i < n; ++i) {
         const LinearParams& p = ps[i];
         guard = guard || p.rows_x % kBlockR != 0 || p.rows_y % kBlockC != 0;
         ktail = ktail || p.K % kBlockK != 0;
-        chain = chain && p.K == ps[0].K;
     }
     if (!ps[0].y_kmajor) b.map.last = halve_last_round((int)total);
     b.map.rows = n == 1 && !ps[0].y_kmajor && by_rows(b.map.g[0], ps[0].K);
@@ -827,12 +843,15 @@ static int launch_backward_small(const LinearParams& lp, const WgradParams* ps, 
 // small_block_columns).  The launch and the shorter product cost nothing then; us of a forward and backward call, two launches / one:
 // MLP 512 x 256 x 768 40.8 / 34.3, 1024 x 256 x 512 39.4 / 31.0, 512 x 512 x 1024 51.5 / 47.7; linear 512 x 1024 x 1024, whose
 // blocks become 64 x 128 where two launches had 64 x 64, 27.4 / 24.1.
-static int launch_backward(const LinearParams& lp, const WgradParams* ps, int n, hipStream_t s) {
-    const int columns = lp.y_kmajor ? 0 : small_block_columns([&](int64_t c) {
+static int choose_together(const LinearParams& lp, const WgradParams* ps, int n) {       // columns of the blocks, or 0: two launches
+    return lp.y_kmajor ? 0 : small_block_columns([&](int64_t c) {
         int64_t total = small_blocks(lp.rows_x, lp.rows_y, c);
         for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
         return total;
     });
+}
+static int launch_backward(const LinearParams& lp, const WgradParams* ps, int n, hipStream_t s) {
+    const int columns = choose_together(lp, ps, n);
     if (columns == 64) return launch_backward_small<RingCoreT<4>, KMajorSplitT<2>>(lp, ps, n, s);
     if (columns == 128) return launch_backward_small<RingCoreT<8>, KMajorSplitT<4>>(lp, ps, n, s);
     const int rc = launch_linear(lp, s);
@@ -884,8 +903,11 @@ static int launch_gated_small(GatedParams gp, bool bwd, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
-static int gated_small_columns(int rows, int64_t I) {
-    return small_block_columns([&](int64_t c) { return small_blocks(rows, 2 * I, c); });
+static BlockChoice choose_gated(int rows, int64_t H, int64_t I) {
+    BlockChoice c = {};
+    c.columns = small_block_columns([&](int64_t cols) { return small_blocks(rows, 2 * I, cols); });
+    if (!c.columns) c.chain = chain_pays((rows + kBlockR - 1) / kBlockR * ((I + 127) / 128), H, true);
+    return c;
 }
 // a = silu(x_t Wg^T) * (x_t Wu^T) for `rows` rows of x; backward (da given, or dy_t and Wd transposed to make it from
 // if the blocks are small): also [dg | du].
@@ -896,7 +918,7 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.X = x_t; gp.ldx = P.H; gp.rows_x = rows; gp.K = (int)P.H;
     gp.Wg = P.Wg; gp.Wu = P.Wu; gp.ldw = P.H; gp.I = (int)P.I;
     gp.da = da; gp.a = a; gp.dgu = dgu;
-    const int columns = gated_small_columns(rows, P.I);
+    const auto [columns, chain] = choose_gated(rows, P.H, P.I);
     if (columns == 64) return launch_gated_small<RingCoreT<4>>(gp, dgu != nullptr, s);
     if (columns == 128) return launch_gated_small<RingCoreT<8>>(gp, dgu != nullptr, s);
     gp.grid = choose_patches((rows + kBlockR - 1) / kBlockR, (int)((P.I + 127) / 128));
@@ -904,7 +926,6 @@ static int launch_gated(const MlpProblem& P, const uint16_t* x_t, int rows, cons
     gp.rows = by_rows(gp.grid, gp.K);
     const int blocks = grid_for_blocks(gp.grid.blocks()), whole = grid_for_blocks(gp.last.full);
     const bool guard = rows % kBlockR != 0 || P.I % 128 != 0, ktail = P.H % kBlockK != 0;
-    const bool chain = chain_pays(gp.grid.blocks(), P.H, true);
     const dim3 all((unsigned)blocks), persistent((unsigned)std::min(blocks, persistent_grid()));
     const dim3 threads(DirectCore::kThreads);
     ProfScope pr(PROF_MLP_LINEAR, s);
@@ -941,6 +962,30 @@ static int run_mlp_forward(const MlpProblem& P) {
     return ALST_OK;
 }
 
+// The extents of backward's products: dx of `rows` rows, the three weight gradients of a group of `rows` rows.
+static LinearParams mlp_dx_extents(const MlpLayout& L, int rows, int H, int I) {
+    LinearParams lp = {};
+    lp.rows_x = rows; lp.ldx = 2 * (int64_t)I; lp.rows_y = H; lp.ldd = H;
+    if (L.weights_t) {
+        // one contraction over the 2 I columns of [dg | du] against [Wg | Wu]^T [H, 2 I]
+        lp.K = 2 * I; lp.ldy = 2 * (int64_t)I;
+    } else {
+        // two contractions over I summed in the accumulators, the weights [I, H] as they are: k = i
+        lp.K = I; lp.ldy = H; lp.y_kmajor = 1;
+    }
+    return lp;
+}
+static void mlp_wgrad_extents(WgradParams (&wp)[kMaxBatch], int64_t rows, int H, int I) {
+    wp[0] = {};
+    wp[0].K = (int)rows;
+    wp[0].ldx = H; wp[0].rows_x = H;                    // x
+    wp[0].ldy = 2 * (int64_t)I; wp[0].rows_y = I;       // dg
+    wp[1] = wp[0];                                      // x, du
+    wp[2] = wp[0];
+    wp[2].ldx = I; wp[2].rows_x = I;                    // a
+    wp[2].ldy = H; wp[2].rows_y = H;                    // dy
+}
+
 static int run_mlp_backward(const MlpProblem& P) {
     int rc = prepare_mlp_kernels();
     if (rc != ALST_OK) return rc;
@@ -972,7 +1017,7 @@ static int run_mlp_backward(const MlpProblem& P) {
         const uint16_t* x_c = P.x + i0 * P.H;
         const uint16_t* dy_c = P.dy + i0 * P.H;
 
-        if (L.weights_t && gated_small_columns(rows, I)) {
+        if (L.weights_t && choose_gated(rows, H, I).columns) {
             rc = launch_gated(P, x_c, rows, nullptr, a_c, dgu_c, s, dy_c, wdt);
             if (rc != ALST_OK) return rc;
         } else {   // da = dy Wd (contraction over H), then g and u again with a, dg, du made in the epilogue
@@ -985,19 +1030,11 @@ static int run_mlp_backward(const MlpProblem& P) {
             if (rc == ALST_OK) rc = launch_gated(P, x_c, rows, a_c, a_c, dgu_c, s);
             if (rc != ALST_OK) return rc;
         }
-        LinearParams lp = {};
-        {   // dx = dg Wg + du Wu
-            lp.X = dgu_c; lp.ldx = I2; lp.rows_x = rows;
-            if (L.weights_t) {
-                // one contraction over the 2 I columns of [dg | du] against [Wg | Wu]^T [H, 2 I]
-                lp.K = (int)I2; lp.Y = wgut; lp.ldy = I2; lp.rows_y = H;
-            } else {
-                // two contractions over I summed in the accumulators, the weights as they are
-                lp.K = I; lp.Y = P.Wg; lp.ldy = H; lp.rows_y = H; lp.y_kmajor = 1;     // Wg [I, H]: k = i
-                lp.X2 = dgu_c + I; lp.Y2 = P.Wu;
-            }
-            lp.D = P.dx + i0 * P.H; lp.ldd = H;
-        }
+        // dx = dg Wg + du Wu
+        LinearParams lp = mlp_dx_extents(L, rows, H, I);
+        lp.X = dgu_c; lp.D = P.dx + i0 * P.H;
+        if (L.weights_t) lp.Y = wgut;
+        else { lp.Y = P.Wg; lp.X2 = dgu_c + I; lp.Y2 = P.Wu; }
         const int64_t in_group = i0 + rows - group0;
         if (in_group < L.rows && i0 + rows < P.N) {
             rc = launch_linear(lp, s);
@@ -1007,17 +1044,11 @@ static int run_mlp_backward(const MlpProblem& P) {
         // the group is complete
         GradOut out = {nullptr, nullptr, 0, 1.f, group0 == 0, i0 + rows == P.N, f32, accum};
         auto into = [&](float* sums, void* dW, int64_t ld) { out.sums = sums; out.out = dW; out.ld = ld; return out; };
-        WgradParams wp[kMaxBatch] = {};
-        wp[0].K = (int)in_group;
-        wp[0].X = P.x + group0 * H; wp[0].ldx = H; wp[0].rows_x = H;
-        wp[0].Y = dgu; wp[0].ldy = I2; wp[0].rows_y = I;
-        wp[0].out = into(acc_g, P.dWg, H);                                       // dWg[i][h]
-        wp[1] = wp[0];
-        wp[1].Y = dgu + I; wp[1].out = into(acc_u, P.dWu, H);                    // dWu[i][h]
-        wp[2] = wp[0];
-        wp[2].X = a; wp[2].ldx = I; wp[2].rows_x = I;
-        wp[2].Y = P.dy + group0 * H; wp[2].ldy = H; wp[2].rows_y = H;
-        wp[2].out = into(acc_d, P.dWd, I);                                       // dWd[h][i]
+        WgradParams wp[kMaxBatch];
+        mlp_wgrad_extents(wp, in_group, H, I);
+        wp[0].X = P.x + group0 * H; wp[0].Y = dgu; wp[0].out = into(acc_g, P.dWg, H);                     // dWg[i][h]
+        wp[1].X = P.x + group0 * H; wp[1].Y = dgu + I; wp[1].out = into(acc_u, P.dWu, H);                 // dWu[i][h]
+        wp[2].X = a; wp[2].Y = P.dy + group0 * H; wp[2].out = into(acc_d, P.dWd, I);                      // dWd[h][i]
         // (weights transposed into the room of the sums: a call of one group, whose gradients don't touch the sums)
         rc = launch_backward(lp, wp, 3, s);
         if (rc != ALST_OK) return rc;
@@ -1044,6 +1075,9 @@ struct LinLayout {
     bool weight_t;         // backward multiplies dy by a transposed copy of W
 };
 
+// Rows of a weight-gradient group.
+static int64_t lin_group_rows(const LinLayout& L) { return std::max<int64_t>(kMlpGroupRows, L.Tp); }
+
 static LinLayout make_lin_layout(int64_t N, int64_t K, int64_t M, int64_t tile, bool backward,
                                  uint32_t flags) {
     LinLayout L = {};
@@ -1058,7 +1092,7 @@ static LinLayout make_lin_layout(int64_t N, int64_t K, int64_t M, int64_t tile, 
         // rows (the fastest layout of the block GEMM).  M that is not whole k-steps: no room of its own, but a call of one
         // group leaves that of the sums unused; else W is read as it is.
         const bool whole = M % kBlockK == 0;
-        L.weight_t = whole || (!in_out && N <= std::max<int64_t>(kMlpGroupRows, L.Tp));
+        L.weight_t = whole || (!in_out && N <= lin_group_rows(L));
         L.wt = take(whole ? (size_t)K * M * 2 : 0);
         if (!whole) L.wt = L.acc;
     }
@@ -1112,6 +1146,21 @@ static int run_lin_forward(const LinProblem& P) {
     return ALST_OK;
 }
 
+// The extents of backward's products: dx of `rows` rows, dW of a group of `rows` rows.
+static LinearParams lin_dx_extents(const LinLayout& L, int rows, int K, int M) {
+    LinearParams lp = {};
+    lp.rows_x = rows; lp.ldx = M; lp.K = M; lp.rows_y = K; lp.ldd = K;
+    if (L.weight_t) lp.ldy = M;                         // W^T [K, M]
+    else { lp.ldy = K; lp.y_kmajor = 1; }               // W [M, K]: k = m
+    return lp;
+}
+static WgradParams lin_wgrad_extents(int64_t rows, int K, int M) {
+    WgradParams wp = {};
+    wp.K = (int)rows;
+    wp.ldx = K; wp.rows_x = K; wp.ldy = M; wp.rows_y = M;
+    return wp;
+}
+
 static int run_lin_backward(const LinProblem& P) {
     int rc = prepare_mlp_kernels();
     if (rc != ALST_OK) return rc;
@@ -1130,23 +1179,19 @@ static int run_lin_backward(const LinProblem& P) {
     const int64_t chunk = lin_chunk_rows(P.N, P.M, P.K, L.weight_t);
     LinearParams lp = {};
     for (int64_t i0 = 0; i0 < P.N; i0 += chunk) {
-        lp.X = P.dy + i0 * P.M; lp.ldx = M; lp.rows_x = (int)std::min(chunk, P.N - i0); lp.K = M;
-        if (L.weight_t) { lp.Y = wt; lp.ldy = M; lp.rows_y = K; }         // W^T [K, M]
-        else { lp.Y = P.W; lp.ldy = K; lp.rows_y = K; lp.y_kmajor = 1; }  // W [M, K]: k = m
-        lp.D = P.dx + i0 * P.K; lp.ldd = K;
+        lp = lin_dx_extents(L, (int)std::min(chunk, P.N - i0), K, M);
+        lp.X = P.dy + i0 * P.M; lp.Y = L.weight_t ? wt : P.W; lp.D = P.dx + i0 * P.K;
         if (i0 + chunk >= P.N) break;                                     // (the last one: with the first group)
         rc = launch_linear(lp, s);
         if (rc != ALST_OK) return rc;
     }
-    const int64_t group = std::max<int64_t>(kMlpGroupRows, L.Tp);
+    const int64_t group = lin_group_rows(L);
     for (int64_t i0 = 0; i0 < P.N; i0 += group) {
         // dW[m][k] += sum over the group's rows of dy[t][m] x[t][k]: both operands are read
         // from the caller's arrays as they are
         const int64_t rows = std::min(group, P.N - i0);
-        WgradParams wp = {};
-        wp.X = P.x + i0 * P.K; wp.ldx = K; wp.rows_x = K;
-        wp.Y = P.dy + i0 * P.M; wp.ldy = M; wp.rows_y = M;
-        wp.K = (int)rows;
+        WgradParams wp = lin_wgrad_extents(rows, K, M);
+        wp.X = P.x + i0 * P.K; wp.Y = P.dy + i0 * P.M;
         wp.out = {acc, P.dW, K, 1.f, i0 == 0, i0 + rows == P.N, f32, accum};
         rc = i0 == 0 ? launch_backward(lp, &wp, 1, s) : launch_wgrad(wp, s);
         if (rc != ALST_OK) return rc;
@@ -1234,6 +1279,60 @@ int64_t alst_debug_chunk_rows(int op, int64_t N, int64_t K, int64_t M, int64_t t
     if (op < 2) return make_mlp_layout(N, K, M, tile, op == 1, 0).chunk;
     if (op == 2) return lin_chunk_rows(N, K, M);
     return lin_chunk_rows(N, M, K, make_lin_layout(N, K, M, tile, true, 0).weight_t);
+}
+
+int alst_debug_layer(int op, int64_t N, int64_t K, int64_t M, int64_t tile, uint32_t flags, alst_debug_layer_info* info) {
+    if (!info) return ALST_ERR_NULL;
+    const int64_t chunk = alst_debug_chunk_rows(op, N, K, M, tile);
+    if (chunk < 0) return (int)-chunk;
+    if (K % 8 != 0 || M % 8 != 0) return ALST_ERR_ALIGN;
+    if (flags & ~(ALST_FLAG_DW_FP32 | ALST_FLAG_DW_ACCUMULATE)) return ALST_ERR_UNSUPPORTED;
+    *info = {};
+    const int H = (int)K, I = (int)M;
+    auto last_rows = [&](int64_t of) { return (int)(N - (N - 1) / of * of); };
+    auto product = [&](const LinearParams& lp) {
+        const BlockChoice c = choose_linear(&lp, 1);
+        info->product_columns = c.columns;
+        info->product_chained = c.chain;
+    };
+    auto gradients = [&](const LinearParams& lp, const WgradParams* ps, int n) {
+        const int both = choose_together(lp, ps, n);
+        product(lp);
+        info->wgrad_columns = small_columns(ps, n);
+        info->together = both != 0;
+        if (both) info->product_columns = info->wgrad_columns = both;
+    };
+    if (op < 2) {
+        const MlpLayout L = make_mlp_layout(N, K, M, tile, op == 1, flags);
+        info->rows = last_rows(L.chunk);
+        const BlockChoice g = choose_gated((int)info->rows, K, M);
+        info->gated_columns = g.columns;
+        info->gated_chained = g.chain;
+        if (op == 0) {
+            LinearParams lp = {};
+            lp.rows_x = (int)info->rows; lp.K = I; lp.rows_y = H;
+            product(lp);
+        } else {
+            info->transposed = L.weights_t;
+            WgradParams wp[kMaxBatch];
+            mlp_wgrad_extents(wp, last_rows(L.rows), H, I);
+            gradients(mlp_dx_extents(L, (int)info->rows, H, I), wp, kMaxBatch);
+        }
+        return ALST_OK;
+    }
+    const LinLayout L = make_lin_layout(N, K, M, tile, op == 3, flags);
+    if (op == 2) {
+        info->rows = last_rows(chunk);
+        LinearParams lp = {};
+        lp.rows_x = (int)info->rows; lp.K = H; lp.rows_y = I;
+        product(lp);
+    } else {
+        info->rows = last_rows(lin_chunk_rows(N, M, K, L.weight_t));
+        info->transposed = L.weight_t;
+        const WgradParams wp = lin_wgrad_extents(std::min(lin_group_rows(L), N), H, I);
+        gradients(lin_dx_extents(L, (int)info->rows, H, I), &wp, 1);
+    }
+    return ALST_OK;
 }
 
 }  // extern "C"

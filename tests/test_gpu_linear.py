@@ -46,9 +46,8 @@ CASES = [
     # block-aligned K and M, rows not a whole number of k-steps: dW's last k-step has 12 rows
     ("aligned_ragged_rows", 1100, 256, 512, 512),
     ("aligned_few_rows", 40, 256, 256, 64),
-    # 4 x 97 output blocks on 256 persistent workgroups: chains of two blocks (the second fetched
-    # during the first one's last k-steps), chains of one, and padding block numbers in between
-    ("chained_blocks", 1024, 384, 24832, 1024),
+    # 4 x 97 output blocks: one and a half rounds of single blocks (chains of two and of one: test_gpu_chains.py)
+    ("blocks_of_two_rounds", 1024, 384, 24832, 1024),
     # 4 x 257 blocks: chains of four and five
     ("long_chains", 1024, 256, 65792, 1024),
 ]

@@ -213,7 +213,7 @@ def test_mlp_hip_graph_replays_match_eager():
 
 
 def test_mlp_random_shapes_against_oracle():
-    """A seeded sweep of odd and block-aligned shapes: chains of blocks and single ones, weights
+    """A seeded sweep of odd and block-aligned shapes, most of them on small blocks: weights
     transposed and as they are, ragged tiles and row counts that are not whole k-steps."""
     g = np.random.default_rng(77)
     for case in range(10):

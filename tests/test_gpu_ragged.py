@@ -27,7 +27,7 @@ SHAPES = [
     (255, 192, 328, 300),
     (129, 200, 520, 100),
     (321, 264, 136, 256),
-    (513, 256, 776, 200),         # whole pairs of k-steps: chains of blocks, rows and columns ragged
+    (513, 256, 776, 200),         # whole k-steps, rows and columns ragged
     (1025, 320, 512, 512),
 ]
 

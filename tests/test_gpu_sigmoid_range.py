@@ -5,6 +5,7 @@ tests."""
 import numpy as np
 import pytest
 
+from paper_2506_13996_amd import binding as B
 from paper_2506_13996_amd import synth
 from tests import gpu_util as G
 from tests import test_gpu_mlp as TM
@@ -13,12 +14,15 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
 
-@pytest.mark.parametrize("N,H,I,tile", [
-    (192, 64, 128, 2048),              # small blocks
-    (1032, 72, 1032, 2048),            # large blocks
-    (4096, 256, 8448, 4096),           # chains of blocks: 16 x 66
+@pytest.mark.parametrize("N,H,I,tile,columns,chained", [
+    (192, 64, 128, 2048, 64, 0),       # small blocks
+    (1032, 72, 1032, 2048, 0, 0),      # large blocks
+    (4096, 256, 8448, 4096, 0, 1),     # chains of blocks: 16 x 66
 ])
-def test_subnormal_sigmoid(N, H, I, tile):
+def test_subnormal_sigmoid(N, H, I, tile, columns, chained):
+    for op in (0, 1):
+        i = B.alst_debug_layer(op, N, H, I, tile)
+        assert (i.gated_columns, i.gated_chained) == (columns, chained)
     g = np.array([-87.5, -88.0, -88.5])[np.arange(N) % 3]
     u = 2.0 ** 20
     x, Wg, Wu = np.zeros((N, H)), np.zeros((I, H)), np.zeros((I, H))
