@@ -983,6 +983,19 @@ inline int small_block_columns(Count count) {
     return count(64) <= kRound ? 64 : count(128) <= kRound ? 128 : 0;
 }
 
+// Columns of the blocks of one launch of two kinds of products, dX (count(c): its blocks of 64 x c) and weight gradients
+// (count_w), or 0: a launch for each.  One while the small blocks of both are at most one round (blocks beyond it wait for a
+// compute unit, which costs more than the launch).  The launch and the shorter kind cost nothing then; but where a kind would have narrower
+// blocks alone, its longest block takes longer in the launch, by about 2 us (dX) or 1.4 us (weight gradients) per
+// 1000 of its contraction: may_widen, may_widen_w say whether that contraction is short enough beside the other's.
+template <class Count, class CountW>
+inline int joint_block_columns(Count count, bool may_widen, CountW count_w, bool may_widen_w) {
+    const int both = small_block_columns([&](int64_t c) { return count(c) + count_w(c); });
+    if (!may_widen && small_block_columns(count) < both) return 0;
+    if (!may_widen_w && small_block_columns(count_w) < both) return 0;
+    return both;
+}
+
 // Waits until at most `steps` (no more than MOST) steps' DMA of PER instructions each is in flight for this wavefront,
 // and for its LDS reads, then joins the wavefronts of the workgroup.
 template <int PER, int MOST>

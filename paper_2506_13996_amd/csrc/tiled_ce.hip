@@ -1454,13 +1454,19 @@ struct GradientLaunches {
     int dh_grid, dw_grid;
 };
 // dHidden in small blocks (a block is 16 of 64 columns or fewer), and dW, which joins its launch while both together are
-// at most one round; us of a call, two launches / one: 512 x 256 x 4096 39.0 / 35.0, 512 x 1024 x 1024 43.8 / 39.3, 300 x
-// 256 x 1000 35.2 / 27.7
+// at most one round; us of a call, two launches / one: 512 x 256 x 4096 40.1 / 38.1, 512 x 1024 x 1024 46.2 / 42.7, 300 x 256 x 1000
+// 36.2 / 30.7.  Where dW's blocks become wider, up to 1024 + 10 times as many rows as a range of V has words: 3500 x 512 x 256 58.1 / 56.4,
+// 5000 x 256 x 512 71.0 / 64.5; beyond: 4096 x 256 x 256 53.3 / 54.2, 7000 x 128 x 256 63.2 / 65.6.  Where dHidden's do, ranges
+// of up to 2048 more words than rows: beyond, 256 x 64 x 24000 54.1 / 58.0.
 static GradientLaunches choose_gradients(const ChunkPlan& c, int64_t H, int64_t V, int64_t Vp) {
     GradientLaunches g = {};
     auto dh_small = [&](int64_t cols) { return c.dh_blocks * 4 * (kBlockC / cols); };
     auto dw_small = [&](int64_t cols) { return small_blocks(H, V, cols); };
-    const int both = !c.group_done ? 0 : small_block_columns([&](int64_t cols) { return dh_small(cols) + dw_small(cols); });
+    int ranges, ksteps;                // of a chunk whose rows are all there
+    dhidden_splits(c.Tr, H, V, c.part_rows, ranges, ksteps);
+    const int64_t range = (int64_t)ksteps * kBlockK, group_rows = c.at + c.rows;
+    const int both = !c.group_done ? 0 : joint_block_columns(dh_small, range <= 2048 + group_rows,
+                                                             dw_small, group_rows <= 1024 + 10 * range);
     g.together = both != 0;
     g.dh_columns = both ? both : small_block_columns(dh_small);
     // (enough workgroups for whatever number of rows and ranges the chunk turns out to have)

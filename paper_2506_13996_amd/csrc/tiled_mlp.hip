@@ -708,14 +708,17 @@ static int64_t number_blocks(Batch& b, const Params* ps, int n, int block_r, int
     b.map.rows = false;
     return total;
 }
+// Small blocks of 64 x c of the n products.
+template <class Params>
+static int64_t count_small(const Params* ps, int n, int64_t c) {
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
+    return total;
+}
 // Columns of small blocks for the n products (small_block_columns), or 0: large ones.
 template <class Params>
 static int small_columns(const Params* ps, int n) {
-    return small_block_columns([&](int64_t c) {
-        int64_t total = 0;
-        for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
-        return total;
-    });
+    return small_block_columns([&](int64_t c) { return count_small(ps, n, c); });
 }
 
 template <class Core>
@@ -838,17 +841,21 @@ static int launch_backward_small(const LinearParams& lp, const WgradParams* ps, 
     return hipGetLastError() == hipSuccess ? ALST_OK : ALST_ERR_HIP;
 }
 
-// dx (lp) and the n weight gradients of the group that it completes.  One launch while the small blocks of all are at most
-// one round, two otherwise (blocks beyond a round wait for a compute unit, which costs more than the launch:
-// small_block_columns).  The launch and the shorter product cost nothing then; us of a forward and backward call, two launches / one:
-// MLP 512 x 256 x 768 40.8 / 34.3, 1024 x 256 x 512 39.4 / 31.0, 512 x 512 x 1024 51.5 / 47.7; linear 512 x 1024 x 1024, whose
-// blocks become 64 x 128 where two launches had 64 x 64, 27.4 / 24.1.
+// dx (lp) and the n weight gradients of the group that it completes, in one launch or two.  us of a backward call, two launches /
+// one (N x K x M, N x H x I):
+//   nothing wider: linear 3800 x 256 x 256 28.8 / 25.8, MLP 2000 x 256 x 512 40.5 / 32.6
+//   the weights' blocks wider, their contraction N at most 512 + 6 times dx's: linear 512 x 1024 x 1024 23.1 / 20.1, 4096 x 256 x
+//     1024 34.1 / 31.0, 3000 x 512 x 512 29.7 / 29.5, MLP 4000 x 256 x 512 60.5 / 57.0, 6000 x 256 x 512 70.8 / 66.8
+//   beyond: linear 2000 x 512 x 200 23.8 / 25.8, 4000 x 256 x 256 29.3 / 33.8, 7900 x 256 x 256 41.9 / 50.3, 14000 x 128 x 256 58.9 / 75.9, MLP
+//     7000 x 256 x 256 64.1 / 68.1, 12000 x 128 x 256 78.2 / 89.7
+//   dx's blocks wider, its contraction at most 2048 (beside three weight gradients 3072) more than N: linear 2000 x 256 x 3072
+//     38.5 / 37.3, 1000 x 320 x 3000 38.6 / 37.4, 600 x 384 x 2600 33.6 / 34.2, MLP 400 x 256 x 1400 46.9 / 45.5
+//   beyond: linear 300 x 512 x 2560 31.3 / 33.8, 1000 x 256 x 4096 39.6 / 45.1, 500 x 128 x 8192 55.3 / 75.5, MLP 256 x 128 x 4096 64.8 / 77.3
 static int choose_together(const LinearParams& lp, const WgradParams* ps, int n) {       // columns of the blocks, or 0: two launches
-    return lp.y_kmajor ? 0 : small_block_columns([&](int64_t c) {
-        int64_t total = small_blocks(lp.rows_x, lp.rows_y, c);
-        for (int i = 0; i < n; ++i) total += small_blocks(ps[i].rows_x, ps[i].rows_y, c);
-        return total;
-    });
+    if (lp.y_kmajor) return 0;
+    const int64_t k = lp.K, k_w = ps[0].K;
+    return joint_block_columns([&](int64_t c) { return small_blocks(lp.rows_x, lp.rows_y, c); }, k <= (n > 1 ? 3072 : 2048) + k_w,
+                               [&](int64_t c) { return count_small(ps, n, c); }, k_w <= 512 + 6 * k);
 }
 static int launch_backward(const LinearParams& lp, const WgradParams* ps, int n, hipStream_t s) {
     const int columns = choose_together(lp, ps, n);

@@ -108,6 +108,16 @@ def test_small_blocks_for_every_number_of_rows():
     assert seen >= {(64, 64, 1), (128, 128, 1), (64, 128, 0), (128, 64, 0), (128, 0, 0), (0, 64, 0), (0, 0, 0)}, seen
 
 
+@pytest.mark.parametrize("N,H,V,together", [
+    (512, 256, 4096, 1), (3500, 512, 256, 1), (5000, 256, 512, 1), (3500, 256, 256, 1),
+    (4096, 256, 256, 0), (7000, 128, 256, 0),          # dW's blocks would be wider, and it contracts over far more than dHidden
+    (256, 64, 24000, 0),                               # dHidden's would be
+])
+def test_dhidden_and_dw_in_one_launch(N, H, V, together):
+    i = _check(N, H, V, 1 << 14, 0, 0, N)
+    assert i.rows == N and i.together == together
+
+
 def test_bad_arguments_are_rejected():
     for a in [(0, 8, 8, 1, 0, 0, 0), (10, 8, 8, 1, 0, 5, 0), (10, 8, 8, 1, 0, 0, 11), (10, 8, 8, 1, 0, -1, 0),
               (10, 8, 8, 1, B.ALST_FLAG_FORWARD_ONLY, 0, 0), (10, 8, 8, 1, 1 << 20, 0, 0)]:

@@ -111,11 +111,12 @@ def test_cross_entropy(name, N, H, V, tile, n_valid, route):
     (512, 512, 1536, 64),              # 64 blocks of dx and 192 of dW: one round
     (520, 512, 1536, 128),             # a row of blocks more
     (1000, 1000, 904, 128),            # ragged in every extent; one round, 15 k-steps
+    (4000, 256, 256, 0),               # one round of 64 x 128, but dW's contraction is too long for blocks of twice the width
     (1024, 1024, 2048, 0),             # 128 + 256 blocks of 64 x 128: two launches, both small: 64 x 64 and 64 x 128
     (5, 8, 16, 64),
 ])
 def test_linear_backward_in_one_launch(N, K, M, joint):
-    assert gradients(LINEAR_BACKWARD, N, K, M, 4096) == ((joint, joint, 1) if joint else (64, 128, 0))
+    assert gradients(LINEAR_BACKWARD, N, K, M, 4096) == ((joint, joint, 1) if joint else (64, 64 if N == 4000 else 128, 0))
     x, W, dy = TL._inputs(N, K, M, 58)
     got = TL._run(x, W, dy, 4096)
     for g, r in zip(got, (lorc.forward(x, W), *lorc.backward(x, W, dy))):
@@ -127,10 +128,11 @@ def test_linear_backward_in_one_launch(N, K, M, joint):
     (1000, 256, 1024, 64),             # 64: one round
     (1032, 256, 1024, 128),
     (300, 520, 1000, 128),             # ragged: transposed weights lie where the sums would
+    (256, 128, 4096, 0),               # the same for dx
     (600, 384, 2048, 0),
 ])
 def test_mlp_backward_in_one_launch(N, H, I, joint):
-    assert gradients(MLP_BACKWARD, N, H, I, 2048) == ((joint, joint, 1) if joint else (64, 0, 0))
+    assert gradients(MLP_BACKWARD, N, H, I, 2048) == ((joint, joint, 1) if joint else (64, 128 if H == 128 else 0, 0))
     wl = synth.MlpWorkload("joint", N, H, I, 2048, seed=59)
     x, Wg, Wu, Wd, dy = synth.make_mlp_inputs(wl)
     y, dx, gW = TM._run(x, Wg, Wu, Wd, dy, 2048)
@@ -145,6 +147,7 @@ def test_mlp_backward_in_one_launch(N, H, I, joint):
     ("no_row_valid", 512, 256, 4096, 512, 0, (128, 128, 128, 1, 1)),
     ("last_chunk_without_rows", 1000, 64, 3000, 128, 120, (128, 64, 64, 1, 0)),
     ("two_launches", 512, 512, 4096, 512, 486, (128, 128, 128, 0, 1)),
+    ("wider_blocks_would_cost_more", 4096, 256, 256, 4096, 4000, (128, 64, 64, 0, 0)),
 ])
 def test_cross_entropy_gradients_in_one_launch(name, N, H, V, tile, n_valid, route):
     test_cross_entropy(name, N, H, V, tile, n_valid, route)

@@ -78,6 +78,22 @@ def test_weights_transposed_or_as_they_are(op, N, K, M, tile, flags, transposed)
     assert _check(op, N, K, M, tile, flags).transposed == transposed
 
 
+@pytest.mark.parametrize("op,N,K,M,together", [
+    # one round of small blocks in all, as wide as each kind's alone
+    (LINEAR_BACKWARD, 3800, 256, 256, 1), (MLP_BACKWARD, 2000, 256, 512, 1),
+    # wider ones for the weight gradients: unless their contraction (N) is far longer than that of dx
+    (LINEAR_BACKWARD, 512, 1024, 1024, 1), (LINEAR_BACKWARD, 5000, 256, 1024, 1), (LINEAR_BACKWARD, 4000, 256, 256, 0),
+    (LINEAR_BACKWARD, 7900, 256, 256, 0), (LINEAR_BACKWARD, 14000, 128, 256, 0), (MLP_BACKWARD, 6000, 256, 512, 1),
+    (MLP_BACKWARD, 7000, 256, 256, 0), (MLP_BACKWARD, 12000, 128, 256, 0),
+    # wider ones for dx
+    (LINEAR_BACKWARD, 2000, 256, 3072, 1), (LINEAR_BACKWARD, 300, 512, 2560, 0), (LINEAR_BACKWARD, 500, 128, 8192, 0),
+    (MLP_BACKWARD, 400, 256, 1400, 1), (MLP_BACKWARD, 256, 128, 4096, 0),
+])
+def test_dx_and_weight_gradients_in_one_launch(op, N, K, M, together):
+    i = _check(op, N, K, M, 1 << 16, 0)
+    assert i.rows == N and i.together == together
+
+
 def test_bad_arguments_are_rejected():
     for a in [(4, 8, 8, 8, 1), (-1, 8, 8, 8, 1), (0, 0, 8, 8, 1), (1, 8, 12, 8, 1), (2, 8, 8, 9, 1), (3, 8, 8, 8, 0),
               (3, 8, 8, 8, 1, B.ALST_FLAG_TILE_SCRATCH)]:
