@@ -831,7 +831,8 @@ __device__ __forceinline__ void logits_epilogue(const LogitsParams& p, typename 
                     *reinterpret_cast<bf16x4_t*>(tw + lp.lrow * kTurnPitch + lp.cw(mt, q) * 2) = o;
             }
         if (MODE != MODE_FWD) {
-            wave_sync<REDO>();
+            // (the rows' sums and label logits are stored by some lanes only, between one tile's turn and the next's)
+            wave_sync<true>();
             const int lrow = lp.lane >> 4, lcol = lp.lane & 15;        // 4 rows x 16 chunks of 16 B
             const int rb = r0 + lp.rbase(nt);
             uint16_t* const out = p.stash + (int64_t)rb * p.Vp + c0 + lp.wc * kGroupC + lcol * 8;
@@ -842,7 +843,7 @@ __device__ __forceinline__ void logits_epilogue(const LogitsParams& p, typename 
                 if (!REDO || p.rowstate[rb + row] != 0)
                     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(out + (int64_t)row * p.Vp));
             }
-            wave_sync<REDO>();
+            wave_sync<true>();
         }
         // label logit: exactly one lane of one block holds column y of row i.  Few wavefronts
         // hold any (a tile's rows x 128 of V columns), so the search sits behind a uniform branch.
