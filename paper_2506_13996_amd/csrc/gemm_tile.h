@@ -17,14 +17,17 @@
 //     D[r][c] = sum_k X[r][k] * Y[c][k]     both k-contiguous: logits, forward projections, and the products
 //                                           with a weight matrix over its row index (dH = dZ W, da = dy Wd,
 //                                           dx = dg Wg + du Wu, dx = dy W) against a copy of the weight
-//                                           transposed once per call (transpose_bf16_kernel)
+//                                           transposed once per call (transpose_piece)
 //     D[r][c] = sum_k X[r][k] * Y[k][c]     "mixed": those products of the MLP and the linear layer with the
-//                                           weight as it is, where an extent is not whole k-steps
+//                                           weight as it is, where an extent is not whole k-steps and the
+//                                           call's workspace has no unused room for the copy
 //     D[r][c] = sum_k X[k][r] * Y[k][c]     both k-major: the weight-gradient products, whose k is
 //                                           the token row
 // Activations and what is made of them are read as they lie; only weights are ever transposed.
 //
-// Three cores with the same accumulator interface, one per layout: DirectCore, MixedCore, KMajorCore.
+// Three cores with the same accumulator interface for these blocks, one per layout: DirectCore, MixedCore,
+// KMajorCore; halves of a block (HalfCore, KMajorHalfCore) and, for launches of few blocks, blocks of 64 x 64 and 64 x 128
+// (RingCoreT, KMajorSplitT) have cores of their own below.
 // 4 wavefronts (one per SIMD), 128 x 128 per wavefront, operands DMA'd straight from global memory
 // into LDS (global_load_lds_dwordx4), MFMA operands of the two k-slices of a step held in registers,
 // one barrier in the middle of a k-step so that the next stage's first operands are read while the
@@ -53,7 +56,7 @@ typedef short i16x8_t __attribute__((ext_vector_type(8)));
 constexpr int kBlockR = 256;          // rows of X per block (MFMA lane dimension)
 constexpr int kBlockC = 256;          // rows of Y per block (MFMA register dimension)
 constexpr int kBlockK = 64;           // k per main-loop step
-constexpr int kGroupC = 128;          // c extent one wavefront covers (all cores)
+constexpr int kGroupC = 128;          // c extent one wavefront covers (DirectCore, HalfCore, RingCoreT<8>), of a softmax partial
 constexpr int kTileBytes = kBlockR * kBlockK * 2;       // one operand tile in LDS (32 KB)
 constexpr int kStageBytes = 4 * kTileBytes;             // X, Y, two stages each (128 KB)
 constexpr int kLdsBytes = kStageBytes + 1024;           // + landing area of the L2 warm-up loads
@@ -156,9 +159,14 @@ __host__ __device__ __forceinline__ Halving halve_last_round(int blocks) {
 //   K = 256: 128 blocks 9.5 / 9.8, 256: 14.6 / 15.5, 384: 22.0 / 22.4, 576: 38.8 / 37.6, 2048: 101 / 85
 //   K = 1024: 128 blocks 18.6 / 19.1, 256: 31.2 / 30.6, 384: 49.2 / 49.1, 576: 78.0 / 77.7, 2048: 234 / 220
 //   K = 4096: 128 blocks 59.2 / 59.3, 256: 97.2 / 95.2, 576: 232 / 229, 2048: 749 / 740
-// Kernels with a long epilogue (softmax, SwiGLU) need more rounds: MLP forward 4096 x 2048 x 2048 (256 gate / up blocks)
-// 84.4 / 86.9, 3000 x 2048 x 4096 (384) 138 / 140, 10000 x 2048 x 8192 (2560) 821 / 815, x 256 x 8192 255 / 247;
-// cross-entropy steps 8000 x 512 x 5000 (640) 272 / 277, 3001 x 1600 x 50257 (2167) 1796 / 1764.
+// Kernels with a long epilogue (softmax, SwiGLU) need more rounds.  us of a call, of K and gate / up or logits blocks:
+//   MLP forward of 2048 rows, K = 256: 512 blocks 75.8 / 73.8, 1024: 135.6 / 132.8, 1280: 166.0 / 160.5, 2560: 317 / 304
+//   K = 1024: 512 blocks 134.7 / 134.8, 1024: 257.5 / 252.2, 1280: 317 / 311; K = 4096: 512 blocks 313.5 / 311.0, 1280: 791 / 776
+//   lse and loss of 2048 rows, K = 512: 512 blocks 64.1 / 65.0, 768: 82.0 / 81.7, 1024: 100.0 / 98.7, 1280: 118.2 / 115.7
+//   K = 1600: 512 blocks 110.8 / 111.0, 768: 152.3 / 151.2, 1024: 193.9 / 190.7; K = 4096: 512 220.1 / 219.2, 1280: 518 / 507
+//   a round begun: MLP forward 3000 x 2048 x 4096 (384) 138 / 140, cross-entropy step 8000 x 512 x 5000 (640) 272 / 277,
+//   3001 x 1600 x 50257 (2167) 1796 / 1764
+// So from four rounds on they gain in all; with two or three it depends on the last one.
 inline bool chain_pays(int64_t blocks, int64_t K, bool long_epilogue) {
     if (K % kBlockK != 0 || K < 4 * kBlockK) return false;
     return long_epilogue ? blocks > 4 * kRound : blocks > 2 * kRound || (blocks >= kRound && K >= 1024);
@@ -583,8 +591,8 @@ struct KMajorDirectT {
     }
 };
 typedef KMajorDirectT<true> KMajorCore;
-// 256 r x 128 c, see HalfCore (ce 512 x 256 x 4096: 124 -> 116 us; mlp 512 x 256 x 768: 126 -> 117 us; no
-// difference beyond the spread in calls of many rounds).
+// 256 r x 128 c, see HalfCore.  Backward calls with whole blocks / halves: linear 8192 x 2048 x 2048 (64 blocks) 207 / 163 us, 4096 x
+// 4096 x 4608 (288) 319 / 292, 16384 x 3072 x 5120 (240: none) 773 / 772, cross-entropy 3001 x 1600 x 50257 (1379) 1371 / 1354.
 typedef KMajorDirectT<true, 2> KMajorHalfCore;
 typedef KMajorDirectT<false> MixedCore;
 
@@ -954,7 +962,7 @@ typedef DirectCoreT<8> DirectCore;
 // Half a block, for a last round that leaves half of the compute units or more idle.  It reads 384
 // operand rows per k-step where a whole block reads 512 for twice the work, so it takes more than half of
 // a block's time.  linear 10000 x 4096 x 4096 (2.5 rounds): 784 -> 765 us; mlp 6000 x 4096 x 14336:
-// 6327 -> 6082 us; calls of a few blocks gain most (mlp 512 x 256 x 768: 176 -> 126 us).
+// 6327 -> 6082 us.  (Launches of up to some 32 blocks run on small blocks instead.)
 typedef DirectCoreT<4> HalfCore;
 
 // ---------------------------------------------------------------------------------------------
@@ -1423,7 +1431,7 @@ struct GradOut {
 // wrote and read 8 bytes per weight more and started only when all of them were done (two
 // micro-batches of 4096 rows on a 128256 x 4096 head, fp32 += : 23.6 -> 21.7 ms).  For that the
 // products are turned around in LDS (`smem`, free once the k-loop is over; each wavefront has its own region), so that sums and results travel
-// as whole row segments of 512 (fp32) or 256 bytes.
+// as whole row segments: 512 (fp32) or 256 bytes of a wavefront's 128 r, half or a quarter of that in small blocks.
 // Rows r >= r_valid (a multiple of 8) and c >= c_valid are skipped.
 template <class Core>
 __device__ __forceinline__ void weight_grad_block(const typename Core::acc_t (&acc)[Core::kMT][Core::kNT],

@@ -433,7 +433,9 @@ __device__ __forceinline__ float from_ordered_int(int k) {
 // time; the dHidden rows of ignored tokens become zeros.  The workgroups behind those transpose W (first chunk, if
 // a gradient is wanted: a launch of its own took 3 us more of the smallest calls).
 // INDEX (N <= kGatherIndexRows, one chunk): there was no launch that numbers the rows; every workgroup counts the valid labels
-// itself, and workgroup 0 leaves the header (512 x 256 x 4096: two launches of 3.8 and 3.4 us become one).
+// itself, and workgroup 0 leaves the header.  A launch less, for four labels a thread counts in every workgroup; us of a call
+// with the launch / without: N = 300 (H = 256, V = 4096) 38.6 / 36.1, 512 40.7 / 38.2, 1024 51.6 / 49.3; with 8 and 16 labels a thread 1500 65.5 /
+// 65.4, 2048 69.4 / 72.7, 3000 80.4 / 92.2.
 constexpr int kGatherIndexRows = 1024;
 struct GatherParams {
     const uint16_t* hidden;      // [N, H]
@@ -1007,7 +1009,7 @@ struct DHiddenParams {
 
 // dH = dZ W runs with both operands k-contiguous (the fastest of the block GEMM's layouts: 9 % on
 // this product): W transposed, [H, Vp] with zeros from V to whole k-steps, is made once per call that
-// computes gradients (transpose_bf16_kernel), for the price of reading and writing W once.
+// computes gradients (transpose_piece), for the price of reading and writing W once.
 
 // r = token row (lane dimension), c = hidden index (register dimension), k = vocabulary; both
 // operands k-contiguous (dZ rows and the rows of W transposed).
@@ -1103,7 +1105,7 @@ __global__ __launch_bounds__(DirectCore::kThreads) void dhidden_kernel(const DHi
     else dhidden_block<HalfCore>(p, T_cur, Trc, splits, ksteps, split, r0 + half * (kBlockR / 2), c0, warm, smem);
 }
 
-// The same in small blocks (the ranges are chosen as for the large ones).
+// The same in small blocks (the ranges are those that suit the large ones).
 template <class Core>
 struct DHiddenSmall {
     const DHiddenParams& p;

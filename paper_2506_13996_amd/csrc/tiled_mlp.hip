@@ -14,9 +14,10 @@
 //                                             reads da; written into the rows of the chunk's group
 //              dx = dg Wg + du Wu             one contraction over the 2 I columns of [dg | du]
 //                                             against [Wg | Wu]^T, transposed once per call
-//                                             (H or I not a multiple of 64, several groups: the weights as
-//                                             they are, k-major operands on MixedCore, which has no halves for
-//                                             a short last round; dx as two contractions over I)
+//                                             (H or I not a multiple of 64 and several groups or fp32
+//                                             overwrite outputs: the weights as they are, k-major operands on
+//                                             MixedCore, which has no halves for a short last round; dx as two
+//                                             contractions over I)
 //   per group  dWg += dg^T x, dWu += du^T x, dWd += dy^T a   (fp32, contraction over the group's rows)
 //
 // The launches work on CHUNKS of consecutive rows whose length is chosen for the hardware
