@@ -96,6 +96,10 @@ int main() {
                         for (int op = 0; op < 4; ++op) {
                             const int64_t rows = alst_debug_chunk_rows(op, N, H, I, T);
                             EXPECT(rows >= 256 && rows % 256 == 0);
+                            alst_debug_layer_info i;
+                            EXPECT(alst_debug_layer(op, N, H, I, T, f, &i) == ALST_OK);
+                            EXPECT(i.rows >= 1 && i.rows <= rows && i.rows <= N);
+                            EXPECT(!i.together || (i.transposed && i.product_columns && i.wgrad_columns));
                         }
                         EXPECT(alst_tiled_mlp_forward(fake(0x10000), fake(0x20000), fake(0x30000),
                                                       fake(0x40000), N, H, I, T, fake(0x50000), fake(0x60000),
