@@ -15,7 +15,8 @@
  * dy are read as they are by every product (no activation is copied or transposed), so the forward
  * pass needs no workspace; the backward pass needs the fp32 dW sums (4 M K bytes; none with fp32
  * overwrite output, whose sums live in dW) and, for M a multiple of 64, a bf16 copy of W transposed
- * (2 M K bytes, made once per call).  `workspace` may be NULL when none is needed.
+ * (2 M K bytes, made once per call; for other M a call that does not use the sums keeps the copy in
+ * their place).  `workspace` may be NULL when none is needed.
  */
 #ifndef ALST_LINEAR_H
 #define ALST_LINEAR_H

@@ -41,7 +41,8 @@ extern "C" {
  * O(tile * I) for the activations of the tiles in flight, plus O(H * I) in backward: the fp32
  * weight-gradient sums (12 H I bytes; absent for fp32 overwrite outputs) and, for H and I that
  * are multiples of 64, bf16 copies of the three weight matrices transposed (6 H I bytes, made once
- * per call, so that the products with a weight over its row index read it along its rows).
+ * per call, so that the products with a weight over its row index read it along its rows; for other H and
+ * I a call that does not use the sums keeps the copies in their place).
  */
 size_t alst_tiled_mlp_workspace_bytes(int64_t N, int64_t H, int64_t I, int64_t tile, int backward,
                                       uint32_t flags);
